@@ -31,6 +31,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for "no logit seen yet"
 constexpr int kXcds = 8;
+constexpr int kCuPerXcd = 32;
+constexpr int kSplitsFirst = 8;      // see map_workgroup
 
 template <int BM_, int BN_, int BK_, int WM_, int WN_>
 struct Tile {
@@ -61,6 +63,7 @@ struct LogprobArgs {
     int64_t T;
     int V, d;
     int n_tb, n_sp, n_vt;
+    int band, n_long;       // work order: n_long bands of `band` token blocks, the rest one shorter (map_workgroup)
 };
 
 // Per-lane online-softmax state: the lane owns token (wave token base + j*32 + lane%32), j < TN.
@@ -169,12 +172,7 @@ __device__ __forceinline__ void write_partials(LaneState<TN>& st, float* red, in
 // are left as they are (the next tile's first MFMAs take 0 as their addend).
 template <int TI, int TJ, int WROWS>
 __device__ __forceinline__ void tile_epilogue16(f32x4 (&acc)[TI][TJ], LaneState<TJ>& st, int vrow0, int V, int lq,
-                                                const int32_t* tgt_wave, int tgt_valid, int l15) {
-    // the lane's targets are fetched again for every tile (from cache) instead of living in registers through
-    // the K loop: tgt_wave (wave-uniform) points at the wave's first token, of which tgt_valid exist
-    int tgt[TJ];
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) tgt[j] = j * 16 + l15 < tgt_valid ? tgt_wave[j * 16 + l15] : -1;
+                                                const int (&tgt)[TJ]) {
     if (vrow0 + WROWS > V) {  // tile hangs over the end of the vocabulary
         const int lim = V - vrow0 - lq * 4;   // rows of this lane from here on are past the end: one value per tile,
 #pragma unroll                                // compared with constants (nothing per (i, v) to keep in registers)
@@ -265,14 +263,32 @@ __device__ __forceinline__ void write_partials16(LaneState<TJ>& st, float* red, 
     }
 }
 
-// workgroup id -> (token block, vocab split): ids congruent mod 8 land on the same XCD, so an XCD
-// works on token blocks xcd, xcd+8, ... and, for each, on all splits back to back.
+// workgroup id -> (token block, vocab split).  Ids congruent mod 8 land on the same XCD, and a round of 256 workgroups
+// (one per compute unit: every kernel here takes most of a unit's LDS) gives each XCD 32 consecutive positions of the
+// work order (the last round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
+// each band with the split fastest where there are up to 8 (1.5-2 % faster than the other way round at 8,000 to 33,000
+// tokens), the token block fastest otherwise (0.6 % at 4,096 tokens x 16 splits), so the 32 resident workgroups of an
+// XCD are a patch of about 6 token blocks x 5 splits that shares its H and W tiles through the XCD's L2, for any
+// number of token blocks.  Dealing token blocks to the XCDs instead leaves 6 of the 8 idle at 311 tokens (1.00 ms with
+// 151,936 x 2048; now 0.26) and makes every XCD read all of W up to some 10,000 tokens (1,000 tokens: 1.00 ms; now 0.50).
 __device__ __forceinline__ bool map_workgroup(const LogprobArgs& a, int& tb, int& sp, int& vt_lo, int& vt_hi) {
-    const int bid = blockIdx.x;
-    const int xcd = bid % kXcds, idx = bid / kXcds;
-    sp = idx % a.n_sp;
-    tb = (idx / a.n_sp) * kXcds + xcd;
-    if (tb >= a.n_tb) return false;
+    constexpr int kRound = kXcds * kCuPerXcd;
+    const int round0 = static_cast<int>(blockIdx.x) / kRound * kRound, id = static_cast<int>(blockIdx.x) - round0;
+    const int64_t left = static_cast<int64_t>(a.n_tb) * a.n_sp - round0;
+    const int in_round = left < kRound ? static_cast<int>(left) : kRound;
+    const int per_xcd = (in_round + kXcds - 1) / kXcds;
+    const int pos = id % kXcds * per_xcd + id / kXcds;
+    if (id / kXcds >= per_xcd || pos >= in_round) return false;
+    int64_t w = static_cast<int64_t>(round0) + pos;
+    // n_long bands of `band` token blocks, then bands of band - 1
+    const int64_t in_long = static_cast<int64_t>(a.n_long) * a.band * a.n_sp;
+    int tb0 = 0, size = a.band;
+    if (w >= in_long) { w -= in_long; tb0 = a.n_long * a.band; --size; }
+    const int64_t per_band = static_cast<int64_t>(size) * a.n_sp;
+    const int b = static_cast<int>(w / per_band), r = static_cast<int>(w - b * per_band);
+    const int tbi = a.n_sp <= kSplitsFirst ? r / a.n_sp : r % size;
+    sp = a.n_sp <= kSplitsFirst ? r - tbi * a.n_sp : r / size;
+    tb = tb0 + b * size + tbi;
     vt_lo = static_cast<int>(static_cast<int64_t>(a.n_vt) * sp / a.n_sp);
     vt_hi = static_cast<int>(static_cast<int64_t>(a.n_vt) * (sp + 1) / a.n_sp);
     return true;
@@ -676,7 +692,14 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
             iteration(kB, std::false_type{});
             iteration(kA, std::false_type{});
         }
-        tile_epilogue16<TI, TJ, BM / C::WM>(acc, st, vt * BM + wm * (BM / C::WM), a.V, lq, tgt_wave, tgt_valid, l15);
+        {
+            // the lane's targets are fetched again for every tile (from cache) instead of living in registers through
+            // the K loop: tgt_wave (wave-uniform) points at the wave's first token, of which tgt_valid exist
+            int tgt[TJ];
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) tgt[j] = j * 16 + l15 < tgt_valid ? tgt_wave[j * 16 + l15] : -1;
+            tile_epilogue16<TI, TJ, BM / C::WM>(acc, st, vt * BM + wm * (BM / C::WM), a.V, lq, tgt);
+        }
         // The fragments of the next chunk are read again here rather than kept across the epilogue: held, their
         // 64 registers pushed the epilogue into scratch memory, whose latency nothing hides (every wave of the
         // workgroup is in its epilogue at the same time).  The slot is certified and not yet released.
@@ -697,20 +720,219 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
                                                    a.T, sp, a.part);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Few tokens (d a multiple of 64): 256 vocabulary rows x 16 TJ tokens per workgroup, 8 wavefronts of 32 rows x all
+// the tokens.  What bounds it is the stream of W from HBM (V d 2 bytes, read once).  A W fragment belongs to one
+// wavefront alone, so W goes from memory straight to registers without LDS or barriers in its way; the H tile, which
+// all wavefronts share, goes to LDS directly.  Loads are requested a group of G K64 steps at a time, one group ahead:
+// 128 G contiguous bytes of each row in one burst (4.2 -> 4.6 TB/s at 64 tokens, 151,936 x 2048, over the same bytes
+// requested 128 at a time 4 steps ahead; 6 and 8 steps ahead changed nothing), and one barrier per group.  134 us
+// there (the ring kernel 173), 255 us = 4.9 TB/s at d = 4096.
+//
+// Stage layout: 16-byte chunk c of token row r sits at position c ^ (r & 6) of its 128-byte row.  By the serving rule
+// given at the ring kernel's fragment reads, lanes that share a bank group differ in lane bit 3 alone: no conflicts.
+//
+// The steps of all vocabulary tiles of the split form one sequence, cut into groups; steps past its end load and
+// multiply the last tile's lines again into accumulators that nobody reads.
+// ---------------------------------------------------------------------------------------------
+template <int TJ_>
+struct StreamTile {
+    static constexpr int BM = 256, TJ = TJ_, BN = 16 * TJ_;
+    static constexpr int NW = 8, NT = NW * ARROL_WAVE;
+    static constexpr int TI = BM / NW / 16;
+    static constexpr int G = TJ <= 4 ? 4 : 2;            // K64 steps per group
+    static constexpr int STAGE_BYTES = BN * 128;
+    static constexpr int NS = 2 * G;
+    static constexpr int RED_BYTES = NW * 3 * BN * 4;    // write_partials16
+    static constexpr int LDS_BYTES = NS * STAGE_BYTES > RED_BYTES ? NS * STAGE_BYTES : RED_BYTES;
+    static constexpr int GROUPS = BN / 8;                // load instructions (8 token rows x 128 bytes) per stage
+    static constexpr int HL = (GROUPS + NW - 1) / NW;    // per wavefront; the surplus ones repeat the last group
+};
+
+template <class C>
+__global__ __launch_bounds__(C::NT) void logprob_stream_kernel(LogprobArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int TI = C::TI, TJ = C::TJ, G = C::G, BM = C::BM, BN = C::BN;
+    typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+    int tb, sp, vt_lo, vt_hi;
+    if (!map_workgroup(a, tb, sp, vt_lo, vt_hi)) return;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, lq = lane >> 4;
+    const int64_t tok0 = static_cast<int64_t>(tb) * BN;
+    const int n_k64 = a.d / 64;
+    const int total = (vt_hi - vt_lo) * n_k64;           // host: at most n_vt * n_k64, checked against INT32_MAX
+    const unsigned row_bytes = static_cast<unsigned>(a.d) * 2;
+
+    // ---- H loader: lane -> (row lane/8 of an 8-row group, position lane%8), rows past the last token repeat it
+    unsigned h_voff[C::HL], h_dst[C::HL];
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    {
+        const int rows_valid = static_cast<int>(a.T - tok0 < BN ? a.T - tok0 : BN);
+#pragma unroll
+        for (int q = 0; q < C::HL; ++q) {
+            int g = q * C::NW + wave;
+            g = g < C::GROUPS ? g : C::GROUPS - 1;
+            int r = g * 8 + (lane >> 3);
+            const int c = (lane & 7) ^ (r & 6);
+            r = r < rows_valid ? r : rows_valid - 1;
+            h_voff[q] = static_cast<unsigned>(r) * row_bytes + c * 16;
+            h_dst[q] = lds0 + g * 1024;
+        }
+    }
+    const char* h_base = reinterpret_cast<const char*>(a.H) + tok0 * static_cast<int64_t>(row_bytes);
+    // ---- W loader: lane -> (row lane%16 of a 16-row block, chunk lane/16 (+4 for the second half of the line))
+    unsigned w_voff[TI];
+    const char* w_base = nullptr;
+    auto point_at_tile = [&](int vt) {
+        const int64_t r0 = static_cast<int64_t>(vt) * BM + wave * (16 * TI);
+        const int64_t first = r0 < a.V ? r0 : a.V - 1;                 // rows past the vocabulary repeat the last one
+        w_base = reinterpret_cast<const char*>(a.W) + first * row_bytes;
+        const int rows_valid = static_cast<int>(a.V - first < 16 * TI ? a.V - first : 16 * TI);
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const int r = i * 16 + l15;
+            w_voff[i] = static_cast<unsigned>(r < rows_valid ? r : rows_valid - 1) * row_bytes + lq * 16;
+        }
+    };
+    u32x4 w[2][G][TI][2];
+    // every split starts at another place of the K extent and wraps around: all of them at the same offset of rows a
+    // power of two apart meet in the same memory channels (149 against 134 us at 64 tokens, 151,936 x 2048)
+    const int k_start = sp * 3 % n_k64;
+    int ld_vt = vt_lo, ld_k = k_start;
+    point_at_tile(vt_lo);
+    // the loads of the next group of steps: W into `dst`, H into the LDS stages of parity `par`
+    auto issue_group = [&](u32x4 (&dst)[G][TI][2], int par) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const char* wk = w_base + static_cast<int64_t>(ld_k) * 128;
+            const char* hb = h_base + static_cast<int64_t>(ld_k) * 128;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) dst[q][i][h] = *reinterpret_cast<const u32x4*>(wk + w_voff[i] + h * 64);
+#pragma unroll
+            for (int g = 0; g < C::HL; ++g)
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(h_voff[g]), "s"(hb),
+                             "s"(h_dst[g] + (par * G + q) * C::STAGE_BYTES) : "memory");
+            ld_k = ld_k + 1 == n_k64 ? 0 : ld_k + 1;
+            if (ld_k == k_start && ld_vt + 1 < vt_hi) point_at_tile(++ld_vt);   // past the last tile: its lines again
+        }
+    };
+
+    LaneState<TJ> st;
+    int tgt[TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+        st.run_m[j] = kNegBig; st.run_s[j] = 0.f; st.tgt_z[j] = 0.f;
+        const int64_t t = tok0 + j * 16 + l15;
+        tgt[j] = t < a.T ? a.targets[t] : -1;
+    }
+    f32x4 acc[TI][TJ];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+    const int h_off = l15 * 128;
+    const int h_pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
+    bf16x8 fb[TJ];       // H fragments: one half K64 step ahead, reloaded one by one
+    auto read_h = [&](int stage, int h, int j) {
+        fb[j] = *reinterpret_cast<const bf16x8*>(lds + stage * C::STAGE_BYTES + h_off + j * 2048 + h_pos[h]);
+    };
+    // 2 TJ MFMAs with the fragments in fb (token block by token block, consecutive ones share an operand); behind each
+    // block its fragment of the next half step is read into the same registers
+    auto half = [&](u32x4 (&wr)[TI][2], int h, int next_stage, int next_h, bool read_next) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ii = 0; ii < TI; ++ii) {
+                const int i = (j & 1) ? TI - 1 - ii : ii;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[i][h]), fb[j], acc[i][j], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (read_next) read_h(next_stage, next_h, j);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int k = 0, vt = vt_lo;
+    auto group = [&](u32x4 (&wr)[G][TI][2], u32x4 (&wn)[G][TI][2], int par) {
+        // this group's loads have landed, for every wavefront, and nobody reads the other stages any more
+        asm volatile("" ::: "memory");
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue_group(wn, par ^ 1);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) read_h(par * G, 0, j);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            half(wr[q], 0, par * G + q, 1, true);
+            half(wr[q], 1, par * G + q + 1, 0, q + 1 < G);
+            if (++k == n_k64 && vt < vt_hi) {
+                tile_epilogue16<TI, TJ, 16 * TI>(acc, st, vt * BM + wave * (16 * TI), a.V, lq, tgt);
+                clear();
+                k = 0;
+                ++vt;
+            }
+        }
+    };
+    issue_group(w[0], 0);
+    for (int s = 0; s < total; s += 2 * G) {
+        group(w[0], w[1], 0);
+        if (s + G < total) group(w[1], w[0], 1);
+    }
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __syncthreads();   // every stage has been read and every load into LDS has landed
+    write_partials16<TJ, C::NW, 1, BN, C::NT>(st, reinterpret_cast<float*>(lds), wave, 0, l15, lq, tid, tok0, a.T, sp, a.part);
+}
+
+// Merges the splits.  256 / GROUPS tokens per workgroup, GROUPS lanes per token that take every GROUPS-th split and
+// are merged through LDS in index order.  One lane per token walks the many splits of a short batch one dependent load
+// after the other: at 64 tokens x 256 splits the whole call took 217 us, with 16 lanes 150 (up to 8 splits one lane is
+// as fast and needs no merge).
+template <int GROUPS>
 __global__ __launch_bounds__(256) void logprob_finalize_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ targets, int64_t T, int V, int n_sp,
     float* __restrict__ logprob_out, float* __restrict__ lse_out) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= T) return;
+    constexpr int TOK = 256 / GROUPS, UNROLL = 4;
+    const int tok = threadIdx.x % TOK, grp = threadIdx.x / TOK;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * TOK + tok;
     float m = kNegBig, s = 0.f, z = 0.f;
-    for (int sp = 0; sp < n_sp; ++sp) {
-        const float* p = part + static_cast<int64_t>(sp) * 3 * T + t;
-        const float om = p[0], os = p[T];
+    auto merge = [&](float om, float os, float oz) {
         const float mm = fmaxf(m, om);
         s = s * exp2f((m - mm) * kLog2e) + os * exp2f((om - mm) * kLog2e);
         m = mm;
-        z += p[2 * T];
+        z += oz;
+    };
+    if (t < T) {
+        for (int sp0 = grp; sp0 < n_sp; sp0 += GROUPS * UNROLL) {
+            float om[UNROLL], os[UNROLL], oz[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const int sp = sp0 + u * GROUPS;
+                const float* p = part + static_cast<int64_t>(sp < n_sp ? sp : sp0) * 3 * T + t;
+                om[u] = p[0]; os[u] = p[T]; oz[u] = p[2 * T];
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (sp0 + u * GROUPS < n_sp) merge(om[u], os[u], oz[u]);
+        }
     }
+    if (GROUPS > 1) {
+        __shared__ float red[3][GROUPS][TOK];
+        red[0][grp][tok] = m; red[1][grp][tok] = s; red[2][grp][tok] = z;
+        __syncthreads();
+        if (grp) return;
+        for (int g = 1; g < GROUPS; ++g) merge(red[0][g][tok], red[1][g][tok], red[2][g][tok]);
+    }
+    if (t >= T) return;
     const float lse = m + logf(s);
     const int y = targets[t];
     logprob_out[t] = (y >= 0 && y < V) ? z - lse : __builtin_nanf("");
@@ -721,32 +943,62 @@ using MainTile = Tile<256, 256, 64, 2, 4>;
 using FastTile = RingTile<256, 256, 2, 4>;
 static_assert(MainTile::BM == FastTile::BM && MainTile::BN == FastTile::BN, "one plan serves both kernels");
 
-struct Plan { int n_tb, n_vt, n_sp; };
+struct Plan { int bn, n_tb, n_vt, n_sp, band, n_long; };   // bn: tokens per workgroup
 
-Plan make_plan(int64_t T, int V, int n_splits) {
+Plan make_plan(int64_t T, int V, int d, int n_splits) {
     Plan p;
-    p.n_tb = static_cast<int>((T + MainTile::BN - 1) / MainTile::BN);
+    // Up to 128 tokens W's stream from HBM is the bound and the stream kernel takes it faster: 134 us against 173 of
+    // the ring kernel at 64 tokens, 153 against 173 at 128 (151,936 x 2048); at 200 tokens, two blocks of 128, it
+    // needs 228 against 173, and from there on the ring kernel's operand reuse wins.
+    p.bn = d % 64 == 0 && T <= 128 ? (T <= 64 ? 64 : 128) : MainTile::BN;
+    p.n_tb = static_cast<int>((T + p.bn - 1) / p.bn);
     p.n_vt = (V + MainTile::BM - 1) / MainTile::BM;
-    int sp = n_splits;
-    if (sp <= 0) {
-        // enough workgroups to fill 256 CUs several times over.  The 32 workgroups resident on an XCD are then
-        // 5 1/3 token blocks x 6 splits: measured at the four benchmark shapes, 6 splits are 0.4-2.1 % faster
-        // than 8 and than 4, 5 or 7
-        sp = 6;
-        while (static_cast<int64_t>(p.n_tb) * sp < 1024 && sp < 64) sp *= 2;
+    const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
+    p.band = (p.n_tb + bands - 1) / bands;
+    p.n_long = p.n_tb - (p.band - 1) * bands;
+    if (n_splits > 0) {
+        p.n_sp = n_splits < p.n_vt ? n_splits : p.n_vt;
+        return p;
     }
-    if (sp > p.n_vt) sp = p.n_vt;
-    if (sp < 1) sp = 1;
-    p.n_sp = sp;
+    // A launch takes rounds of 256 workgroups x the vocabulary tiles of the longest split (plus about a quarter of a
+    // tile's time per workgroup to start and finish).  Candidates: the split counts that just fill 1 ... 8 rounds, and
+    // 4 ... 12.  Fewer than 6 splits widen an XCD's patch to more token blocks and fetch more operand slices per K
+    // step (an eighth of a per cent each); where costs tie the smallest wins.  At 32,768 tokens this gives 6 (27.5 ms;
+    // 12 splits: 28.5).  From 16 rounds on the last one no longer matters: 6, which at the benchmark shapes (T of
+    // 290,000 to 2.4 million) measured 0.4-2.1 % faster than 4, 5, 7 or 8.
+    if (static_cast<int64_t>(p.n_tb) * 6 >= 16 * kXcds * kCuPerXcd) {
+        p.n_sp = p.n_vt < 6 ? p.n_vt : 6;
+        return p;
+    }
+    double best = -1.0;
+    p.n_sp = 1;
+    for (int c = 0; c < 17; ++c) {
+        int64_t sp = c < 9 ? c + 4 : static_cast<int64_t>(kXcds * kCuPerXcd) * (c - 8) / p.n_tb;
+        if (sp > p.n_vt) sp = p.n_vt;
+        if (sp < 1) continue;
+        const int64_t tiles = (p.n_vt + sp - 1) / sp;
+        if (sp > 12) sp = (p.n_vt + tiles - 1) / tiles;       // no more splits than the longest one needs
+        const int64_t rounds = (p.n_tb * sp + kXcds * kCuPerXcd - 1) / (kXcds * kCuPerXcd);
+        const double slices = sp >= 6 ? 11.3 : sp + 32.0 / static_cast<double>(sp);
+        const double cost = static_cast<double>(rounds) * (static_cast<double>(tiles) + 0.25) * (1.0 + 0.00125 * slices);
+        if (best < 0.0 || cost < best || (cost == best && sp < p.n_sp)) { best = cost; p.n_sp = static_cast<int>(sp); }
+    }
     return p;
+}
+
+template <void (*KERNEL)(LogprobArgs), class C>
+int launch_logprob(dim3 grid, hipStream_t st, const LogprobArgs& a) {
+    static arrol_device_flags lds_ok;
+    if (!arrol_allow_lds(KERNEL, C::LDS_BYTES, lds_ok)) return ARROL_EHIP;
+    arrol_launch(KERNEL, grid, dim3(C::NT), C::LDS_BYTES, st, a);
+    return ARROL_OK;
 }
 
 }  // namespace
 
 extern "C" size_t arrol_logprob_workspace_bytes(int64_t T, int32_t V, int32_t d, int32_t n_splits) {
-    (void)d;
     if (T <= 0 || V < 1 || n_splits < 0) return 0;
-    const Plan p = make_plan(T, V, n_splits);
+    const Plan p = make_plan(T, V, d, n_splits);
     return (static_cast<size_t>(p.n_sp) * 3 * static_cast<size_t>(T) * sizeof(float) + 255) & ~static_cast<size_t>(255);
 }
 
@@ -757,29 +1009,33 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
     if (T == 0) return ARROL_OK;
     if (!hidden || !lm_head || !targets || !logprob_out || !arrol_aligned16(hidden) || !arrol_aligned16(lm_head))
         return ARROL_EINVAL;
-    const Plan p = make_plan(T, V, n_splits);
-    if (static_cast<int64_t>(p.n_tb) + kXcds > INT32_MAX / p.n_sp) return ARROL_EINVAL;
+    const Plan p = make_plan(T, V, d, n_splits);
+    // whole rounds of 256, then the rest spread over the 8 XCDs
+    const int64_t grid = (static_cast<int64_t>(p.n_tb) * p.n_sp + kXcds - 1) / kXcds * kXcds;
+    if (grid > INT32_MAX - 256 || static_cast<int64_t>(p.n_vt) * (d / 64) > INT32_MAX - 64) return ARROL_EINVAL;
     if (!workspace || !arrol_aligned16(workspace) || workspace_bytes < arrol_logprob_workspace_bytes(T, V, d, n_splits))
         return ARROL_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    static arrol_device_flags general_ok, fast_ok;
-    if (!arrol_allow_lds(&logprob_kernel<MainTile>, MainTile::LDS_BYTES, general_ok) ||
-        !arrol_allow_lds(&logprob_ring_kernel<FastTile>, FastTile::LDS_BYTES, fast_ok))
-        return ARROL_EHIP;
     LogprobArgs a;
     a.H = static_cast<const uint16_t*>(hidden);
     a.W = static_cast<const uint16_t*>(lm_head);
     a.targets = targets;
     a.part = static_cast<float*>(workspace);
     a.T = T; a.V = V; a.d = d;
-    a.n_tb = p.n_tb; a.n_sp = p.n_sp; a.n_vt = p.n_vt;
-    const int tb_pad = (p.n_tb + kXcds - 1) / kXcds * kXcds;
-    if (d % 64 == 0)
-        arrol_launch(logprob_ring_kernel<FastTile>, dim3(tb_pad * p.n_sp), dim3(FastTile::NT), FastTile::LDS_BYTES, st, a);
-    else
-        arrol_launch(logprob_kernel<MainTile>, dim3(tb_pad * p.n_sp), dim3(MainTile::NT), MainTile::LDS_BYTES, st, a);
+    a.n_tb = p.n_tb; a.n_sp = p.n_sp; a.n_vt = p.n_vt; a.band = p.band; a.n_long = p.n_long;
+    const dim3 g(static_cast<unsigned>(grid));
+    int rc;
+    if (d % 64) rc = launch_logprob<logprob_kernel<MainTile>, MainTile>(g, st, a);
+    else if (p.bn == MainTile::BN) rc = launch_logprob<logprob_ring_kernel<FastTile>, FastTile>(g, st, a);
+    else if (p.bn == 128) rc = launch_logprob<logprob_stream_kernel<StreamTile<8>>, StreamTile<8>>(g, st, a);
+    else rc = launch_logprob<logprob_stream_kernel<StreamTile<4>>, StreamTile<4>>(g, st, a);
+    if (rc != ARROL_OK) return rc;
     if (arrol_launch_failed()) return arrol_launch_status();
-    arrol_launch(logprob_finalize_kernel, dim3(static_cast<unsigned>((T + 255) / 256)), dim3(256), 0, st,
-                       static_cast<const float*>(workspace), targets, T, V, p.n_sp, logprob_out, lse_out);
+    if (p.n_sp > 8)
+        arrol_launch(logprob_finalize_kernel<16>, dim3(static_cast<unsigned>((T + 15) / 16)), dim3(256), 0, st,
+                     static_cast<const float*>(workspace), targets, T, V, p.n_sp, logprob_out, lse_out);
+    else
+        arrol_launch(logprob_finalize_kernel<1>, dim3(static_cast<unsigned>((T + 255) / 256)), dim3(256), 0, st,
+                     static_cast<const float*>(workspace), targets, T, V, p.n_sp, logprob_out, lse_out);
     return arrol_launch_status();
 }
