@@ -21,7 +21,8 @@
 namespace {
 
 using ring_nt::bf16x8;
-typedef float f32x16 __attribute__((ext_vector_type(16)));   // 32x32x16 accumulators of the tile and small-batch kernels
+using ring_nt::f32x4;
+typedef float f32x16 __attribute__((ext_vector_type(16)));   // 32x32x16 accumulators of the tile kernel
 
 constexpr int kThreads = 256;
 constexpr int BU = 256;   // hidden units per pass
@@ -63,8 +64,8 @@ struct MlpArgs {
 };
 
 template <int N>
-__device__ __forceinline__ void mlp_wait_vmcnt() {  // s_waitcnt vmcnt(N) only (gfx9 encoding), N <= 15
-    __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+__device__ __forceinline__ void mlp_wait_vmcnt() {  // s_waitcnt vmcnt(N) only (gfx9 encoding: bits 3:0 and 15:14), N <= 63
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // RING = false: any d (multiple of 8), K chunks staged global -> registers -> LDS, one chunk ahead.
@@ -327,89 +328,162 @@ __global__ __launch_bounds__(kThreads) void score_mlp_kernel(MlpArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Small batches (a few hundred rollouts): the tile kernel above would run on n_rows / 128 compute units and
-// each of them would walk all of K behind a three-stage ring (bytes in flight over memory latency: ~90 us
-// for 512 x 2048 x 512).  Here every wavefront owns one 32-unit x 32-rollout block of the pre-activations
-// over the whole K, n_rows/32 x m/32 wavefronts in all, and takes its MFMA fragments straight from global
-// memory: no LDS, no barrier, kSmallDepth K64 blocks (2 x 4 x 16 bytes per lane each) in flight per lane,
-// one wavefront per workgroup.
-// The contraction does not care in which order K is visited, so a lane loads 64 CONTIGUOUS bytes of its row
-// per K64 block (lane half lh takes k in [32 lh, 32 lh + 32)) and the q-th 16 bytes feed the q-th MFMA of
-// the block, the same assignment on both operands.  Each wavefront writes sum_u w2[u] relu(pre[u] + b1[u])
-// over its 32 units to partial[unit block][rollout]; a second kernel adds the unit blocks in index order.
-constexpr int kSmallMaxRows = 4096;     // beyond this the tile kernel has enough workgroups of its own
-constexpr int kSmallDepth = 4;          // K64 blocks in flight
-constexpr int kSmallThreads = 64;       // one wavefront per workgroup: its lanes address 64 different cache lines per
-                                        // load, so the texture addresser of a compute unit is the resource to spread over
+// Batches below the ring kernels' size, and gathered rows of any number: BM units x BN rollouts per workgroup of four
+// wavefronts (2 x 2), K64 stages of both operands direct to LDS, NS stages deep, one barrier per stage.  What bounds it
+// is a step's chain of barrier, fragment reads and MFMAs while few workgroups run, and each workgroup's (BM + BN) rows
+// of K through its compute unit's L1 path when the chip is full; pick_forward takes the block that makes the sum
+// smallest.  512 x 2048 x 512: 9.6 us with 32 x 32 blocks (11.9 with 64 x 64; a wavefront per 32 x 32 block without
+// LDS took 17), 4,096 x 2048 x 512: 17.7 us with 128 x 64 (69), finish kernel included.
+// Stage layout: 16-byte chunk c of row r at position c ^ (r & 6) of its 128-byte row, which keeps the fragment reads
+// (lane -> row lane % 16, chunk lane / 16) free of bank conflicts by the serving rule given in ring_nt.h.
+template <int BM_, int BN_, int NS_>
+struct MidTile {
+    static constexpr int BM = BM_, BN = BN_, NS = NS_, NT = 256;
+    static constexpr int TI = BM / 32, TJ = BN / 32;
+    static constexpr int STAGE_BYTES = (BM + BN) * 128, LDS_BYTES = NS * STAGE_BYTES;
+    static constexpr int LA = BM / 32, LB = BN / 32, LOADS = LA + LB;   // load instructions (8 rows) per wave and stage
+};
 
-__global__ __launch_bounds__(kSmallThreads) void score_mlp_small_kernel(
-    const uint16_t* __restrict__ hidden, int64_t row_stride, const int64_t* __restrict__ row_index,
-    const uint16_t* __restrict__ w1, const float* __restrict__ b1, const float* __restrict__ w2, int n_rows, int d, int m,
-    int n_ub, float* __restrict__ partial, float* __restrict__ act_t, int64_t act_stride) {
-    const int lane = threadIdx.x & 63;
-    const int l31 = lane & 31, lh = lane >> 5;
-    const int ub = blockIdx.y;                      // unit block
-    const int r0 = blockIdx.x * 32, u0 = ub * 32;
-    int row = r0 + l31;
-    row = row < n_rows ? row : n_rows - 1;
-    int unit = u0 + l31;
-    unit = unit < m ? unit : m - 1;
-    const int64_t src = row_index ? row_index[row] : row;
-    const uint4* hp = reinterpret_cast<const uint4*>(hidden + src * row_stride + lh * 32);
-    const uint4* wp = reinterpret_cast<const uint4*>(w1 + static_cast<int64_t>(unit) * d + lh * 32);
-    const int n_kb = d / 64;                        // host: d is a multiple of 64
-    uint4 fa[kSmallDepth][4], fb[kSmallDepth][4];
-    auto load_block = [&](int slot, int kb) {       // 8 uint4 = one K64 block of this lane's two rows
+struct MlpMidArgs {
+    const uint16_t* hidden; int64_t row_stride; const int64_t* row_index;
+    const uint16_t* w1; const float* b1; const float* w2;
+    int n_rows, d, m;
+    float* partial;                          // [gridDim.y][n_rows]
+    float* act_t; int64_t act_stride;        // NULL, or relu(pre) for the gradient call, [m][act_stride]
+};
+
+template <class C>
+__global__ __launch_bounds__(C::NT, 2) void mlp_mid_kernel(MlpMidArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    typedef __attribute__((address_space(3))) void* lds_ptr_t;
+    constexpr int BM = C::BM, BN = C::BN, NS = C::NS, TI = C::TI, TJ = C::TJ;
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int u0 = blockIdx.y * BM, r0 = blockIdx.x * BN;
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    // loader: lane -> (row lane/8 of an 8-row group, position lane%8); rows past the end repeat the last one
+    const uint16_t* src[C::LOADS];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            fa[slot][q] = wp[kb * 8 + q];
-            fb[slot][q] = hp[kb * 8 + q];
+    for (int q = 0; q < C::LOADS; ++q) {
+        const bool is_a = q < C::LA;
+        const int r = (is_a ? wave * C::LA + q : wave * C::LB + q - C::LA) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ (r & 6);
+        if (is_a) {
+            const int u = u0 + r < a.m ? u0 + r : a.m - 1;
+            src[q] = a.w1 + static_cast<int64_t>(u) * a.d + c * 8;
+        } else {
+            const int row = r0 + r < a.n_rows ? r0 + r : a.n_rows - 1;
+            src[q] = a.hidden + (a.row_index ? a.row_index[row] : row) * a.row_stride + c * 8;
         }
+    }
+    const int n_k64 = a.d / 64;
+    int ld_k = 0, ld_slot = 0;
+    auto issue = [&]() {                     // the next stage; past the last one its lines again
+        const int64_t k = static_cast<int64_t>(ld_k) * 64;
+        const unsigned dst = lds0 + ld_slot * C::STAGE_BYTES;
+#pragma unroll
+        for (int q = 0; q < C::LOADS; ++q) {
+            const unsigned to = dst + (q < C::LA ? (wave * C::LA + q) * 1024 : BM * 128 + (wave * C::LB + q - C::LA) * 1024);
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src[q] + k), "s"(to) : "memory");
+        }
+        ld_slot = ld_slot + 1 == NS ? 0 : ld_slot + 1;
+        if (ld_k + 1 < n_k64) ++ld_k;
     };
+    f32x4 acc[TI][TJ];
 #pragma unroll
-    for (int s = 0; s < kSmallDepth; ++s)
-        if (s < n_kb) load_block(s, s);
-    f32x16 acc;
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (int kb0 = 0; kb0 < n_kb; kb0 += kSmallDepth) {
+        for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int a_off = (wm * (BM / 2) + l15) * 128, b_off = (BM + wn * (BN / 2) + l15) * 128;
+    const int pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
 #pragma unroll
-        for (int s = 0; s < kSmallDepth; ++s) {
-            const int kb = kb0 + s;
-            if (kb < n_kb) {                        // wave-uniform
+    for (int s = 0; s < NS - 1; ++s) issue();
+    int slot = 0;
+    for (int k = 0; k < n_k64; ++k) {
+        // this stage has landed (the NS - 2 after it may fly), for every wavefront, and all have read the one before
+        mlp_wait_vmcnt<(NS - 2) * C::LOADS>();
+        __syncthreads();
+        issue();
+        const unsigned char* st = lds + slot * C::STAGE_BYTES;
+        slot = slot + 1 == NS ? 0 : slot + 1;
+        bf16x8 fa[2][TI], fb[2][TJ];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[s][q]),
-                                                                  __builtin_bit_cast(bf16x8, fb[s][q]), acc, 0, 0, 0);
-                if (kb + kSmallDepth < n_kb) load_block(s, kb + kSmallDepth);
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) fa[h][i] = *reinterpret_cast<const bf16x8*>(st + a_off + i * 2048 + pos[h]);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) fb[h][j] = *reinterpret_cast<const bf16x8*>(st + b_off + j * 2048 + pos[h]);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // all reads first
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
+    }
+    // acc[i][j][v]: unit wm * BM/2 + i*16 + lq*4 + v, rollout wn * BN/2 + j*16 + l15 of the block
+    float part[TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) part[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int u = u0 + wm * (BM / 2) + i * 16 + lq * 4 + v;
+            const bool live = u < a.m;
+            const float bias = (live && a.b1) ? a.b1[u] : 0.f, w = live ? a.w2[u] : 0.f;
+            float* arow = a.act_t ? a.act_t + static_cast<int64_t>(live ? u : 0) * a.act_stride : nullptr;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const float act = fmaxf(acc[i][j][v] + bias, 0.f);
+                part[j] = fmaf(act, w, part[j]);
+                const int col = r0 + wn * (BN / 2) + j * 16 + l15;
+                if (arow && live && col < a.n_rows) arow[col] = act;
             }
         }
-    }
-    // acc[v] = pre-activation of unit u0 + (v/4)*8 + lh*4 + v%4 for rollout r0 + l31
-    float part = 0.f;
+    mlp_wait_vmcnt<0>();
+    __syncthreads();                         // every stage has been read and every load into LDS has landed
+    float* red = reinterpret_cast<float*>(lds);   // [2][BN]
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int u = u0 + (v >> 2) * 8 + lh * 4 + (v & 3);
-        const bool live = u < m;
-        const float bias = (live && b1) ? b1[u] : 0.f;
-        const float w = live ? w2[u] : 0.f;
-        const float act = fmaxf(acc[v] + bias, 0.f);
-        part = fmaf(act, w, part);
-        // the gradient call keeps relu(pre), unit-major (see mlp_delta_kernel)
-        if (act_t && live && r0 + l31 < n_rows) act_t[static_cast<int64_t>(u) * act_stride + r0 + l31] = act;
+    for (int j = 0; j < TJ; ++j) {
+        part[j] += __shfl_xor(part[j], 16, ARROL_WAVE);
+        part[j] += __shfl_xor(part[j], 32, ARROL_WAVE);
+        if (lq == 0) red[wm * BN + wn * (BN / 2) + j * 16 + l15] = part[j];
     }
-    part += __shfl_xor(part, 32, ARROL_WAVE);       // the two lane halves hold different units of one rollout
-    if (lh == 0 && r0 + l31 < n_rows) partial[static_cast<int64_t>(ub) * n_rows + r0 + l31] = part;
+    __syncthreads();
+    if (tid < BN && r0 + tid < a.n_rows)
+        a.partial[static_cast<int64_t>(blockIdx.y) * a.n_rows + r0 + tid] = red[tid] + red[BN + tid];
 }
 
-__global__ __launch_bounds__(256) void score_mlp_small_finish_kernel(const float* __restrict__ partial, int n_ub,
+template <class C>
+int launch_mlp_mid(const MlpMidArgs& a, hipStream_t st) {
+    static arrol_device_flags ok;
+    if (!arrol_allow_lds(&mlp_mid_kernel<C>, C::LDS_BYTES, ok)) return ARROL_EHIP;
+    arrol_launch(mlp_mid_kernel<C>, dim3((a.n_rows + C::BN - 1) / C::BN, (a.m + C::BM - 1) / C::BM), dim3(C::NT), C::LDS_BYTES, st, a);
+    return ARROL_OK;
+}
+
+// The unit blocks' partial scores of rollout i in index order, eight loads in flight.
+__device__ __forceinline__ float sum_unit_blocks(const float* __restrict__ partial, int n_ub, int n_rows, int i) {
+    float s = 0.f;
+    for (int ub0 = 0; ub0 < n_ub; ub0 += 8) {
+        float x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = ub0 + q < n_ub ? partial[static_cast<int64_t>(ub0 + q) * n_rows + i] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += x[q];
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(256) void score_mlp_finish_kernel(const float* __restrict__ partial, int n_ub,
                                                                      int n_rows, float b2, float* __restrict__ score_out,
                                                                      float* __restrict__ prob_out) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_rows) return;
-    float s = 0.f;
-    for (int ub = 0; ub < n_ub; ++ub) s += partial[static_cast<int64_t>(ub) * n_rows + i];
-    s += b2;
+    const float s = sum_unit_blocks(partial, n_ub, n_rows, i) + b2;
     float q;
     if (s >= 0.f) {
         q = 1.f / (1.f + expf(-s));
@@ -422,8 +496,7 @@ __global__ __launch_bounds__(256) void score_mlp_small_finish_kernel(const float
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Large batches (more than kSmallMaxRows rollouts, d a multiple of 64, rows addressed without row_index):
-// the contractions on the 8-wavefront direct-to-LDS ring pipeline of ring_nt.h (v_mfma_f32_16x16x32_bf16), one
+// Large batches (d a multiple of 64, rows addressed without row_index; pick_forward): the contractions on the 8-wavefront direct-to-LDS ring pipeline of ring_nt.h (v_mfma_f32_16x16x32_bf16), one
 // 256 x 256 accumulator tile per workgroup: grid = (blocks of 256 B rows, tiles of 256 A rows, K splits).
 //   forward  A = W1 [m, d], B = hidden [N, d]: bias + ReLU + w2 dot per rollout (lane-local over the
 //            units), partial scores [unit tile][rollout] to the workspace, summed by the finish kernel;
@@ -532,9 +605,59 @@ int launch_mlp_ring(const MlpRingArgs& a, dim3 grid, hipStream_t st) {
     return ARROL_OK;
 }
 
-// the ring kernels address a lane's row with a 32-bit byte offset inside a 256-row tile
-bool ring_applies(int n_rows, int d, int64_t row_stride_elems, const int64_t* row_index) {
-    return n_rows > kSmallMaxRows && d % 64 == 0 && row_index == nullptr && row_stride_elems * 2 * 256 < (1ll << 31);
+using Mid32 = MidTile<32, 32, 8>;
+using Mid64 = MidTile<64, 64, 4>;
+using Mid128 = MidTile<128, 64, 3>;
+
+enum ForwardPath { kPathTile, kPathMid32, kPathMid64, kPathMid128, kPathRing };
+
+int64_t n_blocks(int n_rows, int m, int bn, int bm) { return static_cast<int64_t>((n_rows + bn - 1) / bn) * ((m + bm - 1) / bm); }
+
+// Which forward pass a batch takes: the smallest of the measured times (microseconds at d = 2048, all proportional to d)
+// for up to 256 workgroups and for every 512 (the mid kernels, two workgroups per compute unit) or 256 (ring) beyond.
+// m = 512: 32 x 32 blocks up to some 700 rollouts, 64 x 64 up to 2,048, 128 x 64 up to 10,000, then the ring (at 8,192
+// rollouts 28 us against 43 of the ring; at 16,384 49 against 45).
+ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, const int64_t* row_index) {
+    if (d % 64) return kPathTile;
+    constexpr int kMaxGridY = 65535;         // unit blocks are blockIdx.y
+    auto mid = [&](int bn, int bm, double one, double two) {
+        const int64_t n = n_blocks(n_rows, m, bn, bm);
+        if ((m + bm - 1) / bm > kMaxGridY) return 1e30;
+        return n <= 256 ? one : two * static_cast<double>((n + 511) / 512);
+    };
+    const double t32 = mid(32, 32, 5.0, 8.3), t64 = mid(64, 64, 7.8, 15.5), t128 = mid(64, 128, 12.5, 22.5);
+    ForwardPath best = kPathTile;
+    double t = 1e29;
+    if (t32 < t) { t = t32; best = kPathMid32; }
+    if (t64 < t) { t = t64; best = kPathMid64; }
+    if (t128 < t) { t = t128; best = kPathMid128; }
+    // the ring kernel addresses a lane's row with a 32-bit byte offset inside a 256-row tile
+    if (row_index == nullptr && row_stride_elems * 2 * 256 < (1ll << 31) && (m + 255) / 256 <= kMaxGridY) {
+        const int64_t n = n_blocks(n_rows, m, 256, 256);
+        const double tr = n <= 192 ? 38.0 : 50.0 * static_cast<double>((n + 255) / 256);
+        if (tr < t) best = kPathRing;
+    }
+    return best;
+}
+int unit_block(ForwardPath p) { return p == kPathMid32 ? 32 : p == kPathMid64 ? 64 : p == kPathMid128 ? 128 : 256; }
+
+// Partial scores of every unit block to `partial`, with act_t also the activations (kPathTile: not for this).
+int enqueue_forward(ForwardPath path, const void* hidden, int64_t row_stride_elems, const int64_t* row_index, const void* w1,
+                    const float* b1, const float* w2, int n_rows, int d, int m, float* partial, float* act_t,
+                    int64_t act_stride, hipStream_t st) {
+    if (path == kPathRing) {
+        MlpRingArgs r = {};
+        r.a = static_cast<const uint16_t*>(w1); r.a_stride = static_cast<unsigned>(d) * 2; r.a_rows = m;
+        r.b = static_cast<const uint16_t*>(hidden); r.b_stride = static_cast<unsigned>(row_stride_elems * 2); r.b_rows = n_rows;
+        r.n_k64 = d / 64; r.b1 = b1; r.w2 = w2; r.partial = partial;
+        r.act_t = act_t; r.act_stride = act_stride;
+        const dim3 grid((n_rows + 255) / 256, (m + 255) / 256);
+        return act_t ? launch_mlp_ring<kForwardKeep>(r, grid, st) : launch_mlp_ring<kForward>(r, grid, st);
+    }
+    MlpMidArgs a = {static_cast<const uint16_t*>(hidden), row_stride_elems, row_index, static_cast<const uint16_t*>(w1), b1, w2,
+                    n_rows, d, m, partial, act_t, act_stride};
+    if (path == kPathMid32) return launch_mlp_mid<Mid32>(a, st);
+    return path == kPathMid64 ? launch_mlp_mid<Mid64>(a, st) : launch_mlp_mid<Mid128>(a, st);
 }
 
 // dL/dW1 on the ring pipeline's K-major B form: any batch size, rows addressed in place
@@ -573,7 +696,7 @@ __global__ __launch_bounds__(1024) void mlp_residual_kernel(const float* __restr
 }
 
 // The gradient call after a forward pass that leaves partial scores (partial[unit block][rollout]):
-// score_mlp_small_finish_kernel and mlp_residual_kernel in one launch - score = sum over the unit blocks in index
+// score_mlp_finish_kernel and mlp_residual_kernel in one launch - score = sum over the unit blocks in index
 // order + b2, then r_i and the loss terms as above; neither scores nor probabilities go to memory.
 __global__ __launch_bounds__(1024) void mlp_finish_residual_kernel(const float* __restrict__ partial, int n_ub,
                                                                    float b2, const float* __restrict__ labels,
@@ -584,9 +707,7 @@ __global__ __launch_bounds__(1024) void mlp_finish_residual_kernel(const float* 
     float loss = 0.f, rs = 0.f;
     const int i = blockIdx.x * 1024 + threadIdx.x;
     if (i < n_rows) {
-        float s = 0.f;
-        for (int ub = 0; ub < n_ub; ++ub) s += partial[static_cast<int64_t>(ub) * n_rows + i];
-        s += b2;
+        const float s = sum_unit_blocks(partial, n_ub, n_rows, i) + b2;
         float q;
         if (s >= 0.f) {
             q = 1.f / (1.f + expf(-s));
@@ -761,9 +882,9 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
     p.off_unit = o;  o = align256(o + sizeof(float) * static_cast<size_t>(p.n_rb) * 2 * m);
     p.off_slab = o;
     if (p.splits * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(p.splits) * mt * d);
-    p.off_small = o;                      // partial scores of the small-batch / ring forward pass
+    p.off_small = o;                      // partial scores of the mid / ring forward pass
     if (d % 64 == 0) {
-        const size_t blocks = n_rows <= kSmallMaxRows ? (m + 31) / 32 : (m + 255) / 256;
+        const size_t blocks = (m + 31) / 32;          // of the forward pass with the smallest ones
         o = align256(o + sizeof(float) * blocks * n_rows);
     }
     // ring wgrad: 256-column blocks; K split so that about 256 workgroups run, at most 8 partial slabs
@@ -778,7 +899,7 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
     p.r_splits = (p.n_kc + p.r_k64_per_split - 1) / p.r_k64_per_split;
     p.off_rslab = o;
     if (d % 64 == 0 && p.r_splits * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(p.r_splits) * mt * d);
-    p.off_act = o;                        // small-batch / ring forward pass: kept activations, fp32 [m][n_pad]
+    p.off_act = o;                        // mid / ring forward pass: kept activations, fp32 [m][n_pad]
     if (d % 64 == 0) o = align256(o + sizeof(float) * static_cast<size_t>(m) * p.n_pad);
     p.total = o;
     return p;
@@ -802,8 +923,7 @@ int launch_mlp(const MlpArgs& a, dim3 grid, hipStream_t st) {
 extern "C" size_t arrol_score_mlp_workspace_bytes(int32_t n_rows, int32_t d, int32_t m) {
     if (n_rows < 1 || d < 8 || m < 1) return 0;
     if (d % 64) return 0;   // the one-launch tile kernel needs no scratch
-    const size_t blocks = n_rows <= kSmallMaxRows ? (m + 31) / 32 : (m + 255) / 256;   // unit blocks of the two paths
-    return align256(sizeof(float) * blocks * n_rows);
+    return align256(sizeof(float) * static_cast<size_t>((m + 31) / 32) * n_rows);   // smallest unit blocks of the forward passes
 }
 
 extern "C" int arrol_score_mlp(const void* hidden, int64_t row_stride_elems, const int64_t* row_index,
@@ -815,30 +935,14 @@ extern "C" int arrol_score_mlp(const void* hidden, int64_t row_stride_elems, con
     if (!hidden || !w1 || !w2 || !prob_out || !arrol_aligned16(hidden) || !arrol_aligned16(w1)) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t need = arrol_score_mlp_workspace_bytes(n_rows, d, m);
-    if (need > 0 && workspace && arrol_aligned16(workspace) && workspace_bytes >= need &&
-        ring_applies(n_rows, d, row_stride_elems, row_index)) {
-        // large batch: one 256 x 256 tile per workgroup on the ring pipeline, then the sum over the unit tiles
-        const int n_vt = (m + 255) / 256;
-        MlpRingArgs r = {};
-        r.a = static_cast<const uint16_t*>(w1); r.a_stride = static_cast<unsigned>(d) * 2; r.a_rows = m;
-        r.b = static_cast<const uint16_t*>(hidden); r.b_stride = static_cast<unsigned>(row_stride_elems * 2); r.b_rows = n_rows;
-        r.n_k64 = d / 64; r.b1 = b1; r.w2 = w2; r.partial = static_cast<float*>(workspace);
-        const int rc = launch_mlp_ring<kForward>(r, dim3((n_rows + 255) / 256, n_vt), st);
+    const ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
+    if (path != kPathTile && workspace && arrol_aligned16(workspace) && workspace_bytes >= need) {
+        float* partial = static_cast<float*>(workspace);
+        const int rc = enqueue_forward(path, hidden, row_stride_elems, row_index, w1, b1, w2, n_rows, d, m, partial, nullptr, 0, st);
         if (rc != ARROL_OK) return rc;
         if (arrol_launch_failed()) return arrol_launch_status();
-        arrol_launch(score_mlp_small_finish_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, r.partial, n_vt,
-                     n_rows, b2, score_out, prob_out);
-        return arrol_launch_status();
-    }
-    if (need > 0 && n_rows <= kSmallMaxRows && workspace && arrol_aligned16(workspace) && workspace_bytes >= need) {
-        // small batch: one wavefront per 32 x 32 block of pre-activations, then the sum over the unit blocks
-        const int n_ub = (m + 31) / 32;
-        float* partial = static_cast<float*>(workspace);
-        arrol_launch(score_mlp_small_kernel, dim3((n_rows + 31) / 32, n_ub), dim3(kSmallThreads), 0, st,
-                     static_cast<const uint16_t*>(hidden), row_stride_elems, row_index, static_cast<const uint16_t*>(w1),
-                     b1, w2, n_rows, d, m, n_ub, partial, static_cast<float*>(nullptr), static_cast<int64_t>(0));
-        if (arrol_launch_failed()) return arrol_launch_status();
-        arrol_launch(score_mlp_small_finish_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, partial, n_ub,
+        const int ub = unit_block(path);
+        arrol_launch(score_mlp_finish_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, partial, (m + ub - 1) / ub,
                      n_rows, b2, score_out, prob_out);
         return arrol_launch_status();
     }
@@ -892,36 +996,23 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     float* unit = reinterpret_cast<float*>(ws + p.off_unit);
     float* slab = reinterpret_cast<float*>(ws + p.off_slab);
 
-    // forward pass.  Batches beyond kSmallMaxRows rows: the ring pipeline; smaller ones: one wavefront per block;
-    // both keep relu(pre) for the backward pass.  Otherwise (d not a multiple of 64, or gathered rows of a large
-    // batch) the one-launch tile kernel, whose pre-activations are recomputed below.
+    // forward pass: relu(pre) is kept for the backward pass; only with d not a multiple of 64 the one-launch tile
+    // kernel runs, whose pre-activations are recomputed below
     MlpArgs a = {};
     a.hidden = static_cast<const uint16_t*>(hidden); a.row_stride = row_stride_elems; a.row_index = row_index;
     a.w1 = static_cast<const uint16_t*>(w1); a.a_stride = d; a.b1 = b1; a.w2 = w2; a.b2 = b2;
     a.n_rows = n_rows; a.d = d; a.m = m; a.score_out = score; a.prob_out = prob;
     float* act = reinterpret_cast<float*>(ws + p.off_act);
     float* partial = reinterpret_cast<float*>(ws + p.off_small);
-    bool kept = true;
-    int rc = ARROL_OK, n_ub = 0;
-    if (ring_applies(n_rows, d, row_stride_elems, row_index)) {
-        MlpRingArgs r = {};
-        r.a = a.w1; r.a_stride = static_cast<unsigned>(d) * 2; r.a_rows = m;
-        r.b = a.hidden; r.b_stride = static_cast<unsigned>(row_stride_elems * 2); r.b_rows = n_rows;
-        r.n_k64 = d / 64; r.b1 = b1; r.w2 = w2; r.partial = partial;
-        r.act_t = act; r.act_stride = p.n_pad;
-        rc = launch_mlp_ring<kForwardKeep>(r, dim3((n_rows + 255) / 256, p.r_vt), st);
-        if (rc != ARROL_OK) return rc;
-        n_ub = p.r_vt;
-    } else if (d % 64 == 0 && n_rows <= kSmallMaxRows) {
-        n_ub = (m + 31) / 32;
-        arrol_launch(score_mlp_small_kernel, dim3((n_rows + 31) / 32, n_ub), dim3(kSmallThreads), 0, st,
-                     a.hidden, row_stride_elems, row_index, a.w1, b1, w2, n_rows, d, m, n_ub, partial, act,
-                     static_cast<int64_t>(p.n_pad));
-    } else {
-        kept = false;
+    const ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
+    const bool kept = path != kPathTile;
+    int rc;
+    if (kept)
+        rc = enqueue_forward(path, hidden, row_stride_elems, row_index, w1, b1, w2, n_rows, d, m, partial, act, p.n_pad, st);
+    else
         rc = launch_mlp<kForward>(a, dim3(p.n_rb), st);
-        if (rc != ARROL_OK) return rc;
-    }
+    if (rc != ARROL_OK) return rc;
+    const int n_ub = (m + unit_block(path) - 1) / unit_block(path);
     if (arrol_launch_failed()) return arrol_launch_status();
     if (kept) {
         // scores from the partials, residuals and loss terms in one launch; delta^T, the per-unit sums, the loss

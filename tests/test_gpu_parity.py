@@ -380,6 +380,26 @@ def test_score_mlp_matches_oracle(A, n, d, m):
     assert np.max(np.abs(npy(s_nb) - so_nb)) < 1e-3
 
 
+# the dispatch by size (d a multiple of 64): 32 x 32 blocks, 64 x 64, 128 x 64 and the 256 x 256 ring form, each with
+# remainders on both sides and fewer K64 steps than pipeline stages; gathered rows take all but the ring form
+@pytest.mark.parametrize("gather", [False, True])
+@pytest.mark.parametrize("n,d,m", [(1, 64, 1), (33, 192, 31), (500, 704, 40), (1030, 64, 520), (1500, 320, 450), (2900, 128, 513),
+                                   (4100, 192, 260), (20000, 64, 300)])
+def test_score_mlp_dispatch_by_size(A, n, d, m, gather):
+    say("score_mlp dispatch n=%d d=%d m=%d gather=%d" % (n, d, m, gather))
+    g = torch.Generator(device=DEV); g.manual_seed(2 * n + d + m)
+    hidden = torch.randn(n + 37, d + 64, generator=g, device=DEV).to(torch.bfloat16)[:, :d]      # rows wider than d
+    idx = torch.randint(0, n + 37, (n,), generator=g, device=DEV, dtype=torch.int64) if gather else None
+    rows = hidden[idx] if gather else hidden[:n]
+    w1 = (torch.randn(m, d, generator=g, device=DEV) * d ** -0.5).to(torch.bfloat16)
+    b1 = torch.randn(m, generator=g, device=DEV) * 0.1
+    w2 = torch.randn(m, generator=g, device=DEV) * m ** -0.5
+    s, q = A.arrol_score_mlp(hidden if gather else hidden[:n], w1, b1, w2, b2=0.25, row_index=idx)
+    torch.cuda.synchronize()
+    so, qo = O.score_mlp(bits(rows), bits(w1), npy(b1), npy(w2), 0.25)
+    assert np.max(np.abs(npy(s) - so)) < SCORE_DERIVED and np.max(np.abs(npy(q) - qo)) < SCORE_DERIVED / 4
+
+
 def test_score_mlp_gathered_rows_and_dead_units(A):
     g = torch.Generator(device=DEV); g.manual_seed(8)
     big = torch.randn(200, 512, generator=g, device=DEV).to(torch.bfloat16)
