@@ -605,6 +605,127 @@ int launch_mlp_ring(const MlpRingArgs& a, dim3 grid, hipStream_t st) {
     return ARROL_OK;
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// dL/dW1 = delta^T . H over the rollouts where the ring form has too few 256 x 256 tiles to fill the chip: 128 rows of
+// [hi; lo] delta^T x 64 columns per workgroup, K (rollouts) split over gridDim.z, the same stages as mlp_mid_kernel.  The
+// hidden states are read in place: a stage holds 64 rollouts x 128 bytes, and the B fragments come out through the
+// transposing LDS read (lane layout as in ring_nt.h).  16-byte chunk c of rollout row r sits at position
+// c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different 8-byte bank pairs.
+// 4,096 x 2048 x 512: 128 tiles x 2 splits; the ring form's 16 tiles x 8 splits took 21.6 us and left 8 partial slabs.
+struct WgradMid {
+    static constexpr int BM = 128, BN = 64, NS = 3, NT = 256, TI = 4, TJ = 2;
+    static constexpr int STAGE_BYTES = (BM + BN) * 128, LDS_BYTES = NS * STAGE_BYTES;
+    static constexpr int LA = 4, LB = 2, LOADS = LA + LB;
+};
+
+__global__ __launch_bounds__(WgradMid::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a) {
+    using C = WgradMid;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    typedef __attribute__((address_space(3))) void* lds_ptr_t;
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4* lds_s16x4_t;
+    constexpr int NS = C::NS, TI = C::TI, TJ = C::TJ;
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int u0 = blockIdx.y * C::BM, c0 = blockIdx.x * C::BN;
+    const int k64_lo = static_cast<int>(blockIdx.z) * a.k64_per_split;
+    const int k64_hi = k64_lo + a.k64_per_split < a.n_k64 ? k64_lo + a.k64_per_split : a.n_k64;   // > k64_lo (host)
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    const uint16_t* src_a[C::LA];
+#pragma unroll
+    for (int q = 0; q < C::LA; ++q) {
+        const int r = (wave * C::LA + q) * 8 + (lane >> 3);
+        const int u = u0 + r < a.a_rows ? u0 + r : a.a_rows - 1;
+        src_a[q] = a.a + static_cast<int64_t>(u) * (a.a_stride / 2) + ((lane & 7) ^ (r & 6)) * 8;
+    }
+    int b_row[C::LB];                        // rollout of the stage and first column of this lane's chunk
+    int64_t b_col[C::LB];
+#pragma unroll
+    for (int q = 0; q < C::LB; ++q) {
+        const int r = (wave * C::LB + q) * 8 + (lane >> 3);
+        const int c = c0 + ((lane & 7) ^ (((r >> 1) & 1) << 1) ^ (((r >> 3) & 1) << 2)) * 8;
+        b_row[q] = r;
+        b_col[q] = c < a.b_rows ? c : a.b_rows - 8;      // columns past the end repeat the last chunk (d % 64 == 0)
+    }
+    int ld_k = k64_lo, ld_slot = 0;
+    auto issue = [&]() {                     // the next stage; past the last one its lines again
+        const unsigned dst = lds0 + ld_slot * C::STAGE_BYTES;
+#pragma unroll
+        for (int q = 0; q < C::LA; ++q)
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_a[q] + static_cast<int64_t>(ld_k) * 64),
+                         "s"(dst + (wave * C::LA + q) * 1024) : "memory");
+#pragma unroll
+        for (int q = 0; q < C::LB; ++q) {
+            int k = ld_k * 64 + b_row[q];                // rollouts past the last one repeat it: delta^T is zero there
+            k = k < a.b_k_rows ? k : a.b_k_rows - 1;
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(a.b + static_cast<int64_t>(k) * (a.b_stride / 2) + b_col[q]),
+                         "s"(dst + C::BM * 128 + (wave * C::LB + q) * 1024) : "memory");
+        }
+        ld_slot = ld_slot + 1 == NS ? 0 : ld_slot + 1;
+        if (ld_k + 1 < k64_hi) ++ld_k;
+    };
+    f32x4 acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int a_off = (wm * 64 + l15) * 128;
+    const int pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
+    // lane 16 lq + 4 e + q addresses rollout 32 h + 8 lq + 4 h2 + e, columns wn*32 + 16 j + 4 q .. + 3
+    const int e = l15 >> 2, cq = l15 & 3;
+    int bt[2];
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+        const int chunk = (wn * 4 + (cq >> 1)) ^ ((e >> 1) << 1) ^ ((lq & 1) << 2);
+        bt[h2] = C::BM * 128 + (8 * lq + 4 * h2 + e) * 128 + chunk * 16 + (cq & 1) * 8;
+    }
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) issue();
+    int slot = 0;
+    for (int k = k64_lo; k < k64_hi; ++k) {
+        // this stage has landed (the NS - 2 after it may fly), for every wavefront, and all have read the one before
+        mlp_wait_vmcnt<(NS - 2) * C::LOADS>();
+        __syncthreads();
+        issue();
+        const unsigned char* st = lds + slot * C::STAGE_BYTES;
+        slot = slot + 1 == NS ? 0 : slot + 1;
+        bf16x8 fa[2][TI], fb[2][TJ];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) fa[h][i] = *reinterpret_cast<const bf16x8*>(st + a_off + i * 2048 + pos[h]);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {               // block j is two chunks on: an XOR (they commute with the swizzle)
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t)(st + h * 4096 + (bt[0] ^ (j << 5))));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t)(st + h * 4096 + (bt[1] ^ (j << 5))));
+                fb[h][j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // all reads first
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
+    }
+    mlp_wait_vmcnt<0>();                     // no load into LDS outlives the workgroup
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int u = u0 + wm * 64 + i * 16 + lq * 4 + v;
+            if (u >= a.a_rows) continue;
+            float* crow = a.c_out + (static_cast<int64_t>(blockIdx.z) * a.a_rows + u) * a.c_stride;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int col = c0 + wn * 32 + j * 16 + l15;
+                if (col < a.b_rows) crow[col] = acc[i][j][v];
+            }
+        }
+}
+
 using Mid32 = MidTile<32, 32, 8>;
 using Mid64 = MidTile<64, 64, 4>;
 using Mid128 = MidTile<128, 64, 3>;
@@ -849,7 +970,8 @@ __global__ __launch_bounds__(256) void mlp_transpose_kernel(const uint16_t* __re
 
 struct GradPlan {
     int n_rb, n_pad, n_cb, n_groups, n_kc, splits, kc_per_split;
-    int r_cb, r_vt, r_gt, r_splits, r_k64_per_split;
+    int r_cb, r_gt, r_splits, r_k64_per_split;
+    bool w_mid;                        // dL/dW1 of rows read in place: mid kernel instead of the ring form
     size_t off_score, off_prob, off_resid, off_bsum, off_ht, off_dt, off_unit, off_slab, off_small, off_rslab, off_act, total;
 };
 
@@ -887,22 +1009,70 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
         const size_t blocks = (m + 31) / 32;          // of the forward pass with the smallest ones
         o = align256(o + sizeof(float) * blocks * n_rows);
     }
-    // ring wgrad: 256-column blocks; K split so that about 256 workgroups run, at most 8 partial slabs
+    // rows read in place: kernel and K split with the smallest estimate (microseconds: the measured time per K64 step of
+    // a workgroup when the chip is full, a start of 5 or 7, and the partial slabs written and read once at 4.5 TB/s)
     p.r_cb = (d + 255) / 256;
-    p.r_vt = (m + 255) / 256;          // forward pass
     p.r_gt = (mt + 255) / 256;         // dL/dW1
-    int rs = 256 / (p.r_cb * p.r_gt);
-    if (rs > p.n_kc / 8) rs = p.n_kc / 8;
-    if (rs > 8) rs = 8;
-    if (rs < 1) rs = 1;
-    p.r_k64_per_split = (p.n_kc + rs - 1) / rs;
-    p.r_splits = (p.n_kc + p.r_k64_per_split - 1) / p.r_k64_per_split;
+    const int n_k64 = (n_rows + 63) / 64;
+    const double slab_us = static_cast<double>(mt) * d * 8.0 / 4.5e6;
+    const int64_t ring_tiles = static_cast<int64_t>(p.r_cb) * p.r_gt;
+    const int64_t mid_tiles = static_cast<int64_t>((d + WgradMid::BN - 1) / WgradMid::BN) * ((mt + WgradMid::BM - 1) / WgradMid::BM);
+    double best = -1.0;
+    for (int s = 1; s <= 16 && (s == 1 || n_k64 / s >= 4); ++s) {
+        const int per = (n_k64 + s - 1) / s, used = (n_k64 + per - 1) / per;
+        const double slabs = used * terms > 1 ? 2.5 + used * slab_us : 0.0;
+        const int64_t nr = ring_tiles * used, nm = mid_tiles * used;
+        const double ring = static_cast<double>((nr + 255) / 256) * (per * 1.45 + 7.0) + slabs;
+        const double mid = (mt + WgradMid::BM - 1) / WgradMid::BM > 65535 ? 1e30
+                           : (nm <= 256 ? per * 0.38 + 5.0 : static_cast<double>((nm + 511) / 512) * (per * 0.68 + 5.0)) + slabs;
+        const double t = mid < ring ? mid : ring;
+        if (best < 0.0 || t < best) { best = t; p.w_mid = mid < ring; p.r_k64_per_split = per; p.r_splits = used; }
+    }
     p.off_rslab = o;
     if (d % 64 == 0 && p.r_splits * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(p.r_splits) * mt * d);
     p.off_act = o;                        // mid / ring forward pass: kept activations, fp32 [m][n_pad]
     if (d % 64 == 0) o = align256(o + sizeof(float) * static_cast<size_t>(m) * p.n_pad);
     p.total = o;
     return p;
+}
+
+// out = the slabs' sum in slab order; 16 bytes per lane where the caller's output allows it (the slabs always do: m * d
+// is a multiple of 8).  9 slabs of 4 MB (4,096 x 2048 x 512 with 8 splits): 15 us at 4 bytes per lane in 128-byte rows.
+template <int VEC>
+__global__ __launch_bounds__(256) void reduce_slabs_kernel(const float* __restrict__ slabs, int n_slabs, int64_t width,
+                                                           float* __restrict__ out) {
+    const int64_t c = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * VEC;
+    if (c >= width) return;
+    float s[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) s[v] = 0.f;
+    for (int p0 = 0; p0 < n_slabs; p0 += 4) {
+        float x[4][VEC];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float* src = slabs + static_cast<int64_t>(p0 + q < n_slabs ? p0 + q : p0) * width + c;
+            if constexpr (VEC == 4) {
+                const float4 f = *reinterpret_cast<const float4*>(src);
+                x[q][0] = f.x; x[q][1] = f.y; x[q][2] = f.z; x[q][3] = f.w;
+            } else {
+                x[q][0] = src[0];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (p0 + q < n_slabs) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) s[v] += x[q][v];
+            }
+    }
+    if constexpr (VEC == 4) *reinterpret_cast<float4*>(out + c) = make_float4(s[0], s[1], s[2], s[3]);
+    else out[c] = s[0];
+}
+void launch_reduce_slabs(const float* slabs, int n_slabs, int64_t width, float* out, hipStream_t st) {
+    if (arrol_aligned16(out))
+        arrol_launch(reduce_slabs_kernel<4>, dim3(static_cast<unsigned>((width / 4 + 255) / 256)), dim3(256), 0, st, slabs, n_slabs, width, out);
+    else
+        arrol_launch(reduce_slabs_kernel<1>, dim3(static_cast<unsigned>((width + 255) / 256)), dim3(256), 0, st, slabs, n_slabs, width, out);
 }
 
 template <int MODE>
@@ -1045,11 +1215,17 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
         g.b_rows = d; g.b_k_rows = n_rows;
         g.n_k64 = (n_rows + 63) / 64; g.k64_per_split = p.r_k64_per_split;
         g.c_out = n_slabs > 1 ? rslab : grad_w1; g.c_stride = d;
-        rc = launch_mlp_ring<kWgrad>(g, dim3(p.r_cb, p.r_gt, p.r_splits), st);
-        if (rc != ARROL_OK) return rc;
+        if (p.w_mid) {
+            static arrol_device_flags ok;
+            if (!arrol_allow_lds(&mlp_wgrad_mid_kernel, WgradMid::LDS_BYTES, ok)) return ARROL_EHIP;
+            arrol_launch(mlp_wgrad_mid_kernel, dim3((d + WgradMid::BN - 1) / WgradMid::BN, (mt + WgradMid::BM - 1) / WgradMid::BM, p.r_splits),
+                         dim3(WgradMid::NT), WgradMid::LDS_BYTES, st, g);
+        } else {
+            rc = launch_mlp_ring<kWgrad>(g, dim3(p.r_cb, p.r_gt, p.r_splits), st);
+            if (rc != ARROL_OK) return rc;
+        }
         if (n_slabs > 1)
-            arrol_launch(reduce_rows_f32_kernel<0>, dim3(static_cast<unsigned>((width + 31) / 32)), dim3(256), 0, st,
-                         rslab, n_slabs, width, width, 1.f, grad_w1);
+            launch_reduce_slabs(rslab, n_slabs, width, grad_w1, st);
         return arrol_launch_status();
     }
     // gathered rows or d not a multiple of 64: H^T, then the tile kernel
@@ -1064,7 +1240,6 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     rc = launch_mlp<kWgrad>(g, dim3(p.n_cb, p.splits, p.n_groups), st);
     if (rc != ARROL_OK) return rc;
     if (n_slabs > 1)
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3(static_cast<unsigned>((width + 31) / 32)), dim3(256), 0, st,
-                     slab, n_slabs, width, width, 1.f, grad_w1);
+        launch_reduce_slabs(slab, n_slabs, width, grad_w1, st);
     return arrol_launch_status();
 }

@@ -224,6 +224,33 @@ def test_score_mlp_grad_two_term_delta_is_fp32_accurate(A, n, d, m):
     assert e2 < 0.05 * e1, (e1, e2)
 
 
+# dL/dW1 in 128 x 64 blocks: rollouts that end inside a K64 step or just past one, units that end inside a block, one
+# and several K splits (one and two partial slabs), two-term delta; the last size goes to the 256 x 256 ring form
+@pytest.mark.parametrize("n,d,m,terms", [(1, 64, 1, 1), (63, 64, 127, 1), (65, 192, 129, 2), (129, 128, 128, 1), (1025, 64, 300, 1),
+                                         (2100, 192, 70, 2), (16384, 1024, 512, 1)])
+def test_score_mlp_grad_weight_gradient_blocks(A, n, d, m, terms):
+    print("[case] score_mlp_grad blocks n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=7 * n + d + m)
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.5, labels, delta_terms=terms)
+
+
+def test_score_mlp_grad_into_a_buffer_that_is_only_4_byte_aligned(A):
+    """dL/dW1 is fp32 [m, d] at any 4-byte address: the sum of the partial slabs must not assume 16."""
+    print("[case] score_mlp_grad unaligned output", flush=True)
+    n, d, m = 2100, 192, 70
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=77)
+    ref = A.arrol_score_mlp_grad(hidden, w1, b1, w2, 0.0, labels)
+    L = A.lib()
+    ws = torch.empty(L.arrol_score_mlp_grad_workspace_bytes(n, d, m, 1), dtype=torch.uint8, device=DEV)
+    flat = torch.zeros(m * d + 2, device=DEV)
+    gb, gw2 = torch.empty(m, device=DEV), torch.empty(m, device=DEV)
+    rc = L.arrol_score_mlp_grad(hidden.data_ptr(), d, None, w1.data_ptr(), b1.data_ptr(), w2.data_ptr(), 0.0, labels.data_ptr(), n, d, m,
+                                None, flat.data_ptr() + 4, gb.data_ptr(), gw2.data_ptr(), None, 1, ws.data_ptr(), ws.numel(),
+                                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(flat[1:-1].view(m, d), ref["grad_w1"]) and flat[0] == 0 and flat[-1] == 0
+
+
 def test_score_mlp_grad_two_term_delta_gathered_rows(A):
     print("[case] score_mlp_grad two-term gathered", flush=True)
     hidden, w1, b1, w2, _ = mlp_case(200, 128, 96, seed=5)
