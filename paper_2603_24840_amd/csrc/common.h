@@ -62,37 +62,62 @@ static inline bool arrol_allow_lds(K kernel, int bytes, arrol_device_flags& done
 
 static inline bool arrol_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// 64-bit lane exchange built from two 32-bit shuffles.
-__device__ __forceinline__ int64_t shfl_xor_i64(int64_t v, int mask) {
-    int lo = __shfl_xor(static_cast<int>(v & 0xffffffffll), mask, ARROL_WAVE);
-    int hi = __shfl_xor(static_cast<int>(v >> 32), mask, ARROL_WAVE);
-    return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
+// The value of lane `src` (the same in every lane) in all lanes, by way of a scalar register.
+__device__ __forceinline__ int wave_bcast(int v, int src) { return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src)); }
+__device__ __forceinline__ float wave_bcast(float v, int src) { return __int_as_float(wave_bcast(__float_as_int(v), src)); }
+__device__ __forceinline__ int64_t wave_bcast(int64_t v, int src) {
+    const uint32_t lo = static_cast<uint32_t>(wave_bcast(static_cast<int>(v & 0xffffffffll), src));
+    return (static_cast<int64_t>(wave_bcast(static_cast<int>(v >> 32), src)) << 32) | lo;
 }
-__device__ __forceinline__ int64_t shfl_i64(int64_t v, int src) {
-    int lo = __shfl(static_cast<int>(v & 0xffffffffll), src, ARROL_WAVE);
-    int hi = __shfl(static_cast<int>(v >> 32), src, ARROL_WAVE);
-    return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
+
+// ---- wave-wide reductions: the butterfly 32, 16, 8, 4, 2, 1 without the LDS --------------------------------------
+// __shfl_xor goes through the LDS pipe (some 100 cycles of latency a step, twice for 64 bits); here steps 32 and 16 are
+// the lane-swapping moves of gfx950 and the others DPP moves, a few cycles each.  wave_pair_* returns a value and its
+// partner's, in the order (lower lane's, upper lane's), which is all a commutative operation needs: the pairs and so the
+// results are the shuffle butterfly's, bit for bit.  Rotations by 4 within a row of 16 stand for xor 4 because after
+// step 8 the row repeats every 8 lanes (every 4 after step 4 for the rotation by 2).  All 64 lanes must be active.
+struct wave_pair32 { uint32_t a, b; };
+template <int STEP>
+__device__ __forceinline__ wave_pair32 wave_pair_u32(uint32_t v) {
+    static_assert(STEP == 32 || STEP == 16 || STEP == 8 || STEP == 4 || STEP == 2 || STEP == 1, "butterfly step");
+    if constexpr (STEP == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return {r[0], r[1]};
+    } else if constexpr (STEP == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return {r[0], r[1]};
+    } else {
+        constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x124 : STEP == 2 ? 0x4E : 0xB1;   // row_ror:8, :4, quad_perm
+        return {v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), ctrl, 0xF, 0xF, false))};
+    }
 }
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += shfl_xor_i64(v, m);
-    return v;
+template <int STEP, class T, class Op>
+__device__ __forceinline__ T wave_step(T v, Op op) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- or 64-bit values");
+    if constexpr (sizeof(T) == 4) {
+        const wave_pair32 p = wave_pair_u32<STEP>(__builtin_bit_cast(uint32_t, v));
+        return op(__builtin_bit_cast(T, p.a), __builtin_bit_cast(T, p.b));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const wave_pair32 lo = wave_pair_u32<STEP>(static_cast<uint32_t>(u)), hi = wave_pair_u32<STEP>(static_cast<uint32_t>(u >> 32));
+        return op(__builtin_bit_cast(T, (static_cast<uint64_t>(hi.a) << 32) | lo.a), __builtin_bit_cast(T, (static_cast<uint64_t>(hi.b) << 32) | lo.b));
+    }
 }
-__device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) { int64_t o = shfl_xor_i64(v, m); v = o < v ? o : v; }
-    return v;
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+    v = wave_step<32>(v, op);
+    v = wave_step<16>(v, op);
+    v = wave_step<8>(v, op);
+    v = wave_step<4>(v, op);
+    v = wave_step<2>(v, op);
+    return wave_step<1>(v, op);
 }
-__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) { int64_t o = shfl_xor_i64(v, m); v = o > v ? o : v; }
-    return v;
-}
-__device__ __forceinline__ float wave_sum_f32(float v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, ARROL_WAVE);
-    return v;
-}
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) { return wave_reduce(v, [](int64_t a, int64_t b) { return a + b; }); }
+__device__ __forceinline__ int64_t wave_min_i64(int64_t v) { return wave_reduce(v, [](int64_t a, int64_t b) { return a < b ? a : b; }); }
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) { return wave_reduce(v, [](uint64_t a, uint64_t b) { return a < b ? a : b; }); }
+__device__ __forceinline__ int64_t wave_max_i64(int64_t v) { return wave_reduce(v, [](int64_t a, int64_t b) { return a > b ? a : b; }); }
+__device__ __forceinline__ float wave_sum_f32(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ double wave_sum_f64(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
 __device__ __forceinline__ float bf16_lo(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
 // fp32 -> bf16, round to nearest even (NaN stays a quiet NaN)

@@ -126,11 +126,6 @@ __device__ __forceinline__ double shfl_up_f64(double v, int delta) {
     const int hi = __shfl_up(static_cast<int>(b >> 32), delta, ARROL_WAVE);
     return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
 }
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __longlong_as_double(shfl_xor_i64(__double_as_longlong(v), m));
-    return v;
-}
 // order-preserving map of a double onto unsigned integers
 __device__ __forceinline__ uint64_t key_of(double v) {
     const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
@@ -210,11 +205,7 @@ __global__ __launch_bounds__(kAggThreads) void trace_conf_kernel(
         keys[k] = key;
         kmin = key < kmin ? key : kmin;
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const uint64_t o = static_cast<uint64_t>(shfl_xor_i64(static_cast<int64_t>(kmin), m));
-        kmin = o < kmin ? o : kmin;
-    }
+    kmin = wave_min_u64(kmin);
     if (lane == 0) sh_u[0][wave] = kmin;
     __syncthreads();                                    // also orders keys[] before the passes below
     kmin = sh_u[0][0];

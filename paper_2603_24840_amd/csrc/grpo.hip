@@ -7,12 +7,6 @@
 
 namespace {
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __longlong_as_double(shfl_xor_i64(__double_as_longlong(v), m));
-    return v;
-}
-
 // one wavefront per group
 __global__ __launch_bounds__(ARROL_WAVE) void grpo_advantage_kernel(
     const float* __restrict__ reward, const int64_t* __restrict__ group_offsets, int64_t N, int n_groups, int ddof,

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(
         // (distance, lane) packed so that the minimum is the closest, lowest-index live lane
         const int64_t key = live ? ((dist << 6) | lane) : INT64_MAX;
         const int j = static_cast<int>(wave_min_i64(key) & 63);
-        S -= shfl_i64(k, j);
+        S -= wave_bcast(k, j);
         if (lane == j) live = false;
     }
     const uint64_t ballot = __ballot(live);

@@ -67,6 +67,34 @@ def test_calibrate_matches_oracle(A, W, kappa, rho, lam, p_min, p_max, alpha):
             assert abs(float(np.dot(w, npy(p_lut).astype(np.float64))) - f32(kappa)) < 1e-6   # E[p] = kappa
 
 
+@pytest.mark.parametrize("B", [1, 2, 127, 129, 256, 257, 512, 513, 1024, 1025, 2048])
+def test_calibrate_bin_counts_at_the_edges_of_its_forms(A, B):
+    """One form per bin-count range (15 midpoints at once up to 256 bins, 3 beyond; 8, 16 or 32 bins per lane)."""
+    print("[case] calibrate B=%d" % B, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(B)
+    cp = torch.randint(0, 60, (B,), generator=g, device=DEV)
+    cn = torch.randint(0, 90, (B,), generator=g, device=DEV)
+    cp[-1] = 500                                   # the last bin carries weight
+    args = (0.4, 0.5, 0.7, 0.05, 0.95, 0.5)
+    q_lut, p_lut, delta = A.arrol_calibrate(cp, cn, A.Policy(*args))
+    torch.cuda.synchronize()
+    q_o, p_o, d_o = O.calibrate(npy(cp), npy(cn), *(f32(x) for x in args))
+    assert np.max(np.abs(npy(q_lut) - q_o)) < Q_TOL and np.max(np.abs(npy(p_lut) - p_o)) < Q_TOL
+    assert abs(float(delta[0]) - d_o) < DELTA_TOL
+
+
+@pytest.mark.parametrize("M", [16383, 16384, 16385])
+def test_histogram_at_the_edge_of_the_one_workgroup_form(A, M):
+    print("[case] histogram M=%d" % M, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(M)
+    s = torch.rand(M, generator=g, device=DEV)
+    lab = (torch.rand(M, generator=g, device=DEV) < 0.3).to(torch.uint8)
+    c_pos, c_neg = A.arrol_histogram(s, lab, 100)
+    torch.cuda.synchronize()
+    ref_pos, ref_neg = O.histogram(npy(s), npy(lab), 100)
+    assert np.array_equal(npy(c_pos), ref_pos) and np.array_equal(npy(c_neg), ref_neg)
+
+
 def test_calibrate_empty_buffers(A):
     z = torch.zeros(128, dtype=torch.int64, device=DEV)
     q_lut, p_lut, delta = A.arrol_calibrate(z, z.clone(), A.Policy(0.5, 0.5, 0.5, 0.05, 0.95, 1.0))
