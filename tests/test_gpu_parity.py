@@ -333,6 +333,27 @@ def test_vote_bit_exact(A, Q, C, n_ans):
         assert np.array_equal(npy(win), win_o) and np.array_equal(npy(tally), tally_o)
 
 
+# tallies in LDS up to 1,024 answer ids, swept beyond; full and partly filled wavefronts, scores that tie, infinite ones
+@pytest.mark.parametrize("Q,C,n_ans", [(5, 64, 1024), (5, 64, 1025), (3, 63, 3000), (9, 2, 1), (1, 1, 1024)])
+def test_vote_tally_forms(A, Q, C, n_ans):
+    say("vote forms Q=%d C=%d A=%d" % (Q, C, n_ans))
+    rng = np.random.default_rng(Q * 100 + C + n_ans)
+    p = (rng.integers(0, 5, Q * C) / 4.0).astype(np.float32)
+    p[::7] = np.inf; p[3::11] = -np.inf
+    ans = rng.integers(0, min(n_ans, 9), Q * C).astype(np.int32)
+    ans[1::5] = n_ans - 1
+    outside = np.zeros(Q * C, bool); outside[2::9] = True          # take no part, but are ranked: an extra id to the oracle
+    given = np.where(outside, np.where(np.arange(Q * C) % 2 == 0, -1, n_ans), ans).astype(np.int32)
+    win, tally = A.arrol_weighted_vote(torch.from_numpy(p).to(DEV), torch.from_numpy(given).to(DEV), Q, C, n_ans, want_tally=True)
+    torch.cuda.synchronize()
+    _, tally_o = O.weighted_vote(p, np.where(outside, n_ans, ans), Q, C, n_ans + 1)
+    tally_o = tally_o[:, :n_ans]
+    assert np.array_equal(npy(tally), tally_o)
+    for u in range(Q):
+        ids = sorted(set(ans[u * C:(u + 1) * C][~outside[u * C:(u + 1) * C]].tolist()))
+        assert npy(win)[u] == max(ids, key=lambda a: (tally_o[u, a], -a))
+
+
 def test_score_then_vote_tiny_config(A, W):
     cfg = W.CONFIGS["tiny"]
     hidden, ans = W.vote_inputs(cfg, DEV)
