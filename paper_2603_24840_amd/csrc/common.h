@@ -118,6 +118,26 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) { return wave_reduc
 __device__ __forceinline__ int64_t wave_max_i64(int64_t v) { return wave_reduce(v, [](int64_t a, int64_t b) { return a > b ? a : b; }); }
 __device__ __forceinline__ float wave_sum_f32(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ double wave_sum_f64(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
+
+// Inclusive prefix sum over the lanes, four steps within each row of 16 and two that hand a row's total on (DPP moves, as
+// above; 0 comes in where there is no lower lane).  All 64 lanes must be active.
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T wave_scan_step(T v) {
+    static_assert(sizeof(T) == 8, "64-bit values");
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, ROWS, 0xF, true));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, ROWS, 0xF, true));
+    return v + __builtin_bit_cast(T, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+template <class T>
+__device__ __forceinline__ T wave_scan_sum(T v) {
+    v = wave_scan_step<0x111, 0xF>(v);   // row_shr:1, :2, :4, :8
+    v = wave_scan_step<0x112, 0xF>(v);
+    v = wave_scan_step<0x114, 0xF>(v);
+    v = wave_scan_step<0x118, 0xF>(v);
+    v = wave_scan_step<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    return wave_scan_step<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+}
 __device__ __forceinline__ float bf16_lo(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
 // fp32 -> bf16, round to nearest even (NaN stays a quiet NaN)
@@ -128,25 +148,42 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return static_cast<uint16_t>(u >> 16);
 }
 
-// out[c] = scale * sum_p partial[p*stride + c] for c < width, partials added in index order within each of
-// eight interleaved groups and the groups in order: bit-reproducible.  n_partials == 0 writes zeros.
-// Launch with (width + 31) / 32 workgroups of 256.
-template <int kUnused = 0>
-__global__ __launch_bounds__(256) void reduce_rows_f32_kernel(const float* __restrict__ partial, int n_partials,
-                                                              int64_t stride, int64_t width, float scale,
-                                                              float* __restrict__ out) {
-    __shared__ float red[8][32];
+// Sum over p of partial[p*stride + col]: 32 columns (threadIdx.x & 31) x G groups of rows (threadIdx.x >> 5), workgroups of
+// 32*G.  The partials are added in index order within each of the G interleaved groups and the groups in order: bit-reproducible.
+// Bound by the latency of its loads, so eight are in flight per thread (501 x 2048: 20.3 us with 8 groups and one load at a
+// time, 5.1 us with 32 groups and eight loads).  The sum is valid where threadIdx.x < 32; red: [G][32].
+template <int G>
+__device__ __forceinline__ float reduce_rows_column(const float* __restrict__ partial, int n_partials, int64_t stride,
+                                                    int64_t col, bool valid, float (*red)[32]) {
+    constexpr int kInFlight = 8;
     const int cx = threadIdx.x & 31, ry = threadIdx.x >> 5;
-    const int64_t col = static_cast<int64_t>(blockIdx.x) * 32 + cx;
     float s = 0.f;
-    if (col < width)
-        for (int p = ry; p < n_partials; p += 8) s += partial[static_cast<int64_t>(p) * stride + col];
+    if (valid)
+        for (int p = ry; p < n_partials; p += kInFlight * G) {
+            float x[kInFlight];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u)
+                x[u] = p + u * G < n_partials ? partial[static_cast<int64_t>(p + u * G) * stride + col] : 0.f;
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) s += x[u];
+        }
     red[ry][cx] = s;
     __syncthreads();
-    if (ry == 0 && col < width) {
-        float t = 0.f;
+    float t = 0.f;
+    if (ry == 0)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t += red[k][cx];
-        out[col] = t * scale;
-    }
+        for (int k = 0; k < G; ++k) t += red[k][cx];
+    return t;
+}
+
+// out[c] = scale * sum_p partial[p*stride + c] for c < width; n_partials == 0 writes zeros.
+// Launch with (width + 31) / 32 workgroups of 32*G.
+template <int G>
+__global__ __launch_bounds__(32 * G) void reduce_rows_f32_kernel(const float* __restrict__ partial, int n_partials,
+                                                                 int64_t stride, int64_t width, float scale,
+                                                                 float* __restrict__ out) {
+    __shared__ float red[G][32];
+    const int64_t col = static_cast<int64_t>(blockIdx.x) * 32 + (threadIdx.x & 31);
+    const float t = reduce_rows_column<G>(partial, n_partials, stride, col, col < width, red);
+    if (threadIdx.x < 32 && col < width) out[col] = t * scale;
 }

@@ -116,16 +116,15 @@ __global__ __launch_bounds__(kConfThreads) void token_conf_kernel(
 }
 
 // ---- trace-level aggregates -------------------------------------------------------------------------------
-constexpr int kAggThreads = 256;
-constexpr int kAggWaves = kAggThreads / ARROL_WAVE;
-constexpr int kAggItems = 8;       // tokens per thread per scan chunk
+// Bound by the chain of steps of one workgroup (a trace is a few thousand numbers), so the steps are few: the prefix sums
+// of a trace that one round of the scan covers stay in LDS, every thread keeps up to ITEMS window keys in registers, and the m-th
+// smallest key is found eight bits at a time from LDS counts, from the highest bit in which the keys differ on and only
+// until one key is left (two or three rounds for windows that differ; deciding one bit a round took 64 rounds with a
+// barrier each).  256 traces of 256 to 2,048 tokens, window 1,024: 46.1 -> 9.8 us.
+constexpr int kAggBits = 8;        // bits of the key decided per round
+constexpr int kAggBins = 1 << kAggBits;
 
-__device__ __forceinline__ double shfl_up_f64(double v, int delta) {
-    const int64_t b = __double_as_longlong(v);
-    const int lo = __shfl_up(static_cast<int>(b & 0xffffffffll), delta, ARROL_WAVE);
-    const int hi = __shfl_up(static_cast<int>(b >> 32), delta, ARROL_WAVE);
-    return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) { return wave_reduce(v, [](uint64_t a, uint64_t b) { return a > b ? a : b; }); }
 // order-preserving map of a double onto unsigned integers
 __device__ __forceinline__ uint64_t key_of(double v) {
     const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
@@ -137,13 +136,21 @@ __device__ __forceinline__ double value_of(uint64_t k) {
 }
 
 // One workgroup per trace.  prefix and keys are per-trace slices of the workspace: trace i owns entries
-// [cu[i] + i, cu[i+1] + i + 1) of each (L+1 prefix sums, up to L window keys).
-__global__ __launch_bounds__(kAggThreads) void trace_conf_kernel(
+// [cu[i] + i, cu[i+1] + i + 1) of each (L+1 prefix sums, up to L window keys); they are used only as far as the LDS array
+// and the registers do not reach.
+// ITEMS: tokens per thread and round of the scan, and window keys per thread in registers.
+template <int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void trace_conf_kernel(
     const float* __restrict__ conf, const int64_t* __restrict__ cu, int64_t T, int window, int bottom_percent,
     double* __restrict__ prefix_all, uint64_t* __restrict__ keys_all, double* __restrict__ mean_out,
     double* __restrict__ min_out, double* __restrict__ bottom_out) {
-    __shared__ double sh_d[2][kAggWaves];
-    __shared__ unsigned long long sh_u[2][kAggWaves];
+    constexpr int kWaves = THREADS / ARROL_WAVE;
+    constexpr int64_t kRound = static_cast<int64_t>(ITEMS) * THREADS;   // tokens whose prefix sums fit the LDS array, windows whose keys are in registers
+    __shared__ double sh_prefix[kRound + 1];
+    __shared__ double sh_d[2][kWaves];
+    __shared__ unsigned long long sh_u[2][kWaves];
+    __shared__ unsigned long long sh_bin[3][kAggBins];
+    __shared__ unsigned long long sh_key;
     const int i = blockIdx.x;
     const int lane = threadIdx.x & (ARROL_WAVE - 1), wave = threadIdx.x / ARROL_WAVE;
     int64_t lo = cu[i], hi = cu[i + 1];
@@ -155,97 +162,143 @@ __global__ __launch_bounds__(kAggThreads) void trace_conf_kernel(
         if (threadIdx.x == 0) { mean_out[i] = nan; min_out[i] = nan; bottom_out[i] = nan; }
         return;
     }
+    const bool in_lds = L <= kRound;                    // uniform over the workgroup
     double* prefix = prefix_all + lo + i;
     uint64_t* keys = keys_all + lo + i;
     const float* x = conf + lo;
+    const auto prefix_at = [&](int64_t k) { return in_lds ? sh_prefix[k] : prefix[k]; };
 
-    // ---- inclusive prefix sums in fp64, 2048 tokens per round
+    // ---- inclusive prefix sums in fp64, ITEMS * THREADS tokens per round
     double carry = 0.0;
-    if (threadIdx.x == 0) prefix[0] = 0.0;
+    if (threadIdx.x == 0) { if (in_lds) sh_prefix[0] = 0.0; else prefix[0] = 0.0; }
+    for (int b = threadIdx.x; b < 3 * kAggBins; b += THREADS) sh_bin[b / kAggBins][b % kAggBins] = 0;
     int par = 0;
-    for (int64_t base = 0; base < L; base += kAggThreads * kAggItems, par ^= 1) {
-        const int64_t first = base + static_cast<int64_t>(threadIdx.x) * kAggItems;
-        double v[kAggItems];
+    for (int64_t base = 0; base < L; base += THREADS * ITEMS, par ^= 1) {
+        const int64_t first = base + static_cast<int64_t>(threadIdx.x) * ITEMS;
+        double v[ITEMS];
         double run = 0.0;
 #pragma unroll
-        for (int k = 0; k < kAggItems; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             run += first + k < L ? static_cast<double>(x[first + k]) : 0.0;
             v[k] = run;
         }
-        double incl = run;                              // inclusive scan of the thread totals over the wave
-#pragma unroll
-        for (int dlt = 1; dlt < ARROL_WAVE; dlt <<= 1) {
-            const double o = shfl_up_f64(incl, dlt);
-            if (lane >= dlt) incl += o;
-        }
+        const double incl = wave_scan_sum(run);
         if (lane == ARROL_WAVE - 1) sh_d[par][wave] = incl;
         __syncthreads();
         double before = carry, total = carry;
 #pragma unroll
-        for (int w = 0; w < kAggWaves; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             const double s = sh_d[par][w];
             if (w < wave) before += s;
             total += s;
         }
         const double offset = before + (incl - run);
 #pragma unroll
-        for (int k = 0; k < kAggItems; ++k)
-            if (first + k < L) prefix[first + k + 1] = offset + v[k];
+        for (int k = 0; k < ITEMS; ++k)
+            if (first + k < L) {
+                if (in_lds) sh_prefix[first + k + 1] = offset + v[k];
+                else prefix[first + k + 1] = offset + v[k];
+            }
         carry = total;
     }
-    __syncthreads();                                    // prefix[] of this trace is complete and visible
+    __syncthreads();                                    // the prefix sums of this trace are complete and visible
 
-    // ---- window means, their keys, the minimum
+    // ---- window means, their keys, the smallest and the largest
     const int64_t w_eff = window < L ? window : L;
     const int64_t n_w = L - w_eff + 1;
     const double inv_w = 1.0 / static_cast<double>(w_eff);
-    uint64_t kmin = ~0ull;
-    for (int64_t k = threadIdx.x; k < n_w; k += kAggThreads) {
-        const uint64_t key = key_of((prefix[k + w_eff] - prefix[k]) * inv_w);
+    const auto window_key = [&](int64_t k) { return key_of((prefix_at(k + w_eff) - prefix_at(k)) * inv_w); };
+    uint64_t held[ITEMS];
+    uint64_t kmin = ~0ull, kmax = 0ull;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int64_t k = threadIdx.x + static_cast<int64_t>(j) * THREADS;
+        held[j] = k < n_w ? window_key(k) : 0ull;
+        if (k < n_w) {
+            kmin = held[j] < kmin ? held[j] : kmin;
+            kmax = held[j] > kmax ? held[j] : kmax;
+        }
+    }
+    for (int64_t k = kRound + threadIdx.x; k < n_w; k += THREADS) {   // written and read back by the same thread
+        const uint64_t key = window_key(k);
         keys[k] = key;
         kmin = key < kmin ? key : kmin;
+        kmax = key > kmax ? key : kmax;
     }
+    const auto each_key = [&](auto&& f) {
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (threadIdx.x + static_cast<int64_t>(j) * THREADS < n_w) f(held[j]);
+        for (int64_t k = kRound + threadIdx.x; k < n_w; k += THREADS) f(keys[k]);
+    };
     kmin = wave_min_u64(kmin);
-    if (lane == 0) sh_u[0][wave] = kmin;
-    __syncthreads();                                    // also orders keys[] before the passes below
-    kmin = sh_u[0][0];
+    kmax = wave_max_u64(kmax);
+    if (lane == 0) { sh_u[0][wave] = kmin; sh_u[1][wave] = kmax; }
+    __syncthreads();
 #pragma unroll
-    for (int w = 1; w < kAggWaves; ++w) kmin = sh_u[0][w] < kmin ? sh_u[0][w] : kmin;
+    for (int w = 0; w < kWaves; ++w) {
+        kmin = sh_u[0][w] < kmin ? sh_u[0][w] : kmin;
+        kmax = sh_u[1][w] > kmax ? sh_u[1][w] : kmax;
+    }
 
-    // ---- the m-th smallest window key, bit by bit: the largest X with #{key < X} < m
+    // ---- X = the m-th smallest window key.  The bits above `open` are decided and the same in X and in every key that
+    // still counts; `rank` is X's place among those.  The counts rotate over three arrays, so that one barrier a round is
+    // enough: the array of the next round was last read in the round before the one that ended with the last barrier.
     const int64_t m_low = (n_w * bottom_percent + 99) / 100 < 1 ? 1 : (n_w * bottom_percent + 99) / 100;
-    uint64_t X = 0;
-    par = 1;
-    for (int b = 63; b >= 0; --b, par ^= 1) {
-        const uint64_t cand = X | (1ull << b);
-        unsigned long long cnt = 0;
-        for (int64_t k = threadIdx.x; k < n_w; k += kAggThreads) cnt += keys[k] < cand ? 1u : 0u;
-        cnt = static_cast<unsigned long long>(wave_sum_i64(static_cast<int64_t>(cnt)));
-        if (lane == 0) sh_u[par][wave] = cnt;
+    uint64_t X = kmin;
+    int open = m_low == 1 || kmin == kmax ? 0 : 64 - __clzll(static_cast<long long>(kmin ^ kmax));
+    if (open > 0) X = open == 64 ? 0ull : (kmin >> open) << open;
+    uint64_t rank = static_cast<uint64_t>(m_low);
+    for (int round = 0; open > 0; ++round) {
+        const int bits = open < kAggBits ? open : kAggBits, shift = open - bits;
+        unsigned long long* bin = sh_bin[round % 3];
+        if (round > 0)                                  // the first round's successor is still zero
+            for (int b = threadIdx.x; b < kAggBins; b += THREADS) sh_bin[(round + 1) % 3][b] = 0;
+        each_key([&](uint64_t key) {
+            if (open == 64 || ((key ^ X) >> open) == 0)
+                atomicAdd(&bin[(key >> shift) & ((1u << bits) - 1u)], 1ull);
+        });
         __syncthreads();
-        unsigned long long tot = 0;
+        // every wavefront finds the bin of the rank for itself: four bins per lane, inclusive scan over the lanes
+        constexpr int kPer = kAggBins / ARROL_WAVE;
+        uint64_t c[kPer], own = 0;
 #pragma unroll
-        for (int w = 0; w < kAggWaves; ++w) tot += sh_u[par][w];
-        if (static_cast<int64_t>(tot) < m_low) X = cand;
+        for (int k = 0; k < kPer; ++k) { c[k] = bin[lane * kPer + k]; own += c[k]; }
+        const uint64_t incl = wave_scan_sum(own);
+        uint64_t below = incl - own;
+        const int src = __builtin_ctzll(__ballot(incl >= rank));   // counts sum up to at least the rank: some lane has it
+        int digit = lane * kPer;
+        uint64_t in_bin = c[0];
+#pragma unroll
+        for (int k = 1; k < kPer; ++k)
+            if (below + in_bin < rank) { below += in_bin; in_bin = c[k]; digit = lane * kPer + k; }
+        digit = wave_bcast(digit, src);
+        rank -= static_cast<uint64_t>(wave_bcast(static_cast<int64_t>(below), src));
+        const uint64_t left = static_cast<uint64_t>(wave_bcast(static_cast<int64_t>(in_bin), src));
+        X |= static_cast<uint64_t>(digit) << shift;
+        open = shift;
+        if (left == 1 && open > 0) {                    // one key has these leading bits: its owner publishes it
+            each_key([&](uint64_t key) { if (((key ^ X) >> open) == 0) sh_key = key; });
+            __syncthreads();
+            X = sh_key;
+            open = 0;
+        }
     }
     // sum of the values below X, then as many copies of X as are still missing
     double s_low = 0.0;
-    unsigned long long c_low = 0;
-    for (int64_t k = threadIdx.x; k < n_w; k += kAggThreads) {
-        const uint64_t key = keys[k];
-        if (key < X) { s_low += value_of(key); ++c_low; }
-    }
+    int64_t c_low = 0;
+    each_key([&](uint64_t key) { if (key < X) { s_low += value_of(key); ++c_low; } });
     s_low = wave_sum_f64(s_low);
-    c_low = static_cast<unsigned long long>(wave_sum_i64(static_cast<int64_t>(c_low)));
-    __syncthreads();
-    if (lane == 0) { sh_d[0][wave] = s_low; sh_u[0][wave] = c_low; }
+    c_low = wave_sum_i64(c_low);
+    __syncthreads();                                    // sh_u still held the smallest and largest keys
+    if (lane == 0) { sh_d[0][wave] = s_low; sh_u[0][wave] = static_cast<unsigned long long>(c_low); }
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
         unsigned long long c = 0;
-        for (int w = 0; w < kAggWaves; ++w) { s += sh_d[0][w]; c += sh_u[0][w]; }
+        for (int w = 0; w < kWaves; ++w) { s += sh_d[0][w]; c += sh_u[0][w]; }
         s += static_cast<double>(m_low - static_cast<int64_t>(c)) * value_of(X);
-        mean_out[i] = prefix[L] / static_cast<double>(L);
+        mean_out[i] = prefix_at(L) / static_cast<double>(L);
         min_out[i] = value_of(kmin);
         bottom_out[i] = s / static_cast<double>(m_low);
     }
@@ -275,7 +328,7 @@ extern "C" int arrol_token_confidence(const void* hidden, const void* lm_head, c
     float* partial = colsum + d;
     arrol_launch(colsum_partial_kernel, dim3(nb), dim3(kColThreads), 0, st,
                        static_cast<const u32x4*>(lm_head), V, d / 8, partial);
-    arrol_launch(reduce_rows_f32_kernel<0>, dim3((d + 31) / 32), dim3(256), 0, st, partial, nb,
+    arrol_launch(reduce_rows_f32_kernel<32>, dim3((d + 31) / 32), dim3(1024), 0, st, partial, nb,
                        static_cast<int64_t>(d), static_cast<int64_t>(d), 1.f, colsum);
     const int64_t blocks_needed = (T + kConfWaves - 1) / kConfWaves;
     const int grid = static_cast<int>(blocks_needed < 256 * 8 ? blocks_needed : 256 * 8);
@@ -311,7 +364,15 @@ extern "C" int arrol_trace_confidence(const float* conf, const int64_t* cu_seqle
         return ARROL_EWORKSPACE;
     double* prefix = static_cast<double*>(workspace);
     uint64_t* keys = reinterpret_cast<uint64_t*>(prefix + T + n_seq);
-    arrol_launch(trace_conf_kernel, dim3(n_seq), dim3(kAggThreads), 0, static_cast<hipStream_t>(stream), conf,
-                       cu_seqlens, T, window, bottom_percent, prefix, keys, mean_out, min_out, bottom_out);
+    // Threads by the mean length and the number of traces: a wide workgroup needs fewer rounds for a long trace, but its
+    // barriers and scans cost more and fewer of them fit a compute unit.  256 / 512 / 1,024 threads: 256 traces of 64 to 512
+    // tokens 4.7 / 5.1 / 6.9 us, of 256 to 2,048 8.2 / 7.3 / 9.6, of 512 to 4,096 16.2 / 11.9 / 11.3, of 4,096 to 8,192
+    // 39.9 / 26.0 / 21.1; 1,024 traces of 256 to 2,048 12.2 / 12.6 / 29.9.
+    const int64_t mean = T / n_seq;
+#define ARROL_TRACE(N, ITEMS) arrol_launch(trace_conf_kernel<N, ITEMS>, dim3(n_seq), dim3(N), 0, static_cast<hipStream_t>(stream), conf, cu_seqlens, T, window, bottom_percent, prefix, keys, mean_out, min_out, bottom_out)
+    if (mean > 4096 && n_seq <= 256) ARROL_TRACE(1024, 4);
+    else if (mean > 512 && n_seq <= 512) ARROL_TRACE(512, 4);
+    else ARROL_TRACE(256, 4);
+#undef ARROL_TRACE
     return arrol_launch_status();
 }

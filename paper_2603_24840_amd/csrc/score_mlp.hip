@@ -1139,14 +1139,14 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     if (n_rows == 0) {   // empty batch: zero loss and gradients
         hipStream_t s0 = static_cast<hipStream_t>(stream);
         const int64_t width = static_cast<int64_t>(m) * d;
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3(static_cast<unsigned>((width + 31) / 32)), dim3(256), 0, s0,
+        arrol_launch(reduce_rows_f32_kernel<8>, dim3(static_cast<unsigned>((width + 31) / 32)), dim3(256), 0, s0,
                            nullptr, 0, width, width, 0.f, grad_w1);
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3((m + 31) / 32), dim3(256), 0, s0, nullptr, 0,
+        arrol_launch(reduce_rows_f32_kernel<8>, dim3((m + 31) / 32), dim3(256), 0, s0, nullptr, 0,
                            static_cast<int64_t>(m), static_cast<int64_t>(m), 0.f, grad_b1);
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3((m + 31) / 32), dim3(256), 0, s0, nullptr, 0,
+        arrol_launch(reduce_rows_f32_kernel<8>, dim3((m + 31) / 32), dim3(256), 0, s0, nullptr, 0,
                            static_cast<int64_t>(m), static_cast<int64_t>(m), 0.f, grad_w2);
-        if (loss_out) arrol_launch(reduce_rows_f32_kernel<0>, dim3(1), dim3(256), 0, s0, nullptr, 0, 1, 1, 0.f, loss_out);
-        if (grad_b2) arrol_launch(reduce_rows_f32_kernel<0>, dim3(1), dim3(256), 0, s0, nullptr, 0, 1, 1, 0.f, grad_b2);
+        if (loss_out) arrol_launch(reduce_rows_f32_kernel<8>, dim3(1), dim3(256), 0, s0, nullptr, 0, 1, 1, 0.f, loss_out);
+        if (grad_b2) arrol_launch(reduce_rows_f32_kernel<8>, dim3(1), dim3(256), 0, s0, nullptr, 0, 1, 1, 0.f, grad_b2);
         return arrol_launch_status();
     }
     if (!hidden || !w1 || !w2 || !labels || !arrol_aligned16(hidden) || !arrol_aligned16(w1)) return ARROL_EINVAL;
@@ -1197,9 +1197,9 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
         a.resid = resid; a.delta_t = dt; a.delta_lo = dt_lo; a.delta_stride = p.n_pad; a.unit_partial = unit;
         rc = launch_mlp<kDelta>(a, dim3(p.n_rb), st);
         if (rc != ARROL_OK) return rc;
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3((m + 31) / 32), dim3(256), 0, st, unit, p.n_rb,
+        arrol_launch(reduce_rows_f32_kernel<8>, dim3((m + 31) / 32), dim3(256), 0, st, unit, p.n_rb,
                      static_cast<int64_t>(2) * m, static_cast<int64_t>(m), 1.f, grad_w2);
-        arrol_launch(reduce_rows_f32_kernel<0>, dim3((m + 31) / 32), dim3(256), 0, st, unit + m, p.n_rb,
+        arrol_launch(reduce_rows_f32_kernel<8>, dim3((m + 31) / 32), dim3(256), 0, st, unit + m, p.n_rb,
                      static_cast<int64_t>(2) * m, static_cast<int64_t>(m), 1.f, grad_b1);
     }
     if (arrol_launch_failed()) return arrol_launch_status();

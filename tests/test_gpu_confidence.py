@@ -154,3 +154,36 @@ def test_confidence_chain_end_to_end(A, W):
         assert np.array_equal(np.isnan(got), np.isnan(want))
         ok = ~np.isnan(want)
         assert np.all(np.abs(got[ok] - want[ok]) <= tol)
+
+
+@pytest.mark.parametrize("lens", [[1023, 1024, 1025, 2049, 5, 64, 0] + [12] * 20,       # mean <= 512 tokens: 256 threads
+                                  [2047, 2048, 2049, 4097, 513, 1, 3000],               # up to 4,096: 512 threads
+                                  [4095, 4096, 4097, 9001, 4300],                       # longer: 1,024 threads
+                                  [700] * 513])                                         # more than 512 traces: 256 threads
+@pytest.mark.parametrize("window,pct", [(1, 10), (300, 10), (2, 100)])
+def test_trace_confidence_at_the_edges_of_each_workgroup_size(A, lens, window, pct):
+    """Lengths around one round of the scan (4 tokens a thread); the second half of the values repeats a few numbers, so
+    that many window means are equal in all bits and the low share ends inside a run of ties."""
+    print("[case] trace_confidence lens=%s... window=%d pct=%d" % (lens[:4], window, pct), flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(sum(lens) + window)
+    T = int(sum(lens))
+    conf = (1.5e6 + 400.0 * torch.randn(T, generator=g, device=DEV)).to(torch.float32)
+    conf[T // 2:] = torch.randint(-2, 3, (T - T // 2,), generator=g, device=DEV).float() * 4096.0
+    if window > 1:
+        conf[T // 2:] += 8192.0      # no mean of exactly zero out of sums that cancel: the bound is relative
+    run_trace(A, conf, lens, window, pct)
+
+
+@pytest.mark.parametrize("V", [256 * 31, 256 * 32, 256 * 32 + 1, 256 * 257 - 3])
+def test_token_confidence_column_sums_of_many_blocks(A, W, V):
+    """Numbers of 256-row blocks around 32 groups of one and of more than eight blocks, a width that is no multiple of 32."""
+    print("[case] token_confidence blocks V=%d" % V, flush=True)
+    cfg = W.shrink(W.CONFIGS["tiny"], d=72, vocab=V)
+    hidden, lm_head, _, _ = W.logprob_inputs(cfg, DEV, T=9, vocab=V)
+    lse = torch.full((9,), float(np.log(V)), device=DEV)
+    conf = A.arrol_token_confidence(hidden, lm_head, lse)
+    torch.cuda.synchronize()
+    column = lm_head.double().sum(0)
+    ref = npy(V * lse.double() - hidden.double() @ column)
+    # as in the stage parity above: the fp32 column sums and dot product, and the fp32 result
+    assert np.all(np.abs(npy(conf).astype(np.float64) - ref) <= 1e-5 * np.sqrt(V) + 2e-6 * np.abs(ref))
