@@ -9,7 +9,7 @@ namespace {
 
 constexpr int kGradThreads = 512;
 constexpr int kGradWaves = kGradThreads / ARROL_WAVE;
-constexpr int kGradMaxBlocks = 1024;
+constexpr int kGradMaxBlocks = 256;
 constexpr int kGradMaxD = 8192;          // 16 chunks of 8 columns per lane
 
 __device__ __forceinline__ void unpack8(const u32x4& x, float (&f)[8]) {
@@ -32,6 +32,7 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     // the lane's slice of the weights lives in registers where that measured faster (2048 < d <= 4096: 4.2
     // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
     // 4.5 against 5.2 TB/s), otherwise the weights are read from LDS
+    constexpr bool PREFETCH = CH <= 4;   // wider rows leave no registers for a second one
     constexpr bool W_REG = CH == 8;
     constexpr int NW = W_REG ? CH : 1;
     float4 wra[NW], wrb[NW];
@@ -53,15 +54,25 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
         for (int k = 0; k < 8; ++k) acc[c][k] = 0.f;
     float loss_acc = 0.f, r_acc = 0.f;
     const int wave_stride = gridDim.x * kGradWaves;
-    for (int row = blockIdx.x * kGradWaves + wave; row < n_rows; row += wave_stride) {
+    const auto load_row = [&](int row, u32x4 (&x)[CH], float& y) {
         const int64_t src_row = row_index ? row_index[row] : row;
         const u32x4* p = hidden + src_row * row_stride_vec;
-        u32x4 x[CH];
+        y = labels[row];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int v = c * ARROL_WAVE + lane;
             x[c] = v < d_vec ? __builtin_nontemporal_load(p + v) : u32x4{0u, 0u, 0u, 0u};
         }
+    };
+    u32x4 x[CH];
+    float y = 0.f;
+    int row = blockIdx.x * kGradWaves + wave;
+    if (row < n_rows) load_row(row, x, y);
+    while (row < n_rows) {
+        const int next = row + wave_stride;
+        u32x4 xn[CH];
+        float yn = 0.f;
+        if (PREFETCH && next < n_rows) load_row(next, xn, yn);
         float dot0 = 0.f, dot1 = 0.f;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -78,7 +89,6 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             }
         }
         const float s = wave_sum_f32(dot0 + dot1) + bias;   // every lane holds the sum
-        const float y = labels[row];
         const float e = expf(-fabsf(s));
         const float q = s >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
         const float r = q - y;
@@ -91,6 +101,16 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             unpack8(x[c], f);
 #pragma unroll
             for (int k = 0; k < 8; ++k) acc[c][k] = fmaf(r, f[k], acc[c][k]);
+        }
+        row = next;
+        if (row < n_rows) {
+            if (PREFETCH) {
+#pragma unroll
+                for (int c = 0; c < CH; ++c) x[c] = xn[c];
+                y = yn;
+            } else {
+                load_row(row, x, y);
+            }
         }
     }
     // the workgroup's eight wavefronts add up through LDS, 512 columns at a time, in a fixed order
@@ -122,24 +142,17 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     }
 }
 
-// Adds the per-workgroup partial sums in index order and divides by N.  Blocks 0 .. gridDim.x-2 cover the
-// columns, the last block the loss and the bias gradient.
-__global__ __launch_bounds__(256) void score_grad_reduce_kernel(
+// Adds the per-workgroup partial sums and divides by N.  Blocks 0 .. gridDim.x-2 cover 32 columns each, the last block the
+// loss and the bias gradient.
+constexpr int kReduceGroups = 32;
+__global__ __launch_bounds__(32 * kReduceGroups) void score_grad_reduce_kernel(
     const float* __restrict__ partial, const float* __restrict__ tail, int n_partials, int d, float inv_n,
     float* __restrict__ loss_out, float* __restrict__ grad_w, float* __restrict__ grad_bias) {
+    __shared__ float red[kReduceGroups][32];
     if (blockIdx.x + 1 < gridDim.x) {
-        const int col = blockIdx.x * 256 + threadIdx.x;
-        if (col >= d) return;
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-        int p = 0;
-        for (; p + 4 <= n_partials; p += 4) {
-            s0 += partial[static_cast<int64_t>(p) * d + col];
-            s1 += partial[static_cast<int64_t>(p + 1) * d + col];
-            s2 += partial[static_cast<int64_t>(p + 2) * d + col];
-            s3 += partial[static_cast<int64_t>(p + 3) * d + col];
-        }
-        for (; p < n_partials; ++p) s0 += partial[static_cast<int64_t>(p) * d + col];
-        grad_w[col] = ((s0 + s1) + (s2 + s3)) * inv_n;
+        const int col = blockIdx.x * 32 + (threadIdx.x & 31);
+        const float t = reduce_rows_column<kReduceGroups>(partial, n_partials, d, col, col < d, red);
+        if (threadIdx.x < 32 && col < d) grad_w[col] = t * inv_n;
     } else if (threadIdx.x < ARROL_WAVE) {
         float a = 0.f, b = 0.f;
         for (int p = threadIdx.x; p < n_partials; p += ARROL_WAVE) { a += tail[p * 2]; b += tail[p * 2 + 1]; }
@@ -171,11 +184,12 @@ __global__ __launch_bounds__(256) void adamw_kernel(
     }
 }
 
+// One row per wavefront until every compute unit has a workgroup, then 256 workgroups whatever the batch: more of them only
+// leave more partial sums to add (both launches, 1,024 x 4096: 8 rows a wavefront on 16 compute units 17.5 us, one row on 128 9.6 us;
+// 32,768 x 4096: 512 workgroups 52.7 us, 256 48.5 us).
 int grad_blocks(int n_rows) {
-    const int rows_per_block = kGradWaves * 8;
-    int b = (n_rows + rows_per_block - 1) / rows_per_block;
-    if (b > kGradMaxBlocks) b = kGradMaxBlocks;
-    return b < 1 ? 1 : b;
+    const int b = n_rows / kGradWaves + (n_rows % kGradWaves != 0);
+    return b < 1 ? 1 : b < kGradMaxBlocks ? b : kGradMaxBlocks;
 }
 
 template <int CH>
@@ -206,9 +220,9 @@ extern "C" int arrol_score_grad(const void* hidden, int64_t row_stride_elems, co
         return ARROL_EINVAL;
     if (!grad_w) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int col_blocks = (d + 255) / 256;
+    const int col_blocks = (d + 31) / 32;
     if (n_rows == 0) {   // empty batch: zero loss and gradients
-        arrol_launch(score_grad_reduce_kernel, dim3(col_blocks + 1), dim3(256), 0, st, nullptr, nullptr, 0, d,
+        arrol_launch(score_grad_reduce_kernel, dim3(col_blocks + 1), dim3(32 * kReduceGroups), 0, st, nullptr, nullptr, 0, d,
                            0.f, loss_out, grad_w, grad_bias);
         return arrol_launch_status();
     }
@@ -228,7 +242,7 @@ extern "C" int arrol_score_grad(const void* hidden, int64_t row_stride_elems, co
     else if (chunks <= 8) rc = launch_grad<8>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
     else rc = launch_grad<16>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
     if (rc != ARROL_OK) return rc;
-    arrol_launch(score_grad_reduce_kernel, dim3(col_blocks + 1), dim3(256), 0, st, partial, tail, grid, d,
+    arrol_launch(score_grad_reduce_kernel, dim3(col_blocks + 1), dim3(32 * kReduceGroups), 0, st, partial, tail, grid, d,
                        1.f / static_cast<float>(n_rows), loss_out, grad_w, grad_bias);
     return arrol_launch_status();
 }

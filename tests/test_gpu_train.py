@@ -315,3 +315,12 @@ def test_score_mlp_grad_is_reproducible_and_trains(A):
         for k, (p, gk, (mk, vk)) in enumerate(zip(params, grads, state)):
             A.arrol_adamw_step(p, gk, mk, vk, t, lr=1e-2, param_bf16=w1_bf16.view(-1) if k == 0 else None)
     assert losses[-1] < losses[0] - 0.01, losses
+
+
+@pytest.mark.parametrize("n,d", [(8, 40), (9, 1032), (2047, 512), (2048, 520), (2049, 2056), (2057, 4096), (4099, 3000)])
+def test_score_grad_around_one_row_per_wavefront(A, W, n, d):
+    """Up to 2,048 rows every wavefront has one, beyond that 256 workgroups share them; widths around 32 columns a block."""
+    print("[case] score_grad n=%d d=%d" % (n, d), flush=True)
+    cfg = W.shrink(W.CONFIGS["tiny"], d=d)
+    hidden, w, _, labels = W.head_training_inputs(cfg, DEV, n_rows=n)
+    check_grad(A, hidden, w * 3.0, 0.25, labels)
