@@ -149,9 +149,14 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 }
 
 // Sum over p of partial[p*stride + col]: 32 columns (threadIdx.x & 31) x G groups of rows (threadIdx.x >> 5), workgroups of
-// 32*G.  The partials are added in index order within each of the G interleaved groups and the groups in order: bit-reproducible.
-// Bound by the latency of its loads, so eight are in flight per thread (501 x 2048: 20.3 us with 8 groups and one load at a
-// time, 5.1 us with 32 groups and eight loads).  The sum is valid where threadIdx.x < 32; red: [G][32].
+// 32*G.  Every group adds its rows in index order, eight at a time, the eight and the groups by a fixed tree:
+// bit-reproducible.  Bound by the latency of its loads, so eight are in flight per thread (501 x 2048: 20.3 us with 8 groups
+// and one load at a time, 5.1 us with 32 groups and eight).  The sum is valid where threadIdx.x < 32; red: [G][32].
+template <int N>
+__device__ __forceinline__ float tree_sum(const float* x) {
+    if constexpr (N == 1) return x[0];
+    else return tree_sum<N / 2>(x) + tree_sum<N / 2>(x + N / 2);
+}
 template <int G>
 __device__ __forceinline__ float reduce_rows_column(const float* __restrict__ partial, int n_partials, int64_t stride,
                                                     int64_t col, bool valid, float (*red)[32]) {
@@ -162,18 +167,21 @@ __device__ __forceinline__ float reduce_rows_column(const float* __restrict__ pa
         for (int p = ry; p < n_partials; p += kInFlight * G) {
             float x[kInFlight];
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u)
-                x[u] = p + u * G < n_partials ? partial[static_cast<int64_t>(p + u * G) * stride + col] : 0.f;
+            for (int u = 0; u < kInFlight; ++u) {   // past the end the group's first row again, so that no load waits on a branch
+                const int q = p + u * G;
+                x[u] = partial[static_cast<int64_t>(q < n_partials ? q : p) * stride + col];
+            }
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) s += x[u];
+            for (int u = 0; u < kInFlight; ++u) x[u] = p + u * G < n_partials ? x[u] : 0.f;
+            s += tree_sum<kInFlight>(x);
         }
     red[ry][cx] = s;
     __syncthreads();
-    float t = 0.f;
-    if (ry == 0)
+    float t[G];
+    if (ry != 0) return 0.f;
 #pragma unroll
-        for (int k = 0; k < G; ++k) t += red[k][cx];
-    return t;
+    for (int k = 0; k < G; ++k) t[k] = red[k][cx];
+    return tree_sum<G>(t);
 }
 
 // out[c] = scale * sum_p partial[p*stride + c] for c < width; n_partials == 0 writes zeros.

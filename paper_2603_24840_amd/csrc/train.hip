@@ -29,30 +29,7 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     float* red = lds + d_vec * 8;
     const int lane = threadIdx.x & (ARROL_WAVE - 1);
     const int wave = threadIdx.x / ARROL_WAVE;
-    // the lane's slice of the weights lives in registers where that measured faster (2048 < d <= 4096: 4.2
-    // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
-    // 4.5 against 5.2 TB/s), otherwise the weights are read from LDS
     constexpr bool PREFETCH = CH <= 4;   // wider rows leave no registers for a second one
-    constexpr bool W_REG = CH == 8;
-    constexpr int NW = W_REG ? CH : 1;
-    float4 wra[NW], wrb[NW];
-    if (W_REG) {
-#pragma unroll
-        for (int c = 0; c < NW; ++c) {
-            const int v = c * ARROL_WAVE + lane;
-            wra[c] = v < d_vec ? *reinterpret_cast<const float4*>(w + v * 8) : make_float4(0.f, 0.f, 0.f, 0.f);
-            wrb[c] = v < d_vec ? *reinterpret_cast<const float4*>(w + v * 8 + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    } else {
-        for (int i = threadIdx.x; i < d_vec * 8; i += kGradThreads) w_lds[i] = w[i];
-        __syncthreads();
-    }
-    float acc[CH][8];
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc[c][k] = 0.f;
-    float loss_acc = 0.f, r_acc = 0.f;
     const int wave_stride = gridDim.x * kGradWaves;
     const auto load_row = [&](int row, u32x4 (&x)[CH], float& y) {
         const int64_t src_row = row_index ? row_index[row] : row;
@@ -67,7 +44,31 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     u32x4 x[CH];
     float y = 0.f;
     int row = blockIdx.x * kGradWaves + wave;
-    if (row < n_rows) load_row(row, x, y);
+    if (row < n_rows) load_row(row, x, y);                  // on its way while the weights are fetched
+    // the lane's slice of the weights lives in registers where that measured faster (2048 < d <= 4096: 4.2
+    // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
+    // 4.5 against 5.2 TB/s), otherwise the weights are read from LDS
+    constexpr bool W_REG = CH == 8;
+    constexpr int NW = W_REG ? CH : 1;
+    float4 wra[NW], wrb[NW];
+    if (W_REG) {
+#pragma unroll
+        for (int c = 0; c < NW; ++c) {
+            const int v = c * ARROL_WAVE + lane;
+            wra[c] = v < d_vec ? *reinterpret_cast<const float4*>(w + v * 8) : make_float4(0.f, 0.f, 0.f, 0.f);
+            wrb[c] = v < d_vec ? *reinterpret_cast<const float4*>(w + v * 8 + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    } else {
+        for (int i = threadIdx.x; i < d_vec * 2; i += kGradThreads)
+            reinterpret_cast<float4*>(w_lds)[i] = reinterpret_cast<const float4*>(w)[i];
+        __syncthreads();
+    }
+    float acc[CH][8];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[c][k] = 0.f;
+    float loss_acc = 0.f, r_acc = 0.f;
     while (row < n_rows) {
         const int next = row + wave_stride;
         u32x4 xn[CH];
@@ -124,10 +125,10 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             __syncthreads();
             const int col = c * 512 + threadIdx.x;
             if (col < d_vec * 8) {
-                float sum = 0.f;
+                float part[kGradWaves];
 #pragma unroll
-                for (int k = 0; k < kGradWaves; ++k) sum += red[k * 512 + threadIdx.x];
-                out[col] = sum;
+                for (int k = 0; k < kGradWaves; ++k) part[k] = red[k * 512 + threadIdx.x];
+                out[col] = tree_sum<kGradWaves>(part);
             }
             __syncthreads();
         }
@@ -135,10 +136,10 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     if (lane == 0) { red[wave * 2] = loss_acc; red[wave * 2 + 1] = r_acc; }
     __syncthreads();
     if (threadIdx.x < 2) {
-        float sum = 0.f;
+        double sum = 0.0;                                      // residuals cancel: the few sums per workgroup are added in 64 bits
 #pragma unroll
         for (int k = 0; k < kGradWaves; ++k) sum += red[k * 2 + threadIdx.x];
-        tail[blockIdx.x * 2 + threadIdx.x] = sum;
+        tail[blockIdx.x * 2 + threadIdx.x] = static_cast<float>(sum);
     }
 }
 
@@ -154,13 +155,13 @@ __global__ __launch_bounds__(32 * kReduceGroups) void score_grad_reduce_kernel(
         const float t = reduce_rows_column<kReduceGroups>(partial, n_partials, d, col, col < d, red);
         if (threadIdx.x < 32 && col < d) grad_w[col] = t * inv_n;
     } else if (threadIdx.x < ARROL_WAVE) {
-        float a = 0.f, b = 0.f;
+        double a = 0.0, b = 0.0;
         for (int p = threadIdx.x; p < n_partials; p += ARROL_WAVE) { a += tail[p * 2]; b += tail[p * 2 + 1]; }
-        a = wave_sum_f32(a);
-        b = wave_sum_f32(b);
+        a = wave_sum_f64(a);
+        b = wave_sum_f64(b);
         if (threadIdx.x == 0) {
-            if (loss_out) *loss_out = a * inv_n;
-            if (grad_bias) *grad_bias = b * inv_n;
+            if (loss_out) *loss_out = static_cast<float>(a * inv_n);
+            if (grad_bias) *grad_bias = static_cast<float>(b * inv_n);
         }
     }
 }
