@@ -138,3 +138,17 @@ def test_inplace_pool_beyond_the_one_launch_planner(A, W):
     pick = torch.stack([torch.sort(torch.randperm(cfg.G, generator=g)[:cfg.K])[0] + i * cfg.G
                         for i in range(cfg.n_prompts)]).reshape(-1).to(torch.int32).to(DEV)
     run_case(A, kv, bt, sl, pick)
+
+
+@pytest.mark.parametrize("n_prompts,G,K,ckpt,extra", [(64, 4, 2, 64, 0),       # 8,192 table slots: one batch of the planner
+                                                    (64, 4, 2, 65, 31),      # 128 more
+                                                    (1, 3, 1, 5, 0), (11, 5, 3, 1000, 33)])   # 33,000: five batches
+def test_inplace_planner_slot_batches(A, W, n_prompts, G, K, ckpt, extra):
+    print("[case] inplace planner prompts=%d G=%d K=%d pages=%d" % (n_prompts, G, K, ckpt), flush=True)
+    cfg = W.shrink(W.CONFIGS["tiny"], n_prompts=n_prompts, G=G, K=K, head_dim=8, page_tokens=1, ckpt_len=ckpt, n_layers=1,
+                   n_kv_heads=1)
+    kv, bt, sl, _ = W.compact_inputs(cfg, DEV, extra_pages=extra, ragged=True)
+    g = torch.Generator(device="cpu"); g.manual_seed(ckpt)
+    pick = torch.stack([torch.sort(torch.randperm(G, generator=g)[:K])[0] + i * G
+                        for i in range(n_prompts)]).reshape(-1).to(torch.int32).to(DEV)
+    run_case(A, kv, bt, sl, pick)
