@@ -91,8 +91,9 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
         }
         const float s = wave_sum_f32(dot0 + dot1) + bias;   // every lane holds the sum
         const float e = expf(-fabsf(s));
-        const float q = s >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-        const float r = q - y;
+        // q = 1 / (1 + e^-s); at y = 1 the residual is -(1 - q) without the rounding of q
+        const float v = ((s >= 0.f) != (y == 1.f) ? 1.f : e) / (1.f + e);
+        const float r = y == 1.f ? -v : v - y;
         // -[y log q + (1-y) log(1-q)] = max(s, 0) - y s + log(1 + exp(-|s|))
         loss_acc += fmaxf(s, 0.f) - y * s + log1pf(e);
         r_acc += r;
