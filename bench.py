@@ -415,7 +415,7 @@ def time_extras(A, W, cfg, dev, torch, lp_hidden, lm_head, targets, cu, reps=10)
     sws = torch.empty(sws_bytes, dtype=torch.uint8, device=dev) if sws_bytes else None
     ms = timed(lambda: A.arrol_score_mlp(hidden, w1, b1, w2, workspace=sws))
     out["score_mlp"] = {"ms": ms, "shape": "N=%d, d=%d, m=%d" % (N, d, m), "TFLOPs": 2.0 * N * d * m / ms / 1e9,
-                        "path": "small-batch (wavefront per 32x32 block + finish)" if sws_bytes else "tile kernel",
+                        "path": "32x32 to 128x64 blocks by size + finish" if sws_bytes else "tile kernel",
                         "note": "HIP-event mean over back-to-back calls from Python: a floor of ~20 us per call is host launch cost; "
                                 "kernel durations are in profiles/"}
     mws = torch.empty(max(256, A.lib().arrol_score_mlp_grad_workspace_bytes(N, d, m, 1)), dtype=torch.uint8, device=dev)
