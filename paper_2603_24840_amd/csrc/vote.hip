@@ -37,12 +37,17 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
     __builtin_amdgcn_wave_barrier();            // one wavefront's LDS accesses complete in order
     const float4* others = reinterpret_cast<const float4*>(score[wave]);
     int below = 0, equal = 0;
+    const auto compare = [&](auto reads) {
 #pragma unroll
-    for (int j = 0; j < ARROL_WAVE / 4; ++j) {
-        const float4 o = others[j];
-        below += (o.x < q ? 1 : 0) + (o.y < q ? 1 : 0) + (o.z < q ? 1 : 0) + (o.w < q ? 1 : 0);
-        equal += (o.x == q ? 1 : 0) + (o.y == q ? 1 : 0) + (o.z == q ? 1 : 0) + (o.w == q ? 1 : 0);
-    }
+        for (int j = 0; j < decltype(reads)::value; ++j) {
+            const float4 o = others[j];
+            below += (o.x < q ? 1 : 0) + (o.y < q ? 1 : 0) + (o.z < q ? 1 : 0) + (o.w < q ? 1 : 0);
+            equal += (o.x == q ? 1 : 0) + (o.y == q ? 1 : 0) + (o.z == q ? 1 : 0) + (o.w == q ? 1 : 0);
+        }
+    };
+    if (C <= 16) compare(std::integral_constant<int, 4>{});
+    else if (C <= 32) compare(std::integral_constant<int, 8>{});
+    else compare(std::integral_constant<int, ARROL_WAVE / 4>{});
     const int rank2 = 2 * below + equal - (q == q ? 1 : 0);     // the candidate itself is not one of the equal ones
     if (TALLY_IN_LDS) {
         if (ans >= 0) atomicAdd(&mine[ans], static_cast<unsigned int>(rank2) | 0x10000u);   // at most 64 * 126 below

@@ -354,6 +354,12 @@ def test_vote_tally_forms(A, Q, C, n_ans):
         assert npy(win)[u] == max(ids, key=lambda a: (tally_o[u, a], -a))
 
 
+@pytest.mark.parametrize("C", [15, 16, 17, 31, 32, 33, 63])
+def test_vote_candidates_around_16_and_32(A, C):
+    """Scores are read 16, 32 or 64 at a time."""
+    test_vote_tally_forms(A, 6, C, 20)
+
+
 def test_score_then_vote_tiny_config(A, W):
     cfg = W.CONFIGS["tiny"]
     hidden, ans = W.vote_inputs(cfg, DEV)
