@@ -18,7 +18,8 @@ __device__ __forceinline__ void unpack8(const u32x4& x, float (&f)[8]) {
 }
 
 // One wavefront per row; lane l owns columns [8*(c*64+l), +8) for c < CH for every row it sees, so the
-// gradient accumulators stay in its registers.  partial: [gridDim.x][d] fp32, tail: [gridDim.x][2] (loss, sum r).
+// gradient accumulators stay in its registers.  Bound by HBM for large batches, by one chain of load, dot product,
+// exponential and LDS sums for small ones (1,024 x 4096: 15.8 us with eight rows per wavefront, 7.5 with one).  partial: [gridDim.x][d] fp32, tail: [gridDim.x][2] (loss, sum r).
 template <int CH>
 __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     const u32x4* __restrict__ hidden, int64_t row_stride_vec, const int64_t* __restrict__ row_index,
@@ -47,7 +48,8 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     if (row < n_rows) load_row(row, x, y);                  // on its way while the weights are fetched
     // the lane's slice of the weights lives in registers where that measured faster (2048 < d <= 4096: 4.2
     // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
-    // 4.5 against 5.2 TB/s), otherwise the weights are read from LDS
+    // 4.5 against 5.2 TB/s; both with up to 1,024 workgroups, 5.5 TB/s at 4096 with the 256 of grad_blocks),
+    // otherwise the weights are read from LDS
     constexpr bool W_REG = CH == 8;
     constexpr int NW = W_REG ? CH : 1;
     float4 wra[NW], wrb[NW];
