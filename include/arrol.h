@@ -202,7 +202,8 @@ int arrol_compact_inplace(void* kv, arrol_kv_layout layout, const int32_t* block
  *           tokens; the per-range partials are merged by a second small kernel).  0 lets the library
  *           choose from T and V; a positive value is used as given, capped at the number of 256-row
  *           vocabulary tiles.  The result does not depend on it beyond fp32 rounding of the merge.
- * workspace: arrol_logprob_workspace_bytes(T, V, d, n_splits) bytes for the SAME n_splits, 16-byte aligned.
+ * workspace: arrol_logprob_workspace_bytes(T, V, d, n_splits) bytes for the SAME n_splits, 16-byte aligned.  The size
+ *           never falls as T grows: one workspace sized for the largest batch serves every smaller one.
  */
 size_t arrol_logprob_workspace_bytes(int64_t T, int32_t V, int32_t d, int32_t n_splits);
 int arrol_logprob(const void* hidden, const void* lm_head, const int32_t* targets,

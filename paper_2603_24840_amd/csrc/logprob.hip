@@ -999,7 +999,20 @@ int launch_logprob(dim3 grid, hipStream_t st, const LogprobArgs& a) {
 extern "C" size_t arrol_logprob_workspace_bytes(int64_t T, int32_t V, int32_t d, int32_t n_splits) {
     if (T <= 0 || V < 1 || n_splits < 0) return 0;
     const Plan p = make_plan(T, V, d, n_splits);
-    return (static_cast<size_t>(p.n_sp) * 3 * static_cast<size_t>(T) * sizeof(float) + 255) & ~static_cast<size_t>(255);
+    // Partials per token x tokens.  The plan's own split count falls from one batch to the next larger one, so the
+    // answer for n_splits = 0 is what no smaller batch exceeds: a workspace sized for the largest batch serves all of
+    // them.  make_plan takes up to 12 splits or, of few token blocks, 8 rounds of workgroups, and 6 from 16 rounds on.
+    int64_t rows = static_cast<int64_t>(p.n_sp) * T;
+    if (n_splits == 0) {
+        constexpr int64_t kRound = kXcds * kCuPerXcd, kTwelve = 16 * kRound / 6 * MainTile::BN;   // tokens of 16 rounds
+        int64_t most = 8 * kRound * MainTile::BN;
+        most = most > 6 * T ? most : 6 * T;
+        const int64_t twelve = 12 * (T < kTwelve ? T : kTwelve);
+        most = most > twelve ? most : twelve;
+        most = most < p.n_vt * T ? most : p.n_vt * T;
+        rows = rows > most ? rows : most;
+    }
+    return (static_cast<size_t>(rows) * 3 * sizeof(float) + 255) & ~static_cast<size_t>(255);
 }
 
 extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int32_t* targets,

@@ -236,3 +236,11 @@ def test_binding_argument_counts_match_the_header(pkg):
         params = " ".join(params.split())
         n = 0 if params in ("", "void") else params.count(",") + 1
         assert n == len(binding._SIGNATURES[name][1]), (name, n, len(binding._SIGNATURES[name][1]))
+
+
+def test_logprob_scratch_of_the_largest_batch_serves_every_smaller_one(pkg):
+    """The size never falls as the batch grows (the split count that the library chooses does), for any of its forms."""
+    for V, d in ((300, 64), (5000, 200), (32000, 2048), (151936, 4096)):
+        for splits in (0, 1, 9):
+            sizes = [pkg.arrol_logprob_workspace_bytes(T, V, d, splits) for T in list(range(1, 3000)) + list(range(3000, 400000, 251))]
+            assert all(a <= b for a, b in zip(sizes, sizes[1:])), (V, d, splits)
