@@ -372,7 +372,8 @@ int arrol_score_grad(const void* hidden, int64_t row_stride_elems, const int64_t
  * rounding 2^-17: dL/dW1 to fp32 accuracy, at twice the cost of that contraction).  Other values -> ARROL_EINVAL.
  * n_rows == 0 writes zeros.
  * workspace: arrol_score_mlp_grad_workspace_bytes(n_rows, d, m, delta_terms) bytes, 256-byte aligned,
- * caller-owned, contents undefined afterwards; too small or NULL -> ARROL_EWORKSPACE.
+ * caller-owned, contents undefined afterwards; too small or NULL -> ARROL_EWORKSPACE.  The size never falls as n_rows
+ * grows: one workspace sized for the largest batch serves every smaller one.
  */
 size_t arrol_score_mlp_grad_workspace_bytes(int32_t n_rows, int32_t d, int32_t m, int32_t delta_terms);
 int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems, const int64_t* row_index,

@@ -1017,19 +1017,32 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
     const double slab_us = static_cast<double>(mt) * d * 8.0 / 4.5e6;
     const int64_t ring_tiles = static_cast<int64_t>(p.r_cb) * p.r_gt;
     const int64_t mid_tiles = static_cast<int64_t>((d + WgradMid::BN - 1) / WgradMid::BN) * ((mt + WgradMid::BM - 1) / WgradMid::BM);
-    double best = -1.0;
-    for (int s = 1; s <= 16 && (s == 1 || n_k64 / s >= 4); ++s) {
+    constexpr int kMaxSplits = 16;
+    constexpr double kRingStep = 1.45, kRingStart = 7.0, kMidStep = 0.68, kMidStart = 5.0, kSlabStart = 2.5;
+    double best = -1.0, one = 0.0;
+    for (int s = 1; s <= kMaxSplits && (s == 1 || n_k64 / s >= 4); ++s) {
         const int per = (n_k64 + s - 1) / s, used = (n_k64 + per - 1) / per;
-        const double slabs = used * terms > 1 ? 2.5 + used * slab_us : 0.0;
+        const double slabs = used * terms > 1 ? kSlabStart + used * slab_us : 0.0;
         const int64_t nr = ring_tiles * used, nm = mid_tiles * used;
-        const double ring = static_cast<double>((nr + 255) / 256) * (per * 1.45 + 7.0) + slabs;
+        const double ring = static_cast<double>((nr + 255) / 256) * (per * kRingStep + kRingStart) + slabs;
         const double mid = (mt + WgradMid::BM - 1) / WgradMid::BM > 65535 ? 1e30
-                           : (nm <= 256 ? per * 0.38 + 5.0 : static_cast<double>((nm + 511) / 512) * (per * 0.68 + 5.0)) + slabs;
+                           : (nm <= 256 ? per * 0.38 + kMidStart : static_cast<double>((nm + 511) / 512) * (per * kMidStep + kMidStart)) + slabs;
         const double t = mid < ring ? mid : ring;
+        if (s == 1) one = t;
         if (best < 0.0 || t < best) { best = t; p.w_mid = mid < ring; p.r_k64_per_split = per; p.r_splits = used; }
     }
+    // The split count can fall from one batch to the next larger one, but a workspace sized for the largest batch is to
+    // serve every smaller one.  Room is made for the most splits that a batch up to this one can take: s of them are only
+    // chosen where their slabs and the work on a full chip, which no estimate is below, come to less than one split's
+    // estimate.  What is left of that estimate after the work grows with the batch, and so does the room.
+    int room = 1;
+    const double ring_work = static_cast<double>(ring_tiles) / 256.0 * kRingStep, mid_work = static_cast<double>(mid_tiles) / 512.0 * kMidStep;
+    const double work = n_k64 * (ring_work < mid_work ? ring_work : mid_work) + kMidStart;
+    for (int s = 2; s <= kMaxSplits && n_k64 / s >= 4; ++s)
+        if (kSlabStart + s * slab_us + work <= one + 1e-6) room = s;
+    if (room < p.r_splits) room = p.r_splits;
     p.off_rslab = o;
-    if (d % 64 == 0 && p.r_splits * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(p.r_splits) * mt * d);
+    if (d % 64 == 0 && room * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(room) * mt * d);
     p.off_act = o;                        // mid / ring forward pass: kept activations, fp32 [m][n_pad]
     if (d % 64 == 0) o = align256(o + sizeof(float) * static_cast<size_t>(m) * p.n_pad);
     p.total = o;

@@ -244,3 +244,12 @@ def test_logprob_scratch_of_the_largest_batch_serves_every_smaller_one(pkg):
         for splits in (0, 1, 9):
             sizes = [pkg.arrol_logprob_workspace_bytes(T, V, d, splits) for T in list(range(1, 3000)) + list(range(3000, 400000, 251))]
             assert all(a <= b for a, b in zip(sizes, sizes[1:])), (V, d, splits)
+
+
+def test_mlp_gradient_scratch_of_the_largest_batch_serves_every_smaller_one(pkg):
+    """As above for the partial slabs of dL/dW1, whose number the library chooses too."""
+    size = pkg.lib().arrol_score_mlp_grad_workspace_bytes
+    for d, m in ((64, 8), (512, 64), (1024, 256), (2048, 512), (4096, 128), (4096, 1024), (3968, 669), (2056, 512)):
+        for terms in (1, 2):
+            sizes = [size(n, d, m, terms) for n in list(range(1, 200)) + list(range(200, 40000, 13)) + list(range(40000, 2000000, 6397))]
+            assert all(a <= b for a, b in zip(sizes, sizes[1:])), (d, m, terms)
