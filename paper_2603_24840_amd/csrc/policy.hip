@@ -8,7 +8,8 @@ namespace {
 
 constexpr int kHistThreads = 256;
 constexpr int kHistOneThreads = 1024;
-constexpr int kHistOneMax = 16384;    // entries one workgroup takes alone: 16 per thread
+constexpr int kHistOneMax = 16384;    // entries one workgroup takes alone: 16 per thread, 4.3 us with 128 bins and 5.2 with 2,048
+                                      // where two launches take 5.8 and 7.2
 constexpr int kMaxBins = 2048;        // two fp64 tables of kMaxBins entries fit in LDS
 constexpr int kPruneThreads = 1024;
 constexpr int kBisectIters = 64;
@@ -44,13 +45,20 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(
 }
 
 // The same for a short buffer: one workgroup whose LDS histogram is the result, so nothing has to be zeroed first (one
-// launch instead of two; 4,096 entries: 5.3 us of kernels before).
+// launch instead of two; 4,096 entries, 128 bins: 5.6 us of kernels before, 2.6 now).  Lanes that count in the same word
+// wait for each other, and a head at cold start puts nearly all scores into one bin, so a bin has COPIES words side by
+// side, of which a lane takes the one of its number (16,384 entries in one bin of 128: 12.5 us with one word a bin, 4.3
+// with eight; in two launches 6.2).
+template <int COPIES>
 __global__ __launch_bounds__(kHistOneThreads) void histogram_one_kernel(
     const float* __restrict__ s_norm, const uint8_t* __restrict__ label, int M, int B, int64_t* __restrict__ c_pos,
     int64_t* __restrict__ c_neg) {
-    extern __shared__ unsigned int hist[];   // [2][B]
-    for (int i = threadIdx.x; i < 2 * B; i += kHistOneThreads) hist[i] = 0;
+    constexpr int VEC = COPIES >= 4 ? 4 : 1;
+    typedef unsigned int words __attribute__((ext_vector_type(VEC)));
+    extern __shared__ __attribute__((aligned(16))) unsigned int hist[];   // [2][B][COPIES]
+    for (int i = threadIdx.x; i < 2 * B * COPIES / VEC; i += kHistOneThreads) reinterpret_cast<words*>(hist)[i] = words(0u);
     __syncthreads();
+    const int copy = threadIdx.x % COPIES;
     for (int k0 = threadIdx.x; k0 < M; k0 += kHistOneThreads * 4) {
         float s[4];
         uint8_t l[4];
@@ -62,10 +70,19 @@ __global__ __launch_bounds__(kHistOneThreads) void histogram_one_kernel(
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (k0 + u * kHistOneThreads < M) atomicAdd(&hist[(l[u] ? 0 : B) + bin_of(s[u], B)], 1u);
+            if (k0 + u * kHistOneThreads < M) atomicAdd(&hist[((l[u] ? 0 : B) + bin_of(s[u], B)) * COPIES + copy], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < B; i += kHistOneThreads) { c_pos[i] = hist[i]; c_neg[i] = hist[B + i]; }
+    for (int i = threadIdx.x; i < 2 * B; i += kHistOneThreads) {
+        unsigned int sum = 0;
+#pragma unroll
+        for (int c = 0; c < COPIES / VEC; ++c) {
+            const words x = reinterpret_cast<const words*>(hist)[i * (COPIES / VEC) + c];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sum += x[v];
+        }
+        (i < B ? c_pos[i] : c_neg[i - B]) = sum;
+    }
 }
 
 // Likelihoods, Bayes posterior, survival probability and the bisection for delta; one workgroup, fp64.
@@ -208,8 +225,15 @@ extern "C" int arrol_histogram(const float* s_norm, const uint8_t* label, int64_
     if (M > 0 && (!s_norm || !label)) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (M <= kHistOneMax) {
-        arrol_launch(histogram_one_kernel, dim3(1), dim3(kHistOneThreads), 2 * B * sizeof(unsigned int), st, s_norm, label,
-                     static_cast<int>(M), B, c_pos, c_neg);
+        // Up to 4,096 entries one word a bin is no slower than two launches even with all scores in one bin (4.8 us against
+        // 6.0); beyond, eight words as far as 64 KiB of LDS reach, else four.
+        const auto launch = [&](auto kernel, int copies) {
+            arrol_launch(kernel, dim3(1), dim3(kHistOneThreads), 2 * B * copies * sizeof(unsigned int), st, s_norm, label,
+                         static_cast<int>(M), B, c_pos, c_neg);
+        };
+        if (M <= 4096) launch(histogram_one_kernel<1>, 1);
+        else if (B <= 1024) launch(histogram_one_kernel<8>, 8);
+        else launch(histogram_one_kernel<4>, 4);
         return arrol_launch_status();
     }
     arrol_launch(zero_counts_kernel, dim3((B + 255) / 256), dim3(256), 0, st, c_pos, c_neg, B);

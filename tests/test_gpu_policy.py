@@ -95,6 +95,21 @@ def test_histogram_at_the_edge_of_the_one_workgroup_form(A, M):
     assert np.array_equal(npy(c_pos), ref_pos) and np.array_equal(npy(c_neg), ref_neg)
 
 
+# a word a bin up to 4,096 entries, then eight, or four beyond 1,024 bins; scores that all fall into one bin or two
+@pytest.mark.parametrize("M", [1, 4096, 4097, 9000, 16384])
+@pytest.mark.parametrize("B", [1, 2, 37, 1024, 1025, 2048])
+def test_histogram_of_crowded_bins(A, M, B):
+    print("[case] histogram crowded M=%d B=%d" % (M, B), flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(M + B)
+    lab = (torch.rand(M, generator=g, device=DEV) < 0.3).to(torch.uint8)
+    for s in (torch.full((M,), 0.501, device=DEV), 0.25 + 0.5 * (torch.rand(M, generator=g, device=DEV) < 0.5).float(),
+              torch.rand(M, generator=g, device=DEV)):
+        c_pos, c_neg = A.arrol_histogram(s, lab, B)
+        torch.cuda.synchronize()
+        ref_pos, ref_neg = O.histogram(npy(s), npy(lab), B)
+        assert np.array_equal(npy(c_pos), ref_pos) and np.array_equal(npy(c_neg), ref_neg)
+
+
 def test_calibrate_empty_buffers(A):
     z = torch.zeros(128, dtype=torch.int64, device=DEV)
     q_lut, p_lut, delta = A.arrol_calibrate(z, z.clone(), A.Policy(0.5, 0.5, 0.5, 0.05, 0.95, 1.0))
