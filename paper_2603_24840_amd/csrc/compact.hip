@@ -285,11 +285,13 @@ __global__ __launch_bounds__(kCopyThreads) void inplace_copy_kernel(
 //   hole / mover lists (rank of a page = prefix of its word + popcount below its bit) ->
 //   remapped block tables, lengths, source map, counters.
 // LDS: 2 x 4 bytes per 32 pages, i.e. P / 4 bytes.
-// One workgroup, bound by its chains of dependent loads: eight slots per thread take them together, and the lists are built
-// a page per thread (a word of 32 pages per thread stored uncoalesced).  16,384 pages, 8,192 slots: 19.5 -> 12.1 us.
+// One workgroup, bound by its chains of dependent loads: kSlotBatch slots per thread take them together, and the lists are
+// built a page per thread (a word of 32 pages per thread stored uncoalesced).  16,384 pages, 8,192 slots: 19.5 -> 12.1 us.
+// Tables of no more slots than threads take one each, without the loads of seven more that do not exist (whole call with
+// 4 slots: 5.9 us, 8.1 with eight a thread; 400 slots: 5.0 and 7.2).
 constexpr int64_t kFusedMaxPages = 512 * 1024;   // 128 KiB of LDS
-constexpr int kSlotBatch = 8;
 
+template <int kSlotBatch>
 __global__ __launch_bounds__(kPlanThreads) void inplace_fused_plan_kernel(
     const int32_t* __restrict__ survivor_idx, const int32_t* __restrict__ seq_len_src,
     const int32_t* __restrict__ block_table_src, int n_src, int n_keep, int page_tokens, int ppr, int P,
@@ -664,11 +666,14 @@ extern "C" int arrol_compact_inplace(void* kv, arrol_kv_layout layout, const int
         // planning in one launch (bitmap in LDS), then the copy over the pairs alone
         const int n_words = static_cast<int>((P + 31) >> 5);
         const int lds_bytes = 2 * n_words * static_cast<int>(sizeof(uint32_t));
-        static arrol_device_flags fused_ok;
-        if (!arrol_allow_lds(&inplace_fused_plan_kernel, static_cast<int>(kFusedMaxPages / 4), fused_ok)) return ARROL_EHIP;
-        arrol_launch(inplace_fused_plan_kernel, dim3(1), dim3(kPlanThreads), lds_bytes, st, survivor_idx, seq_len_src,
-                     block_table_src, n_src, n_keep, layout.page_tokens, max_pages_per_seq, static_cast<int>(P),
-                     hole_list, mover_list, counters, block_table_dst, seq_len_dst, src_of_dst, n_pages_used, n_moved);
+        static arrol_device_flags one_ok, batch_ok;
+        if (!arrol_allow_lds(&inplace_fused_plan_kernel<1>, static_cast<int>(kFusedMaxPages / 4), one_ok) ||
+            !arrol_allow_lds(&inplace_fused_plan_kernel<8>, static_cast<int>(kFusedMaxPages / 4), batch_ok))
+            return ARROL_EHIP;
+        arrol_launch(slots <= kPlanThreads ? inplace_fused_plan_kernel<1> : inplace_fused_plan_kernel<8>, dim3(1),
+                     dim3(kPlanThreads), lds_bytes, st, survivor_idx, seq_len_src, block_table_src, n_src, n_keep,
+                     layout.page_tokens, max_pages_per_seq, static_cast<int>(P), hole_list, mover_list, counters,
+                     block_table_dst, seq_len_dst, src_of_dst, n_pages_used, n_moved);
         if (arrol_launch_failed()) return arrol_launch_status();
         // no more pairs than survivor pages, than dead pages (P - live >= holes), or than half the pool
         const int64_t m_bound = slots < P / 2 ? slots : P / 2;

@@ -142,7 +142,9 @@ def test_inplace_pool_beyond_the_one_launch_planner(A, W):
 
 @pytest.mark.parametrize("n_prompts,G,K,ckpt,extra", [(64, 4, 2, 64, 0),       # 8,192 table slots: one batch of the planner
                                                     (64, 4, 2, 65, 31),      # 128 more
-                                                    (1, 3, 1, 5, 0), (11, 5, 3, 1000, 33)])   # 33,000: five batches
+                                                    (1, 3, 1, 5, 0), (11, 5, 3, 1000, 33),   # 33,000: five batches
+                                                    (1, 2, 1, 1, 0), (16, 4, 2, 32, 7),      # 1,024: a slot per thread
+                                                    (41, 6, 5, 5, 3)])                       # 1,025: a batch again
 def test_inplace_planner_slot_batches(A, W, n_prompts, G, K, ckpt, extra):
     print("[case] inplace planner prompts=%d G=%d K=%d pages=%d" % (n_prompts, G, K, ckpt), flush=True)
     cfg = W.shrink(W.CONFIGS["tiny"], n_prompts=n_prompts, G=G, K=K, head_dim=8, page_tokens=1, ckpt_len=ckpt, n_layers=1,
