@@ -42,10 +42,13 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             x[c] = v < d_vec ? __builtin_nontemporal_load(p + v) : u32x4{0u, 0u, 0u, 0u};
         }
     };
+    // Rows of more than 4,096 columns are loaded where they are used: one in flight across the weights and the end of the
+    // loop put 159 registers into scratch memory instead of 93 (65,536 x 8192: 1,586 us, 907 without, 4,096 x 8192: 97 and 68)
+    constexpr bool EARLY = CH <= 8;
     u32x4 x[CH];
     float y = 0.f;
     int row = blockIdx.x * kGradWaves + wave;
-    if (row < n_rows) load_row(row, x, y);                  // on its way while the weights are fetched
+    if (EARLY && row < n_rows) load_row(row, x, y);         // on its way while the weights are fetched
     // the lane's slice of the weights lives in registers where that measured faster (2048 < d <= 4096: 4.2
     // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
     // 4.5 against 5.2 TB/s; both with up to 1,024 workgroups, 5.5 TB/s at 4096 with the 256 of grad_blocks),
@@ -76,6 +79,7 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
         u32x4 xn[CH];
         float yn = 0.f;
         if (PREFETCH && next < n_rows) load_row(next, xn, yn);
+        if (!EARLY) load_row(row, x, y);
         float dot0 = 0.f, dot1 = 0.f;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             for (int k = 0; k < 8; ++k) acc[c][k] = fmaf(r, f[k], acc[c][k]);
         }
         row = next;
-        if (row < n_rows) {
+        if (EARLY && row < n_rows) {
             if (PREFETCH) {
 #pragma unroll
                 for (int c = 0; c < CH; ++c) x[c] = xn[c];

@@ -317,7 +317,8 @@ def test_score_mlp_grad_is_reproducible_and_trains(A):
     assert losses[-1] < losses[0] - 0.01, losses
 
 
-@pytest.mark.parametrize("n,d", [(8, 40), (9, 1032), (2047, 512), (2048, 520), (2049, 2056), (2057, 4096), (4099, 3000)])
+@pytest.mark.parametrize("n,d", [(8, 40), (9, 1032), (2047, 512), (2048, 520), (2049, 2056), (2057, 4096), (4099, 3000),
+                                 (3, 4104), (2049, 8192), (4100, 6152)])
 def test_score_grad_around_one_row_per_wavefront(A, W, n, d):
     """Up to 2,048 rows every wavefront has one, beyond that 256 workgroups share them; widths around 32 columns a block."""
     print("[case] score_grad n=%d d=%d" % (n, d), flush=True)
