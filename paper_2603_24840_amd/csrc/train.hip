@@ -192,12 +192,16 @@ __global__ __launch_bounds__(256) void adamw_kernel(
     }
 }
 
-// One row per wavefront until every compute unit has a workgroup, then 256 workgroups whatever the batch: more of them only
-// leave more partial sums to add (both launches, 1,024 x 4096: 8 rows a wavefront on 16 compute units 17.5 us, one row on 128 9.6 us;
-// 32,768 x 4096: 512 workgroups 52.7 us, 256 48.5 us).
-int grad_blocks(int n_rows) {
+// One row per wavefront until every compute unit has a workgroup, then 256 workgroups: more of them only leave more partial
+// sums to add (both launches, 1,024 x 4096: 8 rows a wavefront on 16 compute units 17.5 us, one row on 128 7.5 + 2.9;
+// 32,768 x 4096: 512 workgroups 53.3 us, 256 49.0; 131,072 x 2048: 1,024 workgroups 92.1, 256 83.9).  Very many narrow rows
+// are bound by the loads in flight instead, which 1,024 workgroups keep more of: 1,048,576 x 64 300 us (256: 384),
+// 524,288 x 512 160 (219), 131,072 x 1024 54.7 (61.8); at 65,536 x 64 26.7 (27.6).
+constexpr int kGradManyBlocks = 1024, kGradManyRows = 131072, kGradNarrow = 1024;
+int grad_blocks(int n_rows, int d) {
     const int b = n_rows / kGradWaves + (n_rows % kGradWaves != 0);
-    return b < 1 ? 1 : b < kGradMaxBlocks ? b : kGradMaxBlocks;
+    const int most = n_rows >= kGradManyRows && d <= kGradNarrow ? kGradManyBlocks : kGradMaxBlocks;
+    return b < 1 ? 1 : b < most ? b : most;
 }
 
 template <int CH>
@@ -217,7 +221,7 @@ int launch_grad(int grid, size_t lds_bytes, hipStream_t st, const void* hidden, 
 
 extern "C" size_t arrol_score_grad_workspace_bytes(int32_t n_rows, int32_t d) {
     if (n_rows < 0 || d < 8) return 0;
-    return static_cast<size_t>(grad_blocks(n_rows)) * (static_cast<size_t>(d) + 2) * sizeof(float);
+    return static_cast<size_t>(grad_blocks(n_rows, d)) * (static_cast<size_t>(d) + 2) * sizeof(float);
 }
 
 extern "C" int arrol_score_grad(const void* hidden, int64_t row_stride_elems, const int64_t* row_index,
@@ -236,7 +240,7 @@ extern "C" int arrol_score_grad(const void* hidden, int64_t row_stride_elems, co
     }
     if (!hidden || !w || !labels || !arrol_aligned16(hidden) || !arrol_aligned16(w)) return ARROL_EINVAL;
     if (!workspace || workspace_bytes < arrol_score_grad_workspace_bytes(n_rows, d)) return ARROL_EWORKSPACE;
-    const int grid = grad_blocks(n_rows);
+    const int grid = grad_blocks(n_rows, d);
     float* partial = static_cast<float*>(workspace);
     float* tail = partial + static_cast<size_t>(grid) * d;
     const size_t lds_bytes = sizeof(float) * (static_cast<size_t>(d) + kGradWaves * 512);

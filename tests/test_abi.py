@@ -247,7 +247,10 @@ def test_logprob_scratch_of_the_largest_batch_serves_every_smaller_one(pkg):
 
 
 def test_mlp_gradient_scratch_of_the_largest_batch_serves_every_smaller_one(pkg):
-    """As above for the partial slabs of dL/dW1, whose number the library chooses too."""
+    """As above for the partial slabs of dL/dW1, whose number the library chooses too, and the linear head's partial sums."""
+    for d in (64, 1024, 4096):
+        sizes = [pkg.lib().arrol_score_grad_workspace_bytes(n, d) for n in range(1, 300000, 5)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), d
     size = pkg.lib().arrol_score_mlp_grad_workspace_bytes
     for d, m in ((64, 8), (512, 64), (1024, 256), (2048, 512), (4096, 128), (4096, 1024), (3968, 669), (2056, 512)):
         for terms in (1, 2):

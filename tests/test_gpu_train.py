@@ -318,9 +318,10 @@ def test_score_mlp_grad_is_reproducible_and_trains(A):
 
 
 @pytest.mark.parametrize("n,d", [(8, 40), (9, 1032), (2047, 512), (2048, 520), (2049, 2056), (2057, 4096), (4099, 3000),
-                                 (3, 4104), (2049, 8192), (4100, 6152)])
+                                 (3, 4104), (2049, 8192), (4100, 6152), (131071, 64), (131072, 136), (140003, 8)])
 def test_score_grad_around_one_row_per_wavefront(A, W, n, d):
-    """Up to 2,048 rows every wavefront has one, beyond that 256 workgroups share them; widths around 32 columns a block."""
+    """Up to 2,048 rows every wavefront has one, beyond that 256 workgroups share them (1,024 from 131,072 narrow rows on);
+    widths around 32 columns a block, and the one form that loads rows late."""
     print("[case] score_grad n=%d d=%d" % (n, d), flush=True)
     cfg = W.shrink(W.CONFIGS["tiny"], d=d)
     hidden, w, _, labels = W.head_training_inputs(cfg, DEV, n_rows=n)
