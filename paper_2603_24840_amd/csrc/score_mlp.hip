@@ -760,6 +760,22 @@ ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, con
     }
     return best;
 }
+// 128 x 64 blocks read every rollout's row once per 128 units, the tile kernel reads it once; where rows are narrow or
+// there are very many of them and the ring form is not to be had (gathered rows), it is the faster one for a forward pass
+// that keeps no activations.  Microseconds measured over 300 to 131,072 gathered rollouts, d of 64 to 4096, 32 to 1,024
+// units; beyond the last-level cache (256 MB) the repeated reads come from memory.  Tile and 128 x 64: 20,000 x 64 x 512
+// 12.1 and 16.5, 32,768 x 1024 x 512 55.0 and 57.5, 131,072 x 2048 x 512 401 and 525, but 32,768 x 2048 x 512 100 and 95,
+// 20,000 x 1024 x 256 29.2 and 26.2.
+bool tile_beats_mid128(int n_rows, int d, int m) {
+    const double rounds = static_cast<double>((n_blocks(n_rows, 1, 128, 1) + 255) / 256);
+    const double tile = 2.0 + rounds * (1.5 + ((m + 255) / 256) * (2.8 + 0.0222 * d));
+    const int64_t blocks = n_blocks(n_rows, m, 64, 128), last = blocks % 512;
+    double mid = 7.6 + 0.0055 * d;
+    if (blocks > 256) mid = 3.5 + (static_cast<double>(blocks / 512) + (last == 0 ? 0.0 : last <= 256 ? 0.75 : 1.0)) * (3.9 + 0.0095 * d);
+    const double bytes = 2.0 * n_rows * d, reads = ((m + 127) / 128) * bytes / 4.0e6;
+    if (bytes > 384e6 && reads > mid) mid = reads;
+    return tile < mid;
+}
 int unit_block(ForwardPath p) { return p == kPathMid32 ? 32 : p == kPathMid64 ? 64 : p == kPathMid128 ? 128 : 256; }
 
 // Partial scores of every unit block to `partial`, with act_t also the activations (kPathTile: not for this).
@@ -1118,7 +1134,8 @@ extern "C" int arrol_score_mlp(const void* hidden, int64_t row_stride_elems, con
     if (!hidden || !w1 || !w2 || !prob_out || !arrol_aligned16(hidden) || !arrol_aligned16(w1)) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t need = arrol_score_mlp_workspace_bytes(n_rows, d, m);
-    const ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
+    ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
+    if (path == kPathMid128 && row_index && tile_beats_mid128(n_rows, d, m)) path = kPathTile;
     if (path != kPathTile && workspace && arrol_aligned16(workspace) && workspace_bytes >= need) {
         float* partial = static_cast<float*>(workspace);
         const int rc = enqueue_forward(path, hidden, row_stride_elems, row_index, w1, b1, w2, n_rows, d, m, partial, nullptr, 0, st);

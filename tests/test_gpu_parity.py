@@ -408,7 +408,8 @@ def test_score_mlp_matches_oracle(A, n, d, m):
 
 
 # the dispatch by size (d a multiple of 64): 32 x 32 blocks, 64 x 64, 128 x 64 and the 256 x 256 ring form, each with
-# remainders on both sides and fewer K64 steps than pipeline stages; gathered rows take all but the ring form
+# remainders on both sides and fewer K64 steps than pipeline stages; gathered rows take the tile kernel instead of the ring
+# form, and instead of 128 x 64 blocks where rows are narrow (2,900 x 128 x 513 still takes those)
 @pytest.mark.parametrize("gather", [False, True])
 @pytest.mark.parametrize("n,d,m", [(1, 64, 1), (33, 192, 31), (500, 704, 40), (1030, 64, 520), (1500, 320, 450), (2900, 128, 513),
                                    (4100, 192, 260), (20000, 64, 300)])
