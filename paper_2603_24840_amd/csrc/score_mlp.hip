@@ -756,7 +756,11 @@ ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, con
     if (row_index == nullptr && row_stride_elems * 2 * 256 < (1ll << 31) && (m + 255) / 256 <= kMaxGridY) {
         const int64_t n = n_blocks(n_rows, m, 256, 256);
         const double tr = n <= 192 ? 38.0 : 50.0 * static_cast<double>((n + 255) / 256);
-        if (tr < t) best = kPathRing;
+        // Up to 128 units two and more rounds of 128 x 64 blocks cost more than their share next to the ring (65,536 rollouts x
+        // 64 / 512 / 2048: 12.6 / 21.3 / 56.2 us against 9.6 / 19.9 / 50.2), until the rows outgrow the last-level cache
+        // (65,536 x 4096: 132 against 139).
+        const bool crowded = best == kPathMid128 && n_blocks(n_rows, m, 64, 128) > 512 && 2.0 * n_rows * d <= 384e6;
+        if (tr < (crowded ? 1.13 * t : t)) best = kPathRing;
     }
     return best;
 }
