@@ -70,6 +70,14 @@ __device__ __forceinline__ int64_t wave_bcast(int64_t v, int src) {
     return (static_cast<int64_t>(wave_bcast(static_cast<int>(v >> 32), src)) << 32) | lo;
 }
 
+// Between the LDS writes of one wavefront's lanes and the reads of its other lanes: the hardware completes one wavefront's
+// LDS accesses in order, the fences hold the compiler to it (the barrier alone does not order memory for it).  No instructions.
+__device__ __forceinline__ void wave_lds_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- wave-wide reductions: the butterfly 32, 16, 8, 4, 2, 1 without the LDS --------------------------------------
 // __shfl_xor goes through the LDS pipe (some 100 cycles of latency a step, twice for 64 bits); here steps 32 and 16 are
 // the lane-swapping moves of gfx950 and the others DPP moves, a few cycles each.  wave_pair_* returns a value and its

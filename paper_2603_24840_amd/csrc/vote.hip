@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
     unsigned int* mine = words + static_cast<size_t>(wave) * n_answers;
     if (TALLY_IN_LDS)
         for (int a = lane; a < n_answers; a += ARROL_WAVE) mine[a] = 0u;
-    __builtin_amdgcn_wave_barrier();            // one wavefront's LDS accesses complete in order
+    wave_lds_exchange();
     const float4* others = reinterpret_cast<const float4*>(score[wave]);
     int below = 0, equal = 0;
     const auto compare = [&](auto reads) {
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
     const int rank2 = 2 * below + equal - (q == q ? 1 : 0);     // the candidate itself is not one of the equal ones
     if (TALLY_IN_LDS) {
         if (ans >= 0) atomicAdd(&mine[ans], static_cast<unsigned int>(rank2) | 0x10000u);   // at most 64 * 126 below
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_exchange();
     }
     // lanes sweep the answer ids 64 at a time; each keeps its best (tally, lowest id) key
     int64_t best = -1;

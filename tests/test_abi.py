@@ -3,6 +3,7 @@ header declares, and rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -256,3 +257,18 @@ def test_mlp_gradient_scratch_of_the_largest_batch_serves_every_smaller_one(pkg)
         for terms in (1, 2):
             sizes = [size(n, d, m, terms) for n in list(range(1, 200)) + list(range(200, 40000, 13)) + list(range(40000, 2000000, 6397))]
             assert all(a <= b for a, b in zip(sizes, sizes[1:])), (d, m, terms)
+
+
+def test_lds_exchanges_within_a_wavefront_are_ordered_for_the_compiler(pkg, tmp_path):
+    """A wave barrier alone orders no memory accesses for the compiler: in the vote kernel's intermediate code, where lanes
+    read what other lanes wrote to the LDS, each one stands between a release and an acquire fence."""
+    from paper_2603_24840_amd import build
+    out = tmp_path / "vote.ll"
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-O3")]
+    subprocess.run([build.hipcc_path()] + flags + ["-O1", "-S", "-emit-llvm", "--offload-device-only", "-I", os.path.join(build.ROOT, "include"),
+                   os.path.join(build.CSRC, "vote.hip"), "-o", str(out)], check=True, stderr=subprocess.DEVNULL)
+    code = [l.strip() for l in out.read_text().splitlines()]
+    at = [i for i, l in enumerate(code) if "call void @llvm.amdgcn.wave.barrier()" in l]
+    assert len(at) >= 3                                     # scores in both forms, tallies in one
+    for i in at:
+        assert code[i - 1].startswith('fence syncscope("wavefront") release') and code[i + 1].startswith('fence syncscope("wavefront") acquire')
