@@ -64,7 +64,6 @@ static inline bool arrol_aligned16(const void* p) { return (reinterpret_cast<uin
 
 // The value of lane `src` (the same in every lane) in all lanes, by way of a scalar register.
 __device__ __forceinline__ int wave_bcast(int v, int src) { return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src)); }
-__device__ __forceinline__ float wave_bcast(float v, int src) { return __int_as_float(wave_bcast(__float_as_int(v), src)); }
 __device__ __forceinline__ int64_t wave_bcast(int64_t v, int src) {
     const uint32_t lo = static_cast<uint32_t>(wave_bcast(static_cast<int>(v & 0xffffffffll), src));
     return (static_cast<int64_t>(wave_bcast(static_cast<int>(v >> 32), src)) << 32) | lo;

@@ -1111,13 +1111,17 @@ void launch_reduce_slabs(const float* slabs, int n_slabs, int64_t width, float* 
 template <int MODE>
 int launch_mlp(const MlpArgs& a, dim3 grid, hipStream_t st) {
     static arrol_device_flags lds_ok, ring_ok;
-    if (a.d % BK == 0) {   // direct-to-LDS path
-        if (!arrol_allow_lds(&score_mlp_kernel<MODE, true>, kRingLdsBytes, ring_ok)) return ARROL_EHIP;
-        arrol_launch((score_mlp_kernel<MODE, true>), grid, dim3(kThreads), kRingLdsBytes, st, a);
-    } else {
-        if (!arrol_allow_lds(&score_mlp_kernel<MODE, false>, kLdsBytes, lds_ok)) return ARROL_EHIP;
-        arrol_launch((score_mlp_kernel<MODE, false>), grid, dim3(kThreads), kLdsBytes, st, a);
+    // direct-to-LDS path; the delta mode only runs where the forward pass keeps no activations: other d, or more units than
+    // a launch of the blocked forward passes can number
+    if constexpr (MODE != kDelta) {
+        if (a.d % BK == 0) {
+            if (!arrol_allow_lds(&score_mlp_kernel<MODE, true>, kRingLdsBytes, ring_ok)) return ARROL_EHIP;
+            arrol_launch((score_mlp_kernel<MODE, true>), grid, dim3(kThreads), kRingLdsBytes, st, a);
+            return arrol_launch_status();
+        }
     }
+    if (!arrol_allow_lds(&score_mlp_kernel<MODE, false>, kLdsBytes, lds_ok)) return ARROL_EHIP;
+    arrol_launch((score_mlp_kernel<MODE, false>), grid, dim3(kThreads), kLdsBytes, st, a);
     return arrol_launch_status();
 }
 
