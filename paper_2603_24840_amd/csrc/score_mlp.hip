@@ -738,7 +738,7 @@ int64_t n_blocks(int n_rows, int m, int bn, int bm) { return static_cast<int64_t
 // for up to 256 workgroups and for every 512 (the mid kernels, two workgroups per compute unit) or 256 (ring) beyond.
 // m = 512: 32 x 32 blocks up to some 700 rollouts, 64 x 64 up to 2,048, 128 x 64 up to 10,000, then the ring (at 8,192
 // rollouts 28 us against 43 of the ring; at 16,384 49 against 45).
-ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, const int64_t* row_index) {
+ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, bool gathered) {
     if (d % 64) return kPathTile;
     constexpr int kMaxGridY = 65535;         // unit blocks are blockIdx.y
     auto mid = [&](int bn, int bm, double one, double two) {
@@ -753,7 +753,7 @@ ForwardPath pick_forward(int n_rows, int d, int m, int64_t row_stride_elems, con
     if (t64 < t) { t = t64; best = kPathMid64; }
     if (t128 < t) { t = t128; best = kPathMid128; }
     // the ring kernel addresses a lane's row with a 32-bit byte offset inside a 256-row tile
-    if (row_index == nullptr && row_stride_elems * 2 * 256 < (1ll << 31) && (m + 255) / 256 <= kMaxGridY) {
+    if (!gathered && row_stride_elems * 2 * 256 < (1ll << 31) && (m + 255) / 256 <= kMaxGridY) {
         const int64_t n = n_blocks(n_rows, m, 256, 256);
         const double tr = n <= 192 ? 38.0 : 50.0 * static_cast<double>((n + 255) / 256);
         // Up to 128 units two and more rounds of 128 x 64 blocks cost more than their share next to the ring (65,536 rollouts x
@@ -780,6 +780,10 @@ bool tile_beats_mid128(int n_rows, int d, int m) {
     if (bytes > 384e6 && reads > mid) mid = reads;
     return tile < mid;
 }
+ForwardPath pick_score(int n_rows, int d, int m, int64_t row_stride_elems, bool gathered) {   // no activations kept
+    const ForwardPath p = pick_forward(n_rows, d, m, row_stride_elems, gathered);
+    return p == kPathMid128 && gathered && tile_beats_mid128(n_rows, d, m) ? kPathTile : p;
+}
 int unit_block(ForwardPath p) { return p == kPathMid32 ? 32 : p == kPathMid64 ? 64 : p == kPathMid128 ? 128 : 256; }
 
 // Partial scores of every unit block to `partial`, with act_t also the activations (kPathTile: not for this).
@@ -802,8 +806,8 @@ int enqueue_forward(ForwardPath path, const void* hidden, int64_t row_stride_ele
 }
 
 // dL/dW1 on the ring pipeline's K-major B form: any batch size, rows addressed in place
-bool ring_wgrad_applies(int d, int64_t row_stride_elems, const int64_t* row_index) {
-    return d % 64 == 0 && row_index == nullptr && row_stride_elems * 2 * 256 < (1ll << 31);
+bool wgrad_in_place(int d, int64_t row_stride_elems, bool gathered) {
+    return d % 64 == 0 && !gathered && row_stride_elems * 2 * 256 < (1ll << 31);
 }
 
 // r_i = (q_i - y_i) / N and the loss: one workgroup per 1024 rows writes its two partial sums, the second
@@ -1142,8 +1146,7 @@ extern "C" int arrol_score_mlp(const void* hidden, int64_t row_stride_elems, con
     if (!hidden || !w1 || !w2 || !prob_out || !arrol_aligned16(hidden) || !arrol_aligned16(w1)) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t need = arrol_score_mlp_workspace_bytes(n_rows, d, m);
-    ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
-    if (path == kPathMid128 && row_index && tile_beats_mid128(n_rows, d, m)) path = kPathTile;
+    const ForwardPath path = pick_score(n_rows, d, m, row_stride_elems, row_index != nullptr);
     if (path != kPathTile && workspace && arrol_aligned16(workspace) && workspace_bytes >= need) {
         float* partial = static_cast<float*>(workspace);
         const int rc = enqueue_forward(path, hidden, row_stride_elems, row_index, w1, b1, w2, n_rows, d, m, partial, nullptr, 0, st);
@@ -1212,7 +1215,7 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     a.n_rows = n_rows; a.d = d; a.m = m; a.score_out = score; a.prob_out = prob;
     float* act = reinterpret_cast<float*>(ws + p.off_act);
     float* partial = reinterpret_cast<float*>(ws + p.off_small);
-    const ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index);
+    const ForwardPath path = pick_forward(n_rows, d, m, row_stride_elems, row_index != nullptr);
     const bool kept = path != kPathTile;
     int rc;
     if (kept)
@@ -1242,7 +1245,7 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     }
     if (arrol_launch_failed()) return arrol_launch_status();
     const int64_t width = static_cast<int64_t>(m) * d;
-    if (ring_wgrad_applies(d, row_stride_elems, row_index)) {
+    if (wgrad_in_place(d, row_stride_elems, row_index != nullptr)) {
         // dL/dW1 = delta^T . H over the rollouts, the hidden states read in place
         float* rslab = reinterpret_cast<float*>(ws + p.off_rslab);
         MlpRingArgs g = {};
@@ -1280,4 +1283,22 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     if (n_slabs > 1)
         launch_reduce_slabs(slab, n_slabs, width, grad_w1, st);
     return arrol_launch_status();
+}
+
+extern "C" int arrol_score_mlp_kernels(int32_t n_rows, int32_t d, int32_t m, int64_t row_stride_elems, int32_t gathered,
+                                       int32_t delta_terms, int32_t* forward, int32_t* weight_gradient, int32_t* splits) {
+    if (n_rows < 1 || d < 8 || (d & 7) || m < 1 || row_stride_elems < d || delta_terms < 0 || delta_terms > 2 || !forward ||
+        !weight_gradient || !splits)
+        return ARROL_EINVAL;
+    const auto pick = delta_terms ? pick_forward : pick_score;
+    *forward = pick(n_rows, d, m, row_stride_elems, gathered != 0);
+    *weight_gradient = -1;
+    *splits = 0;
+    if (delta_terms) {
+        const GradPlan p = make_grad_plan(n_rows, d, m, delta_terms);
+        const bool in_place = wgrad_in_place(d, row_stride_elems, gathered != 0);
+        *weight_gradient = !in_place ? 0 : p.w_mid ? 1 : 2;
+        *splits = in_place ? p.r_splits : p.splits;
+    }
+    return ARROL_OK;
 }

@@ -1,4 +1,6 @@
 """Test-side glue: move torch tensors to the numpy forms the oracle takes."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -24,3 +26,12 @@ def to_dev(x, device, dtype=None):
 def oracle_survivors(O, prob_f32, cfg):
     """Survivors the oracle selects from fp32 probabilities (numpy), as (keep_mask, survivor_idx)."""
     return O.select(np.asarray(prob_f32, dtype=np.float32), cfg.n_prompts, cfg.G, cfg.K, cfg.rho)
+
+
+def mlp_kernels(A, n, d, m, delta_terms, gathered=False, row_stride=None):
+    """(forward, weight gradient, splits) that the MLP calls take for a batch, numbered as in the header: a test that is
+    there for one kernel says so, and fails when a changed choice leads its sizes elsewhere."""
+    out = [ctypes.c_int32() for _ in range(3)]
+    rc = A.lib().arrol_score_mlp_kernels(n, d, m, row_stride or d, int(gathered), delta_terms, *[ctypes.byref(x) for x in out])
+    assert rc == 0
+    return tuple(x.value for x in out)

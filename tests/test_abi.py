@@ -117,11 +117,18 @@ def test_bad_arguments_are_rejected_on_the_host(pkg):
     assert L.arrol_score_mlp(fake, 16, None, fake, None, fake, 0.0, 4, 16, 0, None, fake, None, 0, None) == -1
     assert L.arrol_score_mlp(fake, 16, None, fake, None, None, 0.0, 4, 16, 8, None, fake, None, 0, None) == -1
     assert L.arrol_score_mlp(None, 16, None, None, None, None, 0.0, 0, 16, 8, None, None, None, 0, None) == 0
-    # scratch of the multi-launch paths: partial scores per 32-unit block (small batches) or per 256-unit tile
-    # (beyond 4,096 rows); none when d % 64 != 0 (one-launch tile kernel only)
+    # scratch of the multi-launch paths: partial scores of up to one block per 32 units; none when d % 64 != 0
+    # (one-launch tile kernel only)
     assert L.arrol_score_mlp_workspace_bytes(512, 2048, 512) >= 16 * 512 * 4
     assert L.arrol_score_mlp_workspace_bytes(512, 2056, 512) == 0
     assert L.arrol_score_mlp_workspace_bytes(32768, 4096, 512) >= 2 * 32768 * 4
+    # which kernels a batch takes: bad shapes, terms outside 0 to 2, missing outputs
+    kern = lambda n, d, m, stride, terms, out: L.arrol_score_mlp_kernels(n, d, m, stride, 0, terms, out, out, out)
+    one = ctypes.byref(ctypes.c_int32())
+    assert kern(64, 128, 8, 128, 1, one) == 0
+    for bad in ((0, 128, 8, 128, 1, one), (64, 12, 8, 128, 1, one), (64, 128, 0, 128, 1, one), (64, 128, 8, 64, 1, one),
+                (64, 128, 8, 128, 3, one), (64, 128, 8, 128, -1, one), (64, 128, 8, 128, 1, None)):
+        assert kern(*bad) == -1, bad
     # head training: bad d, missing gradient output, workspace; optimizer: bad step / betas
     assert L.arrol_score_grad(fake, 16, None, fake, 0.0, fake, 4, 12, None, fake, None, fake, 1 << 20, None) == -1
     assert L.arrol_score_grad(fake, 16384, None, fake, 0.0, fake, 4, 16384, None, fake, None, fake, 1 << 20, None) == -1

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
+from helpers import bits, mlp_kernels, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
 
 pytestmark = pytest.mark.gpu
 
@@ -387,7 +387,7 @@ def test_whole_path_is_deterministic(A, W):
 # ------------------------------------------------------------------------------- MLP head
 @pytest.mark.parametrize("n,d,m", [(32, 256, 64), (1, 8, 1), (130, 264, 100), (512, 2048, 512), (300, 4096, 257),
                                    (1000, 3072, 768),
-                                   (4500, 128, 300), (4097, 64, 7), (6000, 1024, 513)])     # beyond 4,096 rows: the ring-pipeline kernel
+                                   (4500, 128, 300), (4097, 64, 7), (6000, 1024, 513)])     # many rows: blocks of 128 x 64 and of 32 x 32
 def test_score_mlp_matches_oracle(A, n, d, m):
     say("score_mlp n=%d d=%d m=%d" % (n, d, m))
     g = torch.Generator(device=DEV); g.manual_seed(n + d + m)
@@ -395,7 +395,7 @@ def test_score_mlp_matches_oracle(A, n, d, m):
     w1 = (torch.randn(m, d, generator=g, device=DEV) * d ** -0.5).to(torch.bfloat16)
     b1 = torch.randn(m, generator=g, device=DEV) * 0.1
     w2 = torch.randn(m, generator=g, device=DEV) * m ** -0.5
-    s, q = A.arrol_score_mlp(hidden, w1, b1, w2, b2=-0.125)                    # with the library's scratch (small-batch path where it applies)
+    s, q = A.arrol_score_mlp(hidden, w1, b1, w2, b2=-0.125)                    # with the library's scratch (blocks, where d is a multiple of 64)
     s1, q1 = A.arrol_score_mlp(hidden, w1, b1, w2, b2=-0.125, workspace=None)  # the one-launch tile kernel
     s_nb, _ = A.arrol_score_mlp(hidden, w1, None, w2)
     torch.cuda.synchronize()
@@ -426,6 +426,16 @@ def test_score_mlp_dispatch_by_size(A, n, d, m, gather):
     torch.cuda.synchronize()
     so, qo = O.score_mlp(bits(rows), bits(w1), npy(b1), npy(w2), 0.25)
     assert np.max(np.abs(npy(s) - so)) < SCORE_DERIVED and np.max(np.abs(npy(q) - qo)) < SCORE_DERIVED / 4
+
+
+# one batch and more for every forward kernel, each with several K64 steps and remainders on both sides
+@pytest.mark.parametrize("n,d,m,gather,forward", [(700, 1024, 200, False, 1), (700, 1024, 200, True, 1), (1203, 1024, 400, False, 2),
+                                                  (6001, 1024, 300, True, 2), (5003, 448, 300, False, 3), (9001, 576, 530, True, 3),
+                                                  (9001, 1088, 530, False, 4), (9001, 320, 1030, False, 4), (50001, 64, 100, False, 4),
+                                                  (17001, 64, 513, True, 0)])
+def test_score_mlp_reaches_each_forward_kernel(A, n, d, m, gather, forward):
+    assert mlp_kernels(A, n, d, m, 0, gathered=gather, row_stride=d + 64) == (forward, -1, 0)
+    test_score_mlp_dispatch_by_size(A, n, d, m, gather)
 
 
 def test_score_mlp_gathered_rows_and_dead_units(A):

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, npy
+from helpers import bits, mlp_kernels, npy
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -195,7 +195,7 @@ def check_mlp_grad(A, hidden, w1, b1, w2, b2, labels, row_index=None, delta_term
 
 @pytest.mark.parametrize("n,d,m", [(1, 8, 1), (32, 256, 64), (130, 264, 100), (300, 1024, 257), (512, 2048, 512),
                                    (1500, 512, 300),
-                                   (4500, 128, 300), (4097, 64, 7), (5000, 192, 512),      # beyond 4,096 rows: the ring-pipeline kernels
+                                   (4500, 128, 300), (4097, 64, 7), (5000, 192, 512),      # many rows, 9 to 16 K splits of dL/dW1
                                    (4200, 320, 70), (8195, 576, 260)])                     # ... more than one 256-column block of dL/dW1
 def test_score_mlp_grad_matches_oracle(A, n, d, m):
     print("[case] score_mlp_grad n=%d d=%d m=%d" % (n, d, m), flush=True)
@@ -204,10 +204,10 @@ def test_score_mlp_grad_matches_oracle(A, n, d, m):
 
 
 @pytest.mark.parametrize("n,d,m", [(130, 264, 100),      # tile kernels (d not a multiple of 64)
-                                   (300, 1024, 257),     # wavefront-per-block forward, in-place dL/dW1, one K split
+                                   (300, 1024, 257),     # 32 x 32 blocks forward, in-place dL/dW1, one K split
                                    (512, 2048, 512),
                                    (2048, 256, 128),     # several K splits
-                                   (4500, 128, 300)])    # ring-pipeline forward
+                                   (4500, 128, 300)])    # 128 x 64 blocks forward, twelve K splits
 def test_score_mlp_grad_two_term_delta_is_fp32_accurate(A, n, d, m):
     """delta_terms = 2: dL/dW1 within 1e-5 of the float64 oracle in norm (2^-8 for the one-term form), and
     strictly closer than the one-term result; everything else unchanged bit for bit."""
@@ -225,13 +225,43 @@ def test_score_mlp_grad_two_term_delta_is_fp32_accurate(A, n, d, m):
 
 
 # dL/dW1 in 128 x 64 blocks: rollouts that end inside a K64 step or just past one, units that end inside a block, one
-# and several K splits (one and two partial slabs), two-term delta; the last size goes to the 256 x 256 ring form
+# and several K splits (one and more partial slabs), two-term delta; the last size has the ring form's forward pass
 @pytest.mark.parametrize("n,d,m,terms", [(1, 64, 1, 1), (63, 64, 127, 1), (65, 192, 129, 2), (129, 128, 128, 1), (1025, 64, 300, 1),
                                          (2100, 192, 70, 2), (16384, 1024, 512, 1)])
 def test_score_mlp_grad_weight_gradient_blocks(A, n, d, m, terms):
     print("[case] score_mlp_grad blocks n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
     hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=7 * n + d + m)
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.5, labels, delta_terms=terms)
+
+
+# dL/dW1 in the 256 x 256 ring form: one to fifteen K splits, one and two terms, units, columns and rollouts that end inside a
+# tile, rows that are views into a wider buffer, behind a forward pass in blocks and in the ring form that keeps activations
+@pytest.mark.parametrize("n,d,m,terms,kernels,pad", [(600, 4096, 1100, 1, (2, 2, 1), 0), (246, 2176, 1047, 2, (2, 2, 1), 64),
+                                                     (590, 2112, 961, 2, (2, 2, 2), 0), (3533, 896, 1183, 2, (4, 2, 4), 64),
+                                                     (4100, 2048, 1100, 1, (4, 2, 5), 8), (6741, 1216, 513, 2, (2, 2, 9), 0),
+                                                     (16320, 704, 589, 2, (4, 2, 15), 0)])
+def test_score_mlp_grad_weight_gradient_ring_form(A, n, d, m, terms, kernels, pad):
+    print("[case] score_mlp_grad ring n=%d d=%d m=%d terms=%d pad=%d" % (n, d, m, terms, pad), flush=True)
+    assert mlp_kernels(A, n, d, m, terms, row_stride=d + pad) == kernels
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=5 * n + d + m)
+    if pad:
+        wide = torch.full((n, d + pad), float("nan"), dtype=torch.bfloat16, device=DEV)   # what lies beside the rows is never read
+        wide[:, :d] = hidden
+        hidden = wide[:, :d]
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.5, labels, delta_terms=terms)
+
+
+# gathered rows: the blocked forward passes that keep activations, dL/dW1 of the transposed rows
+@pytest.mark.parametrize("n,d,m,terms,forward", [(1030, 704, 200, 1, 1), (1500, 512, 300, 2, 2), (2900, 128, 513, 1, 3), (5000, 320, 260, 2, 3),
+                                                 (6000, 192, 130, 1, 3)])
+def test_score_mlp_grad_gathered_rows_by_size(A, n, d, m, terms, forward):
+    print("[case] score_mlp_grad gathered n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
+    assert mlp_kernels(A, n, d, m, terms, gathered=True)[:2] == (forward, 0)
+    hidden, w1, b1, w2, _ = mlp_case(n + 41, d, m, seed=n + 2 * d + m)
+    g = torch.Generator(device=DEV); g.manual_seed(n)
+    idx = torch.randint(0, n + 41, (n,), generator=g, device=DEV, dtype=torch.int64)
+    soft = torch.rand(n, generator=g, device=DEV)
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, -0.25, soft, row_index=idx, delta_terms=terms)
 
 
 def test_score_mlp_grad_into_a_buffer_that_is_only_4_byte_aligned(A):
@@ -281,8 +311,8 @@ def test_score_mlp_grad_gathered_rows_no_bias_dead_units_and_empty_batch(A):
 
 
 def test_score_mlp_grad_large_batch_strided_rows_and_reproducible(A):
-    """Ring-pipeline path on rows that are a view into a wider buffer (dL/dW1 contracts the hidden states in
-    place, rollout-major); two calls give identical bits."""
+    """Rows that are a view into a wider buffer (dL/dW1 contracts the hidden states in place, rollout-major, here in
+    128 x 64 blocks); two calls give identical bits."""
     print("[case] score_mlp_grad n=4300 d=192 of 256 m=130 strided", flush=True)
     hidden, w1, b1, w2, labels = mlp_case(4300, 192, 130, seed=21)
     wide = torch.full((4300, 256), float("nan"), dtype=torch.bfloat16, device=DEV)   # what lies beside the rows is never read
@@ -297,7 +327,7 @@ def test_score_mlp_grad_large_batch_strided_rows_and_reproducible(A):
 def test_score_mlp_grad_is_reproducible_and_trains(A):
     """Two calls give identical bits; gradient + AdamW on all four parameter sets lowers the loss."""
     print("[case] score_mlp_grad reproducible / training loop", flush=True)
-    hidden, w1, b1, w2, labels = mlp_case(2048, 256, 128, seed=9)          # three K splits
+    hidden, w1, b1, w2, labels = mlp_case(2048, 256, 128, seed=9)          # eight K splits
     o1 = A.arrol_score_mlp_grad(hidden, w1, b1, w2, 0.0, labels)
     o2 = A.arrol_score_mlp_grad(hidden, w1, b1, w2, 0.0, labels)
     torch.cuda.synchronize()
