@@ -105,3 +105,29 @@ def test_objective_benchmark_shape(A, W):
     lens = W.response_lengths(cfg).numpy().tolist()
     print("[case] grpo_objective llama1b n=%d T=%d" % (len(lens), sum(lens)), flush=True)
     run_objective(A, lens, [cfg.K] * (len(lens) // cfg.K), seed=11, beta=0.01)
+
+
+def test_objective_at_extreme_ratios(A):
+    """exp(u) is the reciprocal of exp(-u) where that keeps its bits: log-ratios around the ends of that range (ln 1e300 =
+    690.8), beyond the fp64 range, infinite, undefined and zero, both signs of the advantage."""
+    print("[case] grpo_objective extreme ratios", flush=True)
+    u = np.array([0.0, 1e-7, -1e-7, 1.0, -1.0, 87.0, -87.0, 690.5, 691.0, -690.5, -691.0, 709.5, -709.5, 750.0, -750.0, np.inf, -np.inf, np.nan])
+    lens, beta = [len(u)] * 2, 0.5
+    ref = np.concatenate([u, u]).astype(np.float32)
+    adv, cu = np.array([1.0, -0.5], np.float32), np.array([0, len(u), 2 * len(u)])
+    J, grad, n_clip = A.arrol_grpo_objective(torch.zeros(len(ref), device=DEV), to_dev(ref, DEV), dev_i64(cu), to_dev(adv, DEV),
+                                             torch.full((2,), 0.5, device=DEV), 0.2, 0.28, beta)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        u64, a = ref.astype(np.float64), np.repeat(adv.astype(np.float64), lens)
+        ratio = np.exp(-u64)
+        plain, clamped = ratio * a, np.fmin(np.fmax(ratio, 1.0 - f32(0.2)), 1.0 + f32(0.28)) * a
+        want = ((np.where(plain <= clamped, plain, 0.0) - beta * (1.0 - np.exp(u64))) * (0.5 / len(u))).astype(np.float32)
+        clipped = int(np.sum(clamped < plain))
+    got = npy(grad)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    ok = np.isfinite(want)
+    # two rounded fp64 terms that cancel near u = 0 (each up to 1), then one rounding to fp32
+    assert np.all(np.abs(got[ok] - want[ok]) <= 1e-7 * np.abs(want[ok]) + 1e-15 * 0.5 / len(u) * 4)
+    assert np.array_equal(np.signbit(got[~ok & ~np.isnan(want)]), np.signbit(want[~ok & ~np.isnan(want)]))
+    assert int(n_clip) == clipped and np.isnan(float(J))
