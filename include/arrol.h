@@ -85,7 +85,8 @@ int arrol_score(const void* hidden, int64_t row_stride_elems, const int64_t* row
  * call is one kernel whose workgroups each take 128 rollouts; given the queried size (16-byte aligned; the query
  * returns 0 where this does not apply) the batch is spread over the whole GPU instead - blocks of units x blocks of
  * rollouts of a size that fits the batch, partial sums over the units in the workspace, added in a fixed order by a
- * second launch.  Results of the two paths differ by fp32 summation order only.
+ * second launch (large batches of narrow gathered rows stay with the one kernel where it is faster).  Results of the two
+ * paths differ by fp32 summation order only.
  */
 size_t arrol_score_mlp_workspace_bytes(int32_t n_rows, int32_t d, int32_t m);
 int arrol_score_mlp(const void* hidden, int64_t row_stride_elems, const int64_t* row_index,

@@ -175,8 +175,8 @@ def arrol_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=No
 @_on_stream
 def arrol_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto", stream=None):
     """hidden bf16 [R, d], w1 bf16 [m, d], b1 fp32 [m] or None, w2 fp32 [m] -> (score, prob) fp32 [n].
-    workspace: "auto" allocates what the library asks for (the small-batch path), None passes none (the
-    one-launch kernel), or a uint8 tensor."""
+    workspace: "auto" allocates what the library asks for (blocks of units x rollouts over the whole GPU), None passes
+    none (the one-launch kernel), or a uint8 tensor."""
     if hidden.dim() != 2 or hidden.dtype != torch.bfloat16 or not hidden.is_cuda or hidden.stride(1) != 1:
         raise TypeError("hidden must be a 2-D bf16 GPU tensor with contiguous rows")
     d = hidden.shape[1]

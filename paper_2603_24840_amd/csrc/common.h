@@ -80,8 +80,8 @@ __device__ __forceinline__ void wave_lds_exchange() {
 // ---- wave-wide reductions: the butterfly 32, 16, 8, 4, 2, 1 without the LDS --------------------------------------
 // __shfl_xor goes through the LDS pipe (some 100 cycles of latency a step, twice for 64 bits); here steps 32 and 16 are
 // the lane-swapping moves of gfx950 and the others DPP moves, a few cycles each.  wave_pair_* returns a value and its
-// partner's, in the order (lower lane's, upper lane's), which is all a commutative operation needs: the pairs and so the
-// results are the shuffle butterfly's, bit for bit.  Rotations by 4 within a row of 16 stand for xor 4 because after
+// partner's - steps 32 and 16 in the order (lower lane's, upper lane's), the others (own, partner's) - so the operation has
+// to be commutative; the pairs and so the results are the shuffle butterfly's, bit for bit.  Rotations by 4 within a row of 16 stand for xor 4 because after
 // step 8 the row repeats every 8 lanes (every 4 after step 4 for the rotation by 2).  All 64 lanes must be active.
 struct wave_pair32 { uint32_t a, b; };
 template <int STEP>

@@ -120,7 +120,8 @@ __global__ __launch_bounds__(kConfThreads) void token_conf_kernel(
 // of a trace that one round of the scan covers stay in LDS, every thread keeps up to ITEMS window keys in registers, and the m-th
 // smallest key is found eight bits at a time from LDS counts, from the highest bit in which the keys differ on and only
 // until one key is left (two or three rounds for windows that differ; deciding one bit a round took 64 rounds with a
-// barrier each).  256 traces of 256 to 2,048 tokens, window 1,024: 46.1 -> 9.8 us.
+// barrier each).  256 traces of 256 to 2,048 tokens, window 1,024: 46.1 -> 8.7 us under the profiler (7.3 in a graph of
+// such calls, the measure of the launch's rule).
 constexpr int kAggBits = 8;        // bits of the key decided per round
 constexpr int kAggBins = 1 << kAggBits;
 

@@ -264,8 +264,9 @@ __device__ __forceinline__ void write_partials16(LaneState<TJ>& st, float* red, 
 }
 
 // workgroup id -> (token block, vocab split).  Ids congruent mod 8 land on the same XCD, and a round of 256 workgroups
-// (one per compute unit: every kernel here takes most of a unit's LDS) gives each XCD 32 consecutive positions of the
-// work order (the last round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
+// (one per compute unit: the tile kernels take most of a unit's LDS; the stream kernel takes 64 KiB, but has a single token
+// block, whose splits share no more than its tokens) gives each XCD 32 consecutive positions of the work order (the last
+// round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
 // each band with the split fastest where there are up to 8 (1.5-2 % faster than the other way round at 8,000 to 33,000
 // tokens), the token block fastest otherwise (0.6 % at 4,096 tokens x 16 splits), so the 32 resident workgroups of an
 // XCD are a patch of about 6 token blocks x 5 splits that shares its H and W tiles through the XCD's L2, for any

@@ -10,7 +10,8 @@
 //
 // arrol_score_mlp_grad: cross-entropy training gradient of the same head (Sec. 4.2, Sec. 4.3 (iii)).  The same
 // tile loop runs in two more modes:
-//   delta   recomputes the pre-activations and, instead of the w2 dot, writes delta^T[u][i] =
+//   delta   (d not a multiple of 64; else the blocked forward passes keep the activations and mlp_delta_kernel reads them)
+//           recomputes the pre-activations and, instead of the w2 dot, writes delta^T[u][i] =
 //           r_i * w2[u] * [pre > 0] (bf16, unit-major) and the per-workgroup sums for dL/dw2 and dL/db1;
 //   wgrad   the contraction over rollouts dL/dW1 = delta^T . H as the same "A rows x B rows over a shared
 //           contiguous K" product, with A = delta^T [m, N] and B = H^T [d, N] (transposed once into the
