@@ -69,6 +69,18 @@ __device__ __forceinline__ void mlp_wait_vmcnt() {  // s_waitcnt vmcnt(N) only (
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Units past the last one fill up a block; they repeat its row of W1, so their pre-activations may be infinite, and infinity
+// times their zero weight would be NaN.  With this bias they are -inf, or NaN, and fmaxf(pre, 0) is 0 for both.  (Loads from
+// a clamped address: one that may be skipped is waited for before the next.)
+__device__ __forceinline__ float unit_bias(const float* b1, int u, bool live) {
+    const float b = b1 ? b1[live ? u : 0] : 0.f;
+    return live ? b : -__builtin_inff();
+}
+__device__ __forceinline__ float unit_weight(const float* w2, int u, bool live) {
+    const float w = w2[live ? u : 0];
+    return live ? w : 0.f;
+}
+
 // RING = false: any d (multiple of 8), K chunks staged global -> registers -> LDS, one chunk ahead.
 // RING = true (d a multiple of 64): K chunks go global -> LDS directly (no staging registers) into three
 // stages, two chunks ahead, so that a workgroup that is alone on its CU (few rollouts) still hides the
@@ -261,8 +273,8 @@ __global__ __launch_bounds__(kThreads) void score_mlp_kernel(MlpArgs a) {
                             acc[c][j][v] = 0.f;
                         }
                     } else {
-                        const float bias = (live && a.b1) ? a.b1[u] : 0.f;
-                        const float w = live ? a.w2[u] : 0.f;
+                        const float bias = unit_bias(a.b1, u, live);
+                        const float w = unit_weight(a.w2, u, live);
                         if (MODE == kForward) {
 #pragma unroll
                             for (int j = 0; j < TR; ++j) {
@@ -434,7 +446,7 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_mid_kernel(MlpMidArgs a) {
         for (int v = 0; v < 4; ++v) {
             const int u = u0 + wm * (BM / 2) + i * 16 + lq * 4 + v;
             const bool live = u < a.m;
-            const float bias = (live && a.b1) ? a.b1[u] : 0.f, w = live ? a.w2[u] : 0.f;
+            const float bias = unit_bias(a.b1, u, live), w = unit_weight(a.w2, u, live);
             float* arow = a.act_t ? a.act_t + static_cast<int64_t>(live ? u : 0) * a.act_stride : nullptr;
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
@@ -564,8 +576,8 @@ __global__ __launch_bounds__(RingCfg::NT) void mlp_ring_kernel(MlpRingArgs a) {
                         if (live && col < a.b_rows) crow[col] = acc[i][j][v];
                     }
                 } else {
-                    const float bias = (live && a.b1) ? a.b1[u] : 0.f;
-                    const float wu = live ? a.w2[u] : 0.f;
+                    const float bias = unit_bias(a.b1, u, live);
+                    const float wu = unit_weight(a.w2, u, live);
                     float* arow = MODE == kForwardKeep ? a.act_t + static_cast<int64_t>(live ? u : 0) * a.act_stride : nullptr;
 #pragma unroll
                     for (int j = 0; j < TJ; ++j) {

@@ -438,6 +438,29 @@ def test_score_mlp_reaches_each_forward_kernel(A, n, d, m, gather, forward):
     test_score_mlp_dispatch_by_size(A, n, d, m, gather)
 
 
+# a rollout whose pre-activations overflow: the units that fill up the last block (they repeat the last one) add nothing, not
+# infinity times zero
+@pytest.mark.parametrize("n,d,m,gather,forward", [(300, 128, 40, False, 1), (1203, 1024, 416, False, 2), (1203, 1024, 400, True, 2),
+                                                  (5003, 448, 288, False, 3), (9001, 576, 544, False, 4), (17001, 64, 513, True, 0),
+                                                  (200, 72, 33, False, 0)])
+def test_score_mlp_infinite_activations_and_padding_units(A, n, d, m, gather, forward):
+    say("score_mlp infinite n=%d d=%d m=%d" % (n, d, m))
+    assert mlp_kernels(A, n, d, m, 0, gathered=gather)[0] == forward
+    g = torch.Generator(device=DEV); g.manual_seed(n + m)
+    hidden = torch.randn(n, d, generator=g, device=DEV).to(torch.bfloat16)
+    w1 = (torch.randn(m, d, generator=g, device=DEV) * d ** -0.5).to(torch.bfloat16)
+    w1[:, 7] = 0.5
+    w2 = torch.rand(m, generator=g, device=DEV) + 0.1
+    up, down = n // 2, n - 1
+    hidden[up, 7], hidden[down, 7] = float("inf"), float("-inf")
+    idx = torch.arange(n, device=DEV, dtype=torch.int64) if gather else None
+    for ws in ("auto", None):
+        s, q = A.arrol_score_mlp(hidden, w1, None, w2, b2=-1.0, row_index=idx, workspace=ws)
+        torch.cuda.synchronize()
+        assert float(s[up]) == float("inf") and float(q[up]) == 1.0
+        assert float(s[down]) == -1.0 and bool(torch.isfinite(s[:up]).all()) and bool(torch.isfinite(s[up + 1:]).all())
+
+
 def test_score_mlp_gathered_rows_and_dead_units(A):
     g = torch.Generator(device=DEV); g.manual_seed(8)
     big = torch.randn(200, 512, generator=g, device=DEV).to(torch.bfloat16)
