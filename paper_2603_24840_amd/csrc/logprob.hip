@@ -264,8 +264,7 @@ __device__ __forceinline__ void write_partials16(LaneState<TJ>& st, float* red, 
 }
 
 // workgroup id -> (token block, vocab split).  Ids congruent mod 8 land on the same XCD, and a round of 256 workgroups
-// (one per compute unit: the tile kernels take most of a unit's LDS; the stream kernel takes 64 KiB, but has a single token
-// block, whose splits share no more than its tokens) gives each XCD 32 consecutive positions of the work order (the last
+// (one per compute unit: the tile kernels take most of a unit's LDS) gives each XCD 32 consecutive positions of the work order (the last
 // round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
 // each band with the split fastest where there are up to 8 (1.5-2 % faster than the other way round at 8,000 to 33,000
 // tokens), the token block fastest otherwise (0.6 % at 4,096 tokens x 16 splits), so the 32 resident workgroups of an
@@ -453,8 +452,8 @@ struct RingTile {
 };
 
 template <int N>
-__device__ __forceinline__ void wait_vmcnt() {  // s_waitcnt vmcnt(N) only (gfx9 encoding), N <= 15
-    __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+__device__ __forceinline__ void wait_vmcnt() {  // s_waitcnt vmcnt(N) only (gfx9 encoding: bits 3:0 and 15:14), N <= 63
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 template <class C>
@@ -722,38 +721,48 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Few tokens (d a multiple of 64): 256 vocabulary rows x 16 TJ tokens per workgroup, 8 wavefronts of 32 rows x all
-// the tokens.  What bounds it is the stream of W from HBM (V d 2 bytes, read once).  A W fragment belongs to one
-// wavefront alone, so W goes from memory straight to registers without LDS or barriers in its way; the H tile, which
-// all wavefronts share, goes to LDS directly.  Loads are requested a group of G K64 steps at a time, one group ahead:
-// 128 G contiguous bytes of each row in one burst (4.2 -> 4.6 TB/s at 64 tokens, 151,936 x 2048, over the same bytes
-// requested 128 at a time 4 steps ahead; 6 and 8 steps ahead changed nothing), and one barrier per group.  134 us
-// there (the ring kernel 173), 255 us = 4.9 TB/s at d = 4096.
+// Block kernel (d a multiple of 64, up to some 600 tokens): 32 TI vocabulary rows x 64 TJ tokens per workgroup of 2 x 4
+// wavefronts, the narrower forms of the tile above for batches that would leave much of a 256-token block empty.
 //
-// Stage layout: 16-byte chunk c of token row r sits at position c ^ (r & 6) of its 128-byte row.  By the serving rule
-// given at the ring kernel's fragment reads, lanes that share a bank group differ in lane bit 3 alone: no conflicts.
+// What bounds it is the bytes in flight: W comes from HBM, every line once, some 1.2 us away under load; the loads of a
+// wavefront complete in order, so H's, from the L2, wait behind them; and the LDS holds under three K64 steps.  So a step
+// ("pair" of K32 chunks, slots of whole 128-byte lines per operand, NA of W and NB of H) has one barrier, and everything
+// that hides latency hangs on it: all fragments of the next chunk are read ahead into a second register set, so that at the
+// barrier of pair p (in its second chunk, behind row BAR of MFMAs) both of pair p's slots are free, and the loads of H(p + NB)
+// and W(p + NA) all go out right behind it.  The barrier certifies pair p + 1.
+// Every split starts at another place of the K extent and wraps around: all of them at the same offset of rows a power of
+// two apart meet in the same memory channels (128 tokens: 151 us against 119).
 //
-// The steps of all vocabulary tiles of the split form one sequence, cut into groups; steps past its end load and
-// multiply the last tile's lines again into accumulators that nobody reads.
+// Measured at 151,936 x 2048 (before: for up to 128 tokens W straight to registers, else the ring kernel): 64 tokens 134 ->
+// 111 us (5.6 TB/s of W), 128: 153 -> 119, 192: 177 -> 136, 311: 262 -> 193, 384: 264 -> 222.  At 311 tokens with W always
+// from the L2 it would be 160, without any loads 130.  Tried and slower: W and H fetched by different wavefronts, each with
+// its own order (311 tokens: 242); W straight to registers, several steps ahead (128 tokens: 148; half lines at a time).
+//
+// Slot layout: 16-byte chunk c of row r sits at position c ^ (r & 6) of its 128-byte row: by the serving rule given at the
+// ring kernel's fragment reads, lanes that share a bank group differ in lane bit 3 alone: no conflicts.
 // ---------------------------------------------------------------------------------------------
-template <int TJ_>
-struct StreamTile {
-    static constexpr int BM = 256, TJ = TJ_, BN = 16 * TJ_;
-    static constexpr int NW = 8, NT = NW * ARROL_WAVE;
-    static constexpr int TI = BM / NW / 16;
-    static constexpr int G = TJ <= 4 ? 4 : 2;            // K64 steps per group
-    static constexpr int STAGE_BYTES = BN * 128;
-    static constexpr int NS = 2 * G;
-    static constexpr int RED_BYTES = NW * 3 * BN * 4;    // write_partials16
-    static constexpr int LDS_BYTES = NS * STAGE_BYTES > RED_BYTES ? NS * STAGE_BYTES : RED_BYTES;
-    static constexpr int GROUPS = BN / 8;                // load instructions (8 token rows x 128 bytes) per stage
-    static constexpr int HL = (GROUPS + NW - 1) / NW;    // per wavefront; the surplus ones repeat the last group
+template <int TI_, int TJ_, int NA_, int NB_>
+struct BlockTile {
+    static constexpr int TI = TI_, TJ = TJ_, NA = NA_, NB = NB_;
+    static constexpr int WM = 2, WN = 4, NW = WM * WN, NT = NW * ARROL_WAVE;
+    static constexpr int BM = 16 * TI * WM, BN = 16 * TJ * WN;
+    static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;   // one slot: K64 of an operand
+    static constexpr int LDS_BYTES = NA * A_BYTES + NB * B_BYTES;
+    static constexpr int GA = BM / 8;                              // load instructions (8 rows x 128 bytes) per slot of W
+    static constexpr int LA = (GA + NW - 1) / NW, LB = BN / 8 / NW, L = LA + LB;   // per wavefront; surplus ones repeat the last
+    static constexpr int BAR = TI == 8 ? 1 : 0;
+    static constexpr int PER_ROW = 3;                              // loads behind each row of MFMAs from BAR on
+    // in flight at the barrier of pair p + 1: what was requested after H(p + 2)
+    static constexpr int FLY = (NA > NB ? LA : 0) + (NB - 2) * L;
+    static_assert(LDS_BYTES <= 163840 && WM * 3 * BN * 4 <= LDS_BYTES, "LDS (write_partials16 needs the latter)");
+    static_assert(NB >= 2 && (NA == NB || NA == NB + 1), "order of the loads");
+    static_assert((TI - BAR) * PER_ROW >= L, "all loads in the second chunk");
 };
 
 template <class C>
-__global__ __launch_bounds__(C::NT) void logprob_stream_kernel(LogprobArgs a) {
+__global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    constexpr int TI = C::TI, TJ = C::TJ, G = C::G, BM = C::BM, BN = C::BN;
+    constexpr int BM = C::BM, BN = C::BN, TI = C::TI, TJ = C::TJ, NA = C::NA, NB = C::NB, L = C::L;
     typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
     int tb, sp, vt_lo, vt_hi;
@@ -761,137 +770,165 @@ __global__ __launch_bounds__(C::NT) void logprob_stream_kernel(LogprobArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / C::WN, wn = wave % C::WN;
     const int l15 = lane & 15, lq = lane >> 4;
     const int64_t tok0 = static_cast<int64_t>(tb) * BN;
     const int n_k64 = a.d / 64;
-    const int total = (vt_hi - vt_lo) * n_k64;           // host: at most n_vt * n_k64, checked against INT32_MAX
-    const unsigned row_bytes = static_cast<unsigned>(a.d) * 2;
 
-    // ---- H loader: lane -> (row lane/8 of an 8-row group, position lane%8), rows past the last token repeat it
-    unsigned h_voff[C::HL], h_dst[C::HL];
-    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
-    {
-        const int rows_valid = static_cast<int>(a.T - tok0 < BN ? a.T - tok0 : BN);
-#pragma unroll
-        for (int q = 0; q < C::HL; ++q) {
-            int g = q * C::NW + wave;
-            g = g < C::GROUPS ? g : C::GROUPS - 1;
-            int r = g * 8 + (lane >> 3);
-            const int c = (lane & 7) ^ (r & 6);
-            r = r < rows_valid ? r : rows_valid - 1;
-            h_voff[q] = static_cast<unsigned>(r) * row_bytes + c * 16;
-            h_dst[q] = lds0 + g * 1024;
-        }
-    }
-    const char* h_base = reinterpret_cast<const char*>(a.H) + tok0 * static_cast<int64_t>(row_bytes);
-    // ---- W loader: lane -> (row lane%16 of a 16-row block, chunk lane/16 (+4 for the second half of the line))
-    unsigned w_voff[TI];
-    const char* w_base = nullptr;
+    // ---- loader: lane -> (row lane/8 of an 8-row group, position lane%8); rows past the end repeat the last one
+    const unsigned ld_kb = ((lane & 7) ^ ((lane >> 3) & 6)) * 16;
+    const int64_t row_bytes = static_cast<int64_t>(a.d) * 2;
+    const int64_t tile_bytes = BM * row_bytes;
+    unsigned a_voff[C::LA], b_voff[C::LB];
+    auto a_group = [&](int q) { const int g = wave * C::LA + q; return g < C::GA ? g : C::GA - 1; };
     auto point_at_tile = [&](int vt) {
-        const int64_t r0 = static_cast<int64_t>(vt) * BM + wave * (16 * TI);
-        const int64_t first = r0 < a.V ? r0 : a.V - 1;                 // rows past the vocabulary repeat the last one
-        w_base = reinterpret_cast<const char*>(a.W) + first * row_bytes;
-        const int rows_valid = static_cast<int>(a.V - first < 16 * TI ? a.V - first : 16 * TI);
+        const int left = a.V - vt * BM, last = (left < BM ? left : BM) - 1;
 #pragma unroll
-        for (int i = 0; i < TI; ++i) {
-            const int r = i * 16 + l15;
-            w_voff[i] = static_cast<unsigned>(r < rows_valid ? r : rows_valid - 1) * row_bytes + lq * 16;
+        for (int q = 0; q < C::LA; ++q) {
+            const int r = a_group(q) * 8 + (lane >> 3);
+            a_voff[q] = static_cast<unsigned>(r < last ? r : last) * static_cast<unsigned>(row_bytes) + ld_kb;
         }
     };
-    u32x4 w[2][G][TI][2];
-    // every split starts at another place of the K extent and wraps around: all of them at the same offset of rows a
-    // power of two apart meet in the same memory channels (149 against 134 us at 64 tokens, 151,936 x 2048)
-    const int k_start = sp * 3 % n_k64;
-    int ld_vt = vt_lo, ld_k = k_start;
-    point_at_tile(vt_lo);
-    // the loads of the next group of steps: W into `dst`, H into the LDS stages of parity `par`
-    auto issue_group = [&](u32x4 (&dst)[G][TI][2], int par) {
+    {
+        const int last = static_cast<int>(a.T - tok0 < BN ? a.T - tok0 : BN) - 1;
 #pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const char* wk = w_base + static_cast<int64_t>(ld_k) * 128;
-            const char* hb = h_base + static_cast<int64_t>(ld_k) * 128;
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) dst[q][i][h] = *reinterpret_cast<const u32x4*>(wk + w_voff[i] + h * 64);
-#pragma unroll
-            for (int g = 0; g < C::HL; ++g)
-                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(h_voff[g]), "s"(hb),
-                             "s"(h_dst[g] + (par * G + q) * C::STAGE_BYTES) : "memory");
-            ld_k = ld_k + 1 == n_k64 ? 0 : ld_k + 1;
-            if (ld_k == k_start && ld_vt + 1 < vt_hi) point_at_tile(++ld_vt);   // past the last tile: its lines again
+        for (int q = 0; q < C::LB; ++q) {
+            const int r = (wave * C::LB + q) * 8 + (lane >> 3);
+            b_voff[q] = static_cast<unsigned>(r < last ? r : last) * static_cast<unsigned>(row_bytes) + ld_kb;
         }
+    }
+    const int k_start = sp % n_k64;
+    int a_vt = vt_lo, a_k = k_start, a_slot = 0, b_k = k_start, b_slot = 0;
+    const char* a_base = reinterpret_cast<const char*>(a.W) + vt_lo * tile_bytes + k_start * 128;
+    const char* b_base = reinterpret_cast<const char*>(a.H) + tok0 * row_bytes + k_start * 128;
+    point_at_tile(vt_lo);
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    // the n-th load instruction of a pair: its H lines, then its W lines
+    auto issue_one = [&](int n) {
+        const bool b = n < C::LB;
+        const unsigned dst = b ? lds0 + NA * C::A_BYTES + b_slot * C::B_BYTES + (wave * C::LB + n) * 1024
+                               : lds0 + a_slot * C::A_BYTES + a_group(n - C::LB) * 1024;
+        const unsigned voff = b ? b_voff[b ? n : 0] : a_voff[b ? 0 : n - C::LB];
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(b ? b_base : a_base), "s"(dst) : "memory");
+    };
+    auto advance_a = [&]() {
+        a_slot = a_slot + 1 == NA ? 0 : a_slot + 1;
+        a_base += 128;
+        if (++a_k == n_k64) { a_k = 0; a_base -= row_bytes; }
+        if (a_k == k_start && a_vt + 1 < vt_hi) {      // past the last tile: its lines again, into slots nobody reads
+            a_base += tile_bytes;
+            point_at_tile(++a_vt);
+        }
+    };
+    auto advance_b = [&]() {
+        b_slot = b_slot + 1 == NB ? 0 : b_slot + 1;
+        b_base += 128;
+        if (++b_k == n_k64) { b_k = 0; b_base -= row_bytes; }
     };
 
     LaneState<TJ> st;
-    int tgt[TJ];
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
         st.run_m[j] = kNegBig; st.run_s[j] = 0.f; st.tgt_z[j] = 0.f;
-        const int64_t t = tok0 + j * 16 + l15;
-        tgt[j] = t < a.T ? a.targets[t] : -1;
     }
+    // tokens of this wave: tok_wave + 0 .. 16 TJ - 1; the first tgt_valid of them exist (both wave-uniform)
+    const int64_t tok_wave = tok0 + wn * (BN / C::WN);
+    const int32_t* tgt_wave = a.targets + (tok_wave < a.T ? tok_wave : 0);
+    const int tgt_valid = tok_wave < a.T ? static_cast<int>(a.T - tok_wave < BN / C::WN ? a.T - tok_wave : BN / C::WN) : 0;
     f32x4 acc[TI][TJ];
-    auto clear = [&]() {
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned f_off[2] = {static_cast<unsigned>(l15 * 128 + ((lq ^ (l15 & 6)) << 4)),
+                               static_cast<unsigned>(l15 * 128 + (((lq + 4) ^ (l15 & 6)) << 4))};
+    bf16x8 fa[2][TI], fb[2][TJ];       // fragments of a pair's first / second chunk
+    auto read_a = [&](int slot, int h, int i) {
+        fa[h][i] = *reinterpret_cast<const bf16x8*>(lds + (f_off[h] + slot * C::A_BYTES + wm * (BM / C::WM) * 128) + i * 2048);
     };
-    clear();
-    const int h_off = l15 * 128;
-    const int h_pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
-    bf16x8 fb[TJ];       // H fragments: one half K64 step ahead, reloaded one by one
-    auto read_h = [&](int stage, int h, int j) {
-        fb[j] = *reinterpret_cast<const bf16x8*>(lds + stage * C::STAGE_BYTES + h_off + j * 2048 + h_pos[h]);
+    auto read_b = [&](int slot, int h, int j) {
+        fb[h][j] = *reinterpret_cast<const bf16x8*>(lds + (f_off[h] + NA * C::A_BYTES + slot * C::B_BYTES + wn * (BN / C::WN) * 128) + j * 2048);
     };
-    // 2 TJ MFMAs with the fragments in fb (token block by token block, consecutive ones share an operand); behind each
-    // block its fragment of the next half step is read into the same registers
-    auto half = [&](u32x4 (&wr)[TI][2], int h, int next_stage, int next_h, bool read_next) {
+    // up front: W(0) where W has a slot more, then H(p), W(p + NA - NB) for every slot of H
+    if (NA > NB) {
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
+        for (int n = C::LB; n < L; ++n) issue_one(n);
+        advance_a();
+    }
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+#pragma unroll
+        for (int n = 0; n < L; ++n) issue_one(n);
+        advance_b();
+        advance_a();
+    }
+    wait_vmcnt<C::FLY + L>();
+    __syncthreads();
+    int sa = 0, sb = 0;   // slots of the pair in work; from the start of its second chunk on, of the next
+    auto read_first = [&]() {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) read_b(sb, 0, j);
+#pragma unroll
+        for (int i = 0; i < TI; ++i) read_a(sa, 0, i);
+    };
+    read_first();
+    // One K32 chunk: TI rows of TJ MFMAs (token blocks in snake order, so that consecutive ones share an operand).
+    // `first`: first chunk of a vocabulary tile - the addend is the constant 0, so the accumulators are never cleared.
+    auto chunk = [&](auto second, auto first) {
+        constexpr int h = decltype(second)::value ? 1 : 0, hn = 1 - h;
+        if (h) { sa = sa + 1 == NA ? 0 : sa + 1; sb = sb + 1 == NB ? 0 : sb + 1; }
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ii = 0; ii < TI; ++ii) {
-                const int i = (j & 1) ? TI - 1 - ii : ii;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[i][h]), fb[j], acc[i][j], 0, 0, 0);
+            for (int jj = 0; jj < TJ; ++jj) {
+                const int j = (i & 1) ? TJ - 1 - jj : jj;
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], decltype(first)::value ? zero : acc[i][j], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (read_next) read_h(next_stage, next_h, j);
+            if (i == C::BAR) {
+                if (h) {
+                    // the next pair has landed, for every wavefront, and everybody's fragments of this one are in registers
+                    wait_vmcnt<C::FLY>();
+                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) read_b(sb, hn, j);
+#pragma unroll
+                for (int q = 0; q < (TI > 4 ? 2 : TI); ++q) read_a(sa, hn, q);
+            }
+            if (TI > 4 && i > C::BAR) {
+                if (2 * (i - C::BAR) < TI) read_a(sa, hn, 2 * (i - C::BAR));
+                if (2 * (i - C::BAR) + 1 < TI) read_a(sa, hn, 2 * (i - C::BAR) + 1);
+            }
+            if (h && i >= C::BAR) {
+#pragma unroll
+                for (int q = 0; q < C::PER_ROW; ++q)
+                    if ((i - C::BAR) * C::PER_ROW + q < L) issue_one((i - C::BAR) * C::PER_ROW + q);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (h) { advance_b(); advance_a(); }
     };
-    int k = 0, vt = vt_lo;
-    auto group = [&](u32x4 (&wr)[G][TI][2], u32x4 (&wn)[G][TI][2], int par) {
-        // this group's loads have landed, for every wavefront, and nobody reads the other stages any more
-        asm volatile("" ::: "memory");
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        issue_group(wn, par ^ 1);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) read_h(par * G, 0, j);
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            half(wr[q], 0, par * G + q, 1, true);
-            half(wr[q], 1, par * G + q + 1, 0, q + 1 < G);
-            if (++k == n_k64 && vt < vt_hi) {
-                tile_epilogue16<TI, TJ, 16 * TI>(acc, st, vt * BM + wave * (16 * TI), a.V, lq, tgt);
-                clear();
-                k = 0;
-                ++vt;
-            }
+    for (int vt = vt_lo; vt < vt_hi; ++vt) {
+        chunk(std::false_type{}, std::true_type{});
+        chunk(std::true_type{}, std::false_type{});
+        for (int k = 1; k < n_k64; ++k) {
+            chunk(std::false_type{}, std::false_type{});
+            chunk(std::true_type{}, std::false_type{});
         }
-    };
-    issue_group(w[0], 0);
-    for (int s = 0; s < total; s += 2 * G) {
-        group(w[0], w[1], 0);
-        if (s + G < total) group(w[1], w[0], 1);
+        int tgt[TJ];
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) tgt[j] = j * 16 + l15 < tgt_valid ? tgt_wave[j * 16 + l15] : -1;
+        tile_epilogue16<TI, TJ, BM / C::WM>(acc, st, vt * BM + wm * (BM / C::WM), a.V, lq, tgt);
+        // read again rather than kept across the epilogue; the slots are certified and not yet released
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        read_first();
     }
     wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt(0xC07F);
-    __syncthreads();   // every stage has been read and every load into LDS has landed
-    write_partials16<TJ, C::NW, 1, BN, C::NT>(st, reinterpret_cast<float*>(lds), wave, 0, l15, lq, tid, tok0, a.T, sp, a.part);
+    __syncthreads();   // every fragment read and every load into LDS has finished
+    write_partials16<TJ, C::WM, C::WN, BN, C::NT>(st, reinterpret_cast<float*>(lds), wm, wn, l15, lq, tid, tok0,
+                                                   a.T, sp, a.part);
 }
 
 // Merges the splits.  256 / GROUPS tokens per workgroup, GROUPS lanes per token that take every GROUPS-th split and
@@ -944,46 +981,71 @@ using MainTile = Tile<256, 256, 64, 2, 4>;
 using FastTile = RingTile<256, 256, 2, 4>;
 static_assert(MainTile::BM == FastTile::BM && MainTile::BN == FastTile::BN, "one plan serves both kernels");
 
-struct Plan { int bn, n_tb, n_vt, n_sp, band, n_long; };   // bn: tokens per workgroup
+using Block64 = BlockTile<8, 1, 4, 3>;     // 256 vocabulary rows x 64 tokens
+using Block128 = BlockTile<8, 2, 3, 3>;    // 256 x 128
+using Block192 = BlockTile<8, 3, 3, 2>;    // 256 x 192
+using Block320 = BlockTile<5, 5, 3, 2>;    // 160 x 320
 
-Plan make_plan(int64_t T, int V, int d, int n_splits) {
-    Plan p;
-    // Up to 128 tokens W's stream from HBM is the bound and the stream kernel takes it faster: 134 us against 173 of
-    // the ring kernel at 64 tokens, 153 against 173 at 128 (151,936 x 2048); at 200 tokens, two blocks of 128, it
-    // needs 228 against 173, and from there on the ring kernel's operand reuse wins.
-    p.bn = d % 64 == 0 && T <= 128 ? (T <= 64 ? 64 : 128) : MainTile::BN;
-    p.n_tb = static_cast<int>((T + p.bn - 1) / p.bn);
-    p.n_vt = (V + MainTile::BM - 1) / MainTile::BM;
-    const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
-    p.band = (p.n_tb + bands - 1) / bands;
-    p.n_long = p.n_tb - (p.band - 1) * bands;
-    if (n_splits > 0) {
-        p.n_sp = n_splits < p.n_vt ? n_splits : p.n_vt;
-        return p;
-    }
+enum LogprobForm { kFormRing, kForm64, kForm128, kForm192, kForm320, kForms };
+struct FormSize { int bm, bn; double step; };
+// Vocabulary rows and tokens of a workgroup's tile; microseconds per K64 step of a tile when the chip is full, measured over
+// 50,000 to 151,936 x 1024 to 4096 with up to 640 tokens (from there on the ring kernel's step falls to 1.45).
+constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Block64::BM, Block64::BN, 1.15}, {Block128::BM, Block128::BN, 1.25},
+                                        {Block192::BM, Block192::BN, 1.42}, {Block320::BM, Block320::BN, 1.42}};
+constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;
+
+struct Plan { int form, n_tb, n_vt, n_sp, band, n_long; };
+
+// Vocabulary splits of n_tb token blocks x n_vt tiles, and what they cost, in tiles one after the other.
+double pick_splits(int n_tb, int n_vt, int& n_sp) {
+    constexpr int kRound = kXcds * kCuPerXcd;
     // A launch takes rounds of 256 workgroups x the vocabulary tiles of the longest split (plus about a quarter of a
     // tile's time per workgroup to start and finish).  Candidates: the split counts that just fill 1 ... 8 rounds, and
     // 4 ... 12.  Fewer than 6 splits widen an XCD's patch to more token blocks and fetch more operand slices per K
     // step (an eighth of a per cent each); where costs tie the smallest wins.  At 32,768 tokens this gives 6 (27.5 ms;
     // 12 splits: 28.5).  From 16 rounds on the last one no longer matters: 6, which at the benchmark shapes (T of
     // 290,000 to 2.4 million) measured 0.4-2.1 % faster than 4, 5, 7 or 8.
-    if (static_cast<int64_t>(p.n_tb) * 6 >= 16 * kXcds * kCuPerXcd) {
-        p.n_sp = p.n_vt < 6 ? p.n_vt : 6;
-        return p;
+    if (static_cast<int64_t>(n_tb) * 6 >= 16 * kRound) {
+        n_sp = n_vt < 6 ? n_vt : 6;
+        return static_cast<double>(n_tb) * n_sp / kRound * ((n_vt + n_sp - 1) / n_sp);
     }
     double best = -1.0;
-    p.n_sp = 1;
+    n_sp = 1;
     for (int c = 0; c < 17; ++c) {
-        int64_t sp = c < 9 ? c + 4 : static_cast<int64_t>(kXcds * kCuPerXcd) * (c - 8) / p.n_tb;
-        if (sp > p.n_vt) sp = p.n_vt;
+        int64_t sp = c < 9 ? c + 4 : static_cast<int64_t>(kRound) * (c - 8) / n_tb;
+        if (sp > n_vt) sp = n_vt;
         if (sp < 1) continue;
-        const int64_t tiles = (p.n_vt + sp - 1) / sp;
-        if (sp > 12) sp = (p.n_vt + tiles - 1) / tiles;       // no more splits than the longest one needs
-        const int64_t rounds = (p.n_tb * sp + kXcds * kCuPerXcd - 1) / (kXcds * kCuPerXcd);
+        const int64_t tiles = (n_vt + sp - 1) / sp;
+        if (sp > 12) sp = (n_vt + tiles - 1) / tiles;         // no more splits than the longest one needs
+        const int64_t rounds = (n_tb * sp + kRound - 1) / kRound;
         const double slices = sp >= 6 ? 11.3 : sp + 32.0 / static_cast<double>(sp);
         const double cost = static_cast<double>(rounds) * (static_cast<double>(tiles) + 0.25) * (1.0 + 0.00125 * slices);
-        if (best < 0.0 || cost < best || (cost == best && sp < p.n_sp)) { best = cost; p.n_sp = static_cast<int>(sp); }
+        if (best < 0.0 || cost < best || (cost == best && sp < n_sp)) { best = cost; n_sp = static_cast<int>(sp); }
     }
+    return best;
+}
+
+Plan make_plan(int64_t T, int V, int d, int n_splits) {
+    Plan p = {};
+    // The form whose tiles come out cheapest.  At 151,936 x 2048: 64-, 128- and 192-token blocks for up to as many tokens, the
+    // ring kernel up to 256, 160 x 320 up to 320, 2 x 192 up to 384, the ring to 512 (262 us; 3 x 192: 308), 3 x 192 to 576.
+    double best = -1.0;
+    for (int f = 0; f < kForms; ++f) {
+        if (f != kFormRing && (d % 64 || T > kBlockTokens)) continue;
+        const int n_tb = static_cast<int>((T + kFormSize[f].bn - 1) / kFormSize[f].bn), n_vt = (V + kFormSize[f].bm - 1) / kFormSize[f].bm;
+        const int cap = (V + MainTile::BM - 1) / MainTile::BM;        // of splits given: <= n_vt for every form
+        int sp = n_splits < cap ? n_splits : cap;
+        double tiles;
+        if (n_splits > 0)
+            tiles = static_cast<double>((static_cast<int64_t>(n_tb) * sp + 255) / 256 * ((n_vt + sp - 1) / sp));
+        else
+            tiles = pick_splits(n_tb, n_vt, sp);
+        const double cost = tiles * kFormSize[f].step;
+        if (best < 0.0 || cost < best) { best = cost; p.form = f; p.n_tb = n_tb; p.n_vt = n_vt; p.n_sp = sp; }
+    }
+    const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
+    p.band = (p.n_tb + bands - 1) / bands;
+    p.n_long = p.n_tb - (p.band - 1) * bands;
     return p;
 }
 
@@ -1006,11 +1068,12 @@ extern "C" size_t arrol_logprob_workspace_bytes(int64_t T, int32_t V, int32_t d,
     int64_t rows = static_cast<int64_t>(p.n_sp) * T;
     if (n_splits == 0) {
         constexpr int64_t kRound = kXcds * kCuPerXcd, kTwelve = 16 * kRound / 6 * MainTile::BN;   // tokens of 16 rounds
-        int64_t most = 8 * kRound * MainTile::BN;
+        int64_t most = 8 * kRound * kLargestBN;
         most = most > 6 * T ? most : 6 * T;
         const int64_t twelve = 12 * (T < kTwelve ? T : kTwelve);
         most = most > twelve ? most : twelve;
-        most = most < p.n_vt * T ? most : p.n_vt * T;
+        const int64_t most_splits = (V + kSmallestBM - 1) / kSmallestBM;
+        most = most < most_splits * T ? most : most_splits * T;
         rows = rows > most ? rows : most;
     }
     return (static_cast<size_t>(rows) * 3 * sizeof(float) + 255) & ~static_cast<size_t>(255);
@@ -1040,9 +1103,11 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
     const dim3 g(static_cast<unsigned>(grid));
     int rc;
     if (d % 64) rc = launch_logprob<logprob_kernel<MainTile>, MainTile>(g, st, a);
-    else if (p.bn == MainTile::BN) rc = launch_logprob<logprob_ring_kernel<FastTile>, FastTile>(g, st, a);
-    else if (p.bn == 128) rc = launch_logprob<logprob_stream_kernel<StreamTile<8>>, StreamTile<8>>(g, st, a);
-    else rc = launch_logprob<logprob_stream_kernel<StreamTile<4>>, StreamTile<4>>(g, st, a);
+    else if (p.form == kForm64) rc = launch_logprob<logprob_block_kernel<Block64>, Block64>(g, st, a);
+    else if (p.form == kForm128) rc = launch_logprob<logprob_block_kernel<Block128>, Block128>(g, st, a);
+    else if (p.form == kForm192) rc = launch_logprob<logprob_block_kernel<Block192>, Block192>(g, st, a);
+    else if (p.form == kForm320) rc = launch_logprob<logprob_block_kernel<Block320>, Block320>(g, st, a);
+    else rc = launch_logprob<logprob_ring_kernel<FastTile>, FastTile>(g, st, a);
     if (rc != ARROL_OK) return rc;
     if (arrol_launch_failed()) return arrol_launch_status();
     if (p.n_sp > 8)

@@ -264,9 +264,8 @@ def test_logprob_ragged_shapes(A, T, V, d):
     check_logprob(A, hidden, lm_head, targets)
 
 
-# the dispatch by token count: one block of 64 or 128 tokens (W streamed to registers, groups of 4 or 2 K64 steps; d of
-# 1, 3 and 9 steps is no whole number of groups) against 256-token blocks in bands (1, 2, 7 and 10 blocks), vocabularies
-# that end inside a wavefront's 32 rows, and split counts from one to one per tile (the 16-lane merge begins at 9)
+# the dispatch by token count: one block of 64, 128 or 320 tokens against 256-token blocks in bands (2, 7 and 10 blocks),
+# d of 1, 3 and 9 K64 steps, vocabularies that end inside a wavefront's 32 rows, and split counts from one to one per tile (the 16-lane merge begins at 9)
 @pytest.mark.parametrize("T", [2, 63, 64, 65, 128, 129, 257, 1600, 2400])
 @pytest.mark.parametrize("V,d,splits", [(257, 64, 0), (2600, 576, 0), (4097, 192, 9), (300, 1024, 1), (5000, 256, 7)])
 def test_logprob_dispatch_by_token_count(A, T, V, d, splits):
@@ -277,6 +276,23 @@ def test_logprob_dispatch_by_token_count(A, T, V, d, splits):
     targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
     targets[0] = 0; targets[-1] = V - 1
     check_logprob(A, hidden, lm_head, targets, n_splits=splits)
+
+
+# up to 640 tokens the cheapest of five tiles: 256 rows x 64, 128, 192, 160 rows x 320, 256 x 256.  Both sides of every edge,
+# vocabularies of one tile, of a few rows in the last one and (splits = 1) of all tiles in one workgroup, K extents of 1, 2, 3
+# and more steps (the K walk starts at split % steps and wraps); a second call must give the same bits
+@pytest.mark.parametrize("T", [1, 64, 65, 128, 129, 192, 193, 255, 256, 257, 320, 321, 384, 385, 576, 577, 640, 641])
+@pytest.mark.parametrize("V,d,splits", [(161, 64, 0), (1285, 128, 1), (2500, 192, 3), (20011, 512, 0)])
+def test_logprob_block_forms(A, T, V, d, splits):
+    say("logprob block forms T=%d V=%d d=%d splits=%d" % (T, V, d, splits))
+    g = torch.Generator(device=DEV); g.manual_seed(T * 3 + V + d)
+    hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    lm_head = (torch.randn(V, d, generator=g, device=DEV) * (2.0 * d ** -0.5)).to(torch.bfloat16)
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    targets[0] = 0; targets[-1] = V - 1
+    check_logprob(A, hidden, lm_head, targets, n_splits=splits)
+    one, two = (A.arrol_logprob(hidden, lm_head, targets, n_splits=splits) for _ in range(2))
+    assert torch.equal(one, two)
 
 
 @pytest.mark.parametrize("splits", [1, 2, 3, 5, 16])
