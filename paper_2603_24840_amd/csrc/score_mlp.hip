@@ -10,7 +10,7 @@
 //
 // arrol_score_mlp_grad: cross-entropy training gradient of the same head (Sec. 4.2, Sec. 4.3 (iii)).  The same
 // tile loop runs in two more modes:
-//   delta   (d not a multiple of 64; else the blocked forward passes keep the activations and mlp_delta_kernel reads them)
+//   delta   (d not a multiple of 64; else the blocked forward passes keep the activations and mlp_score_delta_kernel reads them)
 //           recomputes the pre-activations and, instead of the w2 dot, writes delta^T[u][i] =
 //           r_i * w2[u] * [pre > 0] (bf16, unit-major) and the per-workgroup sums for dL/dw2 and dL/db1;
 //   wgrad   the contraction over rollouts dL/dW1 = delta^T . H as the same "A rows x B rows over a shared
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(256) void score_mlp_finish_kernel(const float* __re
 //            units), partial scores [unit tile][rollout] to the workspace, summed by the finish kernel;
 //            for the gradient call the same pass also keeps the activations a = relu(pre) in fp32, unit-major
 //            (the accumulator's own layout: 16 lanes = 16 consecutive rollouts), so that nothing is recomputed:
-//            delta^T = r w2 [a > 0] and the per-unit sums are then one streaming pass (mlp_delta_kernel);
+//            delta^T = r w2 [a > 0] and the per-unit sums are then one streaming pass (mlp_score_delta_kernel);
 //   wgrad    A = delta^T [m, n_pad], B = the hidden states themselves, [N, d] = K-major (ring_nt's TN form, no
 //            transposed copy), over K = rollouts (split): fp32 tile stores.
 using RingCfg = ring_nt::RingTile<256, 256, 2, 4>;
@@ -619,90 +619,140 @@ int launch_mlp_ring(const MlpRingArgs& a, dim3 grid, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dL/dW1 = delta^T . H over the rollouts where the ring form has too few 256 x 256 tiles to fill the chip: 128 rows of
-// [hi; lo] delta^T x 64 columns per workgroup, K (rollouts) split over gridDim.z, the same stages as mlp_mid_kernel.  The
-// hidden states are read in place: a stage holds 64 rollouts x 128 bytes, and the B fragments come out through the
-// transposing LDS read (lane layout as in ring_nt.h).  16-byte chunk c of rollout row r sits at position
-// c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different 8-byte bank pairs.
-// 4,096 x 2048 x 512: 128 tiles x 2 splits; the ring form's 16 tiles x 8 splits took 21.6 us and left 8 partial slabs.
-struct WgradMid {
-    static constexpr int BM = 128, BN = 64, NS = 3, NT = 256, TI = 4, TJ = 2;
-    static constexpr int STAGE_BYTES = (BM + BN) * 128, LDS_BYTES = NS * STAGE_BYTES;
-    static constexpr int LA = 4, LB = 2, LOADS = LA + LB;
+// What mlp_score_delta_kernel left to be added up (unit_partial NULL: nothing): [n_blocks][2][m] parts of dL/dw2 and dL/db1, [2][n_blocks] of the loss and
+// dL/db2.  Added in block order, whoever does it.
+struct MlpSums {
+    const float* unit_partial; const float* block_sums;
+    int n_blocks, n_rows, m;
+    float* grad_w2; float* grad_b1; float* loss; float* grad_b2;      // the last two may be NULL
+};
+__device__ __forceinline__ void finish_unit(const MlpSums& f, int u, int which) {
+    const float* part = f.unit_partial + static_cast<int64_t>(which) * f.m + u;
+    float sum = 0.f;
+    for (int b0 = 0; b0 < f.n_blocks; b0 += 8) {
+        float x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = b0 + q < f.n_blocks ? part[static_cast<int64_t>(b0 + q) * 2 * f.m] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum += x[q];
+    }
+    (which ? f.grad_b1 : f.grad_w2)[u] = sum;
+}
+__device__ __forceinline__ void finish_loss(const MlpSums& f) {
+    float l = 0.f, r = 0.f;
+    for (int b = 0; b < f.n_blocks; ++b) { l += f.block_sums[b]; r += f.block_sums[f.n_blocks + b]; }
+    if (f.loss) *f.loss = l / static_cast<float>(f.n_rows);
+    if (f.grad_b2) *f.grad_b2 = r;
+}
+__global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where mlp_wgrad_mid_kernel does not do it
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v < f.m) finish_unit(f, v, blockIdx.y);
+    if (v == 0 && blockIdx.y == 0) finish_loss(f);
+}
+
+// dL/dW1 = delta^T . H over the rollouts where the ring form has too few 256 x 256 tiles to fill the chip: BM rows of
+// delta^T x 64 columns per workgroup of KG groups of WM x WN wavefronts.  Group g takes the K64 steps g, g + KG, ... of the
+// tile, so two wavefronts share a SIMD and a barrier stands for KG steps, and the groups' sums are added in the LDS at the
+// end.  Where tiles are too few, K (rollouts) is also split over gridDim.z into slabs; of two-term deltas the second term's
+// steps follow the first's, into the same sums.  The hidden states are read in place: a step holds 64 rollouts x 128 bytes, and
+// the B fragments come out through the transposing LDS read (lane layout as in ring_nt.h).  16-byte chunk c of rollout row r
+// sits at position c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different 8-byte bank pairs.
+// Bound by the loads into LDS (16 KB a step at 73 bytes per nanosecond and compute unit with 64 x 64).  4,096 x 2048 x 512,
+// 256 tiles of 64 x 64: 17.4 us; before, one group of four wavefronts, 128 x 64, 2 splits and the sum of their slabs: 20.0.
+// 1,024: 9.2 -> 7.3; 4,096 x 4096 x 512 with 128 x 64: 26.6 -> 25.6.
+template <int BM_, int WM_, int WN_, int KG_, int NS_>
+struct WgradTile {
+    static constexpr int BM = BM_, BN = 64, WM = WM_, WN = WN_, KG = KG_, NS = NS_, GW = WM * WN, NT = KG * GW * ARROL_WAVE;
+    static constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;
+    static constexpr int SUB_BYTES = (BM + BN) * 128, STAGE_BYTES = KG * SUB_BYTES;
+    static constexpr int LA = BM / 8 / GW, LB = BN / 8 / GW, LOADS = LA + LB;
+    static constexpr int RED_BYTES = KG * BM * BN * 4, LDS_BYTES = NS * STAGE_BYTES > RED_BYTES ? NS * STAGE_BYTES : RED_BYTES;
+    static_assert(LDS_BYTES <= 163840 && BM % (8 * GW) == 0 && BN % (8 * GW) == 0, "tile");
 };
 
-__global__ __launch_bounds__(WgradMid::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a) {
-    using C = WgradMid;
+template <class C>
+__global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, int terms, MlpSums f) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void* lds_ptr_t;
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4* lds_s16x4_t;
-    constexpr int NS = C::NS, TI = C::TI, TJ = C::TJ;
+    constexpr int NS = C::NS, TI = C::TI, TJ = C::TJ, KG = C::KG, GW = C::GW, BM = C::BM, BN = C::BN;
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int u0 = blockIdx.y * C::BM, c0 = blockIdx.x * C::BN;
+    const int kg = wave / GW, wq = wave % GW, wm = wq / C::WN, wn = wq % C::WN;
+    const int u0 = blockIdx.y * BM, c0 = blockIdx.x * BN;
+    // steps of this split: all terms of its K64 range, one after the other
     const int k64_lo = static_cast<int>(blockIdx.z) * a.k64_per_split;
     const int k64_hi = k64_lo + a.k64_per_split < a.n_k64 ? k64_lo + a.k64_per_split : a.n_k64;   // > k64_lo (host)
-    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    const int per = k64_hi - k64_lo, n_steps = per * terms, n_st = (n_steps + KG - 1) / KG;
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds)) + kg * C::SUB_BYTES;
+    // loader: lane -> (row lane/8 of an 8-row group, position lane%8); rows and columns past the end repeat the last ones
     const uint16_t* src_a[C::LA];
 #pragma unroll
     for (int q = 0; q < C::LA; ++q) {
-        const int r = (wave * C::LA + q) * 8 + (lane >> 3);
+        const int r = (wq * C::LA + q) * 8 + (lane >> 3);
         const int u = u0 + r < a.a_rows ? u0 + r : a.a_rows - 1;
         src_a[q] = a.a + static_cast<int64_t>(u) * (a.a_stride / 2) + ((lane & 7) ^ (r & 6)) * 8;
     }
-    int b_row[C::LB];                        // rollout of the stage and first column of this lane's chunk
+    const int64_t term = static_cast<int64_t>(a.a_rows) * (a.a_stride / 2);
+    int b_row[C::LB];                        // rollout of the step and first column of this lane's chunk
     int64_t b_col[C::LB];
 #pragma unroll
     for (int q = 0; q < C::LB; ++q) {
-        const int r = (wave * C::LB + q) * 8 + (lane >> 3);
+        const int r = (wq * C::LB + q) * 8 + (lane >> 3);
         const int c = c0 + ((lane & 7) ^ (((r >> 1) & 1) << 1) ^ (((r >> 3) & 1) << 2)) * 8;
         b_row[q] = r;
-        b_col[q] = c < a.b_rows ? c : a.b_rows - 8;      // columns past the end repeat the last chunk (d % 64 == 0)
+        b_col[q] = c < a.b_rows ? c : a.b_rows - 8;      // (d % 64 == 0)
     }
-    int ld_k = k64_lo, ld_slot = 0;
-    auto issue = [&]() {                     // the next stage; past the last one its lines again
+    int ld_s = kg < n_steps ? kg : 0, ld_slot = 0;
+    auto issue = [&]() {                     // the group's next step; past the last one its lines again
         const unsigned dst = lds0 + ld_slot * C::STAGE_BYTES;
+        const int t = ld_s >= per, k64 = k64_lo + ld_s - (t ? per : 0);
+        const int64_t ak = t * term + static_cast<int64_t>(k64) * 64;
 #pragma unroll
         for (int q = 0; q < C::LA; ++q)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_a[q] + static_cast<int64_t>(ld_k) * 64),
-                         "s"(dst + (wave * C::LA + q) * 1024) : "memory");
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_a[q] + ak), "s"(dst + (wq * C::LA + q) * 1024) : "memory");
 #pragma unroll
         for (int q = 0; q < C::LB; ++q) {
-            int k = ld_k * 64 + b_row[q];                // rollouts past the last one repeat it: delta^T is zero there
+            int k = k64 * 64 + b_row[q];                 // rollouts past the last one repeat it: delta^T is zero there
             k = k < a.b_k_rows ? k : a.b_k_rows - 1;
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(a.b + static_cast<int64_t>(k) * (a.b_stride / 2) + b_col[q]),
-                         "s"(dst + C::BM * 128 + (wave * C::LB + q) * 1024) : "memory");
+                         "s"(dst + BM * 128 + (wq * C::LB + q) * 1024) : "memory");
         }
         ld_slot = ld_slot + 1 == NS ? 0 : ld_slot + 1;
-        if (ld_k + 1 < k64_hi) ++ld_k;
+        if (ld_s + KG < n_steps) ld_s += KG;
     };
     f32x4 acc[TI][TJ];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int a_off = (wm * 64 + l15) * 128;
+    const int a_off = kg * C::SUB_BYTES + (wm * (BM / C::WM) + l15) * 128;
     const int pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
-    // lane 16 lq + 4 e + q addresses rollout 32 h + 8 lq + 4 h2 + e, columns wn*32 + 16 j + 4 q .. + 3
+    // lane 16 lq + 4 e + q addresses rollout 32 h + 8 lq + 4 h2 + e, columns wn * 16 TJ + 16 j + 4 q .. + 3
     const int e = l15 >> 2, cq = l15 & 3;
     int bt[2];
 #pragma unroll
     for (int h2 = 0; h2 < 2; ++h2) {
-        const int chunk = (wn * 4 + (cq >> 1)) ^ ((e >> 1) << 1) ^ ((lq & 1) << 2);
-        bt[h2] = C::BM * 128 + (8 * lq + 4 * h2 + e) * 128 + chunk * 16 + (cq & 1) * 8;
+        const int chunk = (wn * 2 * TJ + (cq >> 1)) ^ ((e >> 1) << 1) ^ ((lq & 1) << 2);
+        bt[h2] = kg * C::SUB_BYTES + BM * 128 + (8 * lq + 4 * h2 + e) * 128 + chunk * 16 + (cq & 1) * 8;
     }
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) issue();
+    if (f.unit_partial && blockIdx.x == 0 && blockIdx.z == 0) {   // while the first steps are on their way
+        for (int v = tid; v < 2 * BM; v += C::NT)
+            if (u0 + v % BM < f.m) finish_unit(f, u0 + v % BM, v / BM);
+        if (blockIdx.y == 0 && tid == 0) finish_loss(f);
+    }
     int slot = 0;
-    for (int k = k64_lo; k < k64_hi; ++k) {
-        // this stage has landed (the NS - 2 after it may fly), for every wavefront, and all have read the one before
+    for (int s = 0; s < n_st; ++s) {
+        // these steps have landed (the NS - 2 after them may fly), for every wavefront, and all have read the ones before
         mlp_wait_vmcnt<(NS - 2) * C::LOADS>();
         __syncthreads();
         issue();
         const unsigned char* st = lds + slot * C::STAGE_BYTES;
         slot = slot + 1 == NS ? 0 : slot + 1;
+        if (s * KG + kg >= n_steps) continue;
         bf16x8 fa[2][TI], fb[2][TJ];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -723,25 +773,46 @@ __global__ __launch_bounds__(WgradMid::NT, 2) void mlp_wgrad_mid_kernel(MlpRingA
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
     }
-    mlp_wait_vmcnt<0>();                     // no load into LDS outlives the workgroup
+    mlp_wait_vmcnt<0>();
+    __syncthreads();                         // every stage has been read and every load into LDS has landed
+    // block b = (i, j) of a wavefront's tile is finished by group b % KG, the sums added in group order
+    f32x4* red = reinterpret_cast<f32x4*>(lds);   // [group][position][TI TJ][lane]
+    if (KG > 1) {
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+        for (int b = 0; b < TI * TJ; ++b) red[(wave * TI * TJ + b) * 64 + lane] = acc[b / TJ][b % TJ];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int b = 0; b < TI * TJ; ++b) {
+        if (b % KG != kg) continue;
+        f32x4 s = acc[b / TJ][b % TJ];
+        if (KG > 1) s = red[(wq * TI * TJ + b) * 64 + lane];
+#pragma unroll
+        for (int g = 1; g < KG; ++g) s += red[((g * GW + wq) * TI * TJ + b) * 64 + lane];
+        const int col = c0 + wn * (BN / C::WN) + (b % TJ) * 16 + l15;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int u = u0 + wm * 64 + i * 16 + lq * 4 + v;
-            if (u >= a.a_rows) continue;
-            float* crow = a.c_out + (static_cast<int64_t>(blockIdx.z) * a.a_rows + u) * a.c_stride;
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) {
-                const int col = c0 + wn * 32 + j * 16 + l15;
-                if (col < a.b_rows) crow[col] = acc[i][j][v];
-            }
+            const int u = u0 + wm * (BM / C::WM) + (b / TJ) * 16 + lq * 4 + v;
+            if (u < a.a_rows && col < a.b_rows) a.c_out[(static_cast<int64_t>(blockIdx.z) * a.a_rows + u) * a.c_stride + col] = s[v];
         }
+    }
 }
 
 using Mid32 = MidTile<32, 32, 8>;
 using Mid64 = MidTile<64, 64, 4>;
 using Mid128 = MidTile<128, 64, 3>;
+using Wgrad64 = WgradTile<64, 2, 2, 2, 4>;
+using Wgrad128 = WgradTile<128, 2, 2, 2, 3>;
+using Wgrad128Two = WgradTile<128, 2, 2, 1, 3>;      // two workgroups to a compute unit
+
+template <class C>
+int launch_wgrad_mid(const MlpRingArgs& g, int terms, int splits, const MlpSums& f, hipStream_t st) {
+    static arrol_device_flags ok;
+    if (!arrol_allow_lds(&mlp_wgrad_mid_kernel<C>, C::LDS_BYTES, ok)) return ARROL_EHIP;
+    arrol_launch(mlp_wgrad_mid_kernel<C>, dim3((g.b_rows + C::BN - 1) / C::BN, (g.a_rows + C::BM - 1) / C::BM, splits), dim3(C::NT),
+                 C::LDS_BYTES, st, g, terms, f);
+    return ARROL_OK;
+}
 
 enum ForwardPath { kPathTile, kPathMid32, kPathMid64, kPathMid128, kPathRing };
 
@@ -972,6 +1043,107 @@ __global__ __launch_bounds__(kDeltaThreads) void mlp_delta_kernel(const float* _
     }
 }
 
+// The two in one, for up to kFusedRows rows and kFusedSize activations: workgroup (b, g) forms the residuals of rows 512 b .. itself, into the LDS, and then,
+// one unit a wavefront, delta^T of those rows and their parts of dL/dw2 and dL/db1; those with g = 0 also of the loss and dL/db2.  The parts are added in block order by the dL/dW1 kernel that follows, or by mlp_sums_kernel.
+// What bounds it at these sizes is a chain of dependent loads and a launch, beyond the activations' bytes; a row's residual
+// is formed m / 8 times, which costs less than the launch that formed it once: 4,096 x 512
+// 6.2 us against 4.4 + 4.9, 1,024 x 512 4.8 against 3.9 + 4.4; with 1,024 rows a workgroup 7.2, with 256 7.1.  Of larger
+// activations the pair's larger workgroups make more of the bytes (whole call: 4,096 x 768 76 us against 79, 16,384 x 512 113
+// against 115).
+constexpr int kFusedRows = 8192, kFusedSize = 2 << 20;
+constexpr int kPartRows = 512;
+__global__ __launch_bounds__(kPartRows) void mlp_score_delta_kernel(const float* __restrict__ partial, int n_ub, float b2,
+                                                                    const float* __restrict__ labels,
+                                                                    const float* __restrict__ act_t, int64_t act_stride,
+                                                                    const float* __restrict__ w2, int n_rows, int n_pad, int m,
+                                                                    int n_groups,
+                                                                    uint16_t* __restrict__ delta_t, uint16_t* __restrict__ delta_lo,
+                                                                    float* __restrict__ unit_partial, float* __restrict__ block_sums) {
+    constexpr int kWaves = kPartRows / ARROL_WAVE, kSteps = kPartRows / (4 * ARROL_WAVE);
+    __shared__ __attribute__((aligned(16))) float resid[kPartRows];
+    __shared__ float red[2][kWaves];
+    const int lane = threadIdx.x & (ARROL_WAVE - 1), wave = threadIdx.x / ARROL_WAVE;
+    const int block = blockIdx.x / n_groups, group = blockIdx.x - block * n_groups, n_blocks = gridDim.x / n_groups;
+    const int row0 = block * kPartRows;
+    const int unit = group * kWaves + wave, u = unit < m ? unit : m - 1;
+    // the unit's activations are on their way while the residuals are formed (n_pad is a multiple of 4; the columns from n_rows
+    // on hold whatever the workspace held and are masked below)
+    const float* arow = act_t + static_cast<int64_t>(u) * act_stride;
+    float4 a4[kSteps];
+#pragma unroll
+    for (int k = 0; k < kSteps; ++k) {
+        const int i = row0 + (k * ARROL_WAVE + lane) * 4;
+        a4[k] = *reinterpret_cast<const float4*>(arow + (i < n_pad ? i : 0));
+    }
+    const float wu = w2[u];
+    {
+        const int i = row0 + threadIdx.x;
+        float r = 0.f, loss = 0.f;
+        if (i < n_rows) {
+            const float y = labels[i];
+            const float s = sum_unit_blocks(partial, n_ub, n_rows, i) + b2;
+            float q;
+            if (s >= 0.f) {
+                q = 1.f / (1.f + expf(-s));
+            } else {
+                const float e = expf(s);
+                q = e / (1.f + e);
+            }
+            r = (q - y) * (1.f / static_cast<float>(n_rows));
+            if (group == 0) loss = fmaxf(s, 0.f) - y * s + log1pf(expf(-fabsf(s)));
+        }
+        resid[threadIdx.x] = r;
+        if (group == 0) {
+            loss = wave_sum_f32(loss);
+            r = wave_sum_f32(r);
+            if (lane == 0) { red[0][wave] = loss; red[1][wave] = r; }
+        }
+    }
+    __syncthreads();
+    if (group == 0 && threadIdx.x == 0) {
+        float a = 0.f, b = 0.f;
+        for (int w = 0; w < kWaves; ++w) { a += red[0][w]; b += red[1][w]; }
+        block_sums[block] = a;
+        block_sums[n_blocks + block] = b;
+    }
+    if (unit >= m) return;
+    uint16_t* drow = delta_t + static_cast<int64_t>(u) * n_pad;
+    float gw = 0.f, gb = 0.f;
+#pragma unroll
+    for (int k = 0; k < kSteps; ++k) {
+        const int c = (k * ARROL_WAVE + lane) * 4, i = row0 + c;
+        if (i >= n_pad) continue;
+        const float4 r4 = *reinterpret_cast<const float4*>(resid + c);
+        const float av[4] = {a4[k].x, a4[k].y, a4[k].z, a4[k].w}, rv[4] = {r4.x, r4.y, r4.z, r4.w};
+        uint16_t dq[4], lq[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool live = i + q < n_rows;
+            const float dl = live && av[q] > 0.f ? rv[q] * wu : 0.f;
+            gw = live ? fmaf(rv[q], av[q], gw) : gw;
+            gb += dl;
+            dq[q] = f32_to_bf16_rne(dl);
+            lq[q] = f32_to_bf16_rne(dl - bf16_lo(dq[q]));
+        }
+        uint2 o;
+        o.x = static_cast<uint32_t>(dq[0]) | (static_cast<uint32_t>(dq[1]) << 16);
+        o.y = static_cast<uint32_t>(dq[2]) | (static_cast<uint32_t>(dq[3]) << 16);
+        *reinterpret_cast<uint2*>(drow + i) = o;
+        if (delta_lo) {     // second term of the two-term form: what bf16 rounding left of delta
+            o.x = static_cast<uint32_t>(lq[0]) | (static_cast<uint32_t>(lq[1]) << 16);
+            o.y = static_cast<uint32_t>(lq[2]) | (static_cast<uint32_t>(lq[3]) << 16);
+            *reinterpret_cast<uint2*>(delta_lo + static_cast<int64_t>(u) * n_pad + i) = o;
+        }
+    }
+    gw = wave_sum_f32(gw);
+    gb = wave_sum_f32(gb);
+    if (lane == 0) {
+        float* out = unit_partial + static_cast<int64_t>(block) * 2 * m;
+        out[u] = gw;
+        out[m + u] = gb;
+    }
+}
+
 // out[c][i] = hidden[row(i)][c] for i < n_rows, 0 for n_rows <= i < n_pad: 64 x 64 tiles through LDS, 16 bytes
 // per lane on both sides (8 lanes cover the 128 bytes a tile row has in the source and in the destination)
 __global__ __launch_bounds__(256) void mlp_transpose_kernel(const uint16_t* __restrict__ hidden, int64_t row_stride,
@@ -1008,7 +1180,7 @@ __global__ __launch_bounds__(256) void mlp_transpose_kernel(const uint16_t* __re
 struct GradPlan {
     int n_rb, n_pad, n_cb, n_groups, n_kc, splits, kc_per_split;
     int r_cb, r_gt, r_splits, r_k64_per_split;
-    bool w_mid;                        // dL/dW1 of rows read in place: mid kernel instead of the ring form
+    int w_rows, w_groups;              // dL/dW1 of rows read in place: rows of the mid kernel's tile, 64 or 128, and wavefront groups; 256: the ring form
     size_t off_score, off_prob, off_resid, off_bsum, off_ht, off_dt, off_unit, off_slab, off_small, off_rslab, off_act, total;
 };
 
@@ -1034,7 +1206,7 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
     p.off_score = o; o = align256(o + sizeof(float) * n_rows);
     p.off_prob = o;  o = align256(o + sizeof(float) * n_rows);
     p.off_resid = o; o = align256(o + sizeof(float) * n_rows);
-    p.off_bsum = o;  o = align256(o + sizeof(float) * 2 * ((n_rows + 1023) / 1024));
+    p.off_bsum = o;  o = align256(o + sizeof(float) * 2 * ((n_rows + kPartRows - 1) / kPartRows));
     p.off_ht = o;    o = align256(o + sizeof(uint16_t) * static_cast<size_t>(d) * p.n_pad);
     p.off_dt = o;    o = align256(o + sizeof(uint16_t) * static_cast<size_t>(mt) * p.n_pad);
     // per-unit partial sums of the tile kernel: one row per 128 rollouts
@@ -1047,13 +1219,14 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
         o = align256(o + sizeof(float) * blocks * n_rows);
     }
     // rows read in place: kernel and K split with the smallest estimate (microseconds: the measured time per K64 step of
-    // a workgroup when the chip is full, a start of 5 or 7, and the partial slabs written and read once at 4.5 TB/s)
+    // a workgroup when the chip is full, a start of 5 or 7, and the partial slabs written and read once at 4.5 TB/s).  First the
+    // ring form (a slab per split and term) against 128 x 64 tiles of four wavefronts, two workgroups to a compute unit.
     p.r_cb = (d + 255) / 256;
     p.r_gt = (mt + 255) / 256;         // dL/dW1
     const int n_k64 = (n_rows + 63) / 64;
     const double slab_us = static_cast<double>(mt) * d * 8.0 / 4.5e6;
     const int64_t ring_tiles = static_cast<int64_t>(p.r_cb) * p.r_gt;
-    const int64_t mid_tiles = static_cast<int64_t>((d + WgradMid::BN - 1) / WgradMid::BN) * ((mt + WgradMid::BM - 1) / WgradMid::BM);
+    const int64_t mid_tiles = static_cast<int64_t>((d + Wgrad128::BN - 1) / Wgrad128::BN) * ((mt + Wgrad128::BM - 1) / Wgrad128::BM);
     constexpr int kMaxSplits = 16;
     constexpr double kRingStep = 1.45, kRingStart = 7.0, kMidStep = 0.68, kMidStart = 5.0, kSlabStart = 2.5;
     double best = -1.0, one = 0.0;
@@ -1062,24 +1235,55 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
         const double slabs = used * terms > 1 ? kSlabStart + used * slab_us : 0.0;
         const int64_t nr = ring_tiles * used, nm = mid_tiles * used;
         const double ring = static_cast<double>((nr + 255) / 256) * (per * kRingStep + kRingStart) + slabs;
-        const double mid = (mt + WgradMid::BM - 1) / WgradMid::BM > 65535 ? 1e30
+        const double mid = (mt + Wgrad128::BM - 1) / Wgrad128::BM > 65535 ? 1e30
                            : (nm <= 256 ? per * 0.38 + kMidStart : static_cast<double>((nm + 511) / 512) * (per * kMidStep + kMidStart)) + slabs;
         const double t = mid < ring ? mid : ring;
         if (s == 1) one = t;
-        if (best < 0.0 || t < best) { best = t; p.w_mid = mid < ring; p.r_k64_per_split = per; p.r_splits = used; }
+        if (best < 0.0 || t < best) { best = t; p.w_rows = mid < ring ? 128 : 256; p.r_k64_per_split = per; p.r_splits = used; }
     }
     // The split count can fall from one batch to the next larger one, but a workspace sized for the largest batch is to
     // serve every smaller one.  Room is made for the most splits that a batch up to this one can take: s of them are only
     // chosen where their slabs and the work on a full chip, which no estimate is below, come to less than one split's
     // estimate.  What is left of that estimate after the work grows with the batch, and so does the room.
-    int room = 1;
+    int room = 1, room_mid = 1;
     const double ring_work = static_cast<double>(ring_tiles) / 256.0 * kRingStep, mid_work = static_cast<double>(mid_tiles) / 512.0 * kMidStep;
     const double work = n_k64 * (ring_work < mid_work ? ring_work : mid_work) + kMidStart;
     for (int s = 2; s <= kMaxSplits && n_k64 / s >= 4; ++s)
         if (kSlabStart + s * slab_us + work <= one + 1e-6) room = s;
     if (room < p.r_splits) room = p.r_splits;
+    // Then, where the tiles won, which ones and how many splits, all terms in one sum: 64 x 64 or 128 x 64 with K split over two
+    // groups of wavefronts and one workgroup to a compute unit (4,096 x 2048 x 512: 17.4 / 23.2 us without a split, 19.2 with two
+    // of 128 x 64), or four wavefronts, two workgroups to a unit, where there are more tiles than compute units (2,048 x 4096 x 1,024: 35.8 / 28.5 /
+    // 25.9; 4,096 x 3072 x 768: 47.9 / 45.5 / 31.2).
+    const double mid_slab_us = static_cast<double>(m) * d * 8.0 / 4.5e6;
+    const int64_t tiles64 = static_cast<int64_t>((d + 63) / 64) * ((m + 63) / 64), tiles128 = static_cast<int64_t>((d + 63) / 64) * ((m + 127) / 128);
+    constexpr double kStep64 = 0.205, kStep128 = 0.31, kRound64 = 4.3, kRound128 = 5.5;
+    double best_mid = -1.0, one_mid = 0.0;
+    for (int s = 1; s <= kMaxSplits && (s == 1 || n_k64 / s >= 4); ++s) {
+        const int per = (n_k64 + s - 1) / s, used = (n_k64 + per - 1) / per;
+        const double slabs = used > 1 ? kSlabStart + used * mid_slab_us : 0.0;
+        const int64_t n64 = tiles64 * used, n128 = tiles128 * used;
+        const double t64 = (m + 63) / 64 > 65535 ? 1e30 : static_cast<double>((n64 + 255) / 256) * (per * terms * kStep64 + kRound64) + slabs;
+        const double t128 = static_cast<double>((n128 + 255) / 256) * (per * terms * kStep128 + kRound128) + slabs;
+        const double steps = per * terms, last = kMidStep * (n128 % 512) / 512;
+        const double two = static_cast<double>(n128 / 512) * (steps * kMidStep + kMidStart) + (n128 % 512 ? steps * (last > 0.38 ? last : 0.38) + kMidStart : 0.0) + slabs;
+        double t = t64 < t128 ? t64 : t128;
+        t = two < t ? two : t;
+        if (s == 1) one_mid = t;
+        if (best_mid < 0.0 || t < best_mid) {
+            best_mid = t;
+            if (p.w_rows != 256) { p.w_rows = t == t64 ? 64 : 128; p.w_groups = t == two ? 1 : 2; p.r_k64_per_split = per; p.r_splits = used; }
+        }
+    }
+    // the same room for their splits (whichever form this batch takes: a smaller one may take the other)
+    double step_mid = static_cast<double>(tiles64) * kStep64 / 256.0;
+    step_mid = tiles128 * kStep128 / 256.0 < step_mid ? tiles128 * kStep128 / 256.0 : step_mid;
+    step_mid = tiles128 * kMidStep / 512.0 < step_mid ? tiles128 * kMidStep / 512.0 : step_mid;
+    for (int s = 2; s <= kMaxSplits && n_k64 / s >= 4; ++s)
+        if (kSlabStart + s * mid_slab_us + n_k64 * terms * step_mid + kRound64 <= one_mid + 1e-6) room_mid = s;
+    const int room_slabs = room * terms > room_mid ? room * terms : room_mid;
     p.off_rslab = o;
-    if (d % 64 == 0 && room * terms > 1) o = align256(o + sizeof(float) * static_cast<size_t>(room) * mt * d);
+    if (d % 64 == 0 && room_slabs > 1) o = align256(o + sizeof(float) * static_cast<size_t>(room_slabs) * m * d);
     p.off_act = o;                        // mid / ring forward pass: kept activations, fp32 [m][n_pad]
     if (d % 64 == 0) o = align256(o + sizeof(float) * static_cast<size_t>(m) * p.n_pad);
     p.total = o;
@@ -1238,7 +1442,16 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     if (rc != ARROL_OK) return rc;
     const int n_ub = (m + unit_block(path) - 1) / unit_block(path);
     if (arrol_launch_failed()) return arrol_launch_status();
-    if (kept) {
+    const bool in_place = wgrad_in_place(d, row_stride_elems, row_index != nullptr);
+    const int n_pblocks = (n_rows + kPartRows - 1) / kPartRows;
+    const bool fused = kept && n_rows <= kFusedRows && static_cast<int64_t>(n_rows) * m <= kFusedSize;
+    const MlpSums sums = {fused ? unit : nullptr, bsum, n_pblocks, n_rows, m, grad_w2, grad_b1, loss_out, grad_b2};
+    const int n_groups = (m + kPartRows / ARROL_WAVE - 1) / (kPartRows / ARROL_WAVE);
+    if (fused) {
+        arrol_launch(mlp_score_delta_kernel, dim3(static_cast<unsigned>(n_pblocks) * n_groups), dim3(kPartRows), 0, st, partial, n_ub, b2, labels, act,
+                     static_cast<int64_t>(p.n_pad), w2, n_rows, p.n_pad, m, n_groups, dt, dt_lo, unit, bsum);
+        if (!in_place || p.w_rows == 256) arrol_launch(mlp_sums_kernel, dim3((m + 255) / 256, 2), dim3(256), 0, st, sums);
+    } else if (kept) {
         // scores from the partials, residuals and loss terms in one launch; delta^T, the per-unit sums, the loss
         // and dL/db2 in the next
         arrol_launch(mlp_finish_residual_kernel, dim3(n_rblocks), dim3(1024), 0, st, partial, n_ub, b2, labels, n_rows,
@@ -1258,22 +1471,23 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     }
     if (arrol_launch_failed()) return arrol_launch_status();
     const int64_t width = static_cast<int64_t>(m) * d;
-    if (wgrad_in_place(d, row_stride_elems, row_index != nullptr)) {
+    if (in_place) {
         // dL/dW1 = delta^T . H over the rollouts, the hidden states read in place
         float* rslab = reinterpret_cast<float*>(ws + p.off_rslab);
         MlpRingArgs g = {};
-        // the partials [K split][term][m][d] are delta_terms * r_splits slabs of m * d values
-        const int n_slabs = p.r_splits * delta_terms;
+        // the ring form's partials [K split][term][m][d] are delta_terms * r_splits slabs of m * d values
+        const int n_slabs = p.w_rows == 256 ? p.r_splits * delta_terms : p.r_splits;
         g.a = dt; g.a_stride = static_cast<unsigned>(p.n_pad) * 2; g.a_rows = mt;
         g.b = a.hidden; g.b_stride = static_cast<unsigned>(row_stride_elems * 2);
         g.b_rows = d; g.b_k_rows = n_rows;
         g.n_k64 = (n_rows + 63) / 64; g.k64_per_split = p.r_k64_per_split;
         g.c_out = n_slabs > 1 ? rslab : grad_w1; g.c_stride = d;
-        if (p.w_mid) {
-            static arrol_device_flags ok;
-            if (!arrol_allow_lds(&mlp_wgrad_mid_kernel, WgradMid::LDS_BYTES, ok)) return ARROL_EHIP;
-            arrol_launch(mlp_wgrad_mid_kernel, dim3((d + WgradMid::BN - 1) / WgradMid::BN, (mt + WgradMid::BM - 1) / WgradMid::BM, p.r_splits),
-                         dim3(WgradMid::NT), WgradMid::LDS_BYTES, st, g);
+        if (p.w_rows != 256) {
+            g.a_rows = m;
+            rc = p.w_rows == 64    ? launch_wgrad_mid<Wgrad64>(g, delta_terms, p.r_splits, sums, st)
+                 : p.w_groups == 2 ? launch_wgrad_mid<Wgrad128>(g, delta_terms, p.r_splits, sums, st)
+                                   : launch_wgrad_mid<Wgrad128Two>(g, delta_terms, p.r_splits, sums, st);
+            if (rc != ARROL_OK) return rc;
         } else {
             rc = launch_mlp_ring<kWgrad>(g, dim3(p.r_cb, p.r_gt, p.r_splits), st);
             if (rc != ARROL_OK) return rc;
@@ -1310,7 +1524,7 @@ extern "C" int arrol_score_mlp_kernels(int32_t n_rows, int32_t d, int32_t m, int
     if (delta_terms) {
         const GradPlan p = make_grad_plan(n_rows, d, m, delta_terms);
         const bool in_place = wgrad_in_place(d, row_stride_elems, gathered != 0);
-        *weight_gradient = !in_place ? 0 : p.w_mid ? 1 : 2;
+        *weight_gradient = !in_place ? 0 : p.w_rows != 256 ? 1 : 2;
         *splits = in_place ? p.r_splits : p.splits;
     }
     return ARROL_OK;

@@ -234,6 +234,17 @@ def test_score_mlp_grad_weight_gradient_blocks(A, n, d, m, terms):
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.5, labels, delta_terms=terms)
 
 
+# rows around the 512 of a delta workgroup, units around the 8 of one; dL/dW1 in 64 x 64 and
+# 128 x 64 tiles of two wavefront groups (an odd number of K64 steps leaves one group a step short) and, with more tiles than
+# compute units, of one group; one and two terms in the same sums; batches on both sides of the one-launch delta
+@pytest.mark.parametrize("n,d,m,terms", [(511, 64, 9, 1), (512, 128, 8, 2), (513, 64, 17, 1), (520, 1024, 512, 1), (1500, 2048, 1000, 1),
+                                         (1000, 3072, 768, 1), (900, 1024, 520, 2), (1900, 64, 1100, 1), (1906, 64, 1100, 1), (1907, 64, 1100, 1), (8193, 64, 40, 2)])
+def test_score_mlp_grad_one_launch_delta(A, n, d, m, terms):
+    print("[case] score_mlp_grad delta n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=11 * n + d + m)
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.25, labels, delta_terms=terms)
+
+
 # dL/dW1 in the 256 x 256 ring form: one to fifteen K splits, one and two terms, units, columns and rollouts that end inside a
 # tile, rows that are views into a wider buffer, behind a forward pass in blocks and in the ring form that keeps activations
 @pytest.mark.parametrize("n,d,m,terms,kernels,pad", [(600, 4096, 1100, 1, (2, 2, 1), 0), (246, 2176, 1047, 2, (2, 2, 1), 64),
