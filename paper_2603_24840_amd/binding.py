@@ -3,15 +3,22 @@
 Argument marshalling only: every stage runs in the library's HIP kernels.  torch is used
 for device memory and streams.  There is no CPU fallback: if the library is missing or a
 tensor is not on the GPU the call raises.
+
+The short calls go through csrc/marshal.cpp (_marshal.so) first, which does the ordinary case in C++: they are bound by the
+host (arrol_score 7.0 us a call from Python alone, 4.4 so).  It returns None for what it does not take - another
+tensor class, CPU tensors, wrong types, strides or sizes, a stream, a workspace of the caller's, an active mode of torch's - and the
+_py_ function of the same name does that, errors included.
 """
 import ctypes
 import functools
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libarrol.so")
+MARSHAL_PATH = os.path.join(_HERE, "lib", "_marshal.so")
 
 OK, EINVAL, EWORKSPACE, EHIP = 0, -1, -2, -3
 MAX_GROUP = 64
@@ -38,6 +45,7 @@ class Policy(ctypes.Structure):
 
 
 _lib = None
+_marshal = None
 ABI_VERSION = 200     # arrol_version() of the library whose argument lists _SIGNATURES describes
 
 _vp, _i32, _i64, _f32, _sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
@@ -102,6 +110,23 @@ def lib():
     return _lib
 
 
+def _load_marshal():
+    """Loads _marshal.so once, behind the library that it calls; raises if it has not been built."""
+    global _marshal
+    if _marshal is None:
+        lib()
+        if not os.path.exists(MARSHAL_PATH):
+            raise RuntimeError("_marshal.so is not built (%s missing): run `python -m paper_2603_24840_amd.build`" % MARSHAL_PATH)
+        spec = importlib.util.spec_from_file_location("paper_2603_24840_amd._marshal", MARSHAL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        got = module.setup(torch.nn.Parameter, Policy, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
+        if got != ABI_VERSION:
+            raise RuntimeError("%s calls a library of version %d, not %d: rebuild" % (MARSHAL_PATH, got, ABI_VERSION))
+        _marshal = module
+    return _marshal
+
+
 def version():
     return lib().arrol_version()
 
@@ -148,10 +173,17 @@ def _on_stream(fn):
     return wrapper
 
 
-@_on_stream
-def arrol_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=None, want_score=True,
-                stream=None):
+def arrol_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=None, want_score=True, *, stream=None):
     """hidden bf16 [R, d] (rows may be strided), w fp32 [d] -> (score fp32 [n], prob fp32 [n])."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).score(hidden, w, bias, row_index, out_score, out_prob, want_score)
+        if out is not None:
+            return out
+    return _py_score(hidden, w, bias, row_index, out_score, out_prob, want_score, stream=stream)
+
+
+@_on_stream
+def _py_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=None, want_score=True, stream=None):
     if hidden.dim() != 2 or hidden.dtype != torch.bfloat16 or not hidden.is_cuda:
         raise TypeError("hidden must be a 2-D bf16 GPU tensor")
     if hidden.stride(1) != 1:
@@ -172,11 +204,19 @@ def arrol_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=No
     return out_score, out_prob
 
 
-@_on_stream
-def arrol_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto", stream=None):
+def arrol_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto", *, stream=None):
     """hidden bf16 [R, d], w1 bf16 [m, d], b1 fp32 [m] or None, w2 fp32 [m] -> (score, prob) fp32 [n].
     workspace: "auto" allocates what the library asks for (blocks of units x rollouts over the whole GPU), None passes
     none (the one-launch kernel), or a uint8 tensor."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).score_mlp(hidden, w1, b1, w2, b2, row_index, workspace)
+        if out is not None:
+            return out
+    return _py_score_mlp(hidden, w1, b1, w2, b2, row_index, workspace, stream=stream)
+
+
+@_on_stream
+def _py_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto", stream=None):
     if hidden.dim() != 2 or hidden.dtype != torch.bfloat16 or not hidden.is_cuda or hidden.stride(1) != 1:
         raise TypeError("hidden must be a 2-D bf16 GPU tensor with contiguous rows")
     d = hidden.shape[1]
@@ -200,10 +240,18 @@ def arrol_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto"
     return score, prob
 
 
-@_on_stream
-def arrol_score_grad(hidden, w, bias, labels, row_index=None, workspace=None, stream=None):
+def arrol_score_grad(hidden, w, bias, labels, row_index=None, workspace=None, *, stream=None):
     """Cross-entropy loss of the linear head and its gradient: hidden bf16 [R, d], w fp32 [d], labels fp32 [n]
     -> (loss fp32 [1], grad_w fp32 [d], grad_bias fp32 [1])."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).score_grad(hidden, w, bias, labels, row_index, workspace)
+        if out is not None:
+            return out
+    return _py_score_grad(hidden, w, bias, labels, row_index, workspace, stream=stream)
+
+
+@_on_stream
+def _py_score_grad(hidden, w, bias, labels, row_index=None, workspace=None, stream=None):
     if hidden.dim() != 2 or hidden.dtype != torch.bfloat16 or not hidden.is_cuda or hidden.stride(1) != 1:
         raise TypeError("hidden must be a 2-D bf16 GPU tensor with contiguous rows")
     d = hidden.shape[1]
@@ -226,10 +274,18 @@ def arrol_score_grad(hidden, w, bias, labels, row_index=None, workspace=None, st
     return loss, grad_w, grad_b
 
 
-@_on_stream
-def arrol_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index=None, delta_terms=1, workspace=None, stream=None):
+def arrol_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index=None, delta_terms=1, workspace=None, *, stream=None):
     """Cross-entropy loss of the MLP head and its gradients: -> dict(loss [1], grad_w1 [m, d], grad_b1 [m],
     grad_w2 [m], grad_b2 [1]), all fp32.  delta_terms=2: dL/dW1 to fp32 accuracy (two bf16 terms per delta)."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index, delta_terms, workspace)
+        if out is not None:
+            return out
+    return _py_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index, delta_terms, workspace, stream=stream)
+
+
+@_on_stream
+def _py_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index=None, delta_terms=1, workspace=None, stream=None):
     if hidden.dim() != 2 or hidden.dtype != torch.bfloat16 or not hidden.is_cuda or hidden.stride(1) != 1:
         raise TypeError("hidden must be a 2-D bf16 GPU tensor with contiguous rows")
     d = hidden.shape[1]
@@ -258,10 +314,19 @@ def arrol_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index=None, delta_t
     return out
 
 
-@_on_stream
-def arrol_adamw_step(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0,
-                     param_bf16=None, stream=None):
+def arrol_adamw_step(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0, param_bf16=None,
+                     *, stream=None):
     """In-place AdamW update of fp32 param / m / v (all [n]); param_bf16 (optional, bf16 [n]) gets a rounded copy."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).adamw_step(param, grad, m, v, step, lr, beta1, beta2, eps, weight_decay, param_bf16)
+        if out is not None:
+            return out
+    return _py_adamw_step(param, grad, m, v, step, lr, beta1, beta2, eps, weight_decay, param_bf16, stream=stream)
+
+
+@_on_stream
+def _py_adamw_step(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0, param_bf16=None,
+                   stream=None):
     n = param.numel()
     if grad.numel() != n or m.numel() != n or v.numel() != n or (param_bf16 is not None and param_bf16.numel() != n):
         raise ValueError("param, grad, m, v (and param_bf16) must have the same number of elements")
@@ -273,9 +338,17 @@ def arrol_adamw_step(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e
     return param
 
 
-@_on_stream
-def arrol_select(prob, n_groups, G, K, rho=0.5, out_keep=None, out_survivors=None, stream=None):
+def arrol_select(prob, n_groups, G, K, rho=0.5, out_keep=None, out_survivors=None, *, stream=None):
     """prob fp32 [n_groups*G] -> (keep_mask uint8 [n_groups*G], survivor_idx int32 [n_groups*K])."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).select(prob, n_groups, G, K, rho, out_keep, out_survivors)
+        if out is not None:
+            return out
+    return _py_select(prob, n_groups, G, K, rho, out_keep, out_survivors, stream=stream)
+
+
+@_on_stream
+def _py_select(prob, n_groups, G, K, rho=0.5, out_keep=None, out_survivors=None, stream=None):
     dev = prob.device
     if prob.numel() != n_groups * G:
         raise ValueError("prob must have n_groups*G entries")
@@ -450,9 +523,17 @@ def arrol_trace_confidence(conf, cu_seqlens, window, bottom_percent=10, workspac
     return tuple(outs)
 
 
-@_on_stream
-def arrol_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, stream=None):
+def arrol_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, *, stream=None):
     """reward fp32 [N], group_offsets int64 [n_groups+1] -> (advantage fp32 [N], seq_weight fp32 [N])."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).grpo_advantage(reward, group_offsets, ddof, eps)
+        if out is not None:
+            return out
+    return _py_grpo_advantage(reward, group_offsets, ddof, eps, stream=stream)
+
+
+@_on_stream
+def _py_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, stream=None):
     N = reward.numel()
     n_groups = group_offsets.numel() - 1
     adv = torch.zeros(N, dtype=torch.float32, device=reward.device)
@@ -463,10 +544,19 @@ def arrol_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, stream=None):
     return adv, wgt
 
 
-@_on_stream
 def arrol_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low=0.2, eps_high=0.2, beta=0.0,
-                         want_grad=True, workspace=None, stream=None):
+                         want_grad=True, workspace=None, *, stream=None):
     """-> (J fp64 [1], dJ/dlogp fp32 [T] or None, n_clipped int64 [1])."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low, eps_high, beta, want_grad, workspace)
+        if out is not None:
+            return out
+    return _py_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low, eps_high, beta, want_grad, workspace, stream=stream)
+
+
+@_on_stream
+def _py_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low=0.2, eps_high=0.2, beta=0.0,
+                       want_grad=True, workspace=None, stream=None):
     T = logp.numel()
     n = cu_seqlens.numel() - 1
     if logp_ref.numel() != T or advantage.numel() != n or seq_weight.numel() != n:
@@ -487,9 +577,17 @@ def arrol_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_
     return J, grad, n_clip
 
 
-@_on_stream
-def arrol_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally=False, out_winner=None, stream=None):
+def arrol_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally=False, out_winner=None, *, stream=None):
     """prob fp32 [Q*C], answer_id int32 [Q*C] -> winner int32 [Q] (and tally int64 [Q, A])."""
+    if stream is None and not want_tally and out_winner is None:
+        out = (_marshal or _load_marshal()).weighted_vote(prob, answer_id, n_questions, C, n_answers)
+        if out is not None:
+            return out
+    return _py_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally, out_winner, stream=stream)
+
+
+@_on_stream
+def _py_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally=False, out_winner=None, stream=None):
     dev = prob.device
     if prob.numel() != n_questions * C or answer_id.numel() != n_questions * C:
         raise ValueError("prob and answer_id must have n_questions*C entries")
@@ -504,9 +602,17 @@ def arrol_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally=F
     return (winner, tally) if want_tally else winner
 
 
-@_on_stream
-def arrol_histogram(s_norm, label, B, stream=None):
+def arrol_histogram(s_norm, label, B, *, stream=None):
     """s_norm fp32 [M] in [0,1], label uint8 [M] -> (c_pos, c_neg) int64 [B]."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).histogram(s_norm, label, B)
+        if out is not None:
+            return out
+    return _py_histogram(s_norm, label, B, stream=stream)
+
+
+@_on_stream
+def _py_histogram(s_norm, label, B, stream=None):
     dev = s_norm.device
     c_pos = torch.empty(B, dtype=torch.int64, device=dev)
     c_neg = torch.empty(B, dtype=torch.int64, device=dev)
@@ -516,9 +622,17 @@ def arrol_histogram(s_norm, label, B, stream=None):
     return c_pos, c_neg
 
 
-@_on_stream
-def arrol_calibrate(c_pos, c_neg, policy, stream=None):
+def arrol_calibrate(c_pos, c_neg, policy, *, stream=None):
     """int64 histograms [B] + Policy -> (q_lut fp32 [B], p_lut fp32 [B], delta fp64 device scalar)."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).calibrate(c_pos, c_neg, policy)
+        if out is not None:
+            return out
+    return _py_calibrate(c_pos, c_neg, policy, stream=stream)
+
+
+@_on_stream
+def _py_calibrate(c_pos, c_neg, policy, stream=None):
     B = c_pos.numel()
     dev = c_pos.device
     q_lut = torch.empty(B, dtype=torch.float32, device=dev)
@@ -530,10 +644,18 @@ def arrol_calibrate(c_pos, c_neg, policy, stream=None):
     return q_lut, p_lut, delta
 
 
-@_on_stream
-def arrol_prune_bernoulli(s_norm, uniforms, p_lut, want_p=False, stream=None):
+def arrol_prune_bernoulli(s_norm, uniforms, p_lut, want_p=False, *, stream=None):
     """s_norm, uniforms fp32 [N], p_lut fp32 [B] -> dict(keep_mask, survivor_idx (padded with -1),
     n_survivors (device int32), p (optional))."""
+    if stream is None:
+        out = (_marshal or _load_marshal()).prune_bernoulli(s_norm, uniforms, p_lut, want_p)
+        if out is not None:
+            return out
+    return _py_prune_bernoulli(s_norm, uniforms, p_lut, want_p, stream=stream)
+
+
+@_on_stream
+def _py_prune_bernoulli(s_norm, uniforms, p_lut, want_p=False, stream=None):
     N = s_norm.numel()
     dev = s_norm.device
     out = dict(keep_mask=torch.empty(N, dtype=torch.uint8, device=dev),

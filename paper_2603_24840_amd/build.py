@@ -1,4 +1,4 @@
-"""Builds libarrol.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds libarrol.so (HIP, gfx950 only) with hipcc and the binding's C++ marshalling (_marshal.so) with g++, in-tree.
 
     python -m paper_2603_24840_amd.build
 """
@@ -6,12 +6,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libarrol.so")
+MARSHAL_PATH = os.path.join(LIB_DIR, "_marshal.so")
 SOURCES = ["score.hip", "score_mlp.hip", "train.hip", "select.hip", "compact.hip", "logprob.hip", "vote.hip", "confidence.hip", "grpo.hip", "policy.hip", "probe.hip", "api.hip"]
 
 HIPCC_FLAGS = [
@@ -28,10 +30,7 @@ def hipcc_path():
     raise RuntimeError("hipcc not found: the ARRoL library can only be built with the ROCm toolchain")
 
 
-def build(verbose=True):
-    os.makedirs(LIB_DIR, exist_ok=True)
-    cmd = [hipcc_path()] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    cmd += [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -39,7 +38,20 @@ def build(verbose=True):
     if verbose and out.strip():
         print(out, flush=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
+
+
+def build(verbose=True):
+    os.makedirs(LIB_DIR, exist_ok=True)
+    include = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    _run([hipcc_path()] + HIPCC_FLAGS + include + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH], verbose)
+    import torch
+    t = os.path.dirname(torch.__file__)
+    _run([os.environ.get("CXX") or "g++", "-O2", "-fPIC", "-shared", "-std=c++17", "-Wall",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + include +
+         ["-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+          "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", LIB_DIR, "-larrol",
+          "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"], verbose)
     return LIB_PATH
 
 

@@ -1,0 +1,111 @@
+"""The C++ marshalling of the short calls (csrc/marshal.cpp) against the Python marshalling of the same calls: the same
+results, the same errors, and None - so the Python way - for everything but the ordinary case."""
+import pytest
+import torch
+
+import paper_2603_24840_amd as A
+from paper_2603_24840_amd import binding
+
+DEV = "cuda:0"
+
+
+def calls(dev):
+    g = torch.Generator().manual_seed(5)
+
+    def f(*shape):
+        return torch.randn(shape, generator=g).to(dev)
+
+    def ints(hi, n, dtype):
+        return torch.randint(0, hi, (n,), generator=g).to(dtype).to(dev)
+    h, w = f(96, 128).bfloat16(), f(128)
+    idx = torch.arange(0, 96, 3).to(dev)
+    y96, y32 = ints(2, 96, torch.float32), ints(2, 32, torch.float32)
+    w1, b1, w2 = f(40, 128).bfloat16(), f(40), f(40)
+    prob, uni = torch.rand(96, generator=g).to(dev), torch.rand(96, generator=g).to(dev)
+    cu, off = torch.tensor([0, 20, 50, 96]).to(dev), torch.tensor([0, 48, 90]).to(dev)
+    cp, cn = ints(50, 64, torch.int64), ints(50, 64, torch.int64)
+    pol = A.Policy(0.5, 0.5, 0.5, 0.05, 0.95, 1.0)
+    adam = [f(97), f(97), f(97) * 0.01, f(97).abs() * 0.01]
+    return {
+        "score": [((h, w), {}), ((h, w, 0.5, idx), {}), ((h[::2], w, 1), dict(want_score=False)), ((h[:1], torch.nn.Parameter(w)), {}),
+                  ((h, w), dict(out_score=torch.empty(96, device=dev), out_prob=torch.empty(96, device=dev)))],
+        "score_mlp": [((h, w1, b1, w2), {}), ((h, w1, None, w2, 0.25), dict(row_index=idx))],
+        "score_grad": [((h, w, 0.0, y96), {}), ((h, w, 0.5, y32), dict(row_index=idx))],
+        "score_mlp_grad": [((h, w1, b1, w2, 0.0, y96), {}), ((h, w1, None, w2, 0.25, y32), dict(row_index=idx, delta_terms=2))],
+        "adamw_step": [((*adam, 3, 1e-3), {}), ((*adam, 7, 1e-3), dict(weight_decay=0.1, param_bf16=torch.zeros(97, dtype=torch.bfloat16, device=dev)))],
+        "select": [((prob, 12, 8, 3), {}), ((prob, 6, 16, 16, 0.25), {})],
+        "weighted_vote": [((prob, ints(9, 96, torch.int32), 12, 8, 9), {}), ((prob, ints(9, 96, torch.int32), 12, 8, 9), dict(want_tally=True))],
+        "histogram": [((prob, ints(2, 96, torch.uint8), 64), {})],
+        "calibrate": [((cp, cn, pol), {})],
+        "prune_bernoulli": [((prob, uni, torch.rand(64, generator=g).to(dev)), {}), ((prob, uni, torch.rand(64, generator=g).to(dev)), dict(want_p=True))],
+        "grpo_advantage": [((f(96), off), {}), ((f(96), off, 1, 1e-6), {})],
+        "grpo_objective": [((f(96) * 0.1, f(96) * 0.1, cu, f(3), f(3).abs()), {}), ((f(96), f(96), cu, f(3), f(3).abs(), 0.2, 0.28, 0.04), dict(want_grad=False))],
+    }
+
+
+def flat(out):
+    if isinstance(out, dict):
+        return [(k, out[k]) for k in sorted(out)]
+    return list(enumerate(out)) if isinstance(out, tuple) else [(0, out)]
+
+
+def clone(x):
+    return x.clone() if isinstance(x, torch.Tensor) and not isinstance(x, torch.nn.Parameter) and x.is_contiguous() else x
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(calls("cpu")))
+def test_native_marshalling_gives_what_python_gives(name):
+    print("[case] marshal", name, flush=True)
+    fast, slow = getattr(A, "arrol_" + name), getattr(binding, "_py_" + name)
+    for args, kw in calls(DEV)[name]:
+        one = fast(*[clone(a) for a in args], **{k: clone(v) for k, v in kw.items()})
+        two = slow(*[clone(a) for a in args], **{k: clone(v) for k, v in kw.items()})
+        torch.cuda.synchronize()
+        for (k, a), (_, b) in zip(flat(one), flat(two)):
+            assert (a is None) == (b is None), k
+            if a is not None:
+                assert a.dtype == b.dtype and a.shape == b.shape and torch.equal(a.view(torch.uint8), b.view(torch.uint8)), k
+        assert len(flat(one)) == len(flat(two)) and type(one) is type(two)
+
+
+@pytest.mark.gpu
+def test_native_marshalling_takes_the_ordinary_case_only():
+    m = binding._load_marshal()
+    h, w = torch.zeros(8, 64, dtype=torch.bfloat16, device=DEV), torch.zeros(64, device=DEV)
+    ok = [h, w, 0.0, None, None, None, True]
+
+    class Sub(torch.Tensor):
+        pass
+    assert m.score(*ok) is not None
+    for i, odd in ((0, h.float()), (0, h[0]), (0, h.t()), (0, h.as_subclass(Sub)), (0, h.cpu()), (1, w.double()), (1, w.cpu()),
+                   (1, torch.zeros(128, device=DEV)[::2]), (2, "0"), (2, None), (3, torch.zeros(8, dtype=torch.int32, device=DEV)), (5, w.half()), (6, 1)):
+        assert m.score(*ok[:i], odd, *ok[i + 1:]) is None, (i, odd)
+    prob = torch.zeros(16, device=DEV)
+    for bad in ((prob, 2, 9, 1), (prob, 2 ** 32 + 2, 8, 1), (prob, -2, -8, 1), (prob, 2.0, 8, 1)):
+        assert m.select(*bad, 0.5, None, None) is None
+    assert m.calibrate(torch.zeros(4, dtype=torch.int64, device=DEV), torch.zeros(4, dtype=torch.int64, device=DEV), b"x" * 24) is None
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Mode(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+    with Mode():
+        assert m.score(*ok) is None
+    with torch.device(DEV):
+        assert m.score(*ok) is None
+    with pytest.raises(A.ArrolError):                        # the library's own refusal: d not a multiple of 8
+        A.arrol_score(torch.zeros(2, 12, dtype=torch.bfloat16, device=DEV), torch.zeros(12, device=DEV))
+    with pytest.raises(TypeError):
+        A.arrol_score(h.float(), w)
+
+
+def test_native_marshalling_leaves_cpu_tensors_to_python():
+    m = binding._load_marshal()
+    for name, cases in calls("cpu").items():
+        args, kw = cases[0]
+        with pytest.raises((TypeError, ValueError)):
+            getattr(A, "arrol_" + name)(*args, **kw)
+    assert m.histogram(torch.zeros(4), torch.zeros(4, dtype=torch.uint8), 4) is None
+    with pytest.raises(TypeError):
+        m.histogram(torch.zeros(4))
