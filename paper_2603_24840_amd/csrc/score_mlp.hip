@@ -341,20 +341,26 @@ __global__ __launch_bounds__(kThreads) void score_mlp_kernel(MlpArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Batches below the ring kernels' size, and gathered rows of any number: BM units x BN rollouts per workgroup of four
-// wavefronts (2 x 2), K64 stages of both operands direct to LDS, NS stages deep, one barrier per stage.  What bounds it
-// is a step's chain of barrier, fragment reads and MFMAs while few workgroups run, and each workgroup's (BM + BN) rows
-// of K through its compute unit's L1 path when the chip is full; pick_forward takes the block that makes the sum
-// smallest.  512 x 2048 x 512: 9.6 us with 32 x 32 blocks (11.9 with 64 x 64; a wavefront per 32 x 32 block without
-// LDS took 17), 4,096 x 2048 x 512: 17.7 us with 128 x 64 (69), finish kernel included.
+// Batches below the ring kernels' size, and gathered rows of any number: BM units x BN rollouts per workgroup of KG groups of
+// WM x WN wavefronts, K64 steps of both operands direct to LDS, NS stages deep, one barrier per stage.  What bounds it is a
+// step's chain of barrier, fragment reads and MFMAs while few workgroups run, and each workgroup's (BM + BN) rows of K
+// through its compute unit's L1 path when the chip is full; pick_forward takes the block that makes the sum smallest.
+// Where a compute unit has no second workgroup to fill the chain, the groups do: group g takes the steps g, g + KG, ... of the
+// block, a stage is KG steps, and the groups' sums are added in the LDS at the end.  512 x 2048 x 512 with 32 x 32 blocks: 7.7 us
+// with one group, 6.9 with four; 1,024 x 2048 x 512 with 64 x 64: 10.9, 10.4 with two; 4,096 x 4096 x 512 with 128 x 64: 27.1, 25.7.
+// (Of 4,096 x 2048 x 512's 16.7 us the steps take 9.6, the activations kept for the gradient 2.2, an empty launch 2.2.)
 // Stage layout: 16-byte chunk c of row r at position c ^ (r & 6) of its 128-byte row, which keeps the fragment reads
 // (lane -> row lane % 16, chunk lane / 16) free of bank conflicts by the serving rule given in ring_nt.h.
-template <int BM_, int BN_, int NS_>
+template <int BM_, int BN_, int WM_, int WN_, int KG_, int NS_>
 struct MidTile {
-    static constexpr int BM = BM_, BN = BN_, NS = NS_, NT = 256;
-    static constexpr int TI = BM / 32, TJ = BN / 32;
-    static constexpr int STAGE_BYTES = (BM + BN) * 128, LDS_BYTES = NS * STAGE_BYTES;
-    static constexpr int LA = BM / 32, LB = BN / 32, LOADS = LA + LB;   // load instructions (8 rows) per wave and stage
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KG = KG_, NS = NS_;
+    static constexpr int GW = WM * WN, NT = KG * GW * ARROL_WAVE;                  // wavefronts per group
+    static constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;
+    static constexpr int SUB_BYTES = (BM + BN) * 128, STAGE_BYTES = KG * SUB_BYTES;
+    static constexpr int LA = BM / 8 / GW, LB = BN / 8 / GW, LOADS = LA + LB;      // load instructions (8 rows) per wave and stage
+    static constexpr int RED_BYTES = KG > 1 ? KG * BM * BN * 4 : 0, PART_BYTES = KG * WM * BN * 4;
+    static constexpr int LDS_BYTES = NS * STAGE_BYTES > RED_BYTES + PART_BYTES ? NS * STAGE_BYTES : RED_BYTES + PART_BYTES;
+    static_assert(LDS_BYTES <= 163840 && BM % (8 * GW) == 0 && BN % (8 * GW) == 0, "tile");
 };
 
 struct MlpMidArgs {
@@ -369,18 +375,19 @@ template <class C>
 __global__ __launch_bounds__(C::NT, 2) void mlp_mid_kernel(MlpMidArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void* lds_ptr_t;
-    constexpr int BM = C::BM, BN = C::BN, NS = C::NS, TI = C::TI, TJ = C::TJ;
+    constexpr int BM = C::BM, BN = C::BN, NS = C::NS, TI = C::TI, TJ = C::TJ, KG = C::KG, GW = C::GW;
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int kg = wave / GW, wq = wave % GW, wm = wq / C::WN, wn = wq % C::WN;
     const int u0 = blockIdx.y * BM, r0 = blockIdx.x * BN;
-    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds));
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)lds)) + kg * C::SUB_BYTES;
+    const int n_k64 = a.d / 64, n_st = (n_k64 + KG - 1) / KG;
     // loader: lane -> (row lane/8 of an 8-row group, position lane%8); rows past the end repeat the last one
     const uint16_t* src[C::LOADS];
 #pragma unroll
     for (int q = 0; q < C::LOADS; ++q) {
         const bool is_a = q < C::LA;
-        const int r = (is_a ? wave * C::LA + q : wave * C::LB + q - C::LA) * 8 + (lane >> 3);
+        const int r = (is_a ? wq * C::LA + q : wq * C::LB + q - C::LA) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ (r & 6);
         if (is_a) {
             const int u = u0 + r < a.m ? u0 + r : a.m - 1;
@@ -390,36 +397,47 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_mid_kernel(MlpMidArgs a) {
             src[q] = a.hidden + (a.row_index ? a.row_index[row] : row) * a.row_stride + c * 8;
         }
     }
-    const int n_k64 = a.d / 64;
-    int ld_k = 0, ld_slot = 0;
+    int ld_k = kg < n_k64 ? kg : 0, ld_slot = 0;
     auto issue = [&]() {                     // the next stage; past the last one its lines again
         const int64_t k = static_cast<int64_t>(ld_k) * 64;
         const unsigned dst = lds0 + ld_slot * C::STAGE_BYTES;
 #pragma unroll
         for (int q = 0; q < C::LOADS; ++q) {
-            const unsigned to = dst + (q < C::LA ? (wave * C::LA + q) * 1024 : BM * 128 + (wave * C::LB + q - C::LA) * 1024);
+            const unsigned to = dst + (q < C::LA ? (wq * C::LA + q) * 1024 : BM * 128 + (wq * C::LB + q - C::LA) * 1024);
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src[q] + k), "s"(to) : "memory");
         }
         ld_slot = ld_slot + 1 == NS ? 0 : ld_slot + 1;
-        if (ld_k + 1 < n_k64) ++ld_k;
+        if (ld_k + KG < n_k64) ld_k += KG;
     };
     f32x4 acc[TI][TJ];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int a_off = (wm * (BM / 2) + l15) * 128, b_off = (BM + wn * (BN / 2) + l15) * 128;
+    const int a_off = kg * C::SUB_BYTES + (wm * (BM / C::WM) + l15) * 128, b_off = kg * C::SUB_BYTES + (BM + wn * (BN / C::WN) + l15) * 128;
     const int pos[2] = {(lq ^ (l15 & 6)) * 16, ((lq + 4) ^ (l15 & 6)) * 16};
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) issue();
+    // bias and weight of the units this lane finishes, fetched here: at the end their latency would be bare, and once for
+    // every store of an activation
+    float bias[TI][4], wgt[TI][4];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int u = u0 + wm * (BM / C::WM) + i * 16 + lq * 4 + v;
+            bias[i][v] = unit_bias(a.b1, u, u < a.m);
+            wgt[i][v] = unit_weight(a.w2, u, u < a.m);
+        }
     int slot = 0;
-    for (int k = 0; k < n_k64; ++k) {
+    for (int s = 0; s < n_st; ++s) {
         // this stage has landed (the NS - 2 after it may fly), for every wavefront, and all have read the one before
         mlp_wait_vmcnt<(NS - 2) * C::LOADS>();
         __syncthreads();
         issue();
         const unsigned char* st = lds + slot * C::STAGE_BYTES;
         slot = slot + 1 == NS ? 0 : slot + 1;
+        if (KG > 1 && s * KG + kg >= n_k64) continue;
         bf16x8 fa[2][TI], fb[2][TJ];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -436,38 +454,50 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_mid_kernel(MlpMidArgs a) {
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
     }
-    // acc[i][j][v]: unit wm * BM/2 + i*16 + lq*4 + v, rollout wn * BN/2 + j*16 + l15 of the block
+    // the groups' sums: block (i, j) of a wavefront position is finished by the group (i TJ + j) % KG, added in group order
+    mlp_wait_vmcnt<0>();
+    __syncthreads();                         // every stage has been read and every load into LDS has landed
+    f32x4* red = reinterpret_cast<f32x4*>(lds);   // [group][position][TI TJ][lane]
+    if (KG > 1) {
+#pragma unroll
+        for (int b = 0; b < TI * TJ; ++b) red[(wave * TI * TJ + b) * 64 + lane] = acc[b / TJ][b % TJ];
+        __syncthreads();
+    }
     float part[TJ];
 #pragma unroll
     for (int j = 0; j < TJ; ++j) part[j] = 0.f;
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+    for (int b = 0; b < TI * TJ; ++b) {
+        if (b % KG != kg) continue;
+        const int i = b / TJ, j = b % TJ;
+        f32x4 s = acc[i][j];
+        if (KG > 1) s = red[(wq * TI * TJ + b) * 64 + lane];
+#pragma unroll
+        for (int g = 1; g < KG; ++g) s += red[((g * GW + wq) * TI * TJ + b) * 64 + lane];
+        // s[v]: unit wm * BM/WM + i*16 + lq*4 + v, rollout wn * BN/WN + j*16 + l15 of the block
+        const int col = r0 + wn * (BN / C::WN) + j * 16 + l15;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int u = u0 + wm * (BM / 2) + i * 16 + lq * 4 + v;
-            const bool live = u < a.m;
-            const float bias = unit_bias(a.b1, u, live), w = unit_weight(a.w2, u, live);
-            float* arow = a.act_t ? a.act_t + static_cast<int64_t>(live ? u : 0) * a.act_stride : nullptr;
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) {
-                const float act = fmaxf(acc[i][j][v] + bias, 0.f);
-                part[j] = fmaf(act, w, part[j]);
-                const int col = r0 + wn * (BN / 2) + j * 16 + l15;
-                if (arow && live && col < a.n_rows) arow[col] = act;
-            }
+            const int u = u0 + wm * (BM / C::WM) + i * 16 + lq * 4 + v;
+            const float act = fmaxf(s[v] + bias[i][v], 0.f);
+            part[j] = fmaf(act, wgt[i][v], part[j]);
+            if (a.act_t && u < a.m && col < a.n_rows) a.act_t[static_cast<int64_t>(u) * a.act_stride + col] = act;
         }
-    mlp_wait_vmcnt<0>();
-    __syncthreads();                         // every stage has been read and every load into LDS has landed
-    float* red = reinterpret_cast<float*>(lds);   // [2][BN]
+    }
+    float* sums = reinterpret_cast<float*>(lds + C::RED_BYTES);   // [group][wm][BN]
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
         part[j] += __shfl_xor(part[j], 16, ARROL_WAVE);
         part[j] += __shfl_xor(part[j], 32, ARROL_WAVE);
-        if (lq == 0) red[wm * BN + wn * (BN / 2) + j * 16 + l15] = part[j];
+        if (lq == 0) sums[(kg * C::WM + wm) * BN + wn * (BN / C::WN) + j * 16 + l15] = part[j];
     }
     __syncthreads();
-    if (tid < BN && r0 + tid < a.n_rows)
-        a.partial[static_cast<int64_t>(blockIdx.y) * a.n_rows + r0 + tid] = red[tid] + red[BN + tid];
+    if (tid < BN && r0 + tid < a.n_rows) {
+        float s = sums[tid];
+#pragma unroll
+        for (int q = 1; q < KG * C::WM; ++q) s += sums[q * BN + tid];
+        a.partial[static_cast<int64_t>(blockIdx.y) * a.n_rows + r0 + tid] = s;
+    }
 }
 
 template <class C>
@@ -798,9 +828,13 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     }
 }
 
-using Mid32 = MidTile<32, 32, 8>;
-using Mid64 = MidTile<64, 64, 4>;
-using Mid128 = MidTile<128, 64, 3>;
+// one group of wavefronts, two workgroups to a compute unit, and two or four groups, one workgroup to a unit
+using Mid32 = MidTile<32, 32, 2, 2, 1, 8>;
+using Mid64 = MidTile<64, 64, 2, 2, 1, 4>;
+using Mid128 = MidTile<128, 64, 2, 2, 1, 3>;
+using Mid32Groups = MidTile<32, 32, 2, 1, 4, 3>;
+using Mid64Groups = MidTile<64, 64, 2, 2, 2, 4>;
+using Mid128Groups = MidTile<128, 64, 2, 2, 2, 3>;
 using Wgrad64 = WgradTile<64, 2, 2, 2, 4>;
 using Wgrad128 = WgradTile<128, 2, 2, 2, 3>;
 using Wgrad128Two = WgradTile<128, 2, 2, 1, 3>;      // two workgroups to a compute unit
@@ -885,8 +919,12 @@ int enqueue_forward(ForwardPath path, const void* hidden, int64_t row_stride_ele
     }
     MlpMidArgs a = {static_cast<const uint16_t*>(hidden), row_stride_elems, row_index, static_cast<const uint16_t*>(w1), b1, w2,
                     n_rows, d, m, partial, act_t, act_stride};
-    if (path == kPathMid32) return launch_mlp_mid<Mid32>(a, st);
-    return path == kPathMid64 ? launch_mlp_mid<Mid64>(a, st) : launch_mlp_mid<Mid128>(a, st);
+    // groups where a compute unit has one workgroup anyhow and K is long enough to pay for adding them up (d = 320: 6.7 against 7.1
+    // us with 300 rollouts x 1,000, d = 512 even); 64 x 64 blocks of 129 to 256 are not faster for it
+    const bool deep = d >= 768;
+    if (path == kPathMid32) return deep && n_blocks(n_rows, m, 32, 32) <= 256 ? launch_mlp_mid<Mid32Groups>(a, st) : launch_mlp_mid<Mid32>(a, st);
+    if (path == kPathMid64) return deep && n_blocks(n_rows, m, 64, 64) <= 128 ? launch_mlp_mid<Mid64Groups>(a, st) : launch_mlp_mid<Mid64>(a, st);
+    return deep && n_blocks(n_rows, m, 64, 128) <= 256 ? launch_mlp_mid<Mid128Groups>(a, st) : launch_mlp_mid<Mid128>(a, st);
 }
 
 // dL/dW1 on the ring pipeline's K-major B form: any batch size, rows addressed in place
