@@ -321,6 +321,9 @@ int arrol_trace_confidence(const float* conf, const int64_t* cu_seqlens, int64_t
  */
 int arrol_grpo_advantage(const float* reward, const int64_t* group_offsets, int64_t N, int32_t n_groups,
                          int32_t ddof, float eps, float* advantage, float* seq_weight, void* stream);
+/* The same with 0 in both arrays for rollouts outside every group: the caller need not clear them first. */
+int arrol_grpo_advantage_all(const float* reward, const int64_t* group_offsets, int64_t N, int32_t n_groups,
+                             int32_t ddof, float eps, float* advantage, float* seq_weight, void* stream);
 
 /*
  * Clipped-ratio objective of Sec. 3 on packed per-token log-probabilities (rollout i = tokens
@@ -334,7 +337,8 @@ int arrol_grpo_advantage(const float* reward, const int64_t* group_offsets, int6
  * grad_logp NULL or fp32 [T] = dJ/dlogp_t (zero where the clipped branch is the minimum); n_clipped NULL or
  * int64 [1] = tokens where the clipped branch is strictly smaller.  fp64 arithmetic, fixed summation order.
  * 0 <= eps_low <= 1, eps_high >= 0, beta >= 0, else ARROL_EINVAL.  n_seq == 0 writes J = 0.
- * workspace: arrol_grpo_objective_workspace_bytes(n_seq) bytes, 16-byte aligned.
+ * workspace: at least arrol_grpo_objective_workspace_bytes(n_seq) bytes, 16-byte aligned.  With more (up to 8 times as
+ * many are used) long rollouts are cut into parts that several workgroups take, which is faster.
  */
 size_t arrol_grpo_objective_workspace_bytes(int32_t n_seq);
 int arrol_grpo_objective(const float* logp, const float* logp_ref, const int64_t* cu_seqlens, int64_t T,

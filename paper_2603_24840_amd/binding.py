@@ -78,6 +78,7 @@ _SIGNATURES = {
     "arrol_trace_confidence_workspace_bytes": (_sz, [_i64, _i32]),
     "arrol_trace_confidence": (ctypes.c_int, [_vp, _vp, _i64, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "arrol_grpo_advantage": (ctypes.c_int, [_vp, _vp, _i64, _i32, _i32, _f32, _vp, _vp, _vp]),
+    "arrol_grpo_advantage_all": (ctypes.c_int, [_vp, _vp, _i64, _i32, _i32, _f32, _vp, _vp, _vp]),
     "arrol_grpo_objective_workspace_bytes": (_sz, [_i32]),
     "arrol_grpo_objective": (ctypes.c_int, [_vp, _vp, _vp, _i64, _i32, _vp, _vp, _f32, _f32, _f32, _vp, _vp, _vp,
                                             _vp, _sz, _vp]),
@@ -536,10 +537,10 @@ def arrol_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, *, stream=None)
 def _py_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, stream=None):
     N = reward.numel()
     n_groups = group_offsets.numel() - 1
-    adv = torch.zeros(N, dtype=torch.float32, device=reward.device)
-    wgt = torch.zeros(N, dtype=torch.float32, device=reward.device)
-    rc = lib().arrol_grpo_advantage(_ptr(reward, torch.float32, "reward"), _ptr(group_offsets, torch.int64, "group_offsets"),
-                                    N, n_groups, int(ddof), float(eps), adv.data_ptr(), wgt.data_ptr(), _stream(stream))
+    adv = torch.empty(N, dtype=torch.float32, device=reward.device)
+    wgt = torch.empty(N, dtype=torch.float32, device=reward.device)
+    rc = lib().arrol_grpo_advantage_all(_ptr(reward, torch.float32, "reward"), _ptr(group_offsets, torch.int64, "group_offsets"),
+                                        N, n_groups, int(ddof), float(eps), adv.data_ptr(), wgt.data_ptr(), _stream(stream))
     _check("arrol_grpo_advantage", rc)
     return adv, wgt
 
@@ -563,7 +564,8 @@ def _py_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_lo
         raise ValueError("logp/logp_ref must be [T]; advantage/seq_weight [n_seq]")
     dev = logp.device
     if workspace is None:
-        workspace = torch.empty(max(lib().arrol_grpo_objective_workspace_bytes(n), 16), dtype=torch.uint8, device=dev)
+        # eight times what is asked for: room for long rollouts in parts
+        workspace = torch.empty(max(8 * lib().arrol_grpo_objective_workspace_bytes(n), 16), dtype=torch.uint8, device=dev)
     J = torch.empty(1, dtype=torch.float64, device=dev)
     grad = torch.empty(T, dtype=torch.float32, device=dev) if want_grad else None
     n_clip = torch.empty(1, dtype=torch.int64, device=dev)

@@ -7,14 +7,61 @@
 
 namespace {
 
-// one wavefront per group
+__device__ __forceinline__ void group_range(const int64_t* group_offsets, int g, int64_t N, int64_t& lo, int64_t& hi) {
+    lo = group_offsets[g];
+    hi = group_offsets[g + 1];
+    lo = lo < 0 ? 0 : (lo > N ? N : lo);
+    hi = hi < lo ? lo : (hi > N ? N : hi);
+}
+
+// Zeros for the rollouts of no group, by one wavefront, while the others work: of offsets that never fall what lies before the
+// first and behind the last, of others every rollout that no group holds.  Nothing that a group writes is touched.
+__device__ void zero_outside(const int64_t* __restrict__ group_offsets, int64_t N, int n_groups, float* __restrict__ advantage,
+                             float* __restrict__ seq_weight) {
+    int falls = 0;
+    for (int g = threadIdx.x; g < n_groups; g += ARROL_WAVE) falls |= group_offsets[g + 1] < group_offsets[g];
+    const bool ascending = !__any(falls);
+    int64_t lo = 0, hi = 0;
+    if (n_groups > 0) {
+        lo = group_offsets[0];
+        hi = group_offsets[n_groups];
+    }
+    for (int64_t i = threadIdx.x; i < N; i += ARROL_WAVE) {
+        bool outside = i < lo || i >= hi;
+        if (!ascending) {
+            outside = true;
+            for (int g = 0; g < n_groups && outside; ++g) {
+                int64_t a, b;
+                group_range(group_offsets, g, N, a, b);
+                outside = i < a || i >= b;
+            }
+        } else if (!outside) {
+            // on to the last rollouts: none between lo and hi
+            const int64_t skip = (hi - i) / ARROL_WAVE * ARROL_WAVE;
+            if (skip > ARROL_WAVE) i += skip - ARROL_WAVE;
+        }
+        if (outside) {
+            advantage[i] = 0.f;
+            if (seq_weight) seq_weight[i] = 0.f;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void grpo_zero_kernel(int64_t N, float* __restrict__ advantage, float* __restrict__ seq_weight) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= N) return;
+    advantage[i] = 0.f;
+    if (seq_weight) seq_weight[i] = 0.f;
+}
+
+// one wavefront per group; a workgroup more writes the zeros
 __global__ __launch_bounds__(ARROL_WAVE) void grpo_advantage_kernel(
     const float* __restrict__ reward, const int64_t* __restrict__ group_offsets, int64_t N, int n_groups, int ddof,
     double eps, float* __restrict__ advantage, float* __restrict__ seq_weight) {
     const int g = blockIdx.x;
-    int64_t lo = group_offsets[g], hi = group_offsets[g + 1];
-    lo = lo < 0 ? 0 : (lo > N ? N : lo);
-    hi = hi < lo ? lo : (hi > N ? N : hi);
+    if (g == n_groups) return zero_outside(group_offsets, N, n_groups, advantage, seq_weight);
+    int64_t lo, hi;
+    group_range(group_offsets, g, N, lo, hi);
     const int64_t n = hi - lo;
     if (n == 0) return;
     double s = 0.0;
@@ -37,7 +84,7 @@ __global__ __launch_bounds__(ARROL_WAVE) void grpo_advantage_kernel(
 }
 
 constexpr int kObjUnroll = 4;          // tokens per thread whose loads are in flight together
-constexpr int kFinishThreads = 256;
+constexpr int kSegments = 8;           // most workgroups per rollout
 
 // the workgroup's sums of s and c, in thread 0
 template <int WAVES>
@@ -55,9 +102,9 @@ __device__ __forceinline__ void workgroup_sums(double& s, long long& c, double (
     }
 }
 
-// one workgroup per rollout: partial[i] = weight_i * (1/L_i) * sum_t term_t, clipped[i] = tokens on the clipped branch.
-// Bound by latency (two 64-bit exponentials behind two loads, 12 bytes a token): the loads of four tokens go out together
-// and long rollouts get enough wavefronts to hide the rest.
+// n_seg workgroups per rollout, each with an equal part of its tokens: partial[i n_seg + q] = weight_i * (1/L_i) * sum_t term_t,
+// clipped[..] = tokens on the clipped branch.  Bound by latency (64-bit exponentials behind two loads, 12 bytes a token): the
+// loads of four tokens go out together and long rollouts get enough wavefronts to hide the rest.
 template <int kObjThreads>
 __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     const float* __restrict__ logp, const float* __restrict__ logp_ref, const int64_t* __restrict__ cu, int64_t T,
@@ -65,13 +112,18 @@ __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     double beta, float* __restrict__ grad_logp, double* __restrict__ partial, int64_t* __restrict__ clipped) {
     __shared__ double sh_s[kObjThreads / ARROL_WAVE];
     __shared__ long long sh_c[kObjThreads / ARROL_WAVE];
-    const int i = blockIdx.x;
+    const int i = blockIdx.x, n_seg = gridDim.y, out = i * n_seg + blockIdx.y;
     int64_t lo = cu[i], hi = cu[i + 1];
     lo = lo < 0 ? 0 : (lo > T ? T : lo);
     hi = hi < lo ? lo : (hi > T ? T : hi);
     const int64_t L = hi - lo;
-    if (L == 0) {
-        if (threadIdx.x == 0) { partial[i] = 0.0; clipped[i] = 0; }
+    if (n_seg > 1) {
+        const int64_t part = (L + n_seg - 1) / n_seg;
+        lo = lo + blockIdx.y * part < hi ? lo + blockIdx.y * part : hi;
+        hi = lo + part < hi ? lo + part : hi;
+    }
+    if (lo == hi) {
+        if (threadIdx.x == 0) { partial[out] = 0.0; clipped[out] = 0; }
         return;
     }
     const double A = static_cast<double>(advantage[i]);
@@ -107,21 +159,35 @@ __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     }
     workgroup_sums(s, c, sh_s, sh_c);
     if (threadIdx.x == 0) {
-        partial[i] = s * scale;
-        clipped[i] = c;
+        partial[out] = s * scale;
+        clipped[out] = c;
     }
 }
 
-// one workgroup: J = sum_i partial[i] in a fixed order
+// one workgroup: J = the partials' sum in a fixed order
+template <int kFinishThreads>
 __global__ __launch_bounds__(kFinishThreads) void grpo_finish_kernel(const double* __restrict__ partial,
-                                                                     const int64_t* __restrict__ clipped, int n_seq,
+                                                                     const int64_t* __restrict__ clipped, int64_t n,
                                                                      double* __restrict__ objective_out,
                                                                      int64_t* __restrict__ n_clipped) {
     __shared__ double sh_s[kFinishThreads / ARROL_WAVE];
     __shared__ long long sh_c[kFinishThreads / ARROL_WAVE];
     double s = 0.0;
     long long c = 0;
-    for (int64_t i = threadIdx.x; i < n_seq; i += kFinishThreads) { s += partial[i]; c += clipped[i]; }
+    constexpr int kInFlight = kFinishThreads > 256 ? 4 : 1;
+    for (int64_t i0 = threadIdx.x; i0 < n; i0 += kFinishThreads * kInFlight) {
+        double x[kInFlight];
+        int64_t y[kInFlight];
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k) {
+            const int64_t i = i0 + k * kFinishThreads < n ? i0 + k * kFinishThreads : i0;
+            x[k] = partial[i];
+            y[k] = clipped[i];
+        }
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (i0 + k * kFinishThreads < n) { s += x[k]; c += y[k]; }
+    }
     workgroup_sums(s, c, sh_s, sh_c);
     if (threadIdx.x == 0) {
         if (objective_out) *objective_out = s;
@@ -141,6 +207,25 @@ extern "C" int arrol_grpo_advantage(const float* reward, const int64_t* group_of
     return arrol_launch_status();
 }
 
+extern "C" int arrol_grpo_advantage_all(const float* reward, const int64_t* group_offsets, int64_t N, int32_t n_groups,
+                                        int32_t ddof, float eps, float* advantage, float* seq_weight, void* stream) {
+    if (N < 0 || n_groups < 0 || (ddof != 0 && ddof != 1) || !(eps >= 0.f)) return ARROL_EINVAL;
+    if (N == 0) return ARROL_OK;
+    if (!advantage || (n_groups > 0 && (!reward || !group_offsets))) return ARROL_EINVAL;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // one wavefront looks at every offset and rollout: not where that is long beside a launch for the zeros
+    if (n_groups > 0 && n_groups <= 4096 && N <= 65536) {
+        arrol_launch(grpo_advantage_kernel, dim3(n_groups + 1), dim3(ARROL_WAVE), 0, st, reward, group_offsets, N, n_groups, ddof,
+                     static_cast<double>(eps), advantage, seq_weight);
+        return arrol_launch_status();
+    }
+    const int64_t blocks = (N + 255) / 256;
+    if (blocks > INT32_MAX) return ARROL_EINVAL;
+    arrol_launch(grpo_zero_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, N, advantage, seq_weight);
+    if (arrol_launch_failed()) return arrol_launch_status();
+    return arrol_grpo_advantage(reward, group_offsets, N, n_groups, ddof, eps, advantage, seq_weight, stream);
+}
+
 extern "C" size_t arrol_grpo_objective_workspace_bytes(int32_t n_seq) {
     return n_seq < 0 ? 0 : static_cast<size_t>(n_seq) * 16;
 }
@@ -153,22 +238,34 @@ extern "C" int arrol_grpo_objective(const float* logp, const float* logp_ref, co
         return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (n_seq == 0) {
-        arrol_launch(grpo_finish_kernel, dim3(1), dim3(kFinishThreads), 0, st, nullptr, nullptr, 0, objective_out,
-                           n_clipped);
+        arrol_launch(grpo_finish_kernel<256>, dim3(1), dim3(256), 0, st, nullptr, nullptr, 0, objective_out, n_clipped);
         return arrol_launch_status();
     }
     if (!cu_seqlens || !advantage || !seq_weight || (T > 0 && (!logp || !logp_ref))) return ARROL_EINVAL;
-    if (!workspace || !arrol_aligned16(workspace) || workspace_bytes < arrol_grpo_objective_workspace_bytes(n_seq))
-        return ARROL_EWORKSPACE;
+    const int64_t room = static_cast<int64_t>(workspace_bytes / 16 / static_cast<size_t>(n_seq));   // partials per rollout
+    if (!workspace || !arrol_aligned16(workspace) || room < 1) return ARROL_EWORKSPACE;
+    // Rollouts are cut into parts of some 1,024 tokens where there are too few to fill the chip, up to 256 parts in all (one of
+    // 20,000 tokens: 17.3 us whole, 7.2 in 8; 32 of 1,024 to 8,192: 9.7 and 5.9; but 256 of 2,000 6.0 and 7.5 in 4), and, of 3 million
+    // tokens and more, where whole ones leave the units uneven (1,024 of 1,024 to 8,192: 25.3 and 22.6 in 4).
+    int64_t n_seg = (2 * (T / n_seq) + 1023) / 1024;
+    const int64_t most = (T >= 3000000 ? 4096 : 256) / n_seq;
+    n_seg = n_seg < kSegments ? n_seg : kSegments;
+    n_seg = n_seg < most ? n_seg : most;
+    n_seg = n_seg < room ? n_seg : room;
+    n_seg = n_seg > 1 ? n_seg : 1;
+    const int64_t n_parts = n_seq * n_seg;
     double* partial = static_cast<double*>(workspace);
-    int64_t* clipped = reinterpret_cast<int64_t*>(partial + n_seq);
-#define ARROL_OBJECTIVE(N) arrol_launch(grpo_objective_kernel<N>, dim3(n_seq), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta), grad_logp, partial, clipped)
+    int64_t* clipped = reinterpret_cast<int64_t*>(partial + n_parts);
+#define ARROL_OBJECTIVE(N) arrol_launch(grpo_objective_kernel<N>, dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta), grad_logp, partial, clipped)
     // wider workgroups shorten a long rollout's chain while the chip has room for them: 512 rollouts of 512 to 4,096 tokens
     // 10.5 us with 512 threads, 11.3 with 256; 512 of 64 to 512 tokens 5.7 and 5.4; 4,096 of 256 to 2,048 30.0 and 26.1
-    if (T / n_seq > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512);
+    if (n_seg == 1 && T / n_seq > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512);
     else ARROL_OBJECTIVE(256);
 #undef ARROL_OBJECTIVE
-    arrol_launch(grpo_finish_kernel, dim3(1), dim3(kFinishThreads), 0, st, partial, clipped, n_seq, objective_out,
-                       n_clipped);
+    // many: four partials a thread at a time; 256 threads are quicker to add up (one rollout: 4.2 us the call, 4.7 with 1,024)
+    if (n_parts <= 1024)
+        arrol_launch(grpo_finish_kernel<256>, dim3(1), dim3(256), 0, st, partial, clipped, n_parts, objective_out, n_clipped);
+    else
+        arrol_launch(grpo_finish_kernel<1024>, dim3(1), dim3(1024), 0, st, partial, clipped, n_parts, objective_out, n_clipped);
     return arrol_launch_status();
 }

@@ -85,7 +85,7 @@ void none(PyObject* o) {
     if (o != Py_None) throw Odd();
 }
 
-struct Unlocked {     // launches and zeros go without the interpreter lock, as ctypes and torch.zeros do
+struct Unlocked {     // launches go without the interpreter lock, as ctypes calls do
     PyThreadState* save = PyEval_SaveThread();
     ~Unlocked() { PyEval_RestoreThread(save); }
 };
@@ -99,11 +99,6 @@ at::Tensor make(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& li
     if (!g_allocator) throw Odd();
     return at::detail::empty_generic(shape, g_allocator.load(), c10::DispatchKeySet(c10::DispatchKey::CUDA), type, std::nullopt);
 }
-at::Tensor make_zeros(int64_t n, const at::Tensor& like) {
-    const Unlocked u;
-    return at::zeros({n}, at::TensorOptions().dtype(at::kFloat).device(like.device()));
-}
-
 // the current device's current stream, as binding._stream asks for it
 void* stream(const at::Tensor& like) {
     PyObject* dev = PyObject_CallNoArgs(g_device);
@@ -365,12 +360,11 @@ PyObject* grpo_advantage(PyObject* const* a) {
     const int64_t N = r.numel(), groups = off.numel() - 1;
     if (groups < 0 || groups > INT32_MAX) throw Odd();
     void* st = stream(r);
-    // zeros: a rollout of no group keeps them
-    at::Tensor adv = make_zeros(N, r), wgt = make_zeros(N, r);
+    at::Tensor adv = make({N}, at::kFloat, r), wgt = make({N}, at::kFloat, r);
     const float* pr = static_cast<const float*>(data(r));
     const int64_t* po = static_cast<const int64_t*>(data(off));
     float *pa = static_cast<float*>(data(adv)), *pw = static_cast<float*>(data(wgt));
-    if (failed("arrol_grpo_advantage", launch([&] { return arrol_grpo_advantage(pr, po, N, groups, ddof, eps, pa, pw, st); }))) return nullptr;
+    if (failed("arrol_grpo_advantage", launch([&] { return arrol_grpo_advantage_all(pr, po, N, groups, ddof, eps, pa, pw, st); }))) return nullptr;
     return tuple(wrap(std::move(adv)), wrap(std::move(wgt)));
 }
 
@@ -384,7 +378,7 @@ PyObject* grpo_objective(PyObject* const* a) {
     const int64_t T = lp.numel(), n = cu.numel() - 1;
     if (n < 0 || n > INT32_MAX || ref.numel() != T || adv.numel() != n || wgt.numel() != n) throw Odd();
     void* st = stream(lp);
-    size_t need = arrol_grpo_objective_workspace_bytes(static_cast<int32_t>(n));
+    size_t need = 8 * arrol_grpo_objective_workspace_bytes(static_cast<int32_t>(n));
     need = need > 16 ? need : 16;
     at::Tensor ws = make({static_cast<int64_t>(need)}, at::kByte, lp), J = make({1}, at::kDouble, lp), grad, clip = make({1}, at::kLong, lp);
     if (want) grad = make({T}, at::kFloat, lp);

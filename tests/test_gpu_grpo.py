@@ -131,3 +131,44 @@ def test_objective_at_extreme_ratios(A):
     assert np.all(np.abs(got[ok] - want[ok]) <= 1e-7 * np.abs(want[ok]) + 1e-15 * 0.5 / len(u) * 4)
     assert np.array_equal(np.signbit(got[~ok & ~np.isnan(want)]), np.signbit(want[~ok & ~np.isnan(want)]))
     assert int(n_clip) == clipped and np.isnan(float(J))
+
+
+# rollouts cut into parts: lengths around the 1,024 tokens of a part, none, and far more than the mean; the workspace that
+# decides how many parts there are (1, 2, 3 and the 8 the binding makes room for); the same bits again
+@pytest.mark.parametrize("room", [1, 2, 3, 8])
+def test_objective_in_parts(A, room):
+    print("[case] grpo_objective parts room=%d" % room, flush=True)
+    lens = [4096, 1, 0, 1023, 1024, 1025, 5000, 2049, 3, 8191, 4100, 2048]
+    run_objective(A, lens, [4, 2, 6], seed=21, eps_high=0.28, beta=0.01)
+    T, n = sum(lens), len(lens)
+    g = torch.Generator(device=DEV); g.manual_seed(room)
+    ref = -torch.rand(T, generator=g, device=DEV) * 4
+    lp = ref + 0.3 * torch.randn(T, generator=g, device=DEV)
+    adv, wgt, cu = torch.randn(n, generator=g, device=DEV), torch.rand(n, generator=g, device=DEV), dev_i64(np.concatenate([[0], np.cumsum(lens)]))
+    whole = A.arrol_grpo_objective(lp, ref, cu, adv, wgt, beta=0.01)
+    ws = torch.empty(16 * n * room, dtype=torch.uint8, device=DEV)
+    part, again = (A.arrol_grpo_objective(lp, ref, cu, adv, wgt, beta=0.01, workspace=ws) for _ in range(2))
+    torch.cuda.synchronize()
+    assert torch.equal(whole[1], part[1]) and torch.equal(whole[2], part[2])      # per token: no sum in it
+    # sums of T fp64 terms in another order
+    assert abs(float(whole[0]) - float(part[0])) <= 1e-12 * max(1.0, abs(float(whole[0])))
+    assert all(torch.equal(a, b) for a, b in zip(part, again))
+
+
+# rollouts of no group get zeros, whatever the outputs held: before the first offset, behind the last, none, all, between
+# groups whose offsets fall (which leaves ranges that no group holds), in one launch and, of many rollouts, in two
+@pytest.mark.parametrize("offsets,N", [([0, 8, 20], 20), ([5, 8, 20], 33), ([7, 7], 12), ([0], 9), ([-4, 3, 99], 50), ([10, 30, 5, 8, 60, 40, 44], 90),
+                                       ([40, 10], 64), ([3, 70000], 80000), ([60, 90, 20], 70001)])
+def test_advantage_outside_every_group_is_zero(A, offsets, N):
+    print("[case] grpo_advantage outside N=%d" % N, flush=True)
+    reward = torch.randn(N, device=DEV)
+    junk = [torch.full((N,), float("nan"), device=DEV) for _ in range(4)]
+    del junk
+    adv, wgt = A.arrol_grpo_advantage(reward, dev_i64(offsets))
+    torch.cuda.synchronize()
+    held = np.zeros(N, bool)
+    for a, b in zip(offsets, offsets[1:]):
+        a = min(max(a, 0), N)
+        held[a:max(a, min(b, N))] = True
+    assert np.all(npy(adv)[~held] == 0.0) and np.all(npy(wgt)[~held] == 0.0)
+    assert np.all(npy(wgt)[held] > 0.0) and not np.isnan(npy(adv)).any()
