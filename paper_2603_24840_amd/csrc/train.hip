@@ -17,6 +17,17 @@ __device__ __forceinline__ void unpack8(const u32x4& x, float (&f)[8]) {
     f[4] = bf16_lo(x.z); f[5] = bf16_hi(x.z); f[6] = bf16_lo(x.w); f[7] = bf16_hi(x.w);
 }
 
+// Dynamic LDS: the head weights where a lane has no slice of them in registers, then, per wavefront, G blocks of 512 columns of
+// the sums.  All blocks at once where that fits: with a pair of barriers for every 512 columns the whole call took 9.6 us at
+// 1,024 x 4096 and 49.1 at 32,768 x 4096, with one pair 8.7 and 48.0 (d of 1,024 and less: the same within 1 %).
+template <int CH>
+struct GradLds {
+    static constexpr bool W_REG = CH == 8;
+    static constexpr int G = CH <= 8 ? CH : 4;
+    static constexpr int bytes(int d) { return static_cast<int>(sizeof(float)) * ((W_REG ? 0 : d) + kGradWaves * G * 512); }
+    static_assert(G * 512 * kGradWaves * 4 + (W_REG ? 0 : CH * 512 * 4) <= 163840, "LDS");
+};
+
 // One wavefront per row; lane l owns columns [8*(c*64+l), +8) for c < CH for every row it sees, so the
 // gradient accumulators stay in its registers.  Bound by HBM for large batches, by one chain of load, dot product,
 // exponential and LDS sums for small ones (1,024 x 4096: 15.8 us with eight rows per wavefront, 7.5 with one).  partial: [gridDim.x][d] fp32, tail: [gridDim.x][2] (loss, sum r).
@@ -25,9 +36,9 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     const u32x4* __restrict__ hidden, int64_t row_stride_vec, const int64_t* __restrict__ row_index,
     const float* __restrict__ w, float bias, const float* __restrict__ labels, int n_rows, int d_vec,
     float* __restrict__ partial, float* __restrict__ tail) {
-    extern __shared__ float lds[];                 // d floats of head weights, then kGradWaves*512 floats
+    extern __shared__ float lds[];                 // GradLds<CH>
     float* w_lds = lds;
-    float* red = lds + d_vec * 8;
+    float* red = lds + (GradLds<CH>::W_REG ? 0 : d_vec * 8);
     const int lane = threadIdx.x & (ARROL_WAVE - 1);
     const int wave = threadIdx.x / ARROL_WAVE;
     constexpr bool PREFETCH = CH <= 4;   // wider rows leave no registers for a second one
@@ -53,7 +64,7 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     // against 3.9 TB/s; for smaller d the extra registers cost more occupancy than the LDS reads cost time:
     // 4.5 against 5.2 TB/s; both with up to 1,024 workgroups, 5.5 TB/s at 4096 with the 256 of grad_blocks),
     // otherwise the weights are read from LDS
-    constexpr bool W_REG = CH == 8;
+    constexpr bool W_REG = GradLds<CH>::W_REG;
     constexpr int NW = W_REG ? CH : 1;
     float4 wra[NW], wrb[NW];
     if (W_REG) {
@@ -121,21 +132,28 @@ __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
             }
         }
     }
-    // the workgroup's eight wavefronts add up through LDS, 512 columns at a time, in a fixed order
+    // the workgroup's eight wavefronts add up through LDS, GradLds<CH>::G blocks of 512 columns at a time, in a fixed order
     float* out = partial + static_cast<int64_t>(blockIdx.x) * d_vec * 8;
+    constexpr int G = GradLds<CH>::G;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (c * ARROL_WAVE < d_vec) {                          // uniform over the workgroup
-            float* mine = red + wave * 512 + lane * 8;
-            *reinterpret_cast<float4*>(mine) = make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
-            *reinterpret_cast<float4*>(mine + 4) = make_float4(acc[c][4], acc[c][5], acc[c][6], acc[c][7]);
+    for (int c0 = 0; c0 < CH; c0 += G) {
+        if (c0 * ARROL_WAVE < d_vec) {                         // uniform over the workgroup
+#pragma unroll
+            for (int c = 0; c < G; ++c) {
+                float* mine = red + (wave * G + c) * 512 + lane * 8;
+                *reinterpret_cast<float4*>(mine) = make_float4(acc[c0 + c][0], acc[c0 + c][1], acc[c0 + c][2], acc[c0 + c][3]);
+                *reinterpret_cast<float4*>(mine + 4) = make_float4(acc[c0 + c][4], acc[c0 + c][5], acc[c0 + c][6], acc[c0 + c][7]);
+            }
             __syncthreads();
-            const int col = c * 512 + threadIdx.x;
-            if (col < d_vec * 8) {
-                float part[kGradWaves];
 #pragma unroll
-                for (int k = 0; k < kGradWaves; ++k) part[k] = red[k * 512 + threadIdx.x];
-                out[col] = tree_sum<kGradWaves>(part);
+            for (int c = 0; c < G; ++c) {
+                const int col = (c0 + c) * 512 + threadIdx.x;
+                if (col < d_vec * 8) {
+                    float part[kGradWaves];
+#pragma unroll
+                    for (int k = 0; k < kGradWaves; ++k) part[k] = red[(k * G + c) * 512 + threadIdx.x];
+                    out[col] = tree_sum<kGradWaves>(part);
+                }
             }
             __syncthreads();
         }
@@ -205,13 +223,13 @@ int grad_blocks(int n_rows, int d) {
 }
 
 template <int CH>
-int launch_grad(int grid, size_t lds_bytes, hipStream_t st, const void* hidden, int64_t row_stride_vec,
+int launch_grad(int grid, hipStream_t st, const void* hidden, int64_t row_stride_vec,
                 const int64_t* row_index, const float* w, float bias, const float* labels, int n_rows, int d_vec,
                 float* partial, float* tail) {
     static arrol_device_flags lds_ok;
-    if (!arrol_allow_lds(score_grad_kernel<CH>, static_cast<int>(sizeof(float) * (kGradMaxD + kGradWaves * 512)), lds_ok))
+    if (!arrol_allow_lds(score_grad_kernel<CH>, GradLds<CH>::bytes(CH * 512), lds_ok))
         return ARROL_EHIP;
-    arrol_launch(score_grad_kernel<CH>, dim3(grid), dim3(kGradThreads), lds_bytes, st,
+    arrol_launch(score_grad_kernel<CH>, dim3(grid), dim3(kGradThreads), GradLds<CH>::bytes(d_vec * 8), st,
                        static_cast<const u32x4*>(hidden), row_stride_vec, row_index, w, bias, labels, n_rows, d_vec,
                        partial, tail);
     return arrol_launch_status();
@@ -243,16 +261,15 @@ extern "C" int arrol_score_grad(const void* hidden, int64_t row_stride_elems, co
     const int grid = grad_blocks(n_rows, d);
     float* partial = static_cast<float*>(workspace);
     float* tail = partial + static_cast<size_t>(grid) * d;
-    const size_t lds_bytes = sizeof(float) * (static_cast<size_t>(d) + kGradWaves * 512);
     const int d_vec = d / 8;
     const int chunks = (d_vec + ARROL_WAVE - 1) / ARROL_WAVE;
     const int64_t rsv = row_stride_elems / 8;
     int rc;
-    if (chunks <= 1) rc = launch_grad<1>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
-    else if (chunks <= 2) rc = launch_grad<2>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
-    else if (chunks <= 4) rc = launch_grad<4>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
-    else if (chunks <= 8) rc = launch_grad<8>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
-    else rc = launch_grad<16>(grid, lds_bytes, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
+    if (chunks <= 1) rc = launch_grad<1>(grid, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
+    else if (chunks <= 2) rc = launch_grad<2>(grid, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
+    else if (chunks <= 4) rc = launch_grad<4>(grid, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
+    else if (chunks <= 8) rc = launch_grad<8>(grid, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
+    else rc = launch_grad<16>(grid, st, hidden, rsv, row_index, w, bias, labels, n_rows, d_vec, partial, tail);
     if (rc != ARROL_OK) return rc;
     arrol_launch(score_grad_reduce_kernel, dim3(col_blocks + 1), dim3(32 * kReduceGroups), 0, st, partial, tail, grid, d,
                        1.f / static_cast<float>(n_rows), loss_out, grad_w, grad_bias);

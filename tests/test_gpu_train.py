@@ -367,3 +367,13 @@ def test_score_grad_around_one_row_per_wavefront(A, W, n, d):
     cfg = W.shrink(W.CONFIGS["tiny"], d=d)
     hidden, w, _, labels = W.head_training_inputs(cfg, DEV, n_rows=n)
     check_grad(A, hidden, w * 3.0, 0.25, labels)
+
+
+@pytest.mark.parametrize("n,d", [(9, 504), (9, 512), (65, 1016), (33, 1544), (17, 2560), (40, 4088), (12, 6144), (21, 7680), (5, 8184)])
+def test_score_grad_sums_in_blocks_of_512_columns(A, W, n, d):
+    """The wavefronts' sums meet in LDS, up to eight blocks of 512 columns at once: widths that end within, at and before the
+    last block of a round."""
+    print("[case] score_grad n=%d d=%d" % (n, d), flush=True)
+    cfg = W.shrink(W.CONFIGS["tiny"], d=d)
+    hidden, w, _, labels = W.head_training_inputs(cfg, DEV, n_rows=n)
+    check_grad(A, hidden, w * 3.0, 0.25, labels)
