@@ -30,7 +30,8 @@ struct GradLds {
 
 // One wavefront per row; lane l owns columns [8*(c*64+l), +8) for c < CH for every row it sees, so the
 // gradient accumulators stay in its registers.  Bound by HBM for large batches, by one chain of load, dot product,
-// exponential and LDS sums for small ones (1,024 x 4096: 15.8 us with eight rows per wavefront, 7.5 with one).  partial: [gridDim.x][d] fp32, tail: [gridDim.x][2] (loss, sum r).
+// exponential and LDS sums for small ones (1,024 x 4096: 15.8 us with eight rows per wavefront, 7.5 with one,
+// 6.6 with the sums in one round).  partial: [gridDim.x][d] fp32, tail: [gridDim.x][2] (loss, sum r).
 template <int CH>
 __global__ __launch_bounds__(kGradThreads) void score_grad_kernel(
     const u32x4* __restrict__ hidden, int64_t row_stride_vec, const int64_t* __restrict__ row_index,
