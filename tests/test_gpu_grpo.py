@@ -172,3 +172,31 @@ def test_advantage_outside_every_group_is_zero(A, offsets, N):
         held[a:max(a, min(b, N))] = True
     assert np.all(npy(adv)[~held] == 0.0) and np.all(npy(wgt)[~held] == 0.0)
     assert np.all(npy(wgt)[held] > 0.0) and not np.isnan(npy(adv)).any()
+
+
+# both sides of the bounds of the one launch (2,048 groups, 65,536 rollouts), offsets that rise, that hold few rollouts and of
+# which one falls: no order of the offsets may make the call slow (some 25 us here; one wavefront that asked every group about
+# every rollout took 22 ms at 16,384 x 1,024)
+@pytest.mark.parametrize("kind", ["rise", "few", "fall"])
+@pytest.mark.parametrize("N,n_groups", [(16384, 1024), (65536, 2048), (65537, 2048), (65536, 2049), (63, 1500), (129, 1), (1000, 513)])
+def test_advantage_of_any_order_of_offsets(A, N, n_groups, kind):
+    print("[case] grpo_advantage offsets %s N=%d groups=%d" % (kind, N, n_groups), flush=True)
+    offsets = np.linspace(0, N, n_groups + 1).astype(np.int64)
+    if kind == "few":
+        offsets = N // 2 + offsets // 8
+    elif kind == "fall":
+        offsets = offsets // 2
+        offsets[(n_groups + 1) // 2] = 1
+    reward, off = torch.randn(N, device=DEV), dev_i64(offsets)
+    adv, wgt = A.arrol_grpo_advantage(reward, off)
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record()
+    adv, wgt = A.arrol_grpo_advantage(reward, off)
+    end.record()
+    torch.cuda.synchronize()
+    assert start.elapsed_time(end) < 10.0
+    held = np.zeros(N, bool)
+    for a, b in zip(offsets, offsets[1:]):
+        held[a:max(a, min(b, N))] = True
+    assert np.all(npy(adv)[~held] == 0.0) and np.all(npy(wgt)[~held] == 0.0)
+    assert np.all(npy(wgt)[held] > 0.0) and not np.isnan(npy(adv)).any()
