@@ -15,7 +15,7 @@
  *   arrol_compact_inplace                                      hole-filling compaction of the same pool (Sec. 4.3 (i))
  *   arrol_compact_static                                       arrol_compact without a workspace argument (fixed scratch)
  *   arrol_probe_mfma_rate                                      measurement aid: register-only bf16 MFMA rate of this card
- *   arrol_score_mlp_kernels                                    test aid: which kernels the MLP calls take for a batch
+ *   arrol_score_mlp_kernels, arrol_score_mlp_tiles             test aids: which kernels the MLP calls take for a batch
  *   arrol_token_confidence, arrol_trace_confidence             trace confidence (Sec. 3)
  *   arrol_grpo_advantage, arrol_grpo_objective                 group-relative advantage, clipped objective (Sec. 3)
  *
@@ -393,11 +393,20 @@ int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems, const int
  * they ask for), so that a test can say which of them it reaches.  delta_terms 0 asks about arrol_score_mlp, 1 or 2 about
  * arrol_score_mlp_grad; gathered is non-zero for calls with a row_index.
  * *forward          0 one-launch tile kernel; units x rollouts blocks: 1 of 32 x 32, 2 of 64 x 64, 3 of 128 x 64, 4 of 256 x 256
- * *weight_gradient  -1 none; 0 tile kernel on transposed hidden states; in place: 1 in 128 x 64 blocks, 2 in 256 x 256
+ * *weight_gradient  -1 none; 0 tile kernel on transposed hidden states; in place: 1 in 64 x 64 or 128 x 64 blocks, 2 in
+ *                   256 x 256
  * *splits           ranges of rollouts that dL/dW1 is cut into (0: none)
  */
 int arrol_score_mlp_kernels(int32_t n_rows, int32_t d, int32_t m, int64_t row_stride_elems, int32_t gathered,
                             int32_t delta_terms, int32_t* forward, int32_t* weight_gradient, int32_t* splits);
+/*
+ * The same for what is inside those kernels.
+ * *forward_groups   groups of wavefronts that share the K steps of a forward block (1, 2 or 4)
+ * *gradient_rows    units of a block of dL/dW1 in place: 64, 128 or 256; 0 for the others
+ * *gradient_groups  groups of wavefronts that share its K steps (1 or 2); 0 for the others
+ */
+int arrol_score_mlp_tiles(int32_t n_rows, int32_t d, int32_t m, int64_t row_stride_elems, int32_t gathered,
+                          int32_t delta_terms, int32_t* forward_groups, int32_t* gradient_rows, int32_t* gradient_groups);
 
 /*
  * One AdamW update in place (the paper names no optimizer; AdamW with decoupled weight decay is this

@@ -61,6 +61,7 @@ _SIGNATURES = {
     "arrol_score_mlp_grad": (ctypes.c_int, [_vp, _i64, _vp, _vp, _vp, _vp, _f32, _vp, _i32, _i32, _i32, _vp, _vp, _vp,
                                             _vp, _vp, _i32, _vp, _sz, _vp]),
     "arrol_score_mlp_kernels": (ctypes.c_int, [_i32, _i32, _i32, _i64, _i32, _i32, _vp, _vp, _vp]),
+    "arrol_score_mlp_tiles": (ctypes.c_int, [_i32, _i32, _i32, _i64, _i32, _i32, _vp, _vp, _vp]),
     "arrol_adamw_step": (ctypes.c_int, [_vp, _vp, _vp, _vp, _i64, _i32, _f32, _f32, _f32, _f32, _f32, _vp, _vp]),
     "arrol_select": (ctypes.c_int, [_vp, _i32, _i32, _i32, _f32, _vp, _vp, _vp]),
     "arrol_compact_workspace_bytes": (_sz, [_i32]),

@@ -904,6 +904,17 @@ ForwardPath pick_score(int n_rows, int d, int m, int64_t row_stride_elems, bool 
 }
 int unit_block(ForwardPath p) { return p == kPathMid32 ? 32 : p == kPathMid64 ? 64 : p == kPathMid128 ? 128 : 256; }
 
+// Wavefront groups that share a block's K: several where a compute unit has one workgroup anyhow and K is long enough to pay for
+// adding them up (d = 320: 6.7 against 7.1 us with 300 rollouts x 1,000, d = 512 even); 64 x 64 blocks of 129 to 256 are not
+// faster for it.
+int forward_groups(ForwardPath path, int n_rows, int d, int m) {
+    if (d < 768) return 1;
+    if (path == kPathMid32) return n_blocks(n_rows, m, 32, 32) <= 256 ? Mid32Groups::KG : 1;
+    if (path == kPathMid64) return n_blocks(n_rows, m, 64, 64) <= 128 ? Mid64Groups::KG : 1;
+    if (path == kPathMid128) return n_blocks(n_rows, m, 64, 128) <= 256 ? Mid128Groups::KG : 1;
+    return 1;
+}
+
 // Partial scores of every unit block to `partial`, with act_t also the activations (kPathTile: not for this).
 int enqueue_forward(ForwardPath path, const void* hidden, int64_t row_stride_elems, const int64_t* row_index, const void* w1,
                     const float* b1, const float* w2, int n_rows, int d, int m, float* partial, float* act_t,
@@ -919,12 +930,10 @@ int enqueue_forward(ForwardPath path, const void* hidden, int64_t row_stride_ele
     }
     MlpMidArgs a = {static_cast<const uint16_t*>(hidden), row_stride_elems, row_index, static_cast<const uint16_t*>(w1), b1, w2,
                     n_rows, d, m, partial, act_t, act_stride};
-    // groups where a compute unit has one workgroup anyhow and K is long enough to pay for adding them up (d = 320: 6.7 against 7.1
-    // us with 300 rollouts x 1,000, d = 512 even); 64 x 64 blocks of 129 to 256 are not faster for it
-    const bool deep = d >= 768;
-    if (path == kPathMid32) return deep && n_blocks(n_rows, m, 32, 32) <= 256 ? launch_mlp_mid<Mid32Groups>(a, st) : launch_mlp_mid<Mid32>(a, st);
-    if (path == kPathMid64) return deep && n_blocks(n_rows, m, 64, 64) <= 128 ? launch_mlp_mid<Mid64Groups>(a, st) : launch_mlp_mid<Mid64>(a, st);
-    return deep && n_blocks(n_rows, m, 64, 128) <= 256 ? launch_mlp_mid<Mid128Groups>(a, st) : launch_mlp_mid<Mid128>(a, st);
+    const bool groups = forward_groups(path, n_rows, d, m) > 1;
+    if (path == kPathMid32) return groups ? launch_mlp_mid<Mid32Groups>(a, st) : launch_mlp_mid<Mid32>(a, st);
+    if (path == kPathMid64) return groups ? launch_mlp_mid<Mid64Groups>(a, st) : launch_mlp_mid<Mid64>(a, st);
+    return groups ? launch_mlp_mid<Mid128Groups>(a, st) : launch_mlp_mid<Mid128>(a, st);
 }
 
 // dL/dW1 on the ring pipeline's K-major B form: any batch size, rows addressed in place
@@ -1564,6 +1573,23 @@ extern "C" int arrol_score_mlp_kernels(int32_t n_rows, int32_t d, int32_t m, int
         const bool in_place = wgrad_in_place(d, row_stride_elems, gathered != 0);
         *weight_gradient = !in_place ? 0 : p.w_rows != 256 ? 1 : 2;
         *splits = in_place ? p.r_splits : p.splits;
+    }
+    return ARROL_OK;
+}
+
+extern "C" int arrol_score_mlp_tiles(int32_t n_rows, int32_t d, int32_t m, int64_t row_stride_elems, int32_t gathered,
+                                     int32_t delta_terms, int32_t* forward_groups_out, int32_t* gradient_rows, int32_t* gradient_groups) {
+    int32_t forward, gradient, splits;
+    if (!forward_groups_out || !gradient_rows || !gradient_groups) return ARROL_EINVAL;
+    const int rc = arrol_score_mlp_kernels(n_rows, d, m, row_stride_elems, gathered, delta_terms, &forward, &gradient, &splits);
+    if (rc != ARROL_OK) return rc;
+    *forward_groups_out = forward_groups(static_cast<ForwardPath>(forward), n_rows, d, m);
+    *gradient_rows = 0;
+    *gradient_groups = 0;
+    if (gradient > 0) {
+        const GradPlan p = make_grad_plan(n_rows, d, m, delta_terms);
+        *gradient_rows = p.w_rows;
+        *gradient_groups = p.w_rows == 256 ? 1 : p.w_groups;
     }
     return ARROL_OK;
 }

@@ -28,10 +28,19 @@ def oracle_survivors(O, prob_f32, cfg):
     return O.select(np.asarray(prob_f32, dtype=np.float32), cfg.n_prompts, cfg.G, cfg.K, cfg.rho)
 
 
+def _mlp_query(name, A, n, d, m, delta_terms, gathered, row_stride):
+    out = [ctypes.c_int32() for _ in range(3)]
+    rc = getattr(A.lib(), name)(n, d, m, row_stride or d, int(gathered), delta_terms, *[ctypes.byref(x) for x in out])
+    assert rc == 0
+    return tuple(x.value for x in out)
+
+
 def mlp_kernels(A, n, d, m, delta_terms, gathered=False, row_stride=None):
     """(forward, weight gradient, splits) that the MLP calls take for a batch, numbered as in the header: a test that is
     there for one kernel says so, and fails when a changed choice leads its sizes elsewhere."""
-    out = [ctypes.c_int32() for _ in range(3)]
-    rc = A.lib().arrol_score_mlp_kernels(n, d, m, row_stride or d, int(gathered), delta_terms, *[ctypes.byref(x) for x in out])
-    assert rc == 0
-    return tuple(x.value for x in out)
+    return _mlp_query("arrol_score_mlp_kernels", A, n, d, m, delta_terms, gathered, row_stride)
+
+
+def mlp_tiles(A, n, d, m, delta_terms, gathered=False, row_stride=None):
+    """(wavefront groups of the forward blocks, units and wavefront groups of a weight gradient block), as above."""
+    return _mlp_query("arrol_score_mlp_tiles", A, n, d, m, delta_terms, gathered, row_stride)

@@ -129,6 +129,9 @@ def test_bad_arguments_are_rejected_on_the_host(pkg):
     for bad in ((0, 128, 8, 128, 1, one), (64, 12, 8, 128, 1, one), (64, 128, 0, 128, 1, one), (64, 128, 8, 64, 1, one),
                 (64, 128, 8, 128, 3, one), (64, 128, 8, 128, -1, one), (64, 128, 8, 128, 1, None)):
         assert kern(*bad) == -1, bad
+        n, d, m, stride, terms, out = bad
+        assert L.arrol_score_mlp_tiles(n, d, m, stride, 0, terms, out, out, out) == -1, bad
+    assert L.arrol_score_mlp_tiles(64, 128, 8, 128, 0, 1, one, one, one) == 0
     # head training: bad d, missing gradient output, workspace; optimizer: bad step / betas
     assert L.arrol_score_grad(fake, 16, None, fake, 0.0, fake, 4, 12, None, fake, None, fake, 1 << 20, None) == -1
     assert L.arrol_score_grad(fake, 16384, None, fake, 0.0, fake, 4, 16384, None, fake, None, fake, 1 << 20, None) == -1

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, mlp_kernels, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
+from helpers import bits, mlp_kernels, mlp_tiles, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
 
 pytestmark = pytest.mark.gpu
 
@@ -451,6 +451,17 @@ def test_score_mlp_dispatch_by_size(A, n, d, m, gather):
                                                   (17001, 64, 513, True, 0)])
 def test_score_mlp_reaches_each_forward_kernel(A, n, d, m, gather, forward):
     assert mlp_kernels(A, n, d, m, 0, gathered=gather, row_stride=d + 64) == (forward, -1, 0)
+    test_score_mlp_dispatch_by_size(A, n, d, m, gather)
+
+
+# K over two or four wavefront groups: 13, 14, 15 and 17 K64 steps, which leave some groups a step short, in each of the three
+# blocks, with remainders on both sides
+@pytest.mark.parametrize("gather", [False, True])
+@pytest.mark.parametrize("n,d,m,forward,groups", [(130, 832, 33, 1, 4), (201, 896, 257, 1, 4), (77, 960, 300, 1, 4), (31, 1088, 31, 1, 4),
+                                                  (4097, 832, 33, 2, 2), (4097, 1088, 33, 2, 2), (6001, 832, 129, 3, 2), (6001, 960, 250, 3, 2),
+                                                  (300, 704, 257, 1, 1)])
+def test_score_mlp_k_over_wavefront_groups(A, n, d, m, forward, groups, gather):
+    assert mlp_kernels(A, n, d, m, 0, gathered=gather)[0] == forward and mlp_tiles(A, n, d, m, 0, gathered=gather) == (groups, 0, 0)
     test_score_mlp_dispatch_by_size(A, n, d, m, gather)
 
 

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, mlp_kernels, npy
+from helpers import bits, mlp_kernels, mlp_tiles, npy
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -243,6 +243,19 @@ def test_score_mlp_grad_one_launch_delta(A, n, d, m, terms):
     print("[case] score_mlp_grad delta n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
     hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=11 * n + d + m)
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.25, labels, delta_terms=terms)
+
+
+# dL/dW1 in each of its blocks - 64 or 128 units, one or two wavefront groups - with one and two terms, one and several K splits,
+# odd and even numbers of K64 steps, units, columns and rollouts that end inside a block; behind forward blocks with groups
+@pytest.mark.parametrize("n,d,m,terms,tiles,splits", [(2001, 2112, 100, 1, (4, 64, 2), 3), (513, 2048, 513, 1, (2, 128, 2), 1), (129, 2048, 513, 1, (4, 128, 1), 1),
+                                                      (1001, 2112, 100, 2, (4, 64, 2), 3), (257, 2048, 513, 2, (4, 128, 2), 1),
+                                                      (3001, 2048, 129, 2, (1, 128, 2), 4), (129, 2048, 513, 2, (4, 128, 1), 1),
+                                                      (2001, 2112, 200, 2, (2, 128, 1), 4), (3001, 3072, 100, 2, (2, 128, 1), 6)])
+def test_score_mlp_grad_weight_gradient_tiles(A, n, d, m, terms, tiles, splits):
+    print("[case] score_mlp_grad tiles n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
+    assert mlp_tiles(A, n, d, m, terms) == tiles and mlp_kernels(A, n, d, m, terms)[1:] == (1, splits)
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=13 * n + d + m)
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, -0.25, labels, delta_terms=terms)
 
 
 # dL/dW1 in the 256 x 256 ring form: one to fifteen K splits, one and two terms, units, columns and rollouts that end inside a
