@@ -683,8 +683,9 @@ __global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where m
 // dL/dW1 = delta^T . H over the rollouts where the ring form has too few 256 x 256 tiles to fill the chip: BM rows of
 // delta^T x 64 columns per workgroup of KG groups of WM x WN wavefronts.  Group g takes the K64 steps g, g + KG, ... of the
 // tile, so two wavefronts share a SIMD and a barrier stands for KG steps, and the groups' sums are added in the LDS at the
-// end.  Where tiles are too few, K (rollouts) is also split over gridDim.z into slabs; of two-term deltas the second term's
-// steps follow the first's, into the same sums.  The hidden states are read in place: a step holds 64 rollouts x 128 bytes, and
+// end.  Where tiles are too few, K (rollouts) is also split over gridDim.z into slabs.  Of two-term deltas both terms of a K64
+// step come next to each other, into the same sums, while its hidden states are near: one term's steps behind the other's read
+// them from memory twice (131,072 x 1024 x 128, whole call: 298 us, so 251).  The hidden states are read in place: a step holds 64 rollouts x 128 bytes, and
 // the B fragments come out through the transposing LDS read (lane layout as in ring_nt.h).  16-byte chunk c of rollout row r
 // sits at position c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different 8-byte bank pairs.
 // Bound by the loads into LDS (16 KB a step at 73 bytes per nanosecond and compute unit with 64 x 64).  4,096 x 2048 x 512,
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave / GW, wq = wave % GW, wm = wq / C::WN, wn = wq % C::WN;
     const int u0 = blockIdx.y * BM, c0 = blockIdx.x * BN;
-    // steps of this split: all terms of its K64 range, one after the other
+    // steps of this split: of each K64 all terms, one or two, so that the hidden states come from memory once
     const int k64_lo = static_cast<int>(blockIdx.z) * a.k64_per_split;
     const int k64_hi = k64_lo + a.k64_per_split < a.n_k64 ? k64_lo + a.k64_per_split : a.n_k64;   // > k64_lo (host)
     const int per = k64_hi - k64_lo, n_steps = per * terms, n_st = (n_steps + KG - 1) / KG;
@@ -734,23 +735,36 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
         b_row[q] = r;
         b_col[q] = c < a.b_rows ? c : a.b_rows - 8;      // (d % 64 == 0)
     }
-    int ld_s = kg < n_steps ? kg : 0, ld_slot = 0;
-    auto issue = [&]() {                     // the group's next step; past the last one its lines again
-        const unsigned dst = lds0 + ld_slot * C::STAGE_BYTES;
-        const int t = ld_s >= per, k64 = k64_lo + ld_s - (t ? per : 0);
-        const int64_t ak = t * term + static_cast<int64_t>(k64) * 64;
+    // the group's next step: number, first rollout, offset in src_a, LDS slot
+    int ld_s = kg < n_steps ? kg : 0, ld_row = (k64_lo + (ld_s >> (terms - 1))) * 64;
+    int64_t ld_a = (ld_s & (terms - 1)) * term + ld_row;
+    const int move = 64 * KG / terms;        // of a group that stays with one term
+    unsigned ld_dst = lds0;
+    auto issue = [&]() {                     // past the last step its lines again
+        int64_t ak = ld_a;
+        if (KG == 1) asm("" : "+s"(ak));     // one scalar: the compiler makes two vector additions a load of the sum (38.9 -> 37.1 us at
+                                             // 4,096 x 3072 x 768; two groups 1 % slower with it)
 #pragma unroll
         for (int q = 0; q < C::LA; ++q)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_a[q] + ak), "s"(dst + (wq * C::LA + q) * 1024) : "memory");
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_a[q] + ak), "s"(ld_dst + (wq * C::LA + q) * 1024) : "memory");
 #pragma unroll
         for (int q = 0; q < C::LB; ++q) {
-            int k = k64 * 64 + b_row[q];                 // rollouts past the last one repeat it: delta^T is zero there
+            int k = ld_row + b_row[q];                   // rollouts past the last one repeat it: delta^T is zero there
             k = k < a.b_k_rows ? k : a.b_k_rows - 1;
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(a.b + static_cast<int64_t>(k) * (a.b_stride / 2) + b_col[q]),
-                         "s"(dst + BM * 128 + (wq * C::LB + q) * 1024) : "memory");
+                         "s"(ld_dst + BM * 128 + (wq * C::LB + q) * 1024) : "memory");
         }
-        ld_slot = ld_slot + 1 == NS ? 0 : ld_slot + 1;
-        if (ld_s + KG < n_steps) ld_s += KG;
+        ld_dst = ld_dst == lds0 + (NS - 1) * C::STAGE_BYTES ? lds0 : ld_dst + C::STAGE_BYTES;
+        if (ld_s + KG < n_steps) {
+            ld_s += KG;
+            if (KG == 1 && terms == 2) {     // the other term of the same rollouts, then the first of the next
+                ld_a += ld_s & 1 ? term : 64 - term;
+                ld_row += ld_s & 1 ? 0 : 64;
+            } else {
+                ld_a += move;
+                ld_row += move;
+            }
+        }
     };
     f32x4 acc[TI][TJ];
 #pragma unroll
@@ -780,9 +794,9 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
         mlp_wait_vmcnt<(NS - 2) * C::LOADS>();
         __syncthreads();
         issue();
-        const unsigned char* st = lds + slot * C::STAGE_BYTES;
-        slot = slot + 1 == NS ? 0 : slot + 1;
-        if (s * KG + kg >= n_steps) continue;
+        const unsigned char* st = lds + slot;
+        slot = slot == (NS - 1) * C::STAGE_BYTES ? 0 : slot + C::STAGE_BYTES;
+        if (KG > 1 && s * KG + kg >= n_steps) continue;
         bf16x8 fa[2][TI], fb[2][TJ];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
