@@ -1318,6 +1318,12 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
     // 25.9; 4,096 x 3072 x 768: 47.9 / 45.5 / 31.2).
     const double mid_slab_us = static_cast<double>(m) * d * 8.0 / 4.5e6;
     const int64_t tiles64 = static_cast<int64_t>((d + 63) / 64) * ((m + 63) / 64), tiles128 = static_cast<int64_t>((d + 63) / 64) * ((m + 127) / 128);
+    // Of a last round of more than 256 workgroups the pairs on some units set the time (288: 0.5 us a step, 512: 0.68); with their
+    // share of 512 for it 8,192 x 2048 x 257 took 288 workgroups, 26.3 us, instead of 480, 20.5.
+    const auto one_group_us = [&](int64_t n, int steps) {
+        const double last = n % 512 <= 256 ? 0.38 : 0.5 + (kMidStep - 0.5) * static_cast<double>(n % 512 - 256) / 256.0;
+        return static_cast<double>(n / 512) * (steps * kMidStep + kMidStart) + (n % 512 ? steps * last + kMidStart : 0.0);
+    };
     constexpr double kStep64 = 0.205, kStep128 = 0.31, kRound64 = 4.3, kRound128 = 5.5;
     double best_mid = -1.0, one_mid = 0.0;
     for (int s = 1; s <= kMaxSplits && (s == 1 || n_k64 / s >= 4); ++s) {
@@ -1326,8 +1332,7 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
         const int64_t n64 = tiles64 * used, n128 = tiles128 * used;
         const double t64 = (m + 63) / 64 > 65535 ? 1e30 : static_cast<double>((n64 + 255) / 256) * (per * terms * kStep64 + kRound64) + slabs;
         const double t128 = static_cast<double>((n128 + 255) / 256) * (per * terms * kStep128 + kRound128) + slabs;
-        const double steps = per * terms, last = kMidStep * (n128 % 512) / 512;
-        const double two = static_cast<double>(n128 / 512) * (steps * kMidStep + kMidStart) + (n128 % 512 ? steps * (last > 0.38 ? last : 0.38) + kMidStart : 0.0) + slabs;
+        const double two = one_group_us(n128, per * terms) + slabs;
         double t = t64 < t128 ? t64 : t128;
         t = two < t ? two : t;
         if (s == 1) one_mid = t;

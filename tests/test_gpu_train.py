@@ -250,7 +250,8 @@ def test_score_mlp_grad_one_launch_delta(A, n, d, m, terms):
 @pytest.mark.parametrize("n,d,m,terms,tiles,splits", [(2001, 2112, 100, 1, (4, 64, 2), 3), (513, 2048, 513, 1, (2, 128, 2), 1), (129, 2048, 513, 1, (4, 128, 1), 1),
                                                       (1001, 2112, 100, 2, (4, 64, 2), 3), (257, 2048, 513, 2, (4, 128, 2), 1),
                                                       (3001, 2048, 129, 2, (1, 128, 2), 4), (129, 2048, 513, 2, (4, 128, 1), 1),
-                                                      (2001, 2112, 200, 2, (2, 128, 1), 4), (3001, 3072, 100, 2, (2, 128, 1), 6)])
+                                                      (2001, 2112, 200, 2, (2, 128, 2), 3), (3001, 3072, 100, 2, (2, 128, 2), 5),
+                                                      (2500, 960, 1100, 2, (1, 128, 1), 3), (8150, 2048, 257, 1, (1, 128, 1), 5)])
 def test_score_mlp_grad_weight_gradient_tiles(A, n, d, m, terms, tiles, splits):
     print("[case] score_mlp_grad tiles n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
     assert mlp_tiles(A, n, d, m, terms) == tiles and mlp_kernels(A, n, d, m, terms)[1:] == (1, splits)
