@@ -6,8 +6,8 @@ tensor is not on the GPU the call raises.
 
 The short calls go through csrc/marshal.cpp (_marshal.so) first, which does the ordinary case in C++: they are bound by the
 host (arrol_score 7.0 us a call from Python alone, 4.4 so).  It returns None for what it does not take - another
-tensor class, CPU tensors, wrong types, strides or sizes, a stream, a workspace of the caller's, an active mode of torch's - and the
-_py_ function of the same name does that, errors included.
+tensor class, CPU tensors, wrong types, strides or sizes, a stream, an active mode of torch's - and the _py_ function of the same
+name does that, errors included (without a stream its undecorated form, since there is nothing to switch to).
 """
 import ctypes
 import functools
@@ -181,6 +181,7 @@ def arrol_score(hidden, w, bias=0.0, row_index=None, out_score=None, out_prob=No
         out = (_marshal or _load_marshal()).score(hidden, w, bias, row_index, out_score, out_prob, want_score)
         if out is not None:
             return out
+        return _py_score.__wrapped__(hidden, w, bias, row_index, out_score, out_prob, want_score)
     return _py_score(hidden, w, bias, row_index, out_score, out_prob, want_score, stream=stream)
 
 
@@ -214,6 +215,7 @@ def arrol_score_mlp(hidden, w1, b1, w2, b2=0.0, row_index=None, workspace="auto"
         out = (_marshal or _load_marshal()).score_mlp(hidden, w1, b1, w2, b2, row_index, workspace)
         if out is not None:
             return out
+        return _py_score_mlp.__wrapped__(hidden, w1, b1, w2, b2, row_index, workspace)
     return _py_score_mlp(hidden, w1, b1, w2, b2, row_index, workspace, stream=stream)
 
 
@@ -249,6 +251,7 @@ def arrol_score_grad(hidden, w, bias, labels, row_index=None, workspace=None, *,
         out = (_marshal or _load_marshal()).score_grad(hidden, w, bias, labels, row_index, workspace)
         if out is not None:
             return out
+        return _py_score_grad.__wrapped__(hidden, w, bias, labels, row_index, workspace)
     return _py_score_grad(hidden, w, bias, labels, row_index, workspace, stream=stream)
 
 
@@ -283,6 +286,7 @@ def arrol_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index=None, delta_t
         out = (_marshal or _load_marshal()).score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index, delta_terms, workspace)
         if out is not None:
             return out
+        return _py_score_mlp_grad.__wrapped__(hidden, w1, b1, w2, b2, labels, row_index, delta_terms, workspace)
     return _py_score_mlp_grad(hidden, w1, b1, w2, b2, labels, row_index, delta_terms, workspace, stream=stream)
 
 
@@ -323,6 +327,7 @@ def arrol_adamw_step(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e
         out = (_marshal or _load_marshal()).adamw_step(param, grad, m, v, step, lr, beta1, beta2, eps, weight_decay, param_bf16)
         if out is not None:
             return out
+        return _py_adamw_step.__wrapped__(param, grad, m, v, step, lr, beta1, beta2, eps, weight_decay, param_bf16)
     return _py_adamw_step(param, grad, m, v, step, lr, beta1, beta2, eps, weight_decay, param_bf16, stream=stream)
 
 
@@ -346,6 +351,7 @@ def arrol_select(prob, n_groups, G, K, rho=0.5, out_keep=None, out_survivors=Non
         out = (_marshal or _load_marshal()).select(prob, n_groups, G, K, rho, out_keep, out_survivors)
         if out is not None:
             return out
+        return _py_select.__wrapped__(prob, n_groups, G, K, rho, out_keep, out_survivors)
     return _py_select(prob, n_groups, G, K, rho, out_keep, out_survivors, stream=stream)
 
 
@@ -531,6 +537,7 @@ def arrol_grpo_advantage(reward, group_offsets, ddof=0, eps=0.0, *, stream=None)
         out = (_marshal or _load_marshal()).grpo_advantage(reward, group_offsets, ddof, eps)
         if out is not None:
             return out
+        return _py_grpo_advantage.__wrapped__(reward, group_offsets, ddof, eps)
     return _py_grpo_advantage(reward, group_offsets, ddof, eps, stream=stream)
 
 
@@ -553,6 +560,7 @@ def arrol_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_
         out = (_marshal or _load_marshal()).grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low, eps_high, beta, want_grad, workspace)
         if out is not None:
             return out
+        return _py_grpo_objective.__wrapped__(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low, eps_high, beta, want_grad, workspace)
     return _py_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_low, eps_high, beta, want_grad, workspace, stream=stream)
 
 
@@ -582,10 +590,11 @@ def _py_grpo_objective(logp, logp_ref, cu_seqlens, advantage, seq_weight, eps_lo
 
 def arrol_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally=False, out_winner=None, *, stream=None):
     """prob fp32 [Q*C], answer_id int32 [Q*C] -> winner int32 [Q] (and tally int64 [Q, A])."""
-    if stream is None and not want_tally and out_winner is None:
-        out = (_marshal or _load_marshal()).weighted_vote(prob, answer_id, n_questions, C, n_answers)
+    if stream is None:
+        out = None if want_tally or out_winner is not None else (_marshal or _load_marshal()).weighted_vote(prob, answer_id, n_questions, C, n_answers)
         if out is not None:
             return out
+        return _py_weighted_vote.__wrapped__(prob, answer_id, n_questions, C, n_answers, want_tally, out_winner)
     return _py_weighted_vote(prob, answer_id, n_questions, C, n_answers, want_tally, out_winner, stream=stream)
 
 
@@ -611,6 +620,7 @@ def arrol_histogram(s_norm, label, B, *, stream=None):
         out = (_marshal or _load_marshal()).histogram(s_norm, label, B)
         if out is not None:
             return out
+        return _py_histogram.__wrapped__(s_norm, label, B)
     return _py_histogram(s_norm, label, B, stream=stream)
 
 
@@ -631,6 +641,7 @@ def arrol_calibrate(c_pos, c_neg, policy, *, stream=None):
         out = (_marshal or _load_marshal()).calibrate(c_pos, c_neg, policy)
         if out is not None:
             return out
+        return _py_calibrate.__wrapped__(c_pos, c_neg, policy)
     return _py_calibrate(c_pos, c_neg, policy, stream=stream)
 
 
@@ -654,6 +665,7 @@ def arrol_prune_bernoulli(s_norm, uniforms, p_lut, want_p=False, *, stream=None)
         out = (_marshal or _load_marshal()).prune_bernoulli(s_norm, uniforms, p_lut, want_p)
         if out is not None:
             return out
+        return _py_prune_bernoulli.__wrapped__(s_norm, uniforms, p_lut, want_p)
     return _py_prune_bernoulli(s_norm, uniforms, p_lut, want_p, stream=stream)
 
 
