@@ -53,7 +53,9 @@ extern "C" {
 #define ARROL_MAX_GROUP 64      /* largest G (arrol_select) and C (arrol_weighted_vote) */
 #define ARROL_FIXED_POINT_BITS 30
 
-/* Library version (major*10000 + minor*100 + patch); changes whenever an argument list of this header does. */
+/* Library version (major*10000 + minor*100 + patch); changes whenever an argument list or a struct of this header does.
+ * arrol_version() is what the library was compiled with, the macro what its caller was. */
+#define ARROL_VERSION 200
 int arrol_version(void);
 /* Static, NUL-terminated description of a return code. */
 const char* arrol_error_string(int code);

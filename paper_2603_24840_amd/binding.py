@@ -7,12 +7,14 @@ tensor is not on the GPU the call raises.
 The short calls go through csrc/marshal.cpp (_marshal.so) first, which does the ordinary case in C++: they are bound by the
 host (arrol_score 7.0 us a call from Python alone, 4.4 so).  It returns None for what it does not take - another
 tensor class, CPU tensors, wrong types, strides or sizes, a stream, an active mode of torch's - and the _py_ function of the same
-name does that, errors included (without a stream its undecorated form, since there is nothing to switch to).
+name does that, errors included, as it does where _marshal.so is not built (without a stream its undecorated form, since there is nothing to switch to).
 """
 import ctypes
 import functools
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
@@ -112,20 +114,46 @@ def lib():
     return _lib
 
 
+class _NoMarshal:
+    """In the place of _marshal.so where that cannot be used: leaves every call to Python."""
+    def __getattr__(self, name):
+        return self._leave
+
+    @staticmethod
+    def _leave(*args):
+        return None
+
+
+def built_for():
+    """What _marshal.so has to be compiled for, since it uses the internals of both."""
+    return "torch %s, python %d.%d" % ((torch.__version__,) + sys.version_info[:2])
+
+
+def _import_marshal():
+    if not os.path.exists(MARSHAL_PATH):
+        raise ImportError("%s is not built" % MARSHAL_PATH)
+    spec = importlib.util.spec_from_file_location("paper_2603_24840_amd._marshal", MARSHAL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    made = getattr(module, "built_for", lambda: (0, "an unknown torch"))()
+    if made != (ABI_VERSION, built_for()):
+        raise ImportError("%s is built for version %d and %s, not %d and %s" % ((MARSHAL_PATH,) + made + (ABI_VERSION, built_for())))
+    module.setup(torch.nn.Parameter, Policy, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
+    return module
+
+
 def _load_marshal():
-    """Loads _marshal.so once, behind the library that it calls; raises if it has not been built."""
+    """Loads _marshal.so once, behind the library that it calls.  It is a quicker way to the same kernels, not a part of them:
+    where only the library is built, or it is built for another torch, Python makes the calls."""
     global _marshal
     if _marshal is None:
         lib()
-        if not os.path.exists(MARSHAL_PATH):
-            raise RuntimeError("_marshal.so is not built (%s missing): run `python -m paper_2603_24840_amd.build`" % MARSHAL_PATH)
-        spec = importlib.util.spec_from_file_location("paper_2603_24840_amd._marshal", MARSHAL_PATH)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
-        got = module.setup(torch.nn.Parameter, Policy, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
-        if got != ABI_VERSION:
-            raise RuntimeError("%s calls a library of version %d, not %d: rebuild" % (MARSHAL_PATH, got, ABI_VERSION))
-        _marshal = module
+        try:
+            _marshal = _import_marshal()
+        except ImportError as e:
+            warnings.warn("short calls are marshalled in Python, which takes up to twice as long: %s; "
+                          "`python -m paper_2603_24840_amd.build` builds it" % e, RuntimeWarning, stacklevel=3)
+            _marshal = _NoMarshal()
     return _marshal
 
 

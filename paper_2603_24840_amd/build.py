@@ -3,10 +3,12 @@
     python -m paper_2603_24840_amd.build
 """
 import os
+import shlex
 import shutil
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -41,17 +43,32 @@ def _run(cmd, verbose):
         raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
 
 
-def build(verbose=True):
-    os.makedirs(LIB_DIR, exist_ok=True)
-    include = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    _run([hipcc_path()] + HIPCC_FLAGS + include + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH], verbose)
+def build_marshal(verbose=True):
+    """_marshal.so, with g++ (or $CXX) against torch's headers; what was there is gone if that fails."""
     import torch
+    from .binding import built_for
+    if os.path.exists(MARSHAL_PATH):
+        os.remove(MARSHAL_PATH)
     t = os.path.dirname(torch.__file__)
-    _run([os.environ.get("CXX") or "g++", "-O2", "-fPIC", "-shared", "-std=c++17", "-Wall",
-          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + include +
-         ["-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+    _run(shlex.split(os.environ.get("CXX") or "g++") +
+         ["-O2", "-fPIC", "-shared", "-std=c++17", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+          '-DARROL_BUILT_FOR="%s"' % built_for(), "-I", os.path.join(ROOT, "include"),
+          "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", LIB_DIR, "-larrol",
-          "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"], verbose)
+          "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+          "-Wl,-rpath,$ORIGIN", "-Wl,-z,now"], verbose)      # a symbol that another torch lacks is missed on loading, not in a call
+
+
+def build(verbose=True):
+    """The library, and the marshalling, without which it works as well: where that does not compile (no g++, no headers of
+    Python or torch) a warning says so."""
+    os.makedirs(LIB_DIR, exist_ok=True)
+    _run([hipcc_path()] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC] + [os.path.join(CSRC, s) for s in SOURCES] +
+         ["-o", LIB_PATH], verbose)
+    try:
+        build_marshal(verbose)
+    except (RuntimeError, OSError) as e:
+        warnings.warn("built without _marshal.so: %s" % e, RuntimeWarning)
     return LIB_PATH
 
 

@@ -463,6 +463,10 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return out;
 }
 
+// What this file was compiled against: the header's version, and the torch and Python whose internals it uses (ARROL_BUILT_FOR, a
+// text that the build gives).  binding.py looks at both before it calls anything else.
+PyObject* built_for(PyObject*, PyObject*) { return Py_BuildValue("is", ARROL_VERSION, ARROL_BUILT_FOR); }
+
 PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 5) {
         PyErr_SetString(PyExc_TypeError, "5 arguments expected");
@@ -474,11 +478,12 @@ PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
         Py_XDECREF(*slots[i]);
         *slots[i] = args[i];
     }
-    return PyLong_FromLong(arrol_version());
+    Py_RETURN_NONE;
 }
 
 #define ENTRY(name, n) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&entry<name, n>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
+    {"built_for", &built_for, METH_NOARGS, nullptr},
     {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&setup)), METH_FASTCALL, nullptr},
     ENTRY(score, 7), ENTRY(score_mlp, 7), ENTRY(score_grad, 6), ENTRY(score_mlp_grad, 9), ENTRY(adamw_step, 11), ENTRY(select, 7),
     ENTRY(weighted_vote, 5), ENTRY(histogram, 3), ENTRY(calibrate, 3), ENTRY(prune_bernoulli, 4), ENTRY(grpo_advantage, 4),

@@ -169,3 +169,70 @@ def test_leaving_a_call_to_python_costs_next_to_nothing():
     nothing = best(math.gcd, 4, 6)
     assert best(m.histogram, x, l, 4) < 20 * nothing
     assert best(m.score_grad, x, x, 0.0, x, None, l) < 20 * nothing
+
+
+@pytest.fixture
+def reload_marshal(monkeypatch):
+    """The extension is loaded again in the test, and again after it."""
+    monkeypatch.setattr(binding, "_marshal", None)
+
+
+def python_refuses(name="score"):
+    args, kw = calls("cpu")[name][0]
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        with pytest.raises(TypeError):                       # by the Python marshalling, which looks at the device
+            getattr(A, "arrol_" + name)(*args, **kw)
+    assert isinstance(binding._marshal, binding._NoMarshal)
+
+
+def test_calls_go_by_python_where_only_the_library_is_built(reload_marshal, monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    python_refuses()
+
+
+@pytest.mark.parametrize("what,value", [("ABI_VERSION", 201), ("built_for", lambda: "torch 0.0, python 3.10")])
+def test_an_extension_built_for_something_else_is_not_used(reload_marshal, monkeypatch, what, value):
+    monkeypatch.setattr(binding, what, value)
+    python_refuses()
+
+
+def test_a_file_that_is_no_extension_is_not_used(reload_marshal, monkeypatch, tmp_path):
+    (tmp_path / "_marshal.so").write_bytes(b"not this")
+    monkeypatch.setattr(binding, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    python_refuses()
+
+
+def test_the_extension_says_what_it_is_compiled_against():
+    import os
+    import re
+    header = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "arrol.h")
+    macro = int(re.search(r"#define ARROL_VERSION (\d+)", open(header).read()).group(1))
+    assert binding._load_marshal().built_for() == (macro, binding.built_for())
+    assert macro == A.version() == binding.ABI_VERSION
+
+
+def test_build_without_a_host_compiler_keeps_the_library(monkeypatch, tmp_path):
+    from paper_2603_24840_amd import build
+    ran = []
+
+    def run(cmd, verbose):
+        ran.append(cmd)
+        if "marshal.cpp" in " ".join(cmd):
+            raise OSError("no such program: " + cmd[0])
+    for name, value in (("_run", run), ("LIB_DIR", str(tmp_path)), ("LIB_PATH", str(tmp_path / "libarrol.so")),
+                        ("MARSHAL_PATH", str(tmp_path / "_marshal.so")), ("hipcc_path", lambda: "hipcc")):
+        monkeypatch.setattr(build, name, value)
+    monkeypatch.setenv("CXX", "none -m64")
+    (tmp_path / "_marshal.so").write_bytes(b"an older one")
+    with pytest.warns(RuntimeWarning, match="built without _marshal.so"):
+        assert build.build(verbose=False) == build.LIB_PATH
+    assert ran[0][0] == "hipcc" and ran[1][:2] == ["none", "-m64"] and not (tmp_path / "_marshal.so").exists()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(calls("cpu")))
+def test_calls_without_the_extension(monkeypatch, name):
+    monkeypatch.setattr(binding, "_marshal", binding._NoMarshal())
+    for args, kw in calls(DEV)[name]:
+        assert getattr(A, "arrol_" + name)(*[clone(a) for a in args], **{k: clone(v) for k, v in kw.items()}) is not None
+    torch.cuda.synchronize()
