@@ -15,7 +15,7 @@
  *   arrol_compact_inplace                                      hole-filling compaction of the same pool (Sec. 4.3 (i))
  *   arrol_compact_static                                       arrol_compact without a workspace argument (fixed scratch)
  *   arrol_probe_mfma_rate                                      measurement aid: register-only bf16 MFMA rate of this card
- *   arrol_score_mlp_kernels, arrol_score_mlp_tiles             test aids: which kernels the MLP calls take for a batch
+ *   arrol_score_mlp_kernels, arrol_score_mlp_tiles, arrol_logprob_kernel   test aids: which kernels a call takes
  *   arrol_token_confidence, arrol_trace_confidence             trace confidence (Sec. 3)
  *   arrol_grpo_advantage, arrol_grpo_objective                 group-relative advantage, clipped objective (Sec. 3)
  *
@@ -213,6 +213,14 @@ size_t arrol_logprob_workspace_bytes(int64_t T, int32_t V, int32_t d, int32_t n_
 int arrol_logprob(const void* hidden, const void* lm_head, const int32_t* targets,
                   int64_t T, int32_t V, int32_t d, float* logprob_out, float* lse_out,
                   int32_t n_splits, void* workspace, size_t workspace_bytes, void* stream);
+/*
+ * Test and measurement aid, a host computation: what arrol_logprob takes for a call, so that a test can say what it reaches.
+ * *kernel       0 the general one (d no multiple of 64), 1 the ring kernel, 2 the block kernel
+ * *tile_rows, *tile_tokens   of a workgroup's tile: 256 x 256 of kernels 0 and 1, 256 x 64, 128 or 192 or 160 x 320 of 2
+ * *splits       ranges of tiles that the vocabulary is cut into
+ */
+int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* kernel, int32_t* tile_rows,
+                         int32_t* tile_tokens, int32_t* splits);
 
 /*
  * Stage 5 -- rank-weighted vote (Sec. 4.4: candidates are sorted by head score and their

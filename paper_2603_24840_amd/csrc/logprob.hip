@@ -1118,3 +1118,14 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
                      static_cast<const float*>(workspace), targets, T, V, p.n_sp, logprob_out, lse_out);
     return arrol_launch_status();
 }
+
+extern "C" int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* kernel, int32_t* tile_rows,
+                                    int32_t* tile_tokens, int32_t* splits) {
+    if (T < 1 || V < 1 || d < 8 || (d & 7) || n_splits < 0 || !kernel || !tile_rows || !tile_tokens || !splits) return ARROL_EINVAL;
+    const Plan p = make_plan(T, V, d, n_splits);
+    *kernel = d % 64 ? 0 : p.form == kFormRing ? 1 : 2;
+    *tile_rows = kFormSize[p.form].bm;
+    *tile_tokens = kFormSize[p.form].bn;
+    *splits = p.n_sp;
+    return ARROL_OK;
+}

@@ -44,3 +44,10 @@ def mlp_kernels(A, n, d, m, delta_terms, gathered=False, row_stride=None):
 def mlp_tiles(A, n, d, m, delta_terms, gathered=False, row_stride=None):
     """(wavefront groups of the forward blocks, units and wavefront groups of a weight gradient block), as above."""
     return _mlp_query("arrol_score_mlp_tiles", A, n, d, m, delta_terms, gathered, row_stride)
+
+
+def logprob_kernel(A, T, V, d, n_splits=0):
+    """(kernel, tile rows, tile tokens, splits) of a log-prob call, as above."""
+    out = [ctypes.c_int32() for _ in range(4)]
+    assert A.lib().arrol_logprob_kernel(T, V, d, n_splits, *[ctypes.byref(x) for x in out]) == 0
+    return tuple(x.value for x in out)

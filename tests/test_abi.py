@@ -132,6 +132,10 @@ def test_bad_arguments_are_rejected_on_the_host(pkg):
         n, d, m, stride, terms, out = bad
         assert L.arrol_score_mlp_tiles(n, d, m, stride, 0, terms, out, out, out) == -1, bad
     assert L.arrol_score_mlp_tiles(64, 128, 8, 128, 0, 1, one, one, one) == 0
+    what = lambda T, V, d, splits, out: L.arrol_logprob_kernel(T, V, d, splits, out, out, out, out)
+    assert what(1, 1, 8, 0, one) == 0
+    for bad in ((0, 1, 8, 0, one), (1, 0, 8, 0, one), (1, 1, 12, 0, one), (1, 1, 8, -1, one), (1, 1, 8, 0, None)):
+        assert what(*bad) == -1, bad
     # head training: bad d, missing gradient output, workspace; optimizer: bad step / betas
     assert L.arrol_score_grad(fake, 16, None, fake, 0.0, fake, 4, 12, None, fake, None, fake, 1 << 20, None) == -1
     assert L.arrol_score_grad(fake, 16384, None, fake, 0.0, fake, 4, 16384, None, fake, None, fake, 1 << 20, None) == -1

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, mlp_kernels, mlp_tiles, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
+from helpers import bits, logprob_kernel, mlp_kernels, mlp_tiles, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
 
 pytestmark = pytest.mark.gpu
 
@@ -264,8 +264,8 @@ def test_logprob_ragged_shapes(A, T, V, d):
     check_logprob(A, hidden, lm_head, targets)
 
 
-# the dispatch by token count: one block of 64, 128 or 320 tokens against 256-token blocks in bands (2, 7 and 10 blocks),
-# d of 1, 3 and 9 K64 steps, vocabularies that end inside a wavefront's 32 rows, and split counts from one to one per tile (the 16-lane merge begins at 9)
+# the dispatch by token count: blocks of 64 tokens (these vocabularies leave most of the chip idle, so the smallest tiles win)
+# against 256-token blocks in bands (7 and 10 blocks), d of 1, 3, 4, 9 and 16 K64 steps, vocabularies that end inside a wavefront's 32 rows, and split counts from one to one per tile (the 16-lane merge begins at 9)
 @pytest.mark.parametrize("T", [2, 63, 64, 65, 128, 129, 257, 1600, 2400])
 @pytest.mark.parametrize("V,d,splits", [(257, 64, 0), (2600, 576, 0), (4097, 192, 9), (300, 1024, 1), (5000, 256, 7)])
 def test_logprob_dispatch_by_token_count(A, T, V, d, splits):
@@ -278,9 +278,9 @@ def test_logprob_dispatch_by_token_count(A, T, V, d, splits):
     check_logprob(A, hidden, lm_head, targets, n_splits=splits)
 
 
-# up to 640 tokens the cheapest of five tiles: 256 rows x 64, 128, 192, 160 rows x 320, 256 x 256.  Both sides of every edge,
-# vocabularies of one tile, of a few rows in the last one and (splits = 1) of all tiles in one workgroup, K extents of 1, 2, 3
-# and more steps (the K walk starts at split % steps and wraps); a second call must give the same bits
+# up to 640 tokens, vocabularies that leave most of the chip idle: the first three are blocks of 64 tokens at every T up to 640 (one
+# vocabulary tile, all tiles in one workgroup, several; K extents of 1, 2 and 3 steps), the last 64, 128, 192 and 320 as T
+# grows, one vocabulary tile a workgroup; beyond 640 the ring kernel.  A second call must give the same bits
 @pytest.mark.parametrize("T", [1, 64, 65, 128, 129, 192, 193, 255, 256, 257, 320, 321, 384, 385, 576, 577, 640, 641])
 @pytest.mark.parametrize("V,d,splits", [(161, 64, 0), (1285, 128, 1), (2500, 192, 3), (20011, 512, 0)])
 def test_logprob_block_forms(A, T, V, d, splits):
@@ -293,6 +293,42 @@ def test_logprob_block_forms(A, T, V, d, splits):
     check_logprob(A, hidden, lm_head, targets, n_splits=splits)
     one, two = (A.arrol_logprob(hidden, lm_head, targets, n_splits=splits) for _ in range(2))
     assert torch.equal(one, two)
+
+
+# each tile of the block kernel and the ring kernel over three to five vocabulary tiles a workgroup, the last one short (163 rows
+# of 256, 3 of 160), one token block and two, whole and ragged; 1, 3, 5 and 7 K64 steps, at which the K walk of the splits starts
+# in turn: the step to the next tile in the middle of the walk, the fragments read again behind a tile, the running maximum
+@pytest.mark.parametrize("T,V,d,splits,tile", [(1, 100003, 192, 120, (2, 256, 64)), (61, 100003, 448, 130, (2, 256, 64)),
+                                               (100, 100003, 192, 150, (2, 256, 128)), (128, 100003, 320, 150, (2, 256, 128)),
+                                               (128, 200001, 64, 0, (2, 256, 128)), (150, 100003, 192, 150, (2, 256, 192)),
+                                               (192, 100003, 320, 150, (2, 256, 192)), (384, 100003, 192, 120, (2, 256, 192)),
+                                               (300, 100003, 192, 130, (2, 160, 320)), (320, 100003, 448, 130, (2, 160, 320)),
+                                               (640, 100003, 192, 128, (2, 160, 320)), (512, 100003, 320, 120, (1, 256, 256))])
+def test_logprob_tiles_over_several_vocabulary_tiles(A, T, V, d, splits, tile):
+    say("logprob several tiles T=%d V=%d d=%d splits=%d" % (T, V, d, splits))
+    got = logprob_kernel(A, T, V, d, splits)
+    assert got[:3] == tile and got[3] > d // 64 and -(-V // tile[1]) > 2 * got[3]
+    g = torch.Generator(device=DEV); g.manual_seed(T * 5 + V + d)
+    hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    lm_head = (torch.randn(V, d, generator=g, device=DEV) * (2.0 * d ** -0.5)).to(torch.bfloat16)
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    targets[0] = 0; targets[-1] = V - 1
+    lm_head[torch.arange(0, V, 97, device=DEV)] *= 3         # the running maximum moves from tile to tile
+    check_logprob(A, hidden, lm_head, targets, n_splits=splits)
+    one, two = (A.arrol_logprob(hidden, lm_head, targets, n_splits=splits) for _ in range(2))
+    assert torch.equal(one, two)
+
+
+@pytest.mark.parametrize("splits", [1, 3, 16])
+def test_logprob_ring_kernel_independent_of_vocab_splits(A, splits):
+    say("logprob ring forced splits=%d" % splits)
+    T, V, d = 700, 4500, 192
+    assert logprob_kernel(A, T, V, d, splits) == (1, 256, 256, splits)
+    g = torch.Generator(device=DEV); g.manual_seed(98)
+    hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    lm_head = (torch.randn(V, d, generator=g, device=DEV) * 0.2).to(torch.bfloat16)
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    check_logprob(A, hidden, lm_head, targets, n_splits=splits)
 
 
 @pytest.mark.parametrize("splits", [1, 2, 3, 5, 16])
