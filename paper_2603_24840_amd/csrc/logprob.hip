@@ -994,7 +994,13 @@ constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Blo
                                         {Block192::BM, Block192::BN, 1.42}, {Block320::BM, Block320::BN, 1.42}};
 constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;
 
-struct Plan { int form, n_tb, n_vt, n_sp, band, n_long; };
+// The ring and block kernels give a lane its row of a tile as a 32-bit byte offset; of longer rows the general kernel's are 64-bit.
+constexpr bool offsets_fit(int form, int d) {
+    const FormSize f = kFormSize[form];
+    return 2ll * d * ((f.bm > f.bn ? f.bm : f.bn) - 1) + 128 <= UINT32_MAX;
+}
+
+struct Plan { int form, n_tb, n_vt, n_sp, band, n_long; bool general; };
 
 // Vocabulary splits of n_tb token blocks x n_vt tiles, and what they cost, in tiles one after the other.
 double pick_splits(int n_tb, int n_vt, int& n_sp) {
@@ -1031,7 +1037,7 @@ Plan make_plan(int64_t T, int V, int d, int n_splits) {
     // ring kernel up to 256, 160 x 320 up to 320, 2 x 192 up to 384, the ring to 512 (262 us; 3 x 192: 308), 3 x 192 to 576.
     double best = -1.0;
     for (int f = 0; f < kForms; ++f) {
-        if (f != kFormRing && (d % 64 || T > kBlockTokens)) continue;
+        if (f != kFormRing && (d % 64 || T > kBlockTokens || !offsets_fit(f, d))) continue;
         const int n_tb = static_cast<int>((T + kFormSize[f].bn - 1) / kFormSize[f].bn), n_vt = (V + kFormSize[f].bm - 1) / kFormSize[f].bm;
         const int cap = (V + MainTile::BM - 1) / MainTile::BM;        // of splits given: <= n_vt for every form
         int sp = n_splits < cap ? n_splits : cap;
@@ -1043,6 +1049,7 @@ Plan make_plan(int64_t T, int V, int d, int n_splits) {
         const double cost = tiles * kFormSize[f].step;
         if (best < 0.0 || cost < best) { best = cost; p.form = f; p.n_tb = n_tb; p.n_vt = n_vt; p.n_sp = sp; }
     }
+    p.general = d % 64 || !offsets_fit(p.form, d);
     const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
     p.band = (p.n_tb + bands - 1) / bands;
     p.n_long = p.n_tb - (p.band - 1) * bands;
@@ -1102,7 +1109,7 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
     a.n_tb = p.n_tb; a.n_sp = p.n_sp; a.n_vt = p.n_vt; a.band = p.band; a.n_long = p.n_long;
     const dim3 g(static_cast<unsigned>(grid));
     int rc;
-    if (d % 64) rc = launch_logprob<logprob_kernel<MainTile>, MainTile>(g, st, a);
+    if (p.general) rc = launch_logprob<logprob_kernel<MainTile>, MainTile>(g, st, a);
     else if (p.form == kForm64) rc = launch_logprob<logprob_block_kernel<Block64>, Block64>(g, st, a);
     else if (p.form == kForm128) rc = launch_logprob<logprob_block_kernel<Block128>, Block128>(g, st, a);
     else if (p.form == kForm192) rc = launch_logprob<logprob_block_kernel<Block192>, Block192>(g, st, a);
@@ -1123,7 +1130,7 @@ extern "C" int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_s
                                     int32_t* tile_tokens, int32_t* splits) {
     if (T < 1 || V < 1 || d < 8 || (d & 7) || n_splits < 0 || !kernel || !tile_rows || !tile_tokens || !splits) return ARROL_EINVAL;
     const Plan p = make_plan(T, V, d, n_splits);
-    *kernel = d % 64 ? 0 : p.form == kFormRing ? 1 : 2;
+    *kernel = p.general ? 0 : p.form == kFormRing ? 1 : 2;
     *tile_rows = kFormSize[p.form].bm;
     *tile_tokens = kFormSize[p.form].bn;
     *splits = p.n_sp;

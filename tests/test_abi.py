@@ -136,6 +136,14 @@ def test_bad_arguments_are_rejected_on_the_host(pkg):
     assert what(1, 1, 8, 0, one) == 0
     for bad in ((0, 1, 8, 0, one), (1, 0, 8, 0, one), (1, 1, 12, 0, one), (1, 1, 8, -1, one), (1, 1, 8, 0, None)):
         assert what(*bad) == -1, bad
+    # rows so long that a tile's last one is beyond a 32-bit byte offset go to the general kernel
+    from helpers import logprob_kernel
+    for T, tokens, rows in ((64, 64, 256), (128, 64, 256), (600, 64, 256), (700, 256, 256)):
+        fits = (2 ** 32 - 129) // (2 * (rows - 1)) // 64 * 64
+        assert logprob_kernel(pkg, T, 257, fits)[0] in (1, 2) and logprob_kernel(pkg, T, 257, fits)[2] == tokens
+        assert logprob_kernel(pkg, T, 257, fits + 64)[0] == 0
+    fits = (2 ** 32 - 129) // (2 * 319) // 64 * 64
+    assert logprob_kernel(pkg, 300, 151936, fits)[:3] == (2, 160, 320) and logprob_kernel(pkg, 300, 151936, fits + 64)[1:3] != (160, 320)
     # head training: bad d, missing gradient output, workspace; optimizer: bad step / betas
     assert L.arrol_score_grad(fake, 16, None, fake, 0.0, fake, 4, 12, None, fake, None, fake, 1 << 20, None) == -1
     assert L.arrol_score_grad(fake, 16384, None, fake, 0.0, fake, 4, 16384, None, fake, None, fake, 1 << 20, None) == -1

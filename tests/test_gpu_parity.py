@@ -342,6 +342,24 @@ def test_logprob_independent_of_vocab_splits(A, splits):
     check_logprob(A, hidden, lm_head, targets, n_splits=splits)
 
 
+def test_logprob_rows_beyond_32_bit_offsets(A):
+    """Rows of 16.8 MB: the last row of a 256-row tile is 4.29 GB from the first, past a 32-bit byte offset."""
+    T, V, d = 2, 256, 8421568
+    say("logprob T=%d V=%d d=%d" % (T, V, d))
+    assert logprob_kernel(A, T, V, d)[0] == 0 and 2 * d * (V - 1) >= 2 ** 32
+    g = torch.Generator(device=DEV); g.manual_seed(17)
+    hidden = torch.empty(T, d, dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    lm_head = torch.empty(V, d, dtype=torch.bfloat16, device=DEV).normal_(0, 2.0 * d ** -0.5, generator=g)
+    targets = torch.tensor([V - 1, 0], dtype=torch.int32, device=DEV)
+    lp = A.arrol_logprob(hidden, lm_head, targets)
+    z = torch.zeros(T, V, dtype=torch.float64, device=DEV)
+    for c in range(0, d, 1 << 18):
+        z += hidden[:, c:c + (1 << 18)].double() @ lm_head[:, c:c + (1 << 18)].double().t().contiguous()
+    want = torch.log_softmax(z, 1)[torch.arange(T, device=DEV), targets.long()]
+    # some 260,000 fp32 sums in a chain, each half an ulp of about 4: 5e-7 x sqrt(260,000) / 2 = 1e-4; a wrong row is off by 1
+    assert float((lp.double() - want).abs().max()) < 2e-3
+
+
 def test_logprob_extreme_logits_and_bad_target(A):
     say("logprob extreme logits")
     T, V, d = 40, 600, 64
