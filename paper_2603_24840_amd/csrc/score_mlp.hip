@@ -1104,14 +1104,16 @@ __global__ __launch_bounds__(kDeltaThreads) void mlp_delta_kernel(const float* _
     }
 }
 
-// The two in one, for up to kFusedRows rows and kFusedSize activations: workgroup (b, g) forms the residuals of rows 512 b .. itself, into the LDS, and then,
-// one unit a wavefront, delta^T of those rows and their parts of dL/dw2 and dL/db1; those with g = 0 also of the loss and dL/db2.  The parts are added in block order by the dL/dW1 kernel that follows, or by mlp_sums_kernel.
-// What bounds it at these sizes is a chain of dependent loads and a launch, beyond the activations' bytes; a row's residual
-// is formed m / 8 times, which costs less than the launch that formed it once: 4,096 x 512
-// 6.2 us against 4.4 + 4.9, 1,024 x 512 4.8 against 3.9 + 4.4; with 1,024 rows a workgroup 7.2, with 256 7.1.  Of larger
-// activations the pair's larger workgroups make more of the bytes (whole call: 4,096 x 768 76 us against 79, 16,384 x 512 113
-// against 115).
-constexpr int kFusedRows = 8192, kFusedSize = 2 << 20;
+// The two in one: workgroup (b, g) forms the residuals of rows 512 b .. itself, into the LDS, and then, one unit a wavefront,
+// delta^T of those rows and their parts of dL/dw2 and dL/db1; those with g = 0 also of the loss and dL/db2.  The parts are added
+// in block order by the dL/dW1 kernel that follows, or by mlp_sums_kernel.
+// What bounds it is a chain of dependent loads and a launch, beyond the activations' bytes; a row's residual is formed m / 8
+// times, which costs less than the launch that formed it once: 4,096 x 512 6.2 us against 4.4 + 4.9, 1,024 x 512 4.8 against
+// 3.9 + 4.4; with 1,024 rows a workgroup 7.2, with 256 7.1.
+// The line, by whole calls, one launch over the pair (d of 512 to 3072): where the dL/dW1 kernel adds the parts 0.85 - 0.98 up to 3
+// million activations of up to 20,000 rows (4,096 x 768 53.1 us against 55.5), 0.98 - 1.02 of 4 million, 1.01 - 1.05 of 65,536 rows.  Where
+// another launch adds them 0.92 - 1.00 up to 2,048 rows, 1.00 - 1.01 of 4,096 and 1.01 - 1.04 beyond.
+constexpr int kFusedRows = 20000, kFusedRowsAlone = 2048, kFusedSize = 3 << 20;
 constexpr int kPartRows = 512;
 __global__ __launch_bounds__(kPartRows) void mlp_score_delta_kernel(const float* __restrict__ partial, int n_ub, float b2,
                                                                     const float* __restrict__ labels,
@@ -1510,13 +1512,14 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
     if (arrol_launch_failed()) return arrol_launch_status();
     const bool in_place = wgrad_in_place(d, row_stride_elems, row_index != nullptr);
     const int n_pblocks = (n_rows + kPartRows - 1) / kPartRows;
-    const bool fused = kept && n_rows <= kFusedRows && static_cast<int64_t>(n_rows) * m <= kFusedSize;
+    const bool sums_ride = in_place && p.w_rows != 256;
+    const bool fused = kept && n_rows <= (sums_ride ? kFusedRows : kFusedRowsAlone) && static_cast<int64_t>(n_rows) * m <= kFusedSize;
     const MlpSums sums = {fused ? unit : nullptr, bsum, n_pblocks, n_rows, m, grad_w2, grad_b1, loss_out, grad_b2};
     const int n_groups = (m + kPartRows / ARROL_WAVE - 1) / (kPartRows / ARROL_WAVE);
     if (fused) {
         arrol_launch(mlp_score_delta_kernel, dim3(static_cast<unsigned>(n_pblocks) * n_groups), dim3(kPartRows), 0, st, partial, n_ub, b2, labels, act,
                      static_cast<int64_t>(p.n_pad), w2, n_rows, p.n_pad, m, n_groups, dt, dt_lo, unit, bsum);
-        if (!in_place || p.w_rows == 256) arrol_launch(mlp_sums_kernel, dim3((m + 255) / 256, 2), dim3(256), 0, st, sums);
+        if (!sums_ride) arrol_launch(mlp_sums_kernel, dim3((m + 255) / 256, 2), dim3(256), 0, st, sums);
     } else if (kept) {
         // scores from the partials, residuals and loss terms in one launch; delta^T, the per-unit sums, the loss
         // and dL/db2 in the next

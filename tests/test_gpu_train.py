@@ -245,6 +245,19 @@ def test_score_mlp_grad_one_launch_delta(A, n, d, m, terms):
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.25, labels, delta_terms=terms)
 
 
+# both sides of the lines of the one-launch delta: 3 million activations, 20,000 rows, and 2,048 rows where a launch of its own adds
+# the parts (gathered rows, dL/dW1 in the ring form)
+@pytest.mark.parametrize("n,d,m,terms,gather,gradient", [(2859, 64, 1100, 1, False, 1), (2860, 64, 1100, 2, False, 1), (20000, 64, 24, 2, False, 1),
+                                                         (20001, 64, 24, 1, False, 1), (2048, 64, 40, 1, True, 0), (2049, 64, 40, 2, True, 0),
+                                                         (1900, 2112, 961, 2, False, 2), (2100, 2112, 961, 2, False, 2)])
+def test_score_mlp_grad_lines_of_the_one_launch_delta(A, n, d, m, terms, gather, gradient):
+    print("[case] score_mlp_grad delta lines n=%d d=%d m=%d terms=%d gather=%d" % (n, d, m, terms, gather), flush=True)
+    assert mlp_kernels(A, n, d, m, terms, gathered=gather)[1] == gradient
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=17 * n + d + m)
+    idx = torch.randperm(n, device=DEV) if gather else None
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.25, labels, delta_terms=terms, row_index=idx)
+
+
 # dL/dW1 in each of its blocks - 64 or 128 units, one or two wavefront groups - with one and two terms, one and several K splits,
 # odd and even numbers of K64 steps, units, columns and rollouts that end inside a block; behind forward blocks with groups
 @pytest.mark.parametrize("n,d,m,terms,tiles,splits", [(2001, 2112, 100, 1, (4, 64, 2), 3), (513, 2048, 513, 1, (2, 128, 2), 1), (129, 2048, 513, 1, (4, 128, 1), 1),
