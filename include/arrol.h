@@ -348,7 +348,8 @@ int arrol_grpo_advantage_all(const float* reward, const int64_t* group_offsets, 
  * int64 [1] = tokens where the clipped branch is strictly smaller.  fp64 arithmetic, fixed summation order.
  * 0 <= eps_low <= 1, eps_high >= 0, beta >= 0, else ARROL_EINVAL.  n_seq == 0 writes J = 0.
  * workspace: at least arrol_grpo_objective_workspace_bytes(n_seq) bytes, 16-byte aligned.  With more (up to 8 times as
- * many are used) long rollouts are cut into parts that several workgroups take, which is faster.
+ * many are used) long rollouts are cut into parts that several workgroups take, which is faster; J is then the sum of
+ * the same terms in another fixed order.
  */
 size_t arrol_grpo_objective_workspace_bytes(int32_t n_seq);
 int arrol_grpo_objective(const float* logp, const float* logp_ref, const int64_t* cu_seqlens, int64_t T,
@@ -384,7 +385,7 @@ int arrol_score_grad(const void* hidden, int64_t row_stride_elems, const int64_t
  * delta is rounded to bf16 before the contraction over the rollouts (bf16 products, fp32 accumulation);
  * everything else is fp32; sums in a fixed order (bit-reproducible run to run).
  * delta_terms: 1 = delta as one bf16 value (relative rounding 2^-9 per term of dL/dW1); 2 = delta as the sum
- * of two bf16 values, hi = bf16(delta) and lo = bf16(delta - hi), contracted one after the other (relative
+ * of two bf16 values, hi = bf16(delta) and lo = bf16(delta - hi), both contracted (relative
  * rounding 2^-17: dL/dW1 to fp32 accuracy, at twice the cost of that contraction).  Other values -> ARROL_EINVAL.
  * n_rows == 0 writes zeros.
  * workspace: arrol_score_mlp_grad_workspace_bytes(n_rows, d, m, delta_terms) bytes, 256-byte aligned,

@@ -253,7 +253,10 @@ extern "C" int arrol_grpo_objective(const float* logp, const float* logp_ref, co
     const int64_t n_parts = n_seq * n_seg;
     double* partial = static_cast<double*>(workspace);
     int64_t* clipped = reinterpret_cast<int64_t*>(partial + n_parts);
-#define ARROL_OBJECTIVE(N) arrol_launch(grpo_objective_kernel<N>, dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta), grad_logp, partial, clipped)
+#define ARROL_OBJECTIVE(N)                                                                                                     \
+    arrol_launch(grpo_objective_kernel<N>, dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, \
+                 advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta),     \
+                 grad_logp, partial, clipped)
     // wider workgroups shorten a long rollout's chain while the chip has room for them: 512 rollouts of 512 to 4,096 tokens
     // 10.5 us with 512 threads, 11.3 with 256; 512 of 64 to 512 tokens 5.7 and 5.4; 4,096 of 256 to 2,048 30.0 and 26.1
     if (n_seg == 1 && T / n_seq > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512);

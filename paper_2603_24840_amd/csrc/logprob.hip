@@ -264,13 +264,14 @@ __device__ __forceinline__ void write_partials16(LaneState<TJ>& st, float* red, 
 }
 
 // workgroup id -> (token block, vocab split).  Ids congruent mod 8 land on the same XCD, and a round of 256 workgroups
-// (one per compute unit: the tile kernels take most of a unit's LDS) gives each XCD 32 consecutive positions of the work order (the last
-// round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
+// (one per compute unit: the tile kernels take most of a unit's LDS) gives each XCD 32 consecutive positions of the work order
+// (the last round spreads what is left evenly).  The order runs through bands of 5 to 8 token blocks, in
 // each band with the split fastest where there are up to 8 (1.5-2 % faster than the other way round at 8,000 to 33,000
 // tokens), the token block fastest otherwise (0.6 % at 4,096 tokens x 16 splits), so the 32 resident workgroups of an
 // XCD are a patch of about 6 token blocks x 5 splits that shares its H and W tiles through the XCD's L2, for any
-// number of token blocks.  Dealing token blocks to the XCDs instead leaves 6 of the 8 idle at 311 tokens (1.00 ms with
-// 151,936 x 2048; now 0.26) and makes every XCD read all of W up to some 10,000 tokens (1,000 tokens: 1.00 ms; now 0.50).
+// number of token blocks.  Dealing token blocks to the XCDs instead leaves 6 of the 8 idle at 311 tokens (with
+// 151,936 x 2048 in the ring kernel 1.00 ms, 0.26 this way) and makes every XCD read all of W up to some 10,000 tokens (1,000
+// tokens: 1.00 ms and 0.50).
 __device__ __forceinline__ bool map_workgroup(const LogprobArgs& a, int& tb, int& sp, int& vt_lo, int& vt_hi) {
     constexpr int kRound = kXcds * kCuPerXcd;
     const int round0 = static_cast<int>(blockIdx.x) / kRound * kRound, id = static_cast<int>(blockIdx.x) - round0;
@@ -733,8 +734,9 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
 // Every split starts at another place of the K extent and wraps around: all of them at the same offset of rows a power of
 // two apart meet in the same memory channels (128 tokens: 151 us against 119).
 //
-// Measured at 151,936 x 2048 (before: for up to 128 tokens W straight to registers, else the ring kernel): 64 tokens 134 ->
-// 111 us (5.6 TB/s of W), 128: 153 -> 119, 192: 177 -> 136, 311: 262 -> 193, 384: 264 -> 222.  At 311 tokens with W always
+// Measured at 151,936 x 2048, all on one card and as HIP graphs (before: for up to 128 tokens W straight to registers, else the
+// ring kernel; other cards and a profiler's run differ by up to 5 %): 64 tokens 134 -> 111 us (5.6 TB/s of W), 128: 153 -> 119,
+// 192: 177 -> 136, 311: 262 -> 193, 384: 264 -> 222.  At 311 tokens with W always
 // from the L2 it would be 160, without any loads 130.  Tried and slower: W and H fetched by different wavefronts, each with
 // its own order (311 tokens: 242); W straight to registers, several steps ahead (128 tokens: 148; half lines at a time).
 //
@@ -990,6 +992,8 @@ enum LogprobForm { kFormRing, kForm64, kForm128, kForm192, kForm320, kForms };
 struct FormSize { int bm, bn; double step; };
 // Vocabulary rows and tokens of a workgroup's tile; microseconds per K64 step of a tile when the chip is full, measured over
 // 50,000 to 151,936 x 1024 to 4096 with up to 640 tokens (from there on the ring kernel's step falls to 1.45).
+// They choose within 2 % of the best form at most of 15 vocabularies and widths x 14 token counts; the worst: 65,536 x 4096 with 250
+// tokens (ring 170 us, 256 x 128 tiles 140), 65,536 x 2048 with 577 to 640 (256 x 192 and 160 x 320 170 us, the ring 159).
 constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Block64::BM, Block64::BN, 1.15}, {Block128::BM, Block128::BN, 1.25},
                                         {Block192::BM, Block192::BN, 1.42}, {Block320::BM, Block320::BN, 1.42}};
 constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;

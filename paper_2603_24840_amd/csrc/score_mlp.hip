@@ -10,8 +10,8 @@
 //
 // arrol_score_mlp_grad: cross-entropy training gradient of the same head (Sec. 4.2, Sec. 4.3 (iii)).  The same
 // tile loop runs in two more modes:
-//   delta   (d not a multiple of 64; else the blocked forward passes keep the activations and mlp_score_delta_kernel reads them)
-//           recomputes the pre-activations and, instead of the w2 dot, writes delta^T[u][i] =
+//   delta   (d not a multiple of 64; else the blocked forward passes keep the activations, which mlp_score_delta_kernel or, of
+//           larger batches, mlp_delta_kernel reads) recomputes the pre-activations and, instead of the w2 dot, writes delta^T[u][i] =
 //           r_i * w2[u] * [pre > 0] (bf16, unit-major) and the per-workgroup sums for dL/dw2 and dL/db1;
 //   wgrad   the contraction over rollouts dL/dW1 = delta^T . H as the same "A rows x B rows over a shared
 //           contiguous K" product, with A = delta^T [m, N] and B = H^T [d, N] (transposed once into the
@@ -539,13 +539,14 @@ __global__ __launch_bounds__(256) void score_mlp_finish_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Large batches (d a multiple of 64, rows addressed without row_index; pick_forward): the contractions on the 8-wavefront direct-to-LDS ring pipeline of ring_nt.h (v_mfma_f32_16x16x32_bf16), one
-// 256 x 256 accumulator tile per workgroup: grid = (blocks of 256 B rows, tiles of 256 A rows, K splits).
+// Large batches (d a multiple of 64, rows addressed without row_index; pick_forward): the contractions on the 8-wavefront
+// direct-to-LDS ring pipeline of ring_nt.h (v_mfma_f32_16x16x32_bf16), one 256 x 256 accumulator tile per workgroup:
+// grid = (blocks of 256 B rows, tiles of 256 A rows, K splits).
 //   forward  A = W1 [m, d], B = hidden [N, d]: bias + ReLU + w2 dot per rollout (lane-local over the
 //            units), partial scores [unit tile][rollout] to the workspace, summed by the finish kernel;
 //            for the gradient call the same pass also keeps the activations a = relu(pre) in fp32, unit-major
 //            (the accumulator's own layout: 16 lanes = 16 consecutive rollouts), so that nothing is recomputed:
-//            delta^T = r w2 [a > 0] and the per-unit sums are then one streaming pass (mlp_score_delta_kernel);
+//            delta^T = r w2 [a > 0] and the per-unit sums are then one streaming pass (mlp_delta_kernel);
 //   wgrad    A = delta^T [m, n_pad], B = the hidden states themselves, [N, d] = K-major (ring_nt's TN form, no
 //            transposed copy), over K = rollouts (split): fp32 tile stores.
 using RingCfg = ring_nt::RingTile<256, 256, 2, 4>;
@@ -649,8 +650,8 @@ int launch_mlp_ring(const MlpRingArgs& a, dim3 grid, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// What mlp_score_delta_kernel left to be added up (unit_partial NULL: nothing): [n_blocks][2][m] parts of dL/dw2 and dL/db1, [2][n_blocks] of the loss and
-// dL/db2.  Added in block order, whoever does it.
+// What mlp_score_delta_kernel left to be added up (unit_partial NULL: nothing): [n_blocks][2][m] parts of dL/dw2 and dL/db1,
+// [2][n_blocks] of the loss and dL/db2.  Added in block order, whoever does it.
 struct MlpSums {
     const float* unit_partial; const float* block_sums;
     int n_blocks, n_rows, m;
@@ -685,9 +686,10 @@ __global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where m
 // tile, so two wavefronts share a SIMD and a barrier stands for KG steps, and the groups' sums are added in the LDS at the
 // end.  Where tiles are too few, K (rollouts) is also split over gridDim.z into slabs.  Of two-term deltas both terms of a K64
 // step come next to each other, into the same sums, while its hidden states are near: one term's steps behind the other's read
-// them from memory twice (131,072 x 1024 x 128, whole call: 298 us, so 251).  The hidden states are read in place: a step holds 64 rollouts x 128 bytes, and
-// the B fragments come out through the transposing LDS read (lane layout as in ring_nt.h).  16-byte chunk c of rollout row r
-// sits at position c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different 8-byte bank pairs.
+// them from memory twice (131,072 x 1024 x 128, whole call: 298 us, so 251).  The hidden states are read in place: a step holds
+// 64 rollouts x 128 bytes, and the B fragments come out through the transposing LDS read (lane layout as in ring_nt.h).  16-byte
+// chunk c of rollout row r sits at position c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different
+// 8-byte bank pairs.
 // Bound by the loads into LDS (16 KB a step at 73 bytes per nanosecond and compute unit with 64 x 64).  4,096 x 2048 x 512,
 // 256 tiles of 64 x 64: 17.4 us; before, one group of four wavefronts, 128 x 64, 2 splits and the sum of their slabs: 20.0.
 // 1,024: 9.2 -> 7.3; 4,096 x 4096 x 512 with 128 x 64: 26.6 -> 25.6.
