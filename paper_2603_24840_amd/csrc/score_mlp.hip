@@ -657,28 +657,32 @@ struct MlpSums {
     int n_blocks, n_rows, m;
     float* grad_w2; float* grad_b1; float* loss; float* grad_b2;      // the last two may be NULL
 };
+// In 64 bits: up to 40 parts one after the other cost a bit in 32 (16,384 x 1024 x 64: dL/dw2 9.5e-8 off, 2.7e-8 so).
 __device__ __forceinline__ void finish_unit(const MlpSums& f, int u, int which) {
     const float* part = f.unit_partial + static_cast<int64_t>(which) * f.m + u;
-    float sum = 0.f;
+    double sum = 0.0;
     for (int b0 = 0; b0 < f.n_blocks; b0 += 8) {
         float x[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = b0 + q < f.n_blocks ? part[static_cast<int64_t>(b0 + q) * 2 * f.m] : 0.f;
+        for (int q = 0; q < 8; ++q)     // past the end the first one again, so that no load waits on a branch
+            x[q] = part[static_cast<int64_t>(b0 + q < f.n_blocks ? b0 + q : b0) * 2 * f.m];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sum += x[q];
+        for (int q = 0; q < 8; ++q) sum += b0 + q < f.n_blocks ? x[q] : 0.f;
     }
-    (which ? f.grad_b1 : f.grad_w2)[u] = sum;
+    (which ? f.grad_b1 : f.grad_w2)[u] = static_cast<float>(sum);
 }
-__device__ __forceinline__ void finish_loss(const MlpSums& f) {
-    float l = 0.f, r = 0.f;
-    for (int b = 0; b < f.n_blocks; ++b) { l += f.block_sums[b]; r += f.block_sums[f.n_blocks + b]; }
-    if (f.loss) *f.loss = l / static_cast<float>(f.n_rows);
-    if (f.grad_b2) *f.grad_b2 = r;
+__device__ __forceinline__ void finish_loss(const MlpSums& f, int lane) {   // by a whole wavefront
+    double l = 0.0, r = 0.0;
+    for (int b = lane; b < f.n_blocks; b += ARROL_WAVE) { l += f.block_sums[b]; r += f.block_sums[f.n_blocks + b]; }
+    l = wave_sum_f64(l);
+    r = wave_sum_f64(r);
+    if (lane == 0 && f.loss) *f.loss = static_cast<float>(l / f.n_rows);
+    if (lane == 0 && f.grad_b2) *f.grad_b2 = static_cast<float>(r);
 }
 __global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where mlp_wgrad_mid_kernel does not do it
     const int v = blockIdx.x * 256 + threadIdx.x;
     if (v < f.m) finish_unit(f, v, blockIdx.y);
-    if (v == 0 && blockIdx.y == 0) finish_loss(f);
+    if (v < ARROL_WAVE && blockIdx.y == 0) finish_loss(f, v);
 }
 
 // dL/dW1 = delta^T . H over the rollouts where the ring form has too few 256 x 256 tiles to fill the chip: BM rows of
@@ -788,7 +792,7 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     if (f.unit_partial && blockIdx.x == 0 && blockIdx.z == 0) {   // while the first steps are on their way
         for (int v = tid; v < 2 * BM; v += C::NT)
             if (u0 + v % BM < f.m) finish_unit(f, u0 + v % BM, v / BM);
-        if (blockIdx.y == 0 && tid == 0) finish_loss(f);
+        if (blockIdx.y == 0 && wave == GW * KG - 1) finish_loss(f, lane);
     }
     int slot = 0;
     for (int s = 0; s < n_st; ++s) {
