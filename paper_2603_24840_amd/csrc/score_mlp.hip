@@ -708,7 +708,7 @@ struct WgradTile {
 };
 
 template <class C>
-__global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, int terms, MlpSums f) {
+__global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, int terms, int strip, MlpSums f) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void* lds_ptr_t;
     typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -717,7 +717,11 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave / GW, wq = wave % GW, wm = wq / C::WN, wn = wq % C::WN;
-    const int u0 = blockIdx.y * BM, c0 = blockIdx.x * BN;
+    // tiles in strips of `strip` columns, row by row (wgrad_strip)
+    const int n_ub = (a.a_rows + BM - 1) / BM, id = blockIdx.x, in_strip = id % (strip * n_ub);
+    const int ub = in_strip / strip, cb = id / (strip * n_ub) * strip + in_strip % strip;
+    const int u0 = ub * BM, c0 = cb * BN;
+    if (c0 >= a.b_rows) return;              // the last strip's missing columns
     // steps of this split: of each K64 all terms, one or two, so that the hidden states come from memory once
     const int k64_lo = static_cast<int>(blockIdx.z) * a.k64_per_split;
     const int k64_hi = k64_lo + a.k64_per_split < a.n_k64 ? k64_lo + a.k64_per_split : a.n_k64;   // > k64_lo (host)
@@ -789,10 +793,10 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     }
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) issue();
-    if (f.unit_partial && blockIdx.x == 0 && blockIdx.z == 0) {   // while the first steps are on their way
+    if (f.unit_partial && cb == 0 && blockIdx.z == 0) {   // while the first steps are on their way
         for (int v = tid; v < 2 * BM; v += C::NT)
             if (u0 + v % BM < f.m) finish_unit(f, u0 + v % BM, v / BM);
-        if (blockIdx.y == 0 && wave == GW * KG - 1) finish_loss(f, lane);
+        if (ub == 0 && wave == GW * KG - 1) finish_loss(f, lane);
     }
     int slot = 0;
     for (int s = 0; s < n_st; ++s) {
@@ -859,12 +863,24 @@ using Wgrad64 = WgradTile<64, 2, 2, 2, 4>;
 using Wgrad128 = WgradTile<128, 2, 2, 2, 3>;
 using Wgrad128Two = WgradTile<128, 2, 2, 1, 3>;      // two workgroups to a compute unit
 
+// Ids congruent mod 8 are on one XCD.  Strips of 8 columns keep all unit blocks of a column on the same XCD, whose L2 then holds
+// their hidden states once, where the columns are no multiple of 8 and a whole row at a time would spread them (7,426 x 4032 x 256,
+// 63 columns x 4 unit blocks, whole call: 72.2 us, in strips 62.4; 4,096 x 896 x 512 31.3, 29.8) - unless the columns that the last strip
+// lacks leave some XCDs a round more than all have together (4,097 x 768 x 512 with two terms, 12 columns: 39.8, in strips 47.5).
+template <class C>
+int wgrad_strip(int n_cb, int n_ub, int splits) {
+    constexpr int kPerXcd = C::LDS_BYTES > 81920 ? 32 : 64;       // workgroups that run together
+    const int64_t fullest = static_cast<int64_t>((n_cb + 7) / 8) * n_ub * splits, all = static_cast<int64_t>(n_cb) * n_ub * splits;
+    return (fullest + kPerXcd - 1) / kPerXcd == (all + 8 * kPerXcd - 1) / (8 * kPerXcd) ? 8 : n_cb;
+}
+
 template <class C>
 int launch_wgrad_mid(const MlpRingArgs& g, int terms, int splits, const MlpSums& f, hipStream_t st) {
     static arrol_device_flags ok;
     if (!arrol_allow_lds(&mlp_wgrad_mid_kernel<C>, C::LDS_BYTES, ok)) return ARROL_EHIP;
-    arrol_launch(mlp_wgrad_mid_kernel<C>, dim3((g.b_rows + C::BN - 1) / C::BN, (g.a_rows + C::BM - 1) / C::BM, splits), dim3(C::NT),
-                 C::LDS_BYTES, st, g, terms, f);
+    const int n_cb = (g.b_rows + C::BN - 1) / C::BN, n_ub = (g.a_rows + C::BM - 1) / C::BM, strip = wgrad_strip<C>(n_cb, n_ub, splits);
+    arrol_launch(mlp_wgrad_mid_kernel<C>, dim3(static_cast<unsigned>((n_cb + strip - 1) / strip * strip) * n_ub, 1, splits), dim3(C::NT),
+                 C::LDS_BYTES, st, g, terms, strip, f);
     return ARROL_OK;
 }
 
