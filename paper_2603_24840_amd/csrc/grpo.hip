@@ -244,7 +244,7 @@ extern "C" int arrol_grpo_objective(const float* logp, const float* logp_ref, co
     // Rollouts are cut into parts of some 1,024 tokens where there are too few to fill the chip, up to 256 parts in all (one of
     // 20,000 tokens: 17.3 us whole, 7.2 in 8; 32 of 1,024 to 8,192: 9.7 and 5.9; but 256 of 2,000 6.0 and 7.5 in 4), and, of 3 million
     // tokens and more, where whole ones leave the units uneven (1,024 of 1,024 to 8,192: 25.3 and 22.6 in 4).
-    int64_t n_seg = (2 * (T / n_seq) + 1023) / 1024;
+    int64_t n_seg = T < 800 ? 1 : (2 * (T / n_seq) + 1023) / 1024;      // (one of 700: 4.1 us whole, 4.4 in parts)
     const int64_t most = (T >= 3000000 ? 4096 : 256) / n_seq;
     n_seg = n_seg < kSegments ? n_seg : kSegments;
     n_seg = n_seg < most ? n_seg : most;
