@@ -674,9 +674,11 @@ __device__ __forceinline__ void finish_unit(const MlpSums& f, int u, int which) 
 __device__ __forceinline__ void finish_loss(const MlpSums& f, int lane) {   // by a whole wavefront
     double l = 0.0, r = 0.0;
     for (int b = lane; b < f.n_blocks; b += ARROL_WAVE) { l += f.block_sums[b]; r += f.block_sums[f.n_blocks + b]; }
-    l = wave_sum_f64(l);
-    r = wave_sum_f64(r);
-    if (lane == 0 && f.loss) *f.loss = static_cast<float>(l / f.n_rows);
+    if (f.n_blocks > 1) {
+        l = wave_sum_f64(l);
+        r = wave_sum_f64(r);
+    }
+    if (lane == 0 && f.loss) *f.loss = static_cast<float>(l) / static_cast<float>(f.n_rows);
     if (lane == 0 && f.grad_b2) *f.grad_b2 = static_cast<float>(r);
 }
 __global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where mlp_wgrad_mid_kernel does not do it
@@ -708,7 +710,7 @@ struct WgradTile {
 };
 
 template <class C>
-__global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, int terms, int strip, MlpSums f) {
+__global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, int terms, bool strips, MlpSums f) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void* lds_ptr_t;
     typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -717,9 +719,8 @@ __global__ __launch_bounds__(C::NT, 2) void mlp_wgrad_mid_kernel(MlpRingArgs a, 
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave / GW, wq = wave % GW, wm = wq / C::WN, wn = wq % C::WN;
-    // tiles in strips of `strip` columns, row by row (wgrad_strip)
-    const int n_ub = (a.a_rows + BM - 1) / BM, id = blockIdx.x, in_strip = id % (strip * n_ub);
-    const int ub = in_strip / strip, cb = id / (strip * n_ub) * strip + in_strip % strip;
+    // tile (unit block, column): blockIdx.y, .x or, in strips of 8 columns (wgrad_strips), blockIdx.x / 8 and 8 blockIdx.y + blockIdx.x % 8
+    const int ub = strips ? blockIdx.x / 8 : blockIdx.y, cb = strips ? blockIdx.y * 8 + blockIdx.x % 8 : blockIdx.x;
     const int u0 = ub * BM, c0 = cb * BN;
     if (c0 >= a.b_rows) return;              // the last strip's missing columns
     // steps of this split: of each K64 all terms, one or two, so that the hidden states come from memory once
@@ -868,19 +869,20 @@ using Wgrad128Two = WgradTile<128, 2, 2, 1, 3>;      // two workgroups to a comp
 // 63 columns x 4 unit blocks, whole call: 72.2 us, in strips 62.4; 4,096 x 896 x 512 31.3, 29.8) - unless the columns that the last strip
 // lacks leave some XCDs a round more than all have together (4,097 x 768 x 512 with two terms, 12 columns: 39.8, in strips 47.5).
 template <class C>
-int wgrad_strip(int n_cb, int n_ub, int splits) {
+bool wgrad_strips(int n_cb, int n_ub, int splits) {
     constexpr int kPerXcd = C::LDS_BYTES > 81920 ? 32 : 64;       // workgroups that run together
     const int64_t fullest = static_cast<int64_t>((n_cb + 7) / 8) * n_ub * splits, all = static_cast<int64_t>(n_cb) * n_ub * splits;
-    return (fullest + kPerXcd - 1) / kPerXcd == (all + 8 * kPerXcd - 1) / (8 * kPerXcd) ? 8 : n_cb;
+    return n_ub > 65535 || (fullest + kPerXcd - 1) / kPerXcd == (all + 8 * kPerXcd - 1) / (8 * kPerXcd);
 }
 
 template <class C>
 int launch_wgrad_mid(const MlpRingArgs& g, int terms, int splits, const MlpSums& f, hipStream_t st) {
     static arrol_device_flags ok;
     if (!arrol_allow_lds(&mlp_wgrad_mid_kernel<C>, C::LDS_BYTES, ok)) return ARROL_EHIP;
-    const int n_cb = (g.b_rows + C::BN - 1) / C::BN, n_ub = (g.a_rows + C::BM - 1) / C::BM, strip = wgrad_strip<C>(n_cb, n_ub, splits);
-    arrol_launch(mlp_wgrad_mid_kernel<C>, dim3(static_cast<unsigned>((n_cb + strip - 1) / strip * strip) * n_ub, 1, splits), dim3(C::NT),
-                 C::LDS_BYTES, st, g, terms, strip, f);
+    const int n_cb = (g.b_rows + C::BN - 1) / C::BN, n_ub = (g.a_rows + C::BM - 1) / C::BM;
+    const bool strips = wgrad_strips<C>(n_cb, n_ub, splits);
+    arrol_launch(mlp_wgrad_mid_kernel<C>, strips ? dim3(8 * n_ub, (n_cb + 7) / 8, splits) : dim3(n_cb, n_ub, splits), dim3(C::NT),
+                 C::LDS_BYTES, st, g, terms, strips, f);
     return ARROL_OK;
 }
 
@@ -1266,6 +1268,7 @@ struct GradPlan {
     int n_rb, n_pad, n_cb, n_groups, n_kc, splits, kc_per_split;
     int r_cb, r_gt, r_splits, r_k64_per_split;
     int w_rows, w_groups;              // dL/dW1 of rows read in place: rows of the mid kernel's tile, 64 or 128, and wavefront groups; 256: the ring form
+    bool w_stacked;                    // the mid kernel takes two terms as rows of their own, as the ring form does, not into the same sums
     size_t off_score, off_prob, off_resid, off_bsum, off_ht, off_dt, off_unit, off_slab, off_small, off_rslab, off_act, total;
 };
 
@@ -1349,21 +1352,35 @@ GradPlan make_grad_plan(int n_rows, int d, int m, int terms) {
         return static_cast<double>(n / 512) * (steps * kMidStep + kMidStart) + (n % 512 ? steps * last + kMidStart : 0.0);
     };
     constexpr double kStep64 = 0.205, kStep128 = 0.31, kRound64 = 4.3, kRound128 = 5.5;
+    struct Blocks { double us; int rows, groups; };
+    const auto blocks_us = [&](int64_t n64, int64_t n128, int steps) {        // the three forms, of that many tiles
+        const double t64 = static_cast<double>((n64 + 255) / 256) * (steps * kStep64 + kRound64);
+        const double t128 = static_cast<double>((n128 + 255) / 256) * (steps * kStep128 + kRound128), two = one_group_us(n128, steps);
+        if (two < t64 && two < t128) return Blocks{two, 128, 1};
+        return t64 <= t128 ? Blocks{t64, 64, 2} : Blocks{t128, 128, 2};
+    };
     double best_mid = -1.0, one_mid = 0.0;
+    p.w_stacked = false;
     for (int s = 1; s <= kMaxSplits && (s == 1 || n_k64 / s >= 4); ++s) {
         const int per = (n_k64 + s - 1) / s, used = (n_k64 + per - 1) / per;
-        const double slabs = used > 1 ? kSlabStart + used * mid_slab_us : 0.0;
-        const int64_t n64 = tiles64 * used, n128 = tiles128 * used;
-        const double t64 = (m + 63) / 64 > 65535 ? 1e30 : static_cast<double>((n64 + 255) / 256) * (per * terms * kStep64 + kRound64) + slabs;
-        const double t128 = static_cast<double>((n128 + 255) / 256) * (per * terms * kStep128 + kRound128) + slabs;
-        const double two = one_group_us(n128, per * terms) + slabs;
-        double t = t64 < t128 ? t64 : t128;
-        t = two < t ? two : t;
+        const Blocks b = blocks_us(tiles64 * used, tiles128 * used, per * terms);
+        const double t = b.us + (used > 1 ? kSlabStart + used * mid_slab_us : 0.0);
         if (s == 1) one_mid = t;
         if (best_mid < 0.0 || t < best_mid) {
             best_mid = t;
-            if (p.w_rows != 256) { p.w_rows = t == t64 ? 64 : 128; p.w_groups = t == two ? 1 : 2; p.r_k64_per_split = per; p.r_splits = used; }
+            if (p.w_rows != 256) { p.w_rows = b.rows; p.w_groups = b.groups; p.r_k64_per_split = per; p.r_splits = used; }
         }
+    }
+    // Two terms as rows of their own cost a slab more each, but no more time in a tile that they leave room in or on units that
+    // would be idle: whole calls of 21,203 x 2176 x 5 52.8 us in the same sums, 47.9 so, 33,986 x 128 x 128 58.2 and 50.8.  Where the
+    // estimates are close the same sums are faster, since they read the hidden states once (30,014 x 192 x 256, 0.89 by the
+    // estimates: 60.8 and 66.8): a fifth less or nothing.
+    const int64_t st64 = static_cast<int64_t>((d + 63) / 64) * ((mt + 63) / 64), st128 = static_cast<int64_t>((d + 63) / 64) * ((mt + 127) / 128);
+    for (int s = 1; terms == 2 && p.w_rows != 256 && s <= room && (s == 1 || n_k64 / s >= 4); ++s) {
+        const int per = (n_k64 + s - 1) / s, used = (n_k64 + per - 1) / per;
+        const Blocks b = blocks_us(st64 * used, st128 * used, per);
+        const double t = (b.us + kSlabStart + used * slab_us) / 0.8;
+        if (t < best_mid) { best_mid = t; p.w_stacked = true; p.w_rows = b.rows; p.w_groups = b.groups; p.r_k64_per_split = per; p.r_splits = used; }
     }
     // the same room for their splits (whichever form this batch takes: a smaller one may take the other)
     double step_mid = static_cast<double>(tiles64) * kStep64 / 256.0;
@@ -1566,18 +1583,20 @@ extern "C" int arrol_score_mlp_grad(const void* hidden, int64_t row_stride_elems
         // dL/dW1 = delta^T . H over the rollouts, the hidden states read in place
         float* rslab = reinterpret_cast<float*>(ws + p.off_rslab);
         MlpRingArgs g = {};
-        // the ring form's partials [K split][term][m][d] are delta_terms * r_splits slabs of m * d values
-        const int n_slabs = p.w_rows == 256 ? p.r_splits * delta_terms : p.r_splits;
+        // partials [K split][term][m][d] of terms as rows of their own are delta_terms * r_splits slabs of m * d values
+        const bool stacked = p.w_rows == 256 || p.w_stacked;
+        const int n_slabs = stacked ? p.r_splits * delta_terms : p.r_splits;
         g.a = dt; g.a_stride = static_cast<unsigned>(p.n_pad) * 2; g.a_rows = mt;
         g.b = a.hidden; g.b_stride = static_cast<unsigned>(row_stride_elems * 2);
         g.b_rows = d; g.b_k_rows = n_rows;
         g.n_k64 = (n_rows + 63) / 64; g.k64_per_split = p.r_k64_per_split;
         g.c_out = n_slabs > 1 ? rslab : grad_w1; g.c_stride = d;
         if (p.w_rows != 256) {
-            g.a_rows = m;
-            rc = p.w_rows == 64    ? launch_wgrad_mid<Wgrad64>(g, delta_terms, p.r_splits, sums, st)
-                 : p.w_groups == 2 ? launch_wgrad_mid<Wgrad128>(g, delta_terms, p.r_splits, sums, st)
-                                   : launch_wgrad_mid<Wgrad128Two>(g, delta_terms, p.r_splits, sums, st);
+            g.a_rows = stacked ? mt : m;
+            const int terms = stacked ? 1 : delta_terms;
+            rc = p.w_rows == 64    ? launch_wgrad_mid<Wgrad64>(g, terms, p.r_splits, sums, st)
+                 : p.w_groups == 2 ? launch_wgrad_mid<Wgrad128>(g, terms, p.r_splits, sums, st)
+                                   : launch_wgrad_mid<Wgrad128Two>(g, terms, p.r_splits, sums, st);
             if (rc != ARROL_OK) return rc;
         } else {
             rc = launch_mlp_ring<kWgrad>(g, dim3(p.r_cb, p.r_gt, p.r_splits), st);

@@ -255,6 +255,15 @@ def test_score_mlp_grad_columns_that_fill_no_strip(A, n, d, m, terms):
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.125, labels, delta_terms=terms)
 
 
+# two terms as rows of their own in the 64 x 64 blocks, one and several K splits, units that leave room in a block and fill one
+@pytest.mark.parametrize("n,d,m,splits", [(21203, 128, 5, 16), (5000, 128, 100, 16), (3000, 576, 20, 10), (2100, 64, 64, 7)])
+def test_score_mlp_grad_two_terms_as_rows(A, n, d, m, splits):
+    print("[case] score_mlp_grad stacked n=%d d=%d m=%d" % (n, d, m), flush=True)
+    assert mlp_kernels(A, n, d, m, 2)[1:] == (1, splits) and mlp_tiles(A, n, d, m, 2)[1:] == (64, 2)
+    hidden, w1, b1, w2, labels = mlp_case(n, d, m, seed=23 * n + d + m)
+    check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, -0.5, labels, delta_terms=2)
+
+
 # both sides of the lines of the one-launch delta: 3 million activations, 20,000 rows, and 2,048 rows where a launch of its own adds
 # the parts (gathered rows, dL/dW1 in the ring form)
 @pytest.mark.parametrize("n,d,m,terms,gather,gradient", [(2859, 64, 1100, 1, False, 1), (2860, 64, 1100, 2, False, 1), (20000, 64, 24, 2, False, 1),
