@@ -255,8 +255,8 @@ def test_score_mlp_grad_columns_that_fill_no_strip(A, n, d, m, terms):
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.125, labels, delta_terms=terms)
 
 
-# two terms as rows of their own in the 64 x 64 blocks, one and several K splits, units that leave room in a block and fill one
-@pytest.mark.parametrize("n,d,m,splits", [(21203, 128, 5, 16), (5000, 128, 100, 16), (3000, 576, 20, 10), (2100, 64, 64, 7)])
+# two terms as rows of their own in the 64 x 64 blocks (both in one block, across blocks), and, the last, beside them in the same sums
+@pytest.mark.parametrize("n,d,m,splits", [(21203, 128, 5, 16), (11702, 64, 3, 16), (12700, 64, 65, 16), (14001, 192, 64, 16)])
 def test_score_mlp_grad_two_terms_as_rows(A, n, d, m, splits):
     print("[case] score_mlp_grad stacked n=%d d=%d m=%d" % (n, d, m), flush=True)
     assert mlp_kernels(A, n, d, m, 2)[1:] == (1, splits) and mlp_tiles(A, n, d, m, 2)[1:] == (64, 2)
