@@ -867,12 +867,14 @@ using Wgrad128Two = WgradTile<128, 2, 2, 1, 3>;      // two workgroups to a comp
 // Ids congruent mod 8 are on one XCD.  Strips of 8 columns keep all unit blocks of a column on the same XCD, whose L2 then holds
 // their hidden states once, where the columns are no multiple of 8 and a whole row at a time would spread them (7,426 x 4032 x 256,
 // 63 columns x 4 unit blocks, whole call: 72.2 us, in strips 62.4; 4,096 x 896 x 512 31.3, 29.8) - unless the columns that the last strip
-// lacks leave some XCDs a round more than all have together (4,097 x 768 x 512 with two terms, 12 columns: 39.8, in strips 47.5).
+// lacks leave some XCDs a round more than all have together (4,097 x 768 x 512 with two terms, 12 columns: 39.8, in strips 47.5) or
+// are more than a fifth of the strips (65,536 x 64 x 128, whose one column would be all on one XCD: 57.9, in strips 67.2).
 template <class C>
 bool wgrad_strips(int n_cb, int n_ub, int splits) {
     constexpr int kPerXcd = C::LDS_BYTES > 81920 ? 32 : 64;       // workgroups that run together
     const int64_t fullest = static_cast<int64_t>((n_cb + 7) / 8) * n_ub * splits, all = static_cast<int64_t>(n_cb) * n_ub * splits;
-    return n_ub > 65535 || (fullest + kPerXcd - 1) / kPerXcd == (all + 8 * kPerXcd - 1) / (8 * kPerXcd);
+    return n_ub > 65535 ||
+           (4 * 8 * ((n_cb + 7) / 8) <= 5 * n_cb && (fullest + kPerXcd - 1) / kPerXcd == (all + 8 * kPerXcd - 1) / (8 * kPerXcd));
 }
 
 template <class C>

@@ -245,8 +245,8 @@ def test_score_mlp_grad_one_launch_delta(A, n, d, m, terms):
     check_mlp_grad(A, hidden, w1, b1, w2 * 4.0, 0.25, labels, delta_terms=terms)
 
 
-# blocks of dL/dW1 in strips of 8 columns, the last one short (15, 9, 63 and 1 columns of 64; one and several unit blocks and K
-# splits), and a whole row at a time where strips would fill some XCDs twice (12 columns x 4 unit blocks x 5 splits)
+# blocks of dL/dW1 in strips of 8 columns, the last one short (15, 63 and 14 columns of 64; one and several unit blocks and K
+# splits), and a whole row at a time where columns are few (1 and 9) or strips would fill some XCDs twice (12 x 4 unit blocks x 5 splits)
 @pytest.mark.parametrize("n,d,m,terms", [(500, 960, 300, 1), (700, 576, 513, 2), (600, 4032, 130, 1), (300, 64, 200, 2), (2300, 896, 257, 1), (4097, 768, 512, 2)])
 def test_score_mlp_grad_columns_that_fill_no_strip(A, n, d, m, terms):
     print("[case] score_mlp_grad strips n=%d d=%d m=%d terms=%d" % (n, d, m, terms), flush=True)
