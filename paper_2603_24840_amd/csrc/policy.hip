@@ -12,7 +12,6 @@ constexpr int kHistOneMax = 16384;    // entries one workgroup takes alone: 16 p
                                       // where two launches take 5.8 and 7.2
 constexpr int kMaxBins = 2048;        // two fp64 tables of kMaxBins entries fit in LDS
 constexpr int kPruneThreads = 1024;
-constexpr int kBisectIters = 64;
 static_assert(64 * 32 == kMaxBins, "the last form of the calibration takes every bin count");
 
 // b(s') = min(B-1, floor(B s')), product in fp32 (App. A.4)
@@ -85,20 +84,22 @@ __global__ __launch_bounds__(kHistOneThreads) void histogram_one_kernel(
     }
 }
 
-// Likelihoods, Bayes posterior, survival probability and the bisection for delta; one workgroup, fp64.
-// What bounds it is the serial chain of 64 halvings, each a sum over the bins.  LEVELS halvings are taken at once: the
-// 2^LEVELS - 1 midpoints that they can ask for form a binary tree, LPM lanes with PER_LANE bins each in their registers
-// sum at each node (numbered as a heap), and every thread walks the decisions down the tree behind one barrier.
-// Midpoints are those of one halving after the other.  128 bins: 31.3 us with a sum over the whole workgroup and two
-// barriers per halving, now 7.7 (other sizes at the launch).
-template <int LEVELS, int LPM, int PER_LANE>
-__global__ __launch_bounds__((1 << LEVELS) * LPM) void calibrate_kernel(
+// Likelihoods, Bayes posterior, survival probability and the search for delta; one workgroup, fp64.
+// What bounds it is the serial chain of sums over the bins.  2^LOG - 1 points of the bracket are summed at once (LPM lanes with PER_LANE
+// bins each in their registers a point), behind one barrier; the bracket then is between the last point whose sum is too small and
+// the next.  The sum is piecewise linear in delta, so from where both ends' sums are known on the points lie around the secant's root, at
+// distances that fall by powers of two: between two kinks one such round leaves a few ulps, which the last rounds of equal steps share.
+// A round of that kind that has met a kink is followed by one of equal steps, so that two rounds always gain LOG bits.  The bracket ends as
+// 64 halvings would: no double between its ends, or 2^-63 of its start.  128 bins: the whole call 7.6 us
+// with 16 rounds of four halvings each, 4.5 with the four to six rounds of this (5.6 at kappa 0.25; other sizes at the launch).
+template <int LOG, int LPM, int PER_LANE>
+__global__ __launch_bounds__((1 << LOG) * LPM) void calibrate_kernel(
     const int64_t* __restrict__ c_pos, const int64_t* __restrict__ c_neg, int B, arrol_policy pol,
     float* __restrict__ q_lut, float* __restrict__ p_lut, double* __restrict__ delta_out) {
-    constexpr int NODES = 1 << LEVELS, NT = NODES * LPM, WAVES = NT / ARROL_WAVE;
-    static_assert(kBisectIters % LEVELS == 0 && (LPM == 16 || LPM == 64), "a node's lanes lie in one wavefront");
+    constexpr int NODES = 1 << LOG, NT = NODES * LPM, WAVES = NT / ARROL_WAVE;
+    static_assert((LOG == 3 || LOG == 4) && (LPM == 16 || LPM == 64), "a point's lanes lie in one wavefront");
     // off_s: lambda (rho - q), what a bin adds to kappa + delta
-    constexpr int MAX_B = PER_LANE * LPM;                               // the bins of a node's lanes sit in registers
+    constexpr int MAX_B = PER_LANE * LPM;                               // the bins of a point's lanes sit in registers
     __shared__ double q_s[MAX_B], off_s[MAX_B], w_s[MAX_B];
     __shared__ double node_sum[2][NODES];
     __shared__ int64_t cnt[2][WAVES];
@@ -134,18 +135,21 @@ __global__ __launch_bounds__((1 << LEVELS) * LPM) void calibrate_kernel(
         off[k] = b < B ? off_s[b] : 0.0;
         wgt[k] = b < B ? w_s[b] : 0.0;          // adds nothing
     }
-    double lo = p_min - kappa - lam, hi = p_max - kappa + lam;
-    for (int it = 0; it < kBisectIters / LEVELS; ++it) {
-        // my node's midpoint: down from the root by the bits below its top one (node 0 repeats the root)
-        double l = lo, h = hi;
-#pragma unroll
-        for (int bit = LEVELS - 2; bit >= 0; --bit) {
-            if (my_node >= (2 << bit)) {
-                const double mid = 0.5 * (l + h);
-                if ((my_node >> bit) & 1) l = mid; else h = mid;
-            }
-        }
-        const double base = kappa + 0.5 * (l + h);
+    double lo = p_min - kappa - lam, hi = p_max - kappa + lam, sum_lo = 0.0, sum_hi = 0.0;
+    const double enough = (hi - lo) * 0x1p-63;
+    bool known_lo = false, known_hi = false, secant = false;     // the ends' sums; the kind of this round (the same in every thread)
+    for (int it = 0; it < 2 * ((64 + LOG - 1) / LOG); ++it) {
+        const double width = hi - lo, middle = lo + 0.5 * width;
+        if (width <= enough || middle <= lo || middle >= hi) break;
+        const double root = secant ? lo + (kappa - sum_lo) / (sum_hi - sum_lo) * width : 0.0;
+        const auto point = [&](int j) {          // j = 1 .. NODES - 1, ascending
+            if (!secant) return fma(width, j * (1.0 / NODES), lo);
+            const int m = j - NODES / 2, rank = m < 0 ? -m : m;  // steps of 2^-46 ... 2^-4 (2^-6) of the bracket
+            const int e = LOG == 4 ? 53 - 7 * rank : 66 - 20 * rank;
+            const double step = m == 0 ? 0.0 : width * __longlong_as_double(static_cast<long long>(1023 - e) << 52);
+            return fmin(fmax(m < 0 ? root - step : root + step, lo), hi);
+        };
+        const double base = kappa + (my_node > 0 ? point(my_node) : it == 0 ? lo : hi);      // point 0: the start's lower end, then the upper
         double e = 0.0;
 #pragma unroll
         for (int k = 0; k < PER_LANE; ++k) e = fma(wgt[k], fmin(fmax(base + off[k], p_min), p_max), e);
@@ -157,16 +161,21 @@ __global__ __launch_bounds__((1 << LEVELS) * LPM) void calibrate_kernel(
         e = wave_step<1>(e, add);
         if (my_lane == 0) node_sum[it & 1][my_node] = e;
         __syncthreads();
-        // bit n: the sum at node n is too small (the midpoint becomes the lower end)
-        const uint64_t small = __ballot(node_sum[it & 1][lane % NODES] < kappa);
-        int node = 1;                            // 1 the root, 2n the lower half of node n, 2n + 1 the upper
-#pragma unroll
-        for (int level = 0; level < LEVELS; ++level) {
-            const double m = 0.5 * (lo + hi);
-            const int up = static_cast<int>((small >> node) & 1u);
-            if (up) lo = m; else hi = m;
-            node = 2 * node + up;
-        }
+        // kappa is below what any delta gives, or above
+        const double end_sum = node_sum[it & 1][0];
+        if (it == 0 && end_sum >= kappa) { hi = lo; break; }
+        if (it == 1 && !known_hi && end_sum < kappa) { lo = hi; break; }
+        // the first point whose sum is large enough becomes the upper end, the one before it the lower
+        const uint64_t large = __ballot(node_sum[it & 1][lane % NODES] >= kappa) & ((1ull << NODES) - 2);
+        const int first = large ? __builtin_ctzll(large) : NODES;
+        const double new_lo = first > 1 ? point(first - 1) : lo, new_hi = first < NODES ? point(first) : hi;
+        if (first > 1) { sum_lo = node_sum[it & 1][first - 1]; known_lo = true; }
+        if (first < NODES) { sum_hi = node_sum[it & 1][first]; known_hi = true; }
+        lo = new_lo;
+        hi = new_hi;
+        // equal steps first, until the bracket is some 2 / B of its start: every bin has two kinks
+        const bool gained = hi - lo <= width * (1.0 / NODES);
+        secant = known_lo && known_hi && it < 7 && (4ll << (it + 1) * LOG) >= 2 * B && !secant && gained;
     }
     const double delta = 0.5 * (lo + hi);
     for (int b = tid; b < B; b += NT) {
@@ -250,17 +259,17 @@ extern "C" int arrol_calibrate(const int64_t* c_pos, const int64_t* c_neg, int32
                                float* q_lut, float* p_lut, double* delta, void* stream) {
     if (B < 1 || B > kMaxBins || !c_pos || !c_neg || !q_lut || !p_lut || !policy_ok(pol)) return ARROL_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Measured (before: 31 us up to 256 bins, 37, 45, 63 at 512, 1024, 2048): 15 midpoints at once 7.7 and 8.8 us up to
-    // 128 and 256 bins; beyond that the sums of 15 midpoints cost more than the rounds they save (21 us at 1024 against
-    // 15 with 3 midpoints, one wavefront each): 12, 15 and 20 us.
-    const auto launch = [&](auto kernel) {
-        arrol_launch(kernel, dim3(1), dim3(256), 0, st, c_pos, c_neg, B, pol, q_lut, p_lut, delta);
+    // Measured, halvings (15 midpoints at once up to 256 bins, 3 beyond) and this at kappa 0.5 / 0.25: 128 bins 7.6 and 4.5 / 5.6 us, 256 8.7 and
+    // 6.1 / 6.3, 512 12.1 and 6.8 / 8.7, 1,024 15.0 and 7.3 / 11.7, 2,048 20.4 and 15.7.  From 257 bins on a wavefront sums a point, and beyond
+    // 512 seven points a round: 15 of 32 bins a lane would need more registers than 1,024 threads have.
+    const auto launch = [&](auto kernel, int threads) {
+        arrol_launch(kernel, dim3(1), dim3(threads), 0, st, c_pos, c_neg, B, pol, q_lut, p_lut, delta);
     };
-    if (B <= 128) launch(calibrate_kernel<4, 16, 8>);
-    else if (B <= 256) launch(calibrate_kernel<4, 16, 16>);
-    else if (B <= 512) launch(calibrate_kernel<2, 64, 8>);
-    else if (B <= 1024) launch(calibrate_kernel<2, 64, 16>);
-    else launch(calibrate_kernel<2, 64, 32>);
+    if (B <= 128) launch(calibrate_kernel<4, 16, 8>, 256);
+    else if (B <= 256) launch(calibrate_kernel<4, 16, 16>, 256);
+    else if (B <= 512) launch(calibrate_kernel<4, 64, 8>, 1024);
+    else if (B <= 1024) launch(calibrate_kernel<3, 64, 16>, 512);
+    else launch(calibrate_kernel<3, 64, 32>, 512);
     return arrol_launch_status();
 }
 

@@ -83,6 +83,35 @@ def test_calibrate_bin_counts_at_the_edges_of_its_forms(A, B):
     assert abs(float(delta[0]) - d_o) < DELTA_TOL
 
 
+# The search for delta where its rounds can go wrong: no delta reaches kappa or every one does, only one bin has weight, a flat stretch at
+# kappa itself, no slope at all, kinks crowded around the root, probabilities that never move; at the bin counts of each form.
+# Oracle and kernel bracket the same root down to neighbouring doubles, so they differ by the rounding of sums of up to 2,048
+# terms (2,048 * 1.1e-16 of at most 1) over the slope, which is at least the weight of the lightest bin (1 / 3,000): below 1e-9.
+@pytest.mark.parametrize("B", [1, 2, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048])
+@pytest.mark.parametrize("args", [(0.5, 0.5, 0.5, 0.05, 0.95, 1.0), (1.0, 0.5, 0.5, 0.05, 0.95, 1.0), (0.0, 0.5, 0.5, 0.05, 0.95, 1.0),
+                                  (0.5, 0.5, 0.0, 0.0, 1.0, 1.0), (0.4, 0.3, 3.0, 0.25, 0.75, 0.0), (0.5, 0.5, 0.5, 0.5, 0.5, 1.0),
+                                  (0.625, 1.0, 8.0, 0.0, 1.0, 0.0), (0.5, 0.5, 100.0, 0.0, 1.0, 0.01)])
+def test_calibrate_search_at_its_extremes(A, B, args):
+    print("[case] calibrate search B=%d kappa=%g lambda=%g" % (B, args[0], args[2]), flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(B)
+    one = torch.zeros(B, dtype=torch.int64, device=DEV)
+    one[B // 3] = 1000
+    half = torch.zeros(B, dtype=torch.int64, device=DEV)
+    half[: (B + 1) // 2] = 1
+    for cp, cn in ((one, torch.zeros_like(one)), (one, one), (half, half.flip(0)),
+                   (torch.randint(0, 2, (B,), generator=g, device=DEV), torch.randint(0, 2, (B,), generator=g, device=DEV))):
+        q_lut, p_lut, delta = A.arrol_calibrate(cp, cn, A.Policy(*args))
+        torch.cuda.synchronize()
+        q_o, p_o, d_o = O.calibrate(npy(cp), npy(cn), *(f32(x) for x in args))
+        assert np.max(np.abs(npy(q_lut) - q_o)) < Q_TOL
+        w = O.bin_weights(npy(cp), npy(cn))
+        p_g = npy(p_lut).astype(np.float64)
+        if abs(float(delta[0]) - d_o) < DELTA_TOL:
+            assert np.max(np.abs(p_g - p_o)) < Q_TOL
+        else:           # on a flat stretch at kappa the last bit of a sum decides which end is taken: both ends give the mean kappa
+            assert abs(float(np.dot(w, p_g)) - f32(args[0])) < 1e-6 and abs(float(np.dot(w, p_o)) - f32(args[0])) < 1e-6
+
+
 @pytest.mark.parametrize("M", [16383, 16384, 16385])
 def test_histogram_at_the_edge_of_the_one_workgroup_form(A, M):
     print("[case] histogram M=%d" % M, flush=True)
