@@ -78,7 +78,6 @@ __global__ __launch_bounds__(ARROL_WAVE) void grpo_advantage_kernel(
     }
 }
 
-constexpr int kObjUnroll = 4;          // tokens per thread whose loads are in flight together
 constexpr int kSegments = 8;           // most workgroups per rollout
 
 // the workgroup's sums of s and c, in thread 0
@@ -97,10 +96,35 @@ __device__ __forceinline__ void workgroup_sums(double& s, long long& c, double (
     }
 }
 
+// exp(-u) and exp(u), |u| < 700, from one reduction u = k ln 2 + r: exp(+-r) = cosh r +- sinh r, both by their Taylor series in r^2 (|r| <= 0.347:
+// what is left out is below 1e-17 of them).  23 instructions where an exponential and a reciprocal took some 50; each is within 1.9 ulp of
+// the true value, exactly 1 at 0.
+__device__ __forceinline__ void exp_both(double u, double& down, double& up) {
+    const double k = rint(u * 1.4426950408889634);
+    // ln 2 as a double and what that leaves of it
+    const double r = fma(-k, 2.3190468138462996e-17, fma(-k, 0.6931471805599453, u)), t = r * r;
+    double c = 1.0 / 479001600.0, s = 1.0 / 6227020800.0;            // 1 / 12!, 1 / 13!
+    c = fma(c, t, 1.0 / 3628800.0);
+    s = fma(s, t, 1.0 / 39916800.0);
+    c = fma(c, t, 1.0 / 40320.0);
+    s = fma(s, t, 1.0 / 362880.0);
+    c = fma(c, t, 1.0 / 720.0);
+    s = fma(s, t, 1.0 / 5040.0);
+    c = fma(c, t, 1.0 / 24.0);
+    s = fma(s, t, 1.0 / 120.0);
+    c = fma(c, t, 0.5);
+    s = fma(s, t, 1.0 / 6.0);
+    c = fma(c, t, 1.0);
+    s = fma(s * t, r, r);
+    const int e = static_cast<int>(k);
+    down = ldexp(c - s, -e);
+    up = ldexp(c + s, e);
+}
+
 // n_seg workgroups per rollout, each with an equal part of its tokens: partial[i n_seg + q] = weight_i * (1/L_i) * sum_t term_t,
 // clipped[..] = tokens on the clipped branch.  Bound by latency (64-bit exponentials behind two loads, 12 bytes a token): the
-// loads of four tokens go out together and long rollouts get enough wavefronts to hide the rest.
-template <int kObjThreads>
+// loads of kObjUnroll tokens go out together, their arithmetic is interleaved, and long rollouts get enough wavefronts to hide the rest.
+template <int kObjThreads, int kObjUnroll>
 __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     const float* __restrict__ logp, const float* __restrict__ logp_ref, const int64_t* __restrict__ cu, int64_t T,
     const float* __restrict__ advantage, const float* __restrict__ seq_weight, double eps_low, double eps_high,
@@ -134,20 +158,34 @@ __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
             ref[k] = logp_ref[t];
             lp[k] = logp[t];
         }
+        double u[kObjUnroll], ratio[kObjUnroll], eu[kObjUnroll];
+        bool far = false;
 #pragma unroll
         for (int k = 0; k < kObjUnroll; ++k) {
+            u[k] = static_cast<double>(ref[k]) - static_cast<double>(lp[k]);
+            exp_both(u[k], ratio[k], eu[k]);
+            far = far || !(fabs(u[k]) < 700.0);
+        }
+        if (__ballot(far)) {                 // a lane past the ends of the exponentials' range, infinite or undefined
+            asm volatile("");                // (a branch: the compiler would take both sides)
+#pragma unroll 1
+            for (int k = 0; k < kObjUnroll; ++k)
+                if (!(fabs(u[k]) < 700.0)) {
+                    ratio[k] = exp(-u[k]);
+                    eu[k] = exp(u[k]);
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < kObjUnroll; ++k) {      // beside each other: dead ones repeat the first and are not counted
             const int64_t t = t0 + k * kObjThreads;
-            if (t >= hi) break;
-            const double u = static_cast<double>(ref[k]) - static_cast<double>(lp[k]);
-            const double ratio = exp(-u);
-            const double plain = ratio * A;
-            const double clamped = fmin(fmax(ratio, r_lo), r_hi) * A;
-            // 1 / ratio where it neither overflows nor loses bits: 12 instructions for the 45 of a second exponential
-            const double eu = ratio > 1e-300 && ratio < 1e300 ? 1.0 / ratio : exp(u);
-            s += fmin(plain, clamped) - beta * (eu - u - 1.0);
-            c += clamped < plain ? 1 : 0;
-            if (grad_logp) {
-                const double d = (plain <= clamped ? plain : 0.0) - beta * (1.0 - eu);
+            const bool live = t < hi;
+            const double plain = ratio[k] * A;
+            const double clamped = fmin(fmax(ratio[k], r_lo), r_hi) * A;
+            const double term = fmin(plain, clamped) - beta * (eu[k] - u[k] - 1.0);
+            s += live ? term : 0.0;
+            c += live && clamped < plain ? 1 : 0;
+            if (grad_logp && live) {
+                const double d = (plain <= clamped ? plain : 0.0) - beta * (1.0 - eu[k]);
                 grad_logp[t] = static_cast<float>(d * scale);
             }
         }
@@ -253,14 +291,19 @@ extern "C" int arrol_grpo_objective(const float* logp, const float* logp_ref, co
     const int64_t n_parts = n_seq * n_seg;
     double* partial = static_cast<double*>(workspace);
     int64_t* clipped = reinterpret_cast<int64_t*>(partial + n_parts);
-#define ARROL_OBJECTIVE(N)                                                                                                     \
-    arrol_launch(grpo_objective_kernel<N>, dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, \
+#define ARROL_OBJECTIVE(N, U)                                                                                                  \
+    arrol_launch((grpo_objective_kernel<N, U>), dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, \
                  advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta),     \
                  grad_logp, partial, clipped)
-    // wider workgroups shorten a long rollout's chain while the chip has room for them: 512 rollouts of 512 to 4,096 tokens
-    // 10.5 us with 512 threads, 11.3 with 256; 512 of 64 to 512 tokens 5.7 and 5.4; 4,096 of 256 to 2,048 30.0 and 26.1
-    if (n_seg == 1 && T / n_seq > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512);
-    else ARROL_OBJECTIVE(256);
+    // wider workgroups shorten a long rollout's chain while the chip has room for them (one token at a time: 512 rollouts of 512 to 4,096
+    // tokens 10.5 us with 512 threads, 11.3 with 256; 4,096 of 256 to 2,048 30.0 and 26.1)
+    // Tokens in flight a thread: as many as most rollouts have for it, since a step's arithmetic is done whether they are there or not
+    // (512 rollouts of 64 to 512 tokens 4.9 us with two, 5.7 with four; 512 of 300 to 1,100 5.8 and 5.9; 128 of 256 to 2,048 5.1 and 4.9)
+    const int64_t mean = T / (n_seq * n_seg);
+    if (n_seg == 1 && mean > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512, 4);
+    else if (mean > 768) ARROL_OBJECTIVE(256, 4);
+    else if (mean > 128) ARROL_OBJECTIVE(256, 2);
+    else ARROL_OBJECTIVE(256, 1);
 #undef ARROL_OBJECTIVE
     // many: four partials a thread at a time; 256 threads are quicker to add up (one rollout: 4.2 us the call, 4.7 with 1,024)
     if (n_parts <= 1024)

@@ -133,6 +133,43 @@ def test_objective_at_extreme_ratios(A):
     assert int(n_clip) == clipped and np.isnan(float(J))
 
 
+# one, two and four tokens a thread at a time, 256 and 512 threads; lengths that leave some of them none; log-ratios on both sides of the 700
+# from which the library exponential is taken, infinite and undefined ones among ordinary ones of the same wavefront
+@pytest.mark.parametrize("lens", [[100, 128, 1], [130, 700, 257], [900, 1100, 255, 1025], [5000, 2049, 4096, 3]])
+def test_objective_exponentials_by_rollout_length(A, lens):
+    print("[case] grpo_objective exponentials %s" % lens, flush=True)
+    rng = np.random.default_rng(sum(lens))
+    T, beta = sum(lens), 0.04
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    ref = (rng.normal(size=T) * 0.2).astype(np.float32)
+    ref[rng.random(T) < 0.02] = 0.0
+    odd = np.array([699.9, 700.0, 700.1, -699.9, -700.0, -700.1, 745.0, -745.0, 800.0, -800.0, np.inf, -np.inf, np.nan], np.float32)
+    at = rng.choice(T, 26, replace=False)
+    ref[at] = np.tile(odd, 2)
+    adv = rng.normal(size=len(lens)).astype(np.float32)
+    ws = torch.empty(16 * len(lens), dtype=torch.uint8, device=DEV)          # room for one part a rollout
+    J, grad, n_clip = A.arrol_grpo_objective(torch.zeros(T, device=DEV), to_dev(ref, DEV), dev_i64(cu), to_dev(adv, DEV),
+                                             torch.full((len(lens),), 1.0, device=DEV), 0.2, 0.28, beta, workspace=ws)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        u, a, scale = ref.astype(np.float64), np.repeat(adv.astype(np.float64), lens), np.repeat(1.0 / np.array(lens), lens)
+        ratio, eu = np.exp(-u), np.exp(u)
+        plain, clamped = ratio * a, np.fmin(np.fmax(ratio, 1.0 - f32(0.2)), 1.0 + f32(0.28)) * a
+        want = ((np.where(plain <= clamped, plain, 0.0) - f32(beta) * (1.0 - eu)) * scale).astype(np.float32)
+    got = npy(grad)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    ok = np.isfinite(want)
+    # both exponentials within 2 ulp (4.4e-16 of terms of about 1 that cancel near u = 0), then one rounding to fp32
+    assert np.all(np.abs(got[ok] - want[ok]) <= 1e-7 * np.abs(want[ok]) + 1e-15 * scale[ok] * 4)
+    assert int(n_clip) == int(np.sum(clamped < plain)) and np.isnan(float(J))
+    ref[at] = 0.1
+    J = A.arrol_grpo_objective(torch.zeros(T, device=DEV), to_dev(ref, DEV), dev_i64(cu), to_dev(adv, DEV),
+                               torch.full((len(lens),), 1.0, device=DEV), 0.2, 0.28, beta, workspace=ws)[0]
+    u = ref.astype(np.float64); ratio, eu = np.exp(-u), np.exp(u)
+    terms = (np.minimum(ratio * a, np.clip(ratio, 1.0 - f32(0.2), 1.0 + f32(0.28)) * a) - f32(beta) * (eu - u - 1.0)) * scale
+    assert abs(float(J) - terms.sum()) <= 4e-15 * np.abs(terms).sum()
+
+
 # rollouts cut into parts: lengths around the 1,024 tokens of a part, none, and far more than the mean; the workspace that
 # decides how many parts there are (1, 2, 3 and the 8 the binding makes room for); the same bits again
 @pytest.mark.parametrize("room", [1, 2, 3, 8])
