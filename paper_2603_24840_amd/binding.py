@@ -139,7 +139,7 @@ def _import_marshal():
     made = getattr(module, "built_for", lambda: (0, "an unknown torch"))()
     if made != (ABI_VERSION, built_for()):
         raise ImportError("%s is built for version %d and %s, not %d and %s" % ((MARSHAL_PATH,) + made + (ABI_VERSION, built_for())))
-    module.setup(torch.nn.Parameter, Policy, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
+    module.setup(torch.nn.Parameter, Policy, _check)
     return module
 
 

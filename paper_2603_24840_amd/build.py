@@ -52,10 +52,11 @@ def build_marshal(verbose=True):
     t = os.path.dirname(torch.__file__)
     _run(shlex.split(os.environ.get("CXX") or "g++") +
          ["-O2", "-fPIC", "-shared", "-std=c++17", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-          '-DARROL_BUILT_FOR="%s"' % built_for(), "-I", os.path.join(ROOT, "include"),
+          '-DARROL_BUILT_FOR="%s"' % built_for(), "-D__HIP_PLATFORM_AMD__=1", "-I", os.path.join(ROOT, "include"),
+          "-isystem", os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path()))), "include"),
           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", LIB_DIR, "-larrol",
-          "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+          "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10",
           "-Wl,-rpath,$ORIGIN", "-Wl,-z,now"], verbose)      # a symbol that another torch lacks is missed on loading, not in a call
 
 

@@ -12,6 +12,7 @@
 #include <ATen/EmptyTensor.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <atomic>
@@ -23,8 +24,6 @@ namespace {
 
 PyObject* g_parameter = nullptr;      // torch.nn.Parameter
 PyObject* g_policy = nullptr;         // binding.Policy
-PyObject* g_device = nullptr;         // torch._C._cuda_getDevice
-PyObject* g_raw_stream = nullptr;     // torch._C._cuda_getCurrentRawStream
 PyObject* g_check = nullptr;          // binding._check
 
 void* data(const at::Tensor& t) { return t.data_ptr(); }
@@ -106,24 +105,22 @@ struct Unlocked {     // launches go without the interpreter lock, as ctypes cal
 };
 std::atomic<c10::Allocator*> g_allocator{nullptr};      // that of torch.empty's storages
 // An output: what torch.empty gives (the same allocator, on the current stream), without its way through the dispatcher
-// (0.9 -> 0.5 us).  entry() has seen to it that no mode is to be asked and that nothing fills new memory; the lock is let go,
-// since the allocator may wait for the device.
+// (0.9 -> 0.5 us).  entry() has seen to it that no mode is to be asked and that nothing fills new memory; called without the
+// interpreter lock, since the allocator may wait for the device.
 at::Tensor make(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
-    const Unlocked u;
     if (!g_allocator) g_allocator = at::empty({1}, at::TensorOptions().dtype(type).device(like.device())).storage().allocator();
     TORCH_CHECK(g_allocator.load());
     return at::detail::empty_generic(shape, g_allocator.load(), c10::DispatchKeySet(c10::DispatchKey::CUDA), type, std::nullopt);
 }
-// the current device's current stream, as binding._stream asks for it
+template <class T = void>
+T* made(at::Tensor& out, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
+    out = make(shape, type, like);
+    return static_cast<T*>(data(out));
+}
+// The current device's current stream, as torch's C layer gives it to binding._stream: asked of c10 itself (two Python calls were 0.25 us)
 void* stream(Args& a, const at::Tensor& like) {
-    PyObject* dev = PyObject_CallNoArgs(g_device);
-    const long current = dev ? PyLong_AsLong(dev) : -1;
-    PyObject* s = current == like.device().index() ? PyObject_CallOneArg(g_raw_stream, dev) : nullptr;   // make() allocates on the current device
-    Py_XDECREF(dev);
-    void* h = s ? PyLong_AsVoidPtr(s) : nullptr;
-    if (a.refuse(!s || PyErr_Occurred())) PyErr_Clear();
-    Py_XDECREF(s);
-    return h;
+    const auto s = c10::hip::getCurrentHIPStream();
+    return a.refuse(s.device_index() != like.device().index()) ? nullptr : s.stream();       // make() allocates on the current device
 }
 // The caller's uint8 tensor, or, for None (`text`: for a text, and nothing for None), one of `need` bytes for the time of the
 // call: the allocator hands it out again on the stream that the kernels run on.
@@ -131,11 +128,10 @@ struct Scratch {
     at::Tensor own;
     void* p = nullptr;
     size_t bytes = 0;
-    Scratch(Args& a, int i, size_t need, const at::Tensor& like, bool text = false) {
+    bool wanted = false;
+    Scratch(Args& a, int i, size_t need, bool text = false) {
         if (text ? PyUnicode_CheckExact(a[i]) : !a.given(i)) {
-            if (!need) return;
-            own = make({static_cast<int64_t>(need)}, at::kByte, like);
-            p = data(own);
+            wanted = need > 0;
             bytes = need;
         } else if (a.given(i)) {
             const at::Tensor& t = a.tensor(i, at::kByte);
@@ -144,8 +140,12 @@ struct Scratch {
             bytes = static_cast<size_t>(t.numel());
         }
     }
+    void get(const at::Tensor& like) {       // without the interpreter lock
+        if (wanted) p = made(own, {static_cast<int64_t>(bytes)}, at::kByte, like);
+    }
 };
 
+// f makes the outputs and launches
 template <class F>
 int launch(F f) {
     const Unlocked u;
@@ -191,10 +191,13 @@ PyObject* score(Args& a) {
     void* st = stream(a, h.t);
     if (a.odd) return nullptr;
     at::Tensor s, q;
-    if (!a.given(4) && want) { s = make({h.n}, at::kFloat, h.t); ps = static_cast<float*>(data(s)); }
-    if (!a.given(5)) { q = make({h.n}, at::kFloat, h.t); pq = static_cast<float*>(data(q)); }
-    const void* x = data(h.t);
-    if (failed("arrol_score", launch([&] { return arrol_score(x, h.stride, h.index, w, bias, h.n, h.d, ps, pq, st); }))) return nullptr;
+    const bool own_s = !a.given(4) && want, own_q = !a.given(5);
+    if (failed("arrol_score", launch([&] {
+            if (own_s) ps = made<float>(s, {h.n}, at::kFloat, h.t);
+            if (own_q) pq = made<float>(q, {h.n}, at::kFloat, h.t);
+            return arrol_score(data(h.t), h.stride, h.index, w, bias, h.n, h.d, ps, pq, st);
+        })))
+        return nullptr;
     return tuple(s.defined() ? wrap(std::move(s)) : keep(a[4]), q.defined() ? wrap(std::move(q)) : keep(a[5]));
 }
 
@@ -222,12 +225,14 @@ PyObject* score_mlp(Args& a) {
     if (a.odd) return nullptr;
     void* st = stream(a, h.t);
     if (a.odd) return nullptr;
-    const Scratch ws(a, 6, arrol_score_mlp_workspace_bytes(h.n, h.d, p.m), h.t, true);
+    Scratch ws(a, 6, arrol_score_mlp_workspace_bytes(h.n, h.d, p.m), true);
     if (a.odd) return nullptr;
-    at::Tensor s = make({h.n}, at::kFloat, h.t), q = make({h.n}, at::kFloat, h.t);
-    const void* x = data(h.t);
-    float *ps = static_cast<float*>(data(s)), *pq = static_cast<float*>(data(q));
-    if (failed("arrol_score_mlp", launch([&] { return arrol_score_mlp(x, h.stride, h.index, p.w1, p.b1, p.w2, b2, h.n, h.d, p.m, ps, pq, ws.p, ws.bytes, st); })))
+    at::Tensor s, q;
+    if (failed("arrol_score_mlp", launch([&] {
+            ws.get(h.t);
+            float *ps = made<float>(s, {h.n}, at::kFloat, h.t), *pq = made<float>(q, {h.n}, at::kFloat, h.t);
+            return arrol_score_mlp(data(h.t), h.stride, h.index, p.w1, p.b1, p.w2, b2, h.n, h.d, p.m, ps, pq, ws.p, ws.bytes, st);
+        })))
         return nullptr;
     return tuple(wrap(std::move(s)), wrap(std::move(q)));
 }
@@ -242,12 +247,14 @@ PyObject* score_grad(Args& a) {
     void* st = stream(a, h.t);
     if (a.odd) return nullptr;
     const size_t need = arrol_score_grad_workspace_bytes(h.n, h.d);
-    const Scratch ws(a, 5, need ? need : 1, h.t);
+    Scratch ws(a, 5, need ? need : 1);
     if (a.odd) return nullptr;
-    at::Tensor loss = make({1}, at::kFloat, h.t), gw = make({h.d}, at::kFloat, h.t), gb = make({1}, at::kFloat, h.t);
-    const void* x = data(h.t);
-    float *pl = static_cast<float*>(data(loss)), *pg = static_cast<float*>(data(gw)), *pb = static_cast<float*>(data(gb));
-    if (failed("arrol_score_grad", launch([&] { return arrol_score_grad(x, h.stride, h.index, pw, bias, py, h.n, h.d, pl, pg, pb, ws.p, ws.bytes, st); })))
+    at::Tensor loss, gw, gb;
+    if (failed("arrol_score_grad", launch([&] {
+            ws.get(h.t);
+            float *pl = made<float>(loss, {1}, at::kFloat, h.t), *pg = made<float>(gw, {h.d}, at::kFloat, h.t), *pb = made<float>(gb, {1}, at::kFloat, h.t);
+            return arrol_score_grad(data(h.t), h.stride, h.index, pw, bias, py, h.n, h.d, pl, pg, pb, ws.p, ws.bytes, st);
+        })))
         return nullptr;
     return tuple(wrap(std::move(loss)), wrap(std::move(gw)), wrap(std::move(gb)));
 }
@@ -264,15 +271,14 @@ PyObject* score_mlp_grad(Args& a) {
     void* st = stream(a, h.t);
     if (a.odd) return nullptr;
     const size_t need = arrol_score_mlp_grad_workspace_bytes(h.n, h.d, p.m, terms);
-    const Scratch ws(a, 8, need > 256 ? need : 256, h.t);
+    Scratch ws(a, 8, need > 256 ? need : 256);
     if (a.odd) return nullptr;
-    at::Tensor loss = make({1}, at::kFloat, h.t), g1 = make({p.m, h.d}, at::kFloat, h.t), gb1 = make({p.m}, at::kFloat, h.t),
-               g2 = make({p.m}, at::kFloat, h.t), gb2 = make({1}, at::kFloat, h.t);
-    const void* x = data(h.t);
-    float *pl = static_cast<float*>(data(loss)), *p1 = static_cast<float*>(data(g1)), *pb1 = static_cast<float*>(data(gb1)),
-          *p2 = static_cast<float*>(data(g2)), *pb2 = static_cast<float*>(data(gb2));
+    at::Tensor loss, g1, gb1, g2, gb2;
     if (failed("arrol_score_mlp_grad", launch([&] {
-            return arrol_score_mlp_grad(x, h.stride, h.index, p.w1, p.b1, p.w2, b2, py, h.n, h.d, p.m, pl, p1, pb1, p2, pb2, terms, ws.p, ws.bytes, st);
+            ws.get(h.t);
+            float *pl = made<float>(loss, {1}, at::kFloat, h.t), *p1 = made<float>(g1, {p.m, h.d}, at::kFloat, h.t), *pb1 = made<float>(gb1, {p.m}, at::kFloat, h.t),
+                  *p2 = made<float>(g2, {p.m}, at::kFloat, h.t), *pb2 = made<float>(gb2, {1}, at::kFloat, h.t);
+            return arrol_score_mlp_grad(data(h.t), h.stride, h.index, p.w1, p.b1, p.w2, b2, py, h.n, h.d, p.m, pl, p1, pb1, p2, pb2, terms, ws.p, ws.bytes, st);
         })))
         return nullptr;
     PyObject* out = PyDict_New();
@@ -314,10 +320,13 @@ PyObject* select(Args& a) {
     void* st = stream(a, prob);
     if (a.odd) return nullptr;
     at::Tensor mask, surv;
-    if (!a.given(5)) { mask = make({static_cast<int64_t>(groups) * G}, at::kByte, prob); pk = static_cast<uint8_t*>(data(mask)); }
-    if (!a.given(6)) { surv = make({static_cast<int64_t>(groups) * K}, at::kInt, prob); pi = static_cast<int32_t*>(data(surv)); }
-    const float* pp = static_cast<const float*>(data(prob));
-    if (failed("arrol_select", launch([&] { return arrol_select(pp, groups, G, K, rho, pk, pi, st); }))) return nullptr;
+    const bool own_mask = !a.given(5), own_surv = !a.given(6);
+    if (failed("arrol_select", launch([&] {
+            if (own_mask) pk = made<uint8_t>(mask, {static_cast<int64_t>(groups) * G}, at::kByte, prob);
+            if (own_surv) pi = made<int32_t>(surv, {static_cast<int64_t>(groups) * K}, at::kInt, prob);
+            return arrol_select(static_cast<const float*>(data(prob)), groups, G, K, rho, pk, pi, st);
+        })))
+        return nullptr;
     return tuple(mask.defined() ? wrap(std::move(mask)) : keep(a[5]), surv.defined() ? wrap(std::move(surv)) : keep(a[6]));
 }
 
@@ -328,11 +337,11 @@ PyObject* weighted_vote(Args& a) {
     if (a.odd) return nullptr;
     void* st = stream(a, prob);
     if (a.odd) return nullptr;
-    at::Tensor win = make({Q}, at::kInt, prob);
+    at::Tensor win;
     const float* pp = static_cast<const float*>(data(prob));
     const int32_t* pa = static_cast<const int32_t*>(data(ans));
-    int32_t* pw = static_cast<int32_t*>(data(win));
-    if (failed("arrol_weighted_vote", launch([&] { return arrol_weighted_vote(pp, pa, Q, C, A, pw, nullptr, st); }))) return nullptr;
+    if (failed("arrol_weighted_vote", launch([&] { return arrol_weighted_vote(pp, pa, Q, C, A, made<int32_t>(win, {Q}, at::kInt, prob), nullptr, st); })))
+        return nullptr;
     return wrap(std::move(win));
 }
 
@@ -344,11 +353,14 @@ PyObject* histogram(Args& a) {
     const int64_t M = s.numel();
     void* st = stream(a, s);
     if (a.odd) return nullptr;
-    at::Tensor pos = make({B}, at::kLong, s), neg = make({B}, at::kLong, s);
+    at::Tensor pos, neg;
     const float* ps = static_cast<const float*>(data(s));
     const uint8_t* pl = static_cast<const uint8_t*>(data(l));
-    int64_t *pp = static_cast<int64_t*>(data(pos)), *pn = static_cast<int64_t*>(data(neg));
-    if (failed("arrol_histogram", launch([&] { return arrol_histogram(ps, pl, M, B, pp, pn, st); }))) return nullptr;
+    if (failed("arrol_histogram", launch([&] {
+            int64_t *pp = made<int64_t>(pos, {B}, at::kLong, s), *pn = made<int64_t>(neg, {B}, at::kLong, s);
+            return arrol_histogram(ps, pl, M, B, pp, pn, st);
+        })))
+        return nullptr;
     return tuple(wrap(std::move(pos)), wrap(std::move(neg)));
 }
 
@@ -365,11 +377,13 @@ PyObject* calibrate(Args& a) {
     const int32_t B = static_cast<int32_t>(pos.numel());
     void* st = stream(a, pos);
     if (a.odd) return nullptr;
-    at::Tensor q = make({B}, at::kFloat, pos), p = make({B}, at::kFloat, pos), delta = make({1}, at::kDouble, pos);
+    at::Tensor q, p, delta;
     const int64_t *pp = static_cast<const int64_t*>(data(pos)), *pn = static_cast<const int64_t*>(data(neg));
-    float *fq = static_cast<float*>(data(q)), *fp = static_cast<float*>(data(p));
-    double* pd = static_cast<double*>(data(delta));
-    if (failed("arrol_calibrate", launch([&] { return arrol_calibrate(pp, pn, B, policy, fq, fp, pd, st); }))) return nullptr;
+    if (failed("arrol_calibrate", launch([&] {
+            float *fq = made<float>(q, {B}, at::kFloat, pos), *fp = made<float>(p, {B}, at::kFloat, pos);
+            return arrol_calibrate(pp, pn, B, policy, fq, fp, made<double>(delta, {1}, at::kDouble, pos), st);
+        })))
+        return nullptr;
     return tuple(wrap(std::move(q)), wrap(std::move(p)), wrap(std::move(delta)));
 }
 
@@ -381,14 +395,15 @@ PyObject* prune_bernoulli(Args& a) {
     const int64_t N = s.numel();
     void* st = stream(a, s);
     if (a.odd) return nullptr;
-    at::Tensor mask = make({N}, at::kByte, s), idx = make({N}, at::kInt, s), n = make({1}, at::kInt, s), p;
-    if (want) p = make({N}, at::kFloat, s);
+    at::Tensor mask, idx, n, p;
     const float *ps = static_cast<const float*>(data(s)), *pu = static_cast<const float*>(data(u)), *pl = static_cast<const float*>(data(lut));
-    float* pp = want ? static_cast<float*>(data(p)) : nullptr;
-    uint8_t* pm = static_cast<uint8_t*>(data(mask));
-    int32_t *pi = static_cast<int32_t*>(data(idx)), *pn = static_cast<int32_t*>(data(n));
     const int32_t B = static_cast<int32_t>(lut.numel());
-    if (failed("arrol_prune_bernoulli", launch([&] { return arrol_prune_bernoulli(ps, pu, N, pl, B, pp, pm, pi, pn, st); }))) return nullptr;
+    if (failed("arrol_prune_bernoulli", launch([&] {
+            uint8_t* pm = made<uint8_t>(mask, {N}, at::kByte, s);
+            int32_t *pi = made<int32_t>(idx, {N}, at::kInt, s), *pn = made<int32_t>(n, {1}, at::kInt, s);
+            return arrol_prune_bernoulli(ps, pu, N, pl, B, want ? made<float>(p, {N}, at::kFloat, s) : nullptr, pm, pi, pn, st);
+        })))
+        return nullptr;
     PyObject* out = PyDict_New();
     if (!out) return nullptr;
     if (!put(out, "keep_mask", wrap(std::move(mask))) || !put(out, "survivor_idx", wrap(std::move(idx))) || !put(out, "n_survivors", wrap(std::move(n))) ||
@@ -408,11 +423,14 @@ PyObject* grpo_advantage(Args& a) {
     const int64_t N = r.numel(), groups = off.numel() - 1;
     void* st = stream(a, r);
     if (a.odd) return nullptr;
-    at::Tensor adv = make({N}, at::kFloat, r), wgt = make({N}, at::kFloat, r);
+    at::Tensor adv, wgt;
     const float* pr = static_cast<const float*>(data(r));
     const int64_t* po = static_cast<const int64_t*>(data(off));
-    float *pa = static_cast<float*>(data(adv)), *pw = static_cast<float*>(data(wgt));
-    if (failed("arrol_grpo_advantage", launch([&] { return arrol_grpo_advantage_all(pr, po, N, groups, ddof, eps, pa, pw, st); }))) return nullptr;
+    if (failed("arrol_grpo_advantage", launch([&] {
+            float *pa = made<float>(adv, {N}, at::kFloat, r), *pw = made<float>(wgt, {N}, at::kFloat, r);
+            return arrol_grpo_advantage_all(pr, po, N, groups, ddof, eps, pa, pw, st);
+        })))
+        return nullptr;
     return tuple(wrap(std::move(adv)), wrap(std::move(wgt)));
 }
 
@@ -428,16 +446,17 @@ PyObject* grpo_objective(Args& a) {
     void* st = stream(a, lp);
     if (a.odd) return nullptr;
     const size_t need = 8 * arrol_grpo_objective_workspace_bytes(static_cast<int32_t>(n));
-    const Scratch ws(a, 9, need > 16 ? need : 16, lp);
+    Scratch ws(a, 9, need > 16 ? need : 16);
     if (a.odd) return nullptr;
-    at::Tensor J = make({1}, at::kDouble, lp), grad, clip = make({1}, at::kLong, lp);
-    if (want) grad = make({T}, at::kFloat, lp);
+    at::Tensor J, grad, clip;
     const float* pl = static_cast<const float*>(data(lp));
     const int64_t* pc = static_cast<const int64_t*>(data(cu));
-    double* pj = static_cast<double*>(data(J));
-    float* pg = want ? static_cast<float*>(data(grad)) : nullptr;
-    int64_t* pn = static_cast<int64_t*>(data(clip));
-    if (failed("arrol_grpo_objective", launch([&] { return arrol_grpo_objective(pl, pr, pc, T, n, pa, pw, lo, hi, beta, pj, pg, pn, ws.p, ws.bytes, st); })))
+    if (failed("arrol_grpo_objective", launch([&] {
+            ws.get(lp);
+            double* pj = made<double>(J, {1}, at::kDouble, lp);
+            int64_t* pn = made<int64_t>(clip, {1}, at::kLong, lp);
+            return arrol_grpo_objective(pl, pr, pc, T, n, pa, pw, lo, hi, beta, pj, want ? made<float>(grad, {T}, at::kFloat, lp) : nullptr, pn, ws.p, ws.bytes, st);
+        })))
         return nullptr;
     return tuple(wrap(std::move(J)), want ? wrap(std::move(grad)) : keep(Py_None), wrap(std::move(clip)));
 }
@@ -468,12 +487,12 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyObject* built_for(PyObject*, PyObject*) { return Py_BuildValue("is", ARROL_VERSION, ARROL_BUILT_FOR); }
 
 PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != 5) {
-        PyErr_SetString(PyExc_TypeError, "5 arguments expected");
+    if (n != 3) {
+        PyErr_SetString(PyExc_TypeError, "3 arguments expected");
         return nullptr;
     }
-    PyObject** slots[5] = {&g_parameter, &g_policy, &g_device, &g_raw_stream, &g_check};
-    for (int i = 0; i < 5; ++i) {
+    PyObject** slots[3] = {&g_parameter, &g_policy, &g_check};
+    for (int i = 0; i < 3; ++i) {
         Py_INCREF(args[i]);
         Py_XDECREF(*slots[i]);
         *slots[i] = args[i];
