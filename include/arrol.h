@@ -216,7 +216,7 @@ int arrol_logprob(const void* hidden, const void* lm_head, const int32_t* target
 /*
  * Test and measurement aid, a host computation: what arrol_logprob takes for a call, so that a test can say what it reaches.
  * *kernel       0 the general one (d no multiple of 64, or rows of many megabytes), 1 the ring kernel, 2 the block kernel
- * *tile_rows, *tile_tokens   of a workgroup's tile: 256 x 256 of kernels 0 and 1, 256 x 64, 128 or 192 or 160 x 320 of 2
+ * *tile_rows, *tile_tokens   of a workgroup's tile: 256 x 256 of kernels 0 and 1, 256 x 64, 128 or 192, 208 x 256 or 160 x 320 of 2
  * *splits       ranges of tiles that the vocabulary is cut into
  */
 int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* kernel, int32_t* tile_rows,

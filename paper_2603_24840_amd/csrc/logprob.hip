@@ -211,6 +211,102 @@ __device__ __forceinline__ void tile_epilogue16(f32x4 (&acc)[TI][TJ], LaneState<
         // difference first: exactly 0 when the maximum did not move (also for the -1e30 sentinel)
         st.run_s[j] = st.run_s[j] * __builtin_amdgcn_exp2f((st.run_m[j] - m_new) * kLog2e) + sum;
         st.run_m[j] = m_new;
+    }
+}
+
+// End of a workgroup's vocabulary range: merge the two lane halves (same token, different vocab
+// rows), then the WM waves that share a token range (through LDS, `red` = [WM][3][BN] floats, the
+// staging memory being idle by now), and write the (max, sumexp, target logit) partial of split sp.
+template <int TN, int WM, int WN, int BN, int NT>
+__device__ __forceinline__ void write_partials(LaneState<TN>& st, float* red, int wm, int wn, int l31, int lh,
+                                               int tid, int64_t tok0, int64_t T, int sp, float* part) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const float om = __shfl_xor(st.run_m[j], 32, ARROL_WAVE);
+        const float os = __shfl_xor(st.run_s[j], 32, ARROL_WAVE);
+        const float oz = __shfl_xor(st.tgt_z[j], 32, ARROL_WAVE);
+        const float m = fmaxf(st.run_m[j], om);
+        st.run_s[j] = st.run_s[j] * __builtin_amdgcn_exp2f((st.run_m[j] - m) * kLog2e) +
+                      os * __builtin_amdgcn_exp2f((om - m) * kLog2e);
+        st.run_m[j] = m;
+        st.tgt_z[j] += oz;
+    }
+    if (lh == 0) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = wn * (BN / WN) + j * 32 + l31;
+            red[(wm * 3 + 0) * BN + col] = st.run_m[j];
+            red[(wm * 3 + 1) * BN + col] = st.run_s[j];
+            red[(wm * 3 + 2) * BN + col] = st.tgt_z[j];
+        }
+    }
+    __syncthreads();
+    for (int col = tid; col < BN; col += NT) {
+        const int64_t t = tok0 + col;
+        if (t >= T) continue;
+        float m = red[col], s = red[BN + col], z = red[2 * BN + col];
+#pragma unroll
+        for (int w = 1; w < WM; ++w) {
+            const float om = red[(w * 3 + 0) * BN + col], os = red[(w * 3 + 1) * BN + col];
+            const float mm = fmaxf(m, om);
+            s = s * __builtin_amdgcn_exp2f((m - mm) * kLog2e) + os * __builtin_amdgcn_exp2f((om - mm) * kLog2e);
+            m = mm;
+            z += red[(w * 3 + 2) * BN + col];
+        }
+        float* p = part + static_cast<int64_t>(sp) * 3 * T + t;
+        p[0] = m;
+        p[T] = s;
+        p[2 * T] = z;
+    }
+}
+
+// The same for the 16x16x32 MFMA result layout: acc[i][j][v] is the logit of vocab row vrow0 + i*16 + lq*4 + v
+// (lq = lane / 16) for the lane's token of block j (token j*16 + lane%16 of the wave's range).  The accumulators
+// are left as they are (the next tile's first MFMAs take 0 as their addend).
+template <int TI, int TJ, int WROWS>
+__device__ __forceinline__ void tile_epilogue16(f32x4 (&acc)[TI][TJ], LaneState<TJ>& st, int vrow0, int V, int lq,
+                                                const int (&tgt)[TJ]) {
+    if (vrow0 + WROWS > V) {  // tile hangs over the end of the vocabulary
+        const int lim = V - vrow0 - lq * 4;   // rows of this lane from here on are past the end: one value per tile,
+#pragma unroll                                // compared with constants (nothing per (i, v) to keep in registers)
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool dead = i * 16 + v >= lim;
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[i][j][v] = dead ? -INFINITY : acc[i][j][v];
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+        const int rel = tgt[j] - vrow0;
+        const bool mine = rel >= 0 && rel < WROWS && ((rel >> 2) & 3) == lq;
+        if (__any(mine)) {
+            const int code = mine ? ((rel >> 4) * 4 + (rel & 3)) : -1;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (code == i * 4 + v) st.tgt_z[j] = acc[i][j][v];
+        }
+        float mx = acc[0][j][0];
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mx = fmaxf(mx, acc[i][j][v]);
+        const float m_new = fmaxf(st.run_m[j], mx);
+        const float neg = -m_new * kLog2e;
+        // of more than 8 rows in two sums: one of all 52 terms rounds more than 32 terms do, and waits on itself longer
+        constexpr int kSums = TI > 8 ? 2 : 1;
+        float part[kSums] = {};
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[v % kSums] += __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], kLog2e, neg));
+        const float sum = kSums == 2 ? part[0] + part[kSums - 1] : part[0];
+        // difference first: exactly 0 when the maximum did not move (also for the -1e30 sentinel)
+        st.run_s[j] = st.run_s[j] * __builtin_amdgcn_exp2f((st.run_m[j] - m_new) * kLog2e) + sum;
+        st.run_m[j] = m_new;
         __builtin_amdgcn_sched_barrier(0);   // one token column at a time: keeps the temporaries of the exp chains few
     }
 }
@@ -722,8 +818,9 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Block kernel (d a multiple of 64, up to some 600 tokens): 32 TI vocabulary rows x 64 TJ tokens per workgroup of 2 x 4
-// wavefronts, the narrower forms of the tile above for batches that would leave much of a 256-token block empty.
+// Block kernel (d a multiple of 64, up to some 600 tokens): 16 TI WM vocabulary rows x 64 TJ tokens per workgroup of WM x 4
+// wavefronts (WM is 2, of the 208 x 256 form 1): other forms of the tile above for batches that would leave much of a 256-token block empty
+// or of the chip idle.
 //
 // What bounds it is the bytes in flight: W comes from HBM, every line once, some 1.2 us away under load; the loads of a
 // wavefront complete in order, so H's, from the L2, wait behind them; and the LDS holds under three K64 steps.  So a step
@@ -740,19 +837,27 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
 // from the L2 it would be 160, without any loads 130.  Tried and slower: W and H fetched by different wavefronts, each with
 // its own order (311 tokens: 242); W straight to registers, several steps ahead (128 tokens: 148; half lines at a time).
 //
+// 208 x 256 (WM = 1, four wavefronts with the registers of a SIMD each) is for 193 to 256 tokens, where 256 x 256 tiles leave room for two
+// K64 steps and the ring kernel, in 32-column slots of them, waits for W.  13 x 4 MFMAs a chunk fill the registers with one set of W's
+// fragments, so a fragment's successor is read over it; three steps of W fit the LDS.  At 151,936 x 2048 and 200 / 256 tokens 171 / 171 ->
+// 158 / 158 us (ring kernel before), 100,352 x 2048 119 / 125 -> 106 / 107, 49,152 x 4096 124 / 121 -> 98 / 102, 50,000 x 3072 with 512 152 -> 139.
+// Of the 158, 119 are left without loads and 138 with W from the L2.  In the same manner 208 x 320 spills, 160 x 320 gains 2 % at 311
+// tokens and loses 3 at others, and tiles of even shares of 16-row units instead of 208 rows and a short last round gain nothing.
+//
 // Slot layout: 16-byte chunk c of row r sits at position c ^ (r & 6) of its 128-byte row: by the serving rule given at the
 // ring kernel's fragment reads, lanes that share a bank group differ in lane bit 3 alone: no conflicts.
 // ---------------------------------------------------------------------------------------------
-template <int TI_, int TJ_, int NA_, int NB_>
+template <int TI_, int TJ_, int NA_, int NB_, int WM_ = 2>
 struct BlockTile {
     static constexpr int TI = TI_, TJ = TJ_, NA = NA_, NB = NB_;
-    static constexpr int WM = 2, WN = 4, NW = WM * WN, NT = NW * ARROL_WAVE;
+    static constexpr int WM = WM_, WN = 4, NW = WM * WN, NT = NW * ARROL_WAVE;
     static constexpr int BM = 16 * TI * WM, BN = 16 * TJ * WN;
     static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;   // one slot: K64 of an operand
     static constexpr int LDS_BYTES = NA * A_BYTES + NB * B_BYTES;
     static constexpr int GA = BM / 8;                              // load instructions (8 rows x 128 bytes) per slot of W
     static constexpr int LA = (GA + NW - 1) / NW, LB = BN / 8 / NW, L = LA + LB;   // per wavefront; surplus ones repeat the last
-    static constexpr int BAR = TI == 8 ? 1 : 0;
+    static constexpr bool ONE_SET = WM == 1;                       // of W's fragments: of two, 13 rows x 4 would not fit the registers
+    static constexpr int BAR = TI >= 8 ? 1 : 0;
     static constexpr int PER_ROW = 3;                              // loads behind each row of MFMAs from BAR on
     // in flight at the barrier of pair p + 1: what was requested after H(p + 2)
     static constexpr int FLY = (NA > NB ? LA : 0) + (NB - 2) * L;
@@ -818,6 +923,7 @@ __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
         a_base += 128;
         if (++a_k == n_k64) { a_k = 0; a_base -= row_bytes; }
         if (a_k == k_start && a_vt + 1 < vt_hi) {      // past the last tile: its lines again, into slots nobody reads
+            if (C::ONE_SET) asm volatile("");          // a branch: here the compiler would form the next tile's offsets every time
             a_base += tile_bytes;
             point_at_tile(++a_vt);
         }
@@ -840,9 +946,9 @@ __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
     f32x4 acc[TI][TJ];
     const unsigned f_off[2] = {static_cast<unsigned>(l15 * 128 + ((lq ^ (l15 & 6)) << 4)),
                                static_cast<unsigned>(l15 * 128 + (((lq + 4) ^ (l15 & 6)) << 4))};
-    bf16x8 fa[2][TI], fb[2][TJ];       // fragments of a pair's first / second chunk
+    bf16x8 fa[C::ONE_SET ? 1 : 2][TI], fb[2][TJ];   // fragments of a pair's first / second chunk
     auto read_a = [&](int slot, int h, int i) {
-        fa[h][i] = *reinterpret_cast<const bf16x8*>(lds + (f_off[h] + slot * C::A_BYTES + wm * (BM / C::WM) * 128) + i * 2048);
+        fa[C::ONE_SET ? 0 : h][i] = *reinterpret_cast<const bf16x8*>(lds + (f_off[h] + slot * C::A_BYTES + wm * (BM / C::WM) * 128) + i * 2048);
     };
     auto read_b = [&](int slot, int h, int j) {
         fb[h][j] = *reinterpret_cast<const bf16x8*>(lds + (f_off[h] + NA * C::A_BYTES + slot * C::B_BYTES + wn * (BN / C::WN) * 128) + j * 2048);
@@ -875,23 +981,51 @@ __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
     auto chunk = [&](auto second, auto first) {
         constexpr int h = decltype(second)::value ? 1 : 0, hn = 1 - h;
         if (h) { sa = sa + 1 == NA ? 0 : sa + 1; sb = sb + 1 == NB ? 0 : sb + 1; }
+        auto mfma = [&](int i, int jj) {
+            const int j = (i & 1) ? TJ - 1 - jj : jj;
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[C::ONE_SET ? 0 : h][i], fb[h][j], decltype(first)::value ? zero : acc[i][j], 0, 0, 0);
+        };
+        auto next_pair = [&]() {
+            // the next pair has landed, for every wavefront, and everybody's fragments of this one are in registers
+            wait_vmcnt<C::FLY>();
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
+            __syncthreads();
+        };
+        if constexpr (C::ONE_SET) {
+            // One wavefront to a SIMD: nobody fills the matrix pipe while it issues anything else, so at most a read and a load follow each
+            // MFMA.  A fragment of W is read over its predecessor once that one's row has been issued.
+            constexpr int FROM = h ? C::BAR + 1 : 0;   // rows before the barrier
+            static_assert((TI - C::BAR - 1) * TJ >= L && (TI - FROM) * TJ >= TJ + FROM, "all loads in the second chunk, all reads");
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+#pragma unroll
+                for (int jj = 0; jj < TJ; ++jj) {
+                    mfma(i, jj);
+                    const int n = (i - FROM) * TJ + jj;     // MFMAs behind the barrier
+                    if (n >= 0) {
+                        if (h && n < L) issue_one(n);
+                        if (n < TJ) read_b(sb, hn, n);
+                        else if (n < TJ + FROM) read_a(sa, hn, n - TJ);
+                        else if (i > FROM && jj == TJ - 1) read_a(sa, hn, i - 1);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (h && i == C::BAR) next_pair();
+            }
+            read_a(sa, hn, TI - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (h) { advance_b(); advance_a(); }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int jj = 0; jj < TJ; ++jj) {
-                const int j = (i & 1) ? TJ - 1 - jj : jj;
-                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], decltype(first)::value ? zero : acc[i][j], 0, 0, 0);
-            }
+            for (int jj = 0; jj < TJ; ++jj) mfma(i, jj);
             __builtin_amdgcn_sched_barrier(0);
             if (i == C::BAR) {
-                if (h) {
-                    // the next pair has landed, for every wavefront, and everybody's fragments of this one are in registers
-                    wait_vmcnt<C::FLY>();
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
-                    __syncthreads();
-                }
+                if (h) next_pair();
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) read_b(sb, hn, j);
 #pragma unroll
@@ -986,16 +1120,21 @@ static_assert(MainTile::BM == FastTile::BM && MainTile::BN == FastTile::BN, "one
 using Block64 = BlockTile<8, 1, 4, 3>;     // 256 vocabulary rows x 64 tokens
 using Block128 = BlockTile<8, 2, 3, 3>;    // 256 x 128
 using Block192 = BlockTile<8, 3, 3, 2>;    // 256 x 192
+using Block256 = BlockTile<13, 4, 3, 2, 1>; // 208 x 256
 using Block320 = BlockTile<5, 5, 3, 2>;    // 160 x 320
 
-enum LogprobForm { kFormRing, kForm64, kForm128, kForm192, kForm320, kForms };
+enum LogprobForm { kFormRing, kForm64, kForm128, kForm192, kForm256, kForm320, kForms };
 struct FormSize { int bm, bn; double step; };
 // Vocabulary rows and tokens of a workgroup's tile; microseconds per K64 step of a tile when the chip is full, measured over
 // 50,000 to 151,936 x 1024 to 4096 with up to 640 tokens (from there on the ring kernel's step falls to 1.45).
 // They choose within 2 % of the best form at most of 15 vocabularies and widths x 14 token counts; the worst: 65,536 x 4096 with 250
 // tokens (ring 170 us, 256 x 128 tiles 140), 65,536 x 2048 with 577 to 640 (256 x 192 and 160 x 320 170 us, the ring 159).
 constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Block64::BM, Block64::BN, 1.15}, {Block128::BM, Block128::BN, 1.25},
-                                        {Block192::BM, Block192::BN, 1.42}, {Block320::BM, Block320::BN, 1.42}};
+                                        {Block192::BM, Block192::BN, 1.42}, {Block256::BM, Block256::BN, 1.45}, {Block320::BM, Block320::BN, 1.42}};
+// The 208 x 256 form beats the ring kernel, where both take as many rounds, by 5 to 24 % while W comes from memory, and loses 3 to 10 % where
+// the 256 MiB cache in front of it holds W from the call before (28 vocabularies and widths x 200, 256 and 512 tokens: 50,257 x 2048
+// 51 -> 54 us, 100,003 x 1280 64 -> 67, 100,003 x 1536 90 -> 82, 151,936 x 1024 87 -> 83): it is taken from that size on.
+constexpr int64_t kCachedElements = 128 << 20;
 constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;
 
 // The ring and block kernels give a lane its row of a tile as a 32-bit byte offset; of longer rows the general kernel's are 64-bit.
@@ -1037,11 +1176,12 @@ double pick_splits(int n_tb, int n_vt, int& n_sp) {
 
 Plan make_plan(int64_t T, int V, int d, int n_splits) {
     Plan p = {};
-    // The form whose tiles come out cheapest.  At 151,936 x 2048: 64-, 128- and 192-token blocks for up to as many tokens, the
-    // ring kernel up to 256, 160 x 320 up to 320, 2 x 192 up to 384, the ring to 512 (262 us; 3 x 192: 308), 3 x 192 to 576.
+    // The form whose tiles come out cheapest.  At 151,936 x 2048: 64-, 128- and 192-token blocks for up to as many tokens,
+    // 208 x 256 up to 256, 160 x 320 up to 320, 2 x 192 up to 384, the ring to 512 (262 us; 3 x 192: 308), 3 x 192 to 576.
     double best = -1.0;
     for (int f = 0; f < kForms; ++f) {
         if (f != kFormRing && (d % 64 || T > kBlockTokens || !offsets_fit(f, d))) continue;
+        if (f == kForm256 && static_cast<int64_t>(V) * d <= kCachedElements) continue;
         const int n_tb = static_cast<int>((T + kFormSize[f].bn - 1) / kFormSize[f].bn), n_vt = (V + kFormSize[f].bm - 1) / kFormSize[f].bm;
         const int cap = (V + MainTile::BM - 1) / MainTile::BM;        // of splits given: <= n_vt for every form
         int sp = n_splits < cap ? n_splits : cap;
@@ -1117,6 +1257,7 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
     else if (p.form == kForm64) rc = launch_logprob<logprob_block_kernel<Block64>, Block64>(g, st, a);
     else if (p.form == kForm128) rc = launch_logprob<logprob_block_kernel<Block128>, Block128>(g, st, a);
     else if (p.form == kForm192) rc = launch_logprob<logprob_block_kernel<Block192>, Block192>(g, st, a);
+    else if (p.form == kForm256) rc = launch_logprob<logprob_block_kernel<Block256>, Block256>(g, st, a);
     else if (p.form == kForm320) rc = launch_logprob<logprob_block_kernel<Block320>, Block320>(g, st, a);
     else rc = launch_logprob<logprob_ring_kernel<FastTile>, FastTile>(g, st, a);
     if (rc != ARROL_OK) return rc;

@@ -319,6 +319,24 @@ def test_logprob_tiles_over_several_vocabulary_tiles(A, T, V, d, splits, tile):
     assert torch.equal(one, two)
 
 
+# 208 x 256 tiles: one to four vocabulary tiles a workgroup, the last one of the vocabulary of 163, 80 and 1 rows; one token block and
+# two; 21 to 26 K64 steps, all six places that a step's slots (three of W, two of H) can be in when the next tile begins, and 42
+@pytest.mark.parametrize("T,V,d,splits", [(193, 100003, 64 * 21, 161), (256, 100003, 64 * 22, 130), (200, 100049, 64 * 23, 161),
+                                          (256, 100049, 64 * 24, 130), (193, 100003, 64 * 25, 161), (240, 100003, 64 * 26, 0), (512, 50000, 64 * 42, 0)])
+def test_logprob_four_wavefront_tiles(A, T, V, d, splits):
+    say("logprob 208 x 256 T=%d V=%d d=%d splits=%d" % (T, V, d, splits))
+    assert logprob_kernel(A, T, V, d, splits)[:3] == (2, 208, 256)
+    g = torch.Generator(device=DEV); g.manual_seed(T * 7 + V + d)
+    hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    lm_head = (torch.randn(V, d, generator=g, device=DEV) * (2.0 * d ** -0.5)).to(torch.bfloat16)
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    targets[0] = 0; targets[-1] = V - 1
+    lm_head[torch.arange(0, V, 97, device=DEV)] *= 3         # the running maximum moves from tile to tile
+    check_logprob(A, hidden, lm_head, targets, n_splits=splits)
+    one, two = (A.arrol_logprob(hidden, lm_head, targets, n_splits=splits) for _ in range(2))
+    assert torch.equal(one, two)
+
+
 @pytest.mark.parametrize("splits", [1, 3, 16])
 def test_logprob_ring_kernel_independent_of_vocab_splits(A, splits):
     say("logprob ring forced splits=%d" % splits)
