@@ -203,99 +203,6 @@ __device__ __forceinline__ void tile_epilogue16(f32x4 (&acc)[TI][TJ], LaneState<
             for (int v = 0; v < 4; ++v) mx = fmaxf(mx, acc[i][j][v]);
         const float m_new = fmaxf(st.run_m[j], mx);
         const float neg = -m_new * kLog2e;
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], kLog2e, neg));
-        // difference first: exactly 0 when the maximum did not move (also for the -1e30 sentinel)
-        st.run_s[j] = st.run_s[j] * __builtin_amdgcn_exp2f((st.run_m[j] - m_new) * kLog2e) + sum;
-        st.run_m[j] = m_new;
-    }
-}
-
-// End of a workgroup's vocabulary range: merge the two lane halves (same token, different vocab
-// rows), then the WM waves that share a token range (through LDS, `red` = [WM][3][BN] floats, the
-// staging memory being idle by now), and write the (max, sumexp, target logit) partial of split sp.
-template <int TN, int WM, int WN, int BN, int NT>
-__device__ __forceinline__ void write_partials(LaneState<TN>& st, float* red, int wm, int wn, int l31, int lh,
-                                               int tid, int64_t tok0, int64_t T, int sp, float* part) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const float om = __shfl_xor(st.run_m[j], 32, ARROL_WAVE);
-        const float os = __shfl_xor(st.run_s[j], 32, ARROL_WAVE);
-        const float oz = __shfl_xor(st.tgt_z[j], 32, ARROL_WAVE);
-        const float m = fmaxf(st.run_m[j], om);
-        st.run_s[j] = st.run_s[j] * __builtin_amdgcn_exp2f((st.run_m[j] - m) * kLog2e) +
-                      os * __builtin_amdgcn_exp2f((om - m) * kLog2e);
-        st.run_m[j] = m;
-        st.tgt_z[j] += oz;
-    }
-    if (lh == 0) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = wn * (BN / WN) + j * 32 + l31;
-            red[(wm * 3 + 0) * BN + col] = st.run_m[j];
-            red[(wm * 3 + 1) * BN + col] = st.run_s[j];
-            red[(wm * 3 + 2) * BN + col] = st.tgt_z[j];
-        }
-    }
-    __syncthreads();
-    for (int col = tid; col < BN; col += NT) {
-        const int64_t t = tok0 + col;
-        if (t >= T) continue;
-        float m = red[col], s = red[BN + col], z = red[2 * BN + col];
-#pragma unroll
-        for (int w = 1; w < WM; ++w) {
-            const float om = red[(w * 3 + 0) * BN + col], os = red[(w * 3 + 1) * BN + col];
-            const float mm = fmaxf(m, om);
-            s = s * __builtin_amdgcn_exp2f((m - mm) * kLog2e) + os * __builtin_amdgcn_exp2f((om - mm) * kLog2e);
-            m = mm;
-            z += red[(w * 3 + 2) * BN + col];
-        }
-        float* p = part + static_cast<int64_t>(sp) * 3 * T + t;
-        p[0] = m;
-        p[T] = s;
-        p[2 * T] = z;
-    }
-}
-
-// The same for the 16x16x32 MFMA result layout: acc[i][j][v] is the logit of vocab row vrow0 + i*16 + lq*4 + v
-// (lq = lane / 16) for the lane's token of block j (token j*16 + lane%16 of the wave's range).  The accumulators
-// are left as they are (the next tile's first MFMAs take 0 as their addend).
-template <int TI, int TJ, int WROWS>
-__device__ __forceinline__ void tile_epilogue16(f32x4 (&acc)[TI][TJ], LaneState<TJ>& st, int vrow0, int V, int lq,
-                                                const int (&tgt)[TJ]) {
-    if (vrow0 + WROWS > V) {  // tile hangs over the end of the vocabulary
-        const int lim = V - vrow0 - lq * 4;   // rows of this lane from here on are past the end: one value per tile,
-#pragma unroll                                // compared with constants (nothing per (i, v) to keep in registers)
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const bool dead = i * 16 + v >= lim;
-#pragma unroll
-                for (int j = 0; j < TJ; ++j) acc[i][j][v] = dead ? -INFINITY : acc[i][j][v];
-            }
-    }
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-        const int rel = tgt[j] - vrow0;
-        const bool mine = rel >= 0 && rel < WROWS && ((rel >> 2) & 3) == lq;
-        if (__any(mine)) {
-            const int code = mine ? ((rel >> 4) * 4 + (rel & 3)) : -1;
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (code == i * 4 + v) st.tgt_z[j] = acc[i][j][v];
-        }
-        float mx = acc[0][j][0];
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) mx = fmaxf(mx, acc[i][j][v]);
-        const float m_new = fmaxf(st.run_m[j], mx);
-        const float neg = -m_new * kLog2e;
         // of more than 8 rows in two sums: one of all 52 terms rounds more than 32 terms do, and waits on itself longer
         constexpr int kSums = TI > 8 ? 2 : 1;
         float part[kSums] = {};
