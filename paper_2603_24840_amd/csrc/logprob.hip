@@ -773,7 +773,7 @@ struct BlockTile {
     static_assert((TI - BAR) * PER_ROW >= L, "all loads in the second chunk");
 };
 
-template <class C>
+template <class C, bool STREAM = false>   // STREAM: W's lines are each read once and come from memory (kStreamElements)
 __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int BM = C::BM, BN = C::BN, TI = C::TI, TJ = C::TJ, NA = C::NA, NB = C::NB, L = C::L;
@@ -823,7 +823,8 @@ __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
         const unsigned dst = b ? lds0 + NA * C::A_BYTES + b_slot * C::B_BYTES + (wave * C::LB + n) * 1024
                                : lds0 + a_slot * C::A_BYTES + a_group(n - C::LB) * 1024;
         const unsigned voff = b ? b_voff[b ? n : 0] : a_voff[b ? 0 : n - C::LB];
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(b ? b_base : a_base), "s"(dst) : "memory");
+        if (!b && STREAM) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(a_base), "s"(dst) : "memory");
+        else asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(b ? b_base : a_base), "s"(dst) : "memory");
     };
     auto advance_a = [&]() {
         a_slot = a_slot + 1 == NA ? 0 : a_slot + 1;
@@ -1042,6 +1043,12 @@ constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Blo
 // the 256 MiB cache in front of it holds W from the call before (28 vocabularies and widths x 200, 256 and 512 tokens: 50,257 x 2048
 // 51 -> 54 us, 100,003 x 1280 64 -> 67, 100,003 x 1536 90 -> 82, 151,936 x 1024 87 -> 83): it is taken from that size on.
 constexpr int64_t kCachedElements = 128 << 20;
+// A W beyond 9/8 of that cache, read by one token block, is loaded past the caches (nt): they keep nothing of it for the next call, and H stays in the
+// L2.  The same W again and again, us: 16 tokens x 151,936 x 4096 212 -> 188, 64 x 151,936 x 2048 112 -> 105 (5.9 TB/s), 128 x 122 -> 118,
+// 192 x 139 -> 135, 311 x 214 -> 212, 300 x 128,256 x 4096 358 -> 352; near the line 64 x 80,000 x 2048 68 -> 66, 128 x 72,000 x 2048 71 -> 73; below
+// it, where the cache has W, 64 x 64,000 x 2048 46 -> 50 and 64 x 32,000 x 2048 32 -> 38.  The 208 x 256 form and two token blocks (384 tokens)
+// are even with it.
+constexpr int64_t kStreamElements = kCachedElements / 8 * 9;
 constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;
 
 // The ring and block kernels give a lane its row of a tile as a 32-bit byte offset; of longer rows the general kernel's are 64-bit.
@@ -1050,7 +1057,7 @@ constexpr bool offsets_fit(int form, int d) {
     return 2ll * d * ((f.bm > f.bn ? f.bm : f.bn) - 1) + 128 <= UINT32_MAX;
 }
 
-struct Plan { int form, n_tb, n_vt, n_sp, band, n_long; bool general; };
+struct Plan { int form, n_tb, n_vt, n_sp, band, n_long; bool general, stream; };
 
 // Vocabulary splits of n_tb token blocks x n_vt tiles, and what they cost, in tiles one after the other.
 double pick_splits(int n_tb, int n_vt, int& n_sp) {
@@ -1101,6 +1108,7 @@ Plan make_plan(int64_t T, int V, int d, int n_splits) {
         if (best < 0.0 || cost < best) { best = cost; p.form = f; p.n_tb = n_tb; p.n_vt = n_vt; p.n_sp = sp; }
     }
     p.general = d % 64 || !offsets_fit(p.form, d);
+    p.stream = p.n_tb == 1 && static_cast<int64_t>(V) * d > kStreamElements;
     const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
     p.band = (p.n_tb + bands - 1) / bands;
     p.n_long = p.n_tb - (p.band - 1) * bands;
@@ -1113,6 +1121,11 @@ int launch_logprob(dim3 grid, hipStream_t st, const LogprobArgs& a) {
     if (!arrol_allow_lds(KERNEL, C::LDS_BYTES, lds_ok)) return ARROL_EHIP;
     arrol_launch(KERNEL, grid, dim3(C::NT), C::LDS_BYTES, st, a);
     return ARROL_OK;
+}
+
+template <class C>
+int launch_block(bool stream, dim3 grid, hipStream_t st, const LogprobArgs& a) {
+    return stream ? launch_logprob<logprob_block_kernel<C, true>, C>(grid, st, a) : launch_logprob<logprob_block_kernel<C>, C>(grid, st, a);
 }
 
 }  // namespace
@@ -1161,11 +1174,11 @@ extern "C" int arrol_logprob(const void* hidden, const void* lm_head, const int3
     const dim3 g(static_cast<unsigned>(grid));
     int rc;
     if (p.general) rc = launch_logprob<logprob_kernel<MainTile>, MainTile>(g, st, a);
-    else if (p.form == kForm64) rc = launch_logprob<logprob_block_kernel<Block64>, Block64>(g, st, a);
-    else if (p.form == kForm128) rc = launch_logprob<logprob_block_kernel<Block128>, Block128>(g, st, a);
-    else if (p.form == kForm192) rc = launch_logprob<logprob_block_kernel<Block192>, Block192>(g, st, a);
+    else if (p.form == kForm64) rc = launch_block<Block64>(p.stream, g, st, a);
+    else if (p.form == kForm128) rc = launch_block<Block128>(p.stream, g, st, a);
+    else if (p.form == kForm192) rc = launch_block<Block192>(p.stream, g, st, a);
     else if (p.form == kForm256) rc = launch_logprob<logprob_block_kernel<Block256>, Block256>(g, st, a);
-    else if (p.form == kForm320) rc = launch_logprob<logprob_block_kernel<Block320>, Block320>(g, st, a);
+    else if (p.form == kForm320) rc = launch_block<Block320>(p.stream, g, st, a);
     else rc = launch_logprob<logprob_ring_kernel<FastTile>, FastTile>(g, st, a);
     if (rc != ARROL_OK) return rc;
     if (arrol_launch_failed()) return arrol_launch_status();

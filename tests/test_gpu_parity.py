@@ -337,6 +337,25 @@ def test_logprob_four_wavefront_tiles(A, T, V, d, splits):
     assert torch.equal(one, two)
 
 
+# an lm_head that is loaded past the caches (above 9/8 of 256 MiB): each block form from its first to its last token, several vocabulary tiles a
+# workgroup, and the first size on the other side of the line
+@pytest.mark.parametrize("T,V,d,bn", [(1, 112359, 64 * 21, 64), (64, 112348, 64 * 21, 64), (65, 112347, 64 * 21, 128), (128, 78650, 64 * 30, 128),
+                                      (129, 78700, 64 * 30, 192), (192, 112349, 64 * 21, 192), (257, 112350, 64 * 21, 320), (320, 40003, 64 * 60, 320)])
+def test_logprob_lm_head_past_the_caches(A, T, V, d, bn):
+    say("logprob streamed T=%d V=%d d=%d" % (T, V, d))
+    kernel, _, tokens = logprob_kernel(A, T, V, d, 0)[:3]
+    assert (kernel, tokens) == (2, bn)
+    g = torch.Generator(device=DEV); g.manual_seed(T * 7 + V + d)
+    hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    lm_head = (torch.randn(V, d, generator=g, device=DEV) * (2.0 * d ** -0.5)).to(torch.bfloat16)
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    targets[0] = 0; targets[-1] = V - 1
+    lm_head[torch.arange(0, V, 97, device=DEV)] *= 3
+    check_logprob(A, hidden, lm_head, targets)
+    one, two = (A.arrol_logprob(hidden, lm_head, targets) for _ in range(2))
+    assert torch.equal(one, two)
+
+
 @pytest.mark.parametrize("splits", [1, 3, 16])
 def test_logprob_ring_kernel_independent_of_vocab_splits(A, splits):
     say("logprob ring forced splits=%d" % splits)
