@@ -82,6 +82,24 @@ def test_token_confidence_full_vocabulary_sampled_tokens(A, W):
     assert np.all(err <= conf_tol(cfg.vocab, ref)), float(err.max())
 
 
+# The column sum's workgroups: rows of 1, 2, 3, 33, 64 and 65 chunks (row groups of 256 to 4), 128 chunks of a row and a rest side by side, a whole
+# row of 256 and a rest, in turn (384 and 447 blocks of rows) and a workgroup each (383, 448); blocks of 1, 255, 256 and 257 rows.  Small
+# whole numbers: every sum is exact in fp32, so the result is the exact one whatever the order.
+@pytest.mark.parametrize("V,d", [(1, 8), (255, 16), (256, 24), (257, 264), (777, 512), (1025, 520), (256 * 190 + 1, 1032), (256 * 200 - 1, 2048),
+                                 (256 * 383, 2056), (256 * 384 - 255, 2056), (256 * 447, 4096), (256 * 448 - 3, 2064), (256 * 100, 4104)])
+def test_column_sum_exact(A, V, d):
+    print("[case] column sum V=%d d=%d" % (V, d), flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(V + d)
+    lm_head = torch.randint(-3, 4, (V, d), generator=g, device=DEV, dtype=torch.int8).to(torch.bfloat16)
+    hidden = torch.randint(-1, 2, (9, d), generator=g, device=DEV, dtype=torch.int8).to(torch.bfloat16)
+    conf = A.arrol_token_confidence(hidden, lm_head, torch.zeros(9, device=DEV))
+    colsum = torch.zeros(d, dtype=torch.float64, device=DEV)
+    for v in range(0, V, 16384):
+        colsum += lm_head[v:v + 16384].double().sum(0)
+    want = -(hidden.double() * colsum).sum(1)
+    assert torch.equal(conf.double(), want), float((conf.double() - want).abs().max())
+
+
 def run_trace(A, conf, lens, window, pct=10):
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64, device=DEV)
     mean, wmin, bottom = A.arrol_trace_confidence(conf, cu, window, pct)
