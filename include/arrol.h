@@ -268,8 +268,8 @@ typedef struct arrol_policy {
 /*
  * App. A.4: Laplace-smoothed likelihoods P(b|Y) = (c_b + alpha) / (sum c + alpha*B), prior pi = N+/(N+ + N-)
  * (1/2 for empty buffers), Bayes posterior q(b) = pi P(b|1) / (pi P(b|1) + (1-pi) P(b|0)); Eq. 2:
- * p(b) = clip(kappa + delta + lambda (rho - q(b)), p_min, p_max), with delta found by 64 bisection steps on
- * [p_min - kappa - lambda, p_max - kappa + lambda] so that sum_b w_b p(b) = kappa, w_b = (c_b^+ + c_b^-)/total
+ * p(b) = clip(kappa + delta + lambda (rho - q(b)), p_min, p_max), with delta as exact as 64 bisection steps on
+ * [p_min - kappa - lambda, p_max - kappa + lambda] find it, so that sum_b w_b p(b) = kappa, w_b = (c_b^+ + c_b^-)/total
  * (the buffer distribution; uniform for empty buffers).  Computed in fp64.
  * q_lut, p_lut fp32 [B]; delta NULL or a device double.  Policy fields must satisfy 0 <= kappa, rho <= 1,
  * lambda >= 0, 0 <= p_min <= p_max <= 1, alpha >= 0.
