@@ -125,9 +125,12 @@ class _NoMarshal:
         return None
 
 
+MARSHAL_INTERFACE = 2    # of setup() and the argument lists of marshal.cpp; 1 was without a number
+
+
 def built_for():
-    """What _marshal.so has to be compiled for, since it uses the internals of both."""
-    return "torch %s, python %d.%d" % ((torch.__version__,) + sys.version_info[:2])
+    """What _marshal.so has to be compiled for: this binding, and torch and Python, since it uses the internals of both."""
+    return "binding interface %d, torch %s, python %d.%d" % ((MARSHAL_INTERFACE, torch.__version__) + sys.version_info[:2])
 
 
 def _import_marshal():
@@ -139,7 +142,10 @@ def _import_marshal():
     made = getattr(module, "built_for", lambda: (0, "an unknown torch"))()
     if made != (ABI_VERSION, built_for()):
         raise ImportError("%s is built for version %d and %s, not %d and %s" % ((MARSHAL_PATH,) + made + (ABI_VERSION, built_for())))
-    module.setup(torch.nn.Parameter, Policy, _check)
+    try:
+        module.setup(torch.nn.Parameter, Policy, _check)
+    except TypeError as e:
+        raise ImportError("%s is built for another binding: %s" % (MARSHAL_PATH, e))
     return module
 
 

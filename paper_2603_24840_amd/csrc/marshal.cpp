@@ -482,8 +482,8 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return out;
 }
 
-// What this file was compiled against: the header's version, and the torch and Python whose internals it uses (ARROL_BUILT_FOR, a
-// text that the build gives).  binding.py looks at both before it calls anything else.
+// What this file was compiled against: the header's version, and binding.py's interface number (raised there with every change of an
+// argument list here), torch and Python (ARROL_BUILT_FOR, a text that the build gives).  binding.py looks at both before it calls anything else.
 PyObject* built_for(PyObject*, PyObject*) { return Py_BuildValue("is", ARROL_VERSION, ARROL_BUILT_FOR); }
 
 PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {

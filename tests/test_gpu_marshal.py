@@ -1,6 +1,7 @@
 """The C++ marshalling of the short calls (csrc/marshal.cpp) against the Python marshalling of the same calls: the same
 results, the same errors, and None - so the Python way - for everything but the ordinary case."""
 import inspect
+import sys
 
 import numpy as np
 import pytest
@@ -200,6 +201,20 @@ def test_a_file_that_is_no_extension_is_not_used(reload_marshal, monkeypatch, tm
     (tmp_path / "_marshal.so").write_bytes(b"not this")
     monkeypatch.setattr(binding, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
     python_refuses()
+
+
+# Of the library's version, torch and Python of today, as a file that outlives a change of marshal.cpp is: one without the
+# interface in its text, one whose setup() wants other arguments, and one that fits, for the difference
+@pytest.mark.parametrize("text,setup,used", [("torch %s, python %d.%d" % ((torch.__version__,) + sys.version_info[:2]), "*a", False),
+                                             (binding.built_for(), "a, b, c, d, e", False), (binding.built_for(), "a, b, c", True)])
+def test_an_extension_of_another_binding_is_not_used(reload_marshal, monkeypatch, tmp_path, text, setup, used):
+    (tmp_path / "_marshal.py").write_text("def built_for(): return %r\ndef setup(%s): pass\ndef score(*a): return 'taken'\n" %
+                                          ((binding.ABI_VERSION, text), setup))
+    monkeypatch.setattr(binding, "MARSHAL_PATH", str(tmp_path / "_marshal.py"))
+    if used:
+        assert A.arrol_score(*calls("cpu")["score"][0][0]) == "taken"
+    else:
+        python_refuses()
 
 
 def test_the_extension_says_what_it_is_compiled_against():
