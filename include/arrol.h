@@ -276,6 +276,11 @@ typedef struct arrol_policy {
  */
 int arrol_calibrate(const int64_t* c_pos, const int64_t* c_neg, int32_t B, arrol_policy pol,
                     float* q_lut, float* p_lut, double* delta, void* stream);
+/*
+ * Test and measurement aid, a host computation on HOST arrays: arrol_calibrate's search for delta.  *rounds is how many rounds of sums
+ * it takes, which is what its time hangs on; *delta what it finds (its sums are added in another order than on the GPU).
+ */
+int arrol_calibrate_search(const int64_t* c_pos, const int64_t* c_neg, int32_t B, arrol_policy pol, int32_t* rounds, double* delta);
 
 /*
  * Alg. 1, backend: a rollout that reaches the detection length is pruned with probability 1 - p_i and the

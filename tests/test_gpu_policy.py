@@ -69,7 +69,7 @@ def test_calibrate_matches_oracle(A, W, kappa, rho, lam, p_min, p_max, alpha):
 
 @pytest.mark.parametrize("B", [1, 2, 127, 129, 256, 257, 512, 513, 1024, 1025, 2048])
 def test_calibrate_bin_counts_at_the_edges_of_its_forms(A, B):
-    """One form per bin-count range (15 midpoints at once up to 256 bins, 3 beyond; 8, 16 or 32 bins per lane)."""
+    """One form per bin-count range (15 points at once up to 512 bins, 7 beyond; 8, 16 or 32 bins per lane)."""
     print("[case] calibrate B=%d" % B, flush=True)
     g = torch.Generator(device=DEV); g.manual_seed(B)
     cp = torch.randint(0, 60, (B,), generator=g, device=DEV)
@@ -106,6 +106,9 @@ def test_calibrate_search_at_its_extremes(A, B, args):
         assert np.max(np.abs(npy(q_lut) - q_o)) < Q_TOL
         w = O.bin_weights(npy(cp), npy(cn))
         p_g = npy(p_lut).astype(np.float64)
+        kappa, rho, lam, p_min, p_max = (f32(x) for x in args[:5])
+        # every bin, those without weight among them, has the probability that the delta found gives it
+        assert np.max(np.abs(p_g - np.clip(kappa + float(delta[0]) + lam * (rho - q_o), p_min, p_max))) < Q_TOL
         if abs(float(delta[0]) - d_o) < DELTA_TOL:
             assert np.max(np.abs(p_g - p_o)) < Q_TOL
         else:           # on a flat stretch at kappa the last bit of a sum decides which end is taken: both ends give the mean kappa
