@@ -123,8 +123,8 @@ __device__ __forceinline__ void exp_both(double u, double& down, double& up) {
 
 // n_seg workgroups per rollout, each with an equal part of its tokens: partial[i n_seg + q] = weight_i * (1/L_i) * sum_t term_t,
 // clipped[..] = tokens on the clipped branch.  Bound by latency (64-bit exponentials behind two loads, 12 bytes a token): the
-// loads of kObjUnroll tokens go out together, their arithmetic is interleaved, and long rollouts get enough wavefronts to hide the rest.
-template <int kObjThreads, int kObjUnroll>
+// loads of up to four tokens go out together, their arithmetic is interleaved, and long rollouts get enough wavefronts to hide the rest.
+template <int kObjThreads>
 __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     const float* __restrict__ logp, const float* __restrict__ logp_ref, const int64_t* __restrict__ cu, int64_t T,
     const float* __restrict__ advantage, const float* __restrict__ seq_weight, double eps_low, double eps_high,
@@ -150,33 +150,36 @@ __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
     const double r_lo = 1.0 - eps_low, r_hi = 1.0 + eps_high;
     double s = 0.0;
     long long c = 0;
-    for (int64_t t0 = lo + threadIdx.x; t0 < hi; t0 += kObjThreads * kObjUnroll) {
-        float ref[kObjUnroll], lp[kObjUnroll];
+    // the tokens t0, t0 + kObjThreads, ...: as many as `step` says, as far as they are there
+    const auto tokens = [&](auto step, int64_t t0) {
+        constexpr int N = decltype(step)::value;
+        if (t0 >= hi) return;
+        float ref[N], lp[N];
 #pragma unroll
-        for (int k = 0; k < kObjUnroll; ++k) {
+        for (int k = 0; k < N; ++k) {
             const int64_t t = t0 + k * kObjThreads < hi ? t0 + k * kObjThreads : t0;   // a load that may be skipped would be waited for
             ref[k] = logp_ref[t];
             lp[k] = logp[t];
         }
-        double u[kObjUnroll], ratio[kObjUnroll], eu[kObjUnroll];
+        double u[N], ratio[N], eu[N];
         bool far = false;
 #pragma unroll
-        for (int k = 0; k < kObjUnroll; ++k) {
+        for (int k = 0; k < N; ++k) {
             u[k] = static_cast<double>(ref[k]) - static_cast<double>(lp[k]);
             exp_both(u[k], ratio[k], eu[k]);
             far = far || !(fabs(u[k]) < 700.0);
         }
-        if (__ballot(far)) {                 // a lane past the ends of the exponentials' range, infinite or undefined
+        if (__builtin_expect(__ballot(far) != 0, 0)) {                 // a lane past the ends of the exponentials' range, infinite or undefined
             asm volatile("");                // (a branch: the compiler would take both sides)
 #pragma unroll 1
-            for (int k = 0; k < kObjUnroll; ++k)
+            for (int k = 0; k < N; ++k)
                 if (!(fabs(u[k]) < 700.0)) {
                     ratio[k] = exp(-u[k]);
                     eu[k] = exp(u[k]);
                 }
         }
 #pragma unroll
-        for (int k = 0; k < kObjUnroll; ++k) {      // beside each other: dead ones repeat the first and are not counted
+        for (int k = 0; k < N; ++k) {       // beside each other: dead ones repeat the first and are not counted
             const int64_t t = t0 + k * kObjThreads;
             const bool live = t < hi;
             const double plain = ratio[k] * A;
@@ -189,7 +192,19 @@ __global__ __launch_bounds__(kObjThreads) void grpo_objective_kernel(
                 grad_logp[t] = static_cast<float>(d * scale);
             }
         }
+    };
+    // Four tokens a thread at a time while there are more than three, then two, then one: a step's arithmetic is done whether its tokens are
+    // there or not.  By each rollout's own length: with one number for all, of their mean, 255 rollouts of 64 tokens and one of
+    // 8,192 took 12.7 us (now 8.9), 512 of 1,200 6.6 (5.9), of 2,500 8.6 (7.4), of 250 5.3 (4.9); with four always, and the missing ones
+    // skipped one by one, 11.9, 6.2, 8.2 and 5.1.
+    int64_t t0 = lo + threadIdx.x;
+    const auto left = [&] { return hi - t0 + threadIdx.x; };
+    for (; left() > 3 * kObjThreads; t0 += 4 * kObjThreads) tokens(std::integral_constant<int, 4>{}, t0);
+    if (left() > kObjThreads) {
+        tokens(std::integral_constant<int, 2>{}, t0);
+        t0 += 2 * kObjThreads;
     }
+    tokens(std::integral_constant<int, 1>{}, t0);
     workgroup_sums(s, c, sh_s, sh_c);
     if (threadIdx.x == 0) {
         partial[out] = s * scale;
@@ -291,19 +306,14 @@ extern "C" int arrol_grpo_objective(const float* logp, const float* logp_ref, co
     const int64_t n_parts = n_seq * n_seg;
     double* partial = static_cast<double*>(workspace);
     int64_t* clipped = reinterpret_cast<int64_t*>(partial + n_parts);
-#define ARROL_OBJECTIVE(N, U)                                                                                                  \
-    arrol_launch((grpo_objective_kernel<N, U>), dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, \
+#define ARROL_OBJECTIVE(N)                                                                                                     \
+    arrol_launch(grpo_objective_kernel<N>, dim3(n_seq, static_cast<unsigned>(n_seg)), dim3(N), 0, st, logp, logp_ref, cu_seqlens, T, \
                  advantage, seq_weight, static_cast<double>(eps_low), static_cast<double>(eps_high), static_cast<double>(beta),     \
                  grad_logp, partial, clipped)
     // wider workgroups shorten a long rollout's chain while the chip has room for them (one token at a time: 512 rollouts of 512 to 4,096
     // tokens 10.5 us with 512 threads, 11.3 with 256; 4,096 of 256 to 2,048 30.0 and 26.1)
-    // Tokens in flight a thread: as many as most rollouts have for it, since a step's arithmetic is done whether they are there or not
-    // (512 rollouts of 64 to 512 tokens 4.9 us with two, 5.7 with four; 512 of 300 to 1,100 5.8 and 5.9; 128 of 256 to 2,048 5.1 and 4.9)
-    const int64_t mean = T / (n_seq * n_seg);
-    if (n_seg == 1 && mean > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512, 4);
-    else if (mean > 768) ARROL_OBJECTIVE(256, 4);
-    else if (mean > 128) ARROL_OBJECTIVE(256, 2);
-    else ARROL_OBJECTIVE(256, 1);
+    if (n_seg == 1 && T / n_seq > 1024 && n_seq <= 1024) ARROL_OBJECTIVE(512);
+    else ARROL_OBJECTIVE(256);
 #undef ARROL_OBJECTIVE
     // many: four partials a thread at a time; 256 threads are quicker to add up (one rollout: 4.2 us the call, 4.7 with 1,024)
     if (n_parts <= 1024)

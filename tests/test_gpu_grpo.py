@@ -133,7 +133,35 @@ def test_objective_at_extreme_ratios(A):
     assert int(n_clip) == clipped and np.isnan(float(J))
 
 
-# one, two and four tokens a thread at a time, 256 and 512 threads; lengths that leave some of them none; log-ratios on both sides of the 700
+# A rollout goes in steps of four, two and one tokens a thread, by its own length: lengths on both sides of each step's line for workgroups of
+# 256 threads and of 512 (a mean above 1,024), none, one, and a rollout of many steps among short ones
+@pytest.mark.parametrize("N", [256, 512])
+def test_objective_steps_by_rollout_length(A, N):
+    print("[case] grpo_objective steps of %d threads" % N, flush=True)
+    lens = np.array([0, 1, 63, N - 1, N, N + 1, 2 * N - 1, 2 * N, 2 * N + 1, 3 * N - 1, 3 * N, 3 * N + 1, 4 * N, 4 * N + 1, 5 * N, 5 * N + 1, 6 * N + 1, 7 * N,
+                     7 * N + 1, 8 * N + 3, 3, 0] + [20 * N + 7] * (N == 512) + [64] * (20 if N == 256 else 0))
+    T, n, beta = int(lens.sum()), len(lens), 0.04
+    assert (T // n > 1024) == (N == 512)
+    rng = np.random.default_rng(N)
+    rng.shuffle(lens)
+    logp, ref = ((rng.normal(size=T) * 0.2 - 2).astype(np.float32) for _ in range(2))
+    adv, weight = rng.normal(size=n).astype(np.float32), rng.random(n).astype(np.float32)
+    ws = torch.empty(16 * n, dtype=torch.uint8, device=DEV)                  # room for one part a rollout
+    J, grad, n_clip = A.arrol_grpo_objective(to_dev(logp, DEV), to_dev(ref, DEV), dev_i64(np.concatenate([[0], np.cumsum(lens)])), to_dev(adv, DEV),
+                                             to_dev(weight, DEV), 0.2, 0.28, beta, workspace=ws)
+    torch.cuda.synchronize()
+    u, a = ref.astype(np.float64) - logp.astype(np.float64), np.repeat(adv.astype(np.float64), lens)
+    scale = np.repeat(weight.astype(np.float64) / np.maximum(lens, 1), lens)
+    ratio, eu = np.exp(-u), np.exp(u)
+    plain, clamped = ratio * a, np.clip(ratio, 1.0 - f32(0.2), 1.0 + f32(0.28)) * a
+    terms = (np.minimum(plain, clamped) - f32(beta) * (eu - u - 1.0)) * scale
+    want = (np.where(plain <= clamped, plain, 0.0) - f32(beta) * (1.0 - eu)) * scale
+    assert np.all(np.abs(npy(grad) - want) <= 1e-7 * np.abs(want) + 4e-15 * scale)      # one rounding to fp32; exponentials within 2 ulp
+    assert int(n_clip) == int(np.sum(clamped < plain))
+    assert abs(float(J) - terms.sum()) <= 4e-15 * np.abs(terms).sum()
+
+
+# lengths that leave some threads none; log-ratios on both sides of the 700
 # from which the library exponential is taken, infinite and undefined ones among ordinary ones of the same wavefront
 @pytest.mark.parametrize("lens", [[100, 128, 1], [130, 700, 257], [900, 1100, 255, 1025], [5000, 2049, 4096, 3]])
 def test_objective_exponentials_by_rollout_length(A, lens):
