@@ -96,13 +96,14 @@ __device__ __forceinline__ void workgroup_sums(double& s, long long& c, double (
     }
 }
 
-// exp(-u) and exp(u), |u| < 700, from one reduction u = k ln 2 + r: exp(+-r) = cosh r +- sinh r, both by their Taylor series in r^2 (|r| <= 0.347:
-// what is left out is below 1e-17 of them).  23 instructions where an exponential and a reciprocal took some 50; each is within 1.9 ulp of
-// the true value, exactly 1 at 0.
+// exp(-u) and exp(u), |u| < 700, from one reduction u = k ln 2 + r: exp(+-r) = 1 + ((cosh r - 1) +- sinh r), both by their Taylor series in r^2
+// (|r| <= 0.347: what is left out is below 1e-17 of them).  25 instructions where an exponential and a reciprocal took some 50.  Each is
+// within 1.24 ulp of the true value, 0.33 in the root mean square (1 million of them each in +-690, +-20 and normal ones of 0.2), and
+// exactly 1 at 0; the library's exponential and its reciprocal had 0.85 and 1.49, 0.30 and 0.45.
 __device__ __forceinline__ void exp_both(double u, double& down, double& up) {
     const double k = rint(u * 1.4426950408889634);
-    // ln 2 as a double and what that leaves of it
-    const double r = fma(-k, 2.3190468138462996e-17, fma(-k, 0.6931471805599453, u)), t = r * r;
+    // ln 2 in 42 bits and what they leave of it: k times the first is exact, and so is the difference
+    const double r = fma(-k, 5.497923018708371e-14, fma(-k, 0.6931471805598903, u)), t = r * r;
     double c = 1.0 / 479001600.0, s = 1.0 / 6227020800.0;            // 1 / 12!, 1 / 13!
     c = fma(c, t, 1.0 / 3628800.0);
     s = fma(s, t, 1.0 / 39916800.0);
@@ -114,11 +115,11 @@ __device__ __forceinline__ void exp_both(double u, double& down, double& up) {
     s = fma(s, t, 1.0 / 120.0);
     c = fma(c, t, 0.5);
     s = fma(s, t, 1.0 / 6.0);
-    c = fma(c, t, 1.0);
+    c *= t;
     s = fma(s * t, r, r);
     const int e = static_cast<int>(k);
-    down = ldexp(c - s, -e);
-    up = ldexp(c + s, e);
+    down = ldexp(1.0 + (c - s), -e);
+    up = ldexp(1.0 + (c + s), e);
 }
 
 // n_seg workgroups per rollout, each with an equal part of its tokens: partial[i n_seg + q] = weight_i * (1/L_i) * sum_t term_t,

@@ -161,6 +161,24 @@ def test_objective_steps_by_rollout_length(A, N):
     assert abs(float(J) - terms.sum()) <= 4e-15 * np.abs(terms).sum()
 
 
+# The exponentials themselves: with a clip range that never binds, weight 1 and one token, J is exp(-u) for advantage 1 and beta 0, and
+# -(exp(u) - u - 1) for advantage 0 and beta 1, where from u = 60 on u + 1 is less than half an ulp of exp(u).  Rounded are r, sinh r, their
+# sum with cosh r - 1 (a quarter of an ulp each where the result is just below a power of two, less elsewhere) and the last
+# addition (half a one): 1.25, and for what the polynomials' terms before add 1.3; evenly distributed errors of those sizes have a root mean
+# square of 0.38.
+def test_objective_exponentials_to_the_last_bit(A):
+    rng = np.random.default_rng(3)
+    u = np.concatenate([rng.uniform(-690, 690, 300), rng.uniform(-80, 80, 300), rng.normal(size=300) * 0.2]).astype(np.float32)
+    one, cu, lp = torch.ones(1, device=DEV), dev_i64(np.array([0, 1])), torch.zeros(1, device=DEV)
+    ws, ref = torch.empty(128, dtype=torch.uint8, device=DEV), to_dev(u, DEV)
+    down, up = (npy(torch.stack([A.arrol_grpo_objective(lp, ref[i:i + 1], cu, adv, one, 1.0, 3e38, beta, want_grad=False, workspace=ws)[0][0]
+                                 for i in range(len(u))])) for adv, beta in ((one, 0.0), (one * 0, 1.0)))
+    x = u.astype(np.longdouble)
+    for got, want, at in ((down, np.exp(-x), np.abs(u) < 80), (-up, np.exp(x) - x - 1, u > 60)):
+        ulps = np.abs(got.astype(np.longdouble) - want)[at] / np.spacing(want[at].astype(np.float64))
+        assert float(ulps.max()) <= 1.3 and float(np.sqrt((ulps * ulps).mean())) <= 0.38, (float(ulps.max()), float(np.sqrt((ulps * ulps).mean())))
+
+
 # lengths that leave some threads none; log-ratios on both sides of the 700
 # from which the library exponential is taken, infinite and undefined ones among ordinary ones of the same wavefront
 @pytest.mark.parametrize("lens", [[100, 128, 1], [130, 700, 257], [900, 1100, 255, 1025], [5000, 2049, 4096, 3]])
