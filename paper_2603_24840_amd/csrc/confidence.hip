@@ -13,55 +13,54 @@ namespace {
 constexpr int kColThreads = 256;
 constexpr int kColRows = 256;      // LM-head rows per workgroup of the column-sum pass
 constexpr int kColUnroll = 8;
+constexpr int kColUnits = 256;     // compute units
 
-// partial[b][c] = sum of W[v][c] over the rows v of block b.  Thread -> (row group, 16-byte chunk of a row): `lanes` chunks (a power of two) and
-// 256 / lanes groups, which take every so many-th row and meet in LDS in a fixed order.  Bound by HBM where all units have loads in flight: a
-// group to each row of 256 chunks left units idle for small vocabularies and threads idle for narrow rows.  us a confidence call, one
-// group always -> as colsum_lanes has it: 128,256 x 256 40 -> 20, x 512 47 -> 30, 32,000 x 2048 47 -> 33, x 4096 84 -> 55,
-// 151,936 x 4096 254 -> 213 (rows of two slabs, a workgroup each).
+// partial[b][c] = sum of W[v][c] over the `rows` rows v of block b.  Thread -> (row group, 16-byte chunk of a row): `lanes` chunks (a power of
+// two) and 256 / lanes groups, which take every so many-th row and meet in LDS in a fixed order.  Bound by HBM where all units have loads
+// in flight, and by the unit with most rows (colsum_plan).  us a confidence call, one group a block of 256 rows with all chunks in turn -> now:
+// 128,256 x 256 36 -> 15, x 512 40 -> 25, 32,000 x 2048 42 -> 26, x 4096 76 -> 47, 151,936 x 2048 107 -> 99, x 4096 241 -> 196 (6.4 TB/s).
+// Error against 64 bits of 7.1e-8 in both.
 __global__ __launch_bounds__(kColThreads) void colsum_partial_kernel(
-    const u32x4* __restrict__ lm_head, int V, int d_vec, int lanes, float* __restrict__ partial) {
+    const u32x4* __restrict__ lm_head, int V, int d_vec, int lanes, int rows, float* __restrict__ partial) {
     __shared__ float4 sums[2][kColThreads];
     const int groups = kColThreads / lanes, group = threadIdx.x / lanes, lane = threadIdx.x % lanes;
-    const int v0 = blockIdx.x * kColRows;
-    const int v1 = v0 + kColRows < V ? v0 + kColRows : V;
+    const int v0 = blockIdx.x * rows, n = V - v0 < rows ? V - v0 : rows;
     float* out = partial + static_cast<int64_t>(blockIdx.x) * d_vec * 8;
-    for (int c0 = blockIdx.y * lanes; c0 < d_vec; c0 += gridDim.y * lanes) {
-        const int c = c0 + lane;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (c < d_vec) {
-            const u32x4* p = lm_head + c;
-            for (int v = v0 + group; v < v1; v += kColUnroll * groups) {
-                u32x4 x[kColUnroll];
+    const int c = blockIdx.y * lanes + lane;
+    float acc[2][8] = {};            // two sums a column: none of more than 200 rows, where one had 256
+    if (c < d_vec) {
+        const u32x4* p = lm_head + static_cast<int64_t>(v0) * d_vec + c;
+        for (int r = group; r < n; r += kColUnroll * groups) {
+            u32x4 x[kColUnroll];
 #pragma unroll
-                for (int u = 0; u < kColUnroll; ++u)
-                    x[u] = v + u * groups < v1 ? __builtin_nontemporal_load(p + static_cast<int64_t>(v + u * groups) * d_vec)
-                                               : u32x4{0u, 0u, 0u, 0u};
+            for (int u = 0; u < kColUnroll; ++u)
+                x[u] = r + u * groups < n ? __builtin_nontemporal_load(p + static_cast<int64_t>(r + u * groups) * d_vec)
+                                          : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int u = 0; u < kColUnroll; ++u) {
-                    acc[0] += bf16_lo(x[u].x); acc[1] += bf16_hi(x[u].x);
-                    acc[2] += bf16_lo(x[u].y); acc[3] += bf16_hi(x[u].y);
-                    acc[4] += bf16_lo(x[u].z); acc[5] += bf16_hi(x[u].z);
-                    acc[6] += bf16_lo(x[u].w); acc[7] += bf16_hi(x[u].w);
-                }
+            for (int u = 0; u < kColUnroll; ++u) {
+                float* a = acc[u & 1];
+                a[0] += bf16_lo(x[u].x); a[1] += bf16_hi(x[u].x);
+                a[2] += bf16_lo(x[u].y); a[3] += bf16_hi(x[u].y);
+                a[4] += bf16_lo(x[u].z); a[5] += bf16_hi(x[u].z);
+                a[6] += bf16_lo(x[u].w); a[7] += bf16_hi(x[u].w);
             }
         }
-        float4 lo = make_float4(acc[0], acc[1], acc[2], acc[3]), hi = make_float4(acc[4], acc[5], acc[6], acc[7]);
-        if (groups > 1) {
-            __syncthreads();                     // of the slab before, everything has been read
-            sums[0][threadIdx.x] = lo;
-            sums[1][threadIdx.x] = hi;
-            __syncthreads();
-            for (int g = 1; group == 0 && g < groups; ++g) {
-                const float4 a = sums[0][g * lanes + lane], b = sums[1][g * lanes + lane];
-                lo.x += a.x; lo.y += a.y; lo.z += a.z; lo.w += a.w;
-                hi.x += b.x; hi.y += b.y; hi.z += b.z; hi.w += b.w;
-            }
+    }
+    for (int k = 0; k < 8; ++k) acc[0][k] += acc[1][k];
+    float4 lo = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]), hi = make_float4(acc[0][4], acc[0][5], acc[0][6], acc[0][7]);
+    if (groups > 1) {
+        sums[0][threadIdx.x] = lo;
+        sums[1][threadIdx.x] = hi;
+        __syncthreads();
+        for (int g = 1; group == 0 && g < groups; ++g) {
+            const float4 a = sums[0][g * lanes + lane], b = sums[1][g * lanes + lane];
+            lo.x += a.x; lo.y += a.y; lo.z += a.z; lo.w += a.w;
+            hi.x += b.x; hi.y += b.y; hi.z += b.z; hi.w += b.w;
         }
-        if (group == 0 && c < d_vec) {
-            *reinterpret_cast<float4*>(out + c * 8) = lo;
-            *reinterpret_cast<float4*>(out + c * 8 + 4) = hi;
-        }
+    }
+    if (group == 0 && c < d_vec) {
+        *reinterpret_cast<float4*>(out + c * 8) = lo;
+        *reinterpret_cast<float4*>(out + c * 8 + 4) = hi;
     }
 }
 
@@ -330,20 +329,29 @@ __global__ __launch_bounds__(THREADS) void trace_conf_kernel(
 
 int colsum_blocks(int V) { return (V + kColRows - 1) / kColRows; }
 
-// Chunks of a row side by side in a workgroup: as many as a row has, but 64 to 128 rather than 256 where there would be fewer than 1.5 workgroups
-// to a compute unit (32,000 x 4096: 55 us a call with 64, 84 with 256; 80,000 x 2048 64 with 128, 65 with 256; but of more workgroups
-// whole kilobytes read side by side count: 128,256 x 2048 92 with 256, 98 with 128, 102 with 64).
-int colsum_lanes(int n_blocks, int d_vec) {
-    int lanes = kColThreads;
-    while (lanes > 1 && lanes / 2 >= d_vec) lanes /= 2;
-    while (lanes > ARROL_WAVE && static_cast<int64_t>(n_blocks) * ((d_vec + lanes - 1) / lanes) < 384) lanes /= 2;
-    return lanes;
-}
+// The column sum's workgroups: blocks of `rows` rows x slabs of `lanes` chunks.
+struct ColsumPlan { int lanes, slabs, rows, blocks; };
 
-// Workgroups to a block of rows: one to each slab of `lanes` chunks, but one that takes them in turn where 1.5 to 1.75 to a compute unit become 3 to 3.5
-// (100,000 x 4096: 142 us a call in turn, 153 side by side, 110,000 158 and 173; but 64,000 100 and 94, 120,000 199 and 174, 128,256 189 and 178).
-int colsum_slabs(int n_blocks, int d_vec, int lanes) {
-    return lanes == kColThreads && n_blocks >= 384 && n_blocks < 448 ? 1 : (d_vec + lanes - 1) / lanes;
+ColsumPlan colsum_plan(int V, int d_vec) {
+    ColsumPlan p = {kColThreads, 1, kColRows, colsum_blocks(V)};
+    // Chunks of a row side by side: as many as a row has, but 64 to 128 rather than 256 where there would be fewer than 1.5 workgroups
+    // to a compute unit (32,000 x 4096: 55 us a call with 64, 84 with 256; 80,000 x 2048 64 with 128, 65 with 256; but of more workgroups
+    // whole kilobytes read side by side count: 128,256 x 2048 83 with 256, 88 with 128, 101 with 64).
+    while (p.lanes > 1 && p.lanes / 2 >= d_vec) p.lanes /= 2;
+    while (p.lanes > ARROL_WAVE && static_cast<int64_t>(p.blocks) * ((d_vec + p.lanes - 1) / p.lanes) < 384) p.lanes /= 2;
+    p.slabs = (d_vec + p.lanes - 1) / p.lanes;
+    // As many workgroups to each unit, from two on: what would be a last round for some of them goes into longer blocks.  us a call with
+    // blocks of 256 rows and so: 100,000 x 3072 110 -> 100, x 3584 130 -> 116, x 4096 145 -> 128, x 8192 299 -> 277, 140,000 x 1024
+    // 56 -> 49, x 4096 192 -> 184; of 2.9 rounds 96,000 x 4096 128 -> 121, but 64,000 x 5120 108 -> 113; of 1.96 rounds 128,256 x 2048 83 -> 86:
+    // a unit needs two workgroups.  A last slab of less than half its chunks does not count: 128,256 x 2056 89 -> 92 if it did.
+    const int rest = d_vec % p.lanes, full = p.slabs - (p.slabs > 1 && rest && 2 * rest < p.lanes ? 1 : 0);
+    const int rounds = static_cast<int>(static_cast<int64_t>(p.blocks) * full / kColUnits);
+    if (rounds >= 2) {
+        const int blocks = static_cast<int>(static_cast<int64_t>(rounds) * kColUnits / full);
+        p.rows = (V - 1) / blocks + 1;
+        p.blocks = (V - 1) / p.rows + 1;
+    }
+    return p;
 }
 
 }  // namespace
@@ -363,13 +371,12 @@ extern "C" int arrol_token_confidence(const void* hidden, const void* lm_head, c
     if (!workspace || !arrol_aligned16(workspace) || workspace_bytes < arrol_token_confidence_workspace_bytes(V, d))
         return ARROL_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int nb = colsum_blocks(V);
+    const ColsumPlan p = colsum_plan(V, d / 8);
     float* colsum = static_cast<float*>(workspace);
     float* partial = colsum + d;
-    const int lanes = colsum_lanes(nb, d / 8);
-    arrol_launch(colsum_partial_kernel, dim3(nb, colsum_slabs(nb, d / 8, lanes)), dim3(kColThreads), 0, st,
-                       static_cast<const u32x4*>(lm_head), V, d / 8, lanes, partial);
-    arrol_launch(reduce_rows_f32_kernel<32>, dim3((d + 31) / 32), dim3(1024), 0, st, partial, nb,
+    arrol_launch(colsum_partial_kernel, dim3(p.blocks, p.slabs), dim3(kColThreads), 0, st,
+                       static_cast<const u32x4*>(lm_head), V, d / 8, p.lanes, p.rows, partial);
+    arrol_launch(reduce_rows_f32_kernel<32>, dim3((d + 31) / 32), dim3(1024), 0, st, partial, p.blocks,
                        static_cast<int64_t>(d), static_cast<int64_t>(d), 1.f, colsum);
     const int64_t blocks_needed = (T + kConfWaves - 1) / kConfWaves;
     const int grid = static_cast<int>(blocks_needed < 256 * 8 ? blocks_needed : 256 * 8);

@@ -83,10 +83,12 @@ def test_token_confidence_full_vocabulary_sampled_tokens(A, W):
 
 
 # The column sum's workgroups: rows of 1, 2, 3, 33, 64 and 65 chunks (row groups of 256 to 4), 128 chunks of a row and a rest side by side, a whole
-# row of 256 and a rest, in turn (384 and 447 blocks of rows) and a workgroup each (383, 448); blocks of 1, 255, 256 and 257 rows.  Small
-# whole numbers: every sum is exact in fp32, so the result is the exact one whatever the order.
+# row of 256 and a rest, the rest less than half a slab, half a one and more; blocks of 256 rows, the last one of 1, 255 or 256, and longer
+# ones where a unit has two workgroups and more: of 257 (the last one of 1, 3 and 131), 274, 298, 300 and 341.  Small whole numbers: every
+# sum is exact in fp32, so the result is the exact one whatever the order.
 @pytest.mark.parametrize("V,d", [(1, 8), (255, 16), (256, 24), (257, 264), (777, 512), (1025, 520), (256 * 190 + 1, 1032), (256 * 200 - 1, 2048),
-                                 (256 * 383, 2056), (256 * 384 - 255, 2056), (256 * 447, 4096), (256 * 448 - 3, 2064), (256 * 100, 4104)])
+                                 (256 * 383, 2056), (256 * 384 - 255, 2056), (256 * 447, 4096), (256 * 448 - 3, 2064), (256 * 100, 4104),
+                                 (131073, 1024), (256 * 300, 2048), (98305, 3072), (140000, 2560), (131072 + 256, 248), (256 * 341, 5120)])
 def test_column_sum_exact(A, V, d):
     print("[case] column sum V=%d d=%d" % (V, d), flush=True)
     g = torch.Generator(device=DEV); g.manual_seed(V + d)
