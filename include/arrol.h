@@ -221,6 +221,8 @@ int arrol_logprob(const void* hidden, const void* lm_head, const int32_t* target
  */
 int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* kernel, int32_t* tile_rows,
                          int32_t* tile_tokens, int32_t* splits);
+/* In the same manner: *streamed is 1 where the lm_head is loaded past the caches (kernel 2, one token block, an lm_head beyond 288 MiB). */
+int arrol_logprob_streamed(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* streamed);
 
 /*
  * Stage 5 -- rank-weighted vote (Sec. 4.4: candidates are sorted by head score and their

@@ -77,6 +77,7 @@ _SIGNATURES = {
     "arrol_logprob_workspace_bytes": (_sz, [_i64, _i32, _i32, _i32]),
     "arrol_logprob": (ctypes.c_int, [_vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _i32, _vp, _sz, _vp]),
     "arrol_logprob_kernel": (ctypes.c_int, [_i64, _i32, _i32, _i32, _vp, _vp, _vp, _vp]),
+    "arrol_logprob_streamed": (ctypes.c_int, [_i64, _i32, _i32, _i32, _vp]),
     "arrol_token_confidence_workspace_bytes": (_sz, [_i32, _i32]),
     "arrol_token_confidence": (ctypes.c_int, [_vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _sz, _vp]),
     "arrol_trace_confidence_workspace_bytes": (_sz, [_i64, _i32]),

@@ -744,11 +744,14 @@ __global__ __launch_bounds__(C::NT) void logprob_ring_kernel(LogprobArgs a) {
 // from the L2 it would be 160, without any loads 130.  Tried and slower: W and H fetched by different wavefronts, each with
 // its own order (311 tokens: 242); W straight to registers, several steps ahead (128 tokens: 148; half lines at a time).
 //
-// 208 x 256 (WM = 1, four wavefronts with the registers of a SIMD each) is for 193 to 256 tokens, where 256 x 256 tiles leave room for two
-// K64 steps and the ring kernel, in 32-column slots of them, waits for W.  13 x 4 MFMAs a chunk fill the registers with one set of W's
+// 208 x 256 (WM = 1, four wavefronts with the registers of a SIMD each) is for 193 to 256 tokens (and two blocks of them) where it needs no
+// more rounds of workgroups than the ring kernel: with an lm_head beyond 256 MiB, vocabularies of 40,961 to 53,248, 81,921 to 106,496 and
+// 131,073 to 159,744 rows, so 151,936 but not 128,256.  There 256 x 256 tiles leave room for two K64 steps and the ring kernel, in
+// 32-column slots of them, waits for W.  13 x 4 MFMAs a chunk fill the registers with one set of W's
 // fragments, so a fragment's successor is read over it; three steps of W fit the LDS.  At 151,936 x 2048 and 200 / 256 tokens 171 / 171 ->
 // 158 / 158 us (ring kernel before), 100,352 x 2048 119 / 125 -> 106 / 107, 49,152 x 4096 124 / 121 -> 98 / 102, 50,000 x 3072 with 512 152 -> 139.
-// Of the 158, 119 are left without loads and 138 with W from the L2.  In the same manner 208 x 320 spills, 160 x 320 gains 2 % at 311
+// Of the 158, 119 are left without loads and 138 with W from the L2.  (The compiler keeps 139 scalars of it in vector registers; a step reads two
+// back.)  In the same manner 208 x 320 spills, 160 x 320 gains 2 % at 311
 // tokens and loses 3 at others, and tiles of even shares of 16-row units instead of 208 rows and a short last round gain nothing.
 //
 // Slot layout: 16-byte chunk c of row r sits at position c ^ (r & 6) of its 128-byte row: by the serving rule given at the
@@ -773,7 +776,7 @@ struct BlockTile {
     static_assert((TI - BAR) * PER_ROW >= L, "all loads in the second chunk");
 };
 
-template <class C, bool STREAM = false>   // STREAM: W's lines are each read once and come from memory (kStreamElements)
+template <class C, bool STREAM = false>   // STREAM: W's lines come from memory, and are read once but for a workgroup's last NA slots (kStreamElements)
 __global__ __launch_bounds__(C::NT) void logprob_block_kernel(LogprobArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int BM = C::BM, BN = C::BN, TI = C::TI, TJ = C::TJ, NA = C::NA, NB = C::NB, L = C::L;
@@ -1041,13 +1044,16 @@ constexpr FormSize kFormSize[kForms] = {{FastTile::BM, FastTile::BN, 1.66}, {Blo
                                         {Block192::BM, Block192::BN, 1.42}, {Block256::BM, Block256::BN, 1.45}, {Block320::BM, Block320::BN, 1.42}};
 // The 208 x 256 form beats the ring kernel, where both take as many rounds, by 5 to 24 % while W comes from memory, and loses 3 to 10 % where
 // the 256 MiB cache in front of it holds W from the call before (28 vocabularies and widths x 200, 256 and 512 tokens: 50,257 x 2048
-// 51 -> 54 us, 100,003 x 1280 64 -> 67, 100,003 x 1536 90 -> 82, 151,936 x 1024 87 -> 83): it is taken from that size on.
+// 51 -> 54 us, 100,003 x 1280 64 -> 67, 100,003 x 1536 90 -> 82, 151,936 x 1024 87 -> 83): it is taken from that size on.  Where other data
+// passes between the calls a smaller W comes from memory too, and the line costs what it saves elsewhere: 256 tokens x 50,257 x 2048 after
+// 1 GB read 80 -> 67 us, after 600 MB written 112 -> 86.
 constexpr int64_t kCachedElements = 128 << 20;
 // A W beyond 9/8 of that cache, read by one token block, is loaded past the caches (nt): they keep nothing of it for the next call, and H stays in the
 // L2.  The same W again and again, us: 16 tokens x 151,936 x 4096 212 -> 188, 64 x 151,936 x 2048 112 -> 105 (5.9 TB/s), 128 x 122 -> 118,
-// 192 x 139 -> 135, 311 x 214 -> 212, 300 x 128,256 x 4096 358 -> 352; near the line 64 x 80,000 x 2048 68 -> 66, 128 x 72,000 x 2048 71 -> 73; below
-// it, where the cache has W, 64 x 64,000 x 2048 46 -> 50 and 64 x 32,000 x 2048 32 -> 38.  The 208 x 256 form and two token blocks (384 tokens)
-// are even with it.
+// 192 x 139 -> 135, 311 x 214 -> 212, 300 x 128,256 x 4096 358 -> 352; just above the line (1,344 to 4,096 wide) 1 to 64 tokens 2 to 6 %, 128 2 to
+// 4, 192 and 311 even; below it, where the cache has W, plain loads: 128 x 64,000 x 2048 would go 48 -> 51, 64 x 32,000 x 4096 45 -> 59.  After
+// 600 MB written in between, which the plain loads have to push out of the cache: 64 x 73,984 x 2048 110 -> 70, and below the line
+// 64 x 64,000 x 2048 would go 98 -> 56.  The 208 x 256 form and two token blocks (384 tokens) are even with it.
 constexpr int64_t kStreamElements = kCachedElements / 8 * 9;
 constexpr int kSmallestBM = Block320::BM, kLargestBN = Block320::BN, kBlockTokens = 640;
 
@@ -1108,7 +1114,7 @@ Plan make_plan(int64_t T, int V, int d, int n_splits) {
         if (best < 0.0 || cost < best) { best = cost; p.form = f; p.n_tb = n_tb; p.n_vt = n_vt; p.n_sp = sp; }
     }
     p.general = d % 64 || !offsets_fit(p.form, d);
-    p.stream = p.n_tb == 1 && static_cast<int64_t>(V) * d > kStreamElements;
+    p.stream = !p.general && p.form != kFormRing && p.form != kForm256 && p.n_tb == 1 && static_cast<int64_t>(V) * d > kStreamElements;
     const int bands = (p.n_tb + 3) / 6 > 1 ? (p.n_tb + 3) / 6 : 1;
     p.band = (p.n_tb + bands - 1) / bands;
     p.n_long = p.n_tb - (p.band - 1) * bands;
@@ -1199,5 +1205,11 @@ extern "C" int arrol_logprob_kernel(int64_t T, int32_t V, int32_t d, int32_t n_s
     *tile_rows = kFormSize[p.form].bm;
     *tile_tokens = kFormSize[p.form].bn;
     *splits = p.n_sp;
+    return ARROL_OK;
+}
+
+extern "C" int arrol_logprob_streamed(int64_t T, int32_t V, int32_t d, int32_t n_splits, int32_t* streamed) {
+    if (T < 1 || V < 1 || d < 8 || (d & 7) || n_splits < 0 || !streamed) return ARROL_EINVAL;
+    *streamed = make_plan(T, V, d, n_splits).stream ? 1 : 0;
     return ARROL_OK;
 }

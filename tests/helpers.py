@@ -51,3 +51,10 @@ def logprob_kernel(A, T, V, d, n_splits=0):
     out = [ctypes.c_int32() for _ in range(4)]
     assert A.lib().arrol_logprob_kernel(T, V, d, n_splits, *[ctypes.byref(x) for x in out]) == 0
     return tuple(x.value for x in out)
+
+
+def logprob_streamed(A, T, V, d, n_splits=0):
+    """Whether that call loads the LM head past the caches."""
+    out = ctypes.c_int32()
+    assert A.lib().arrol_logprob_streamed(T, V, d, n_splits, ctypes.byref(out)) == 0
+    return bool(out.value)

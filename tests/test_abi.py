@@ -144,6 +144,13 @@ def test_bad_arguments_are_rejected_on_the_host(pkg):
         assert logprob_kernel(pkg, T, 257, fits + 64)[0] == 0
     fits = (2 ** 32 - 129) // (2 * 319) // 64 * 64
     assert logprob_kernel(pkg, 300, 151936, fits)[:3] == (2, 160, 320) and logprob_kernel(pkg, 300, 151936, fits + 64)[1:3] != (160, 320)
+    # whose lm_head goes past the caches: one token block of the block kernel but 208 x 256, from 9/8 of 256 MiB on
+    for bad in ((0, 1, 8, 0, one), (1, 0, 8, 0, one), (1, 1, 12, 0, one), (1, 1, 8, -1, one), (1, 1, 8, 0, None)):
+        assert L.arrol_logprob_streamed(*bad) == -1, bad
+    from helpers import logprob_streamed
+    for T, V, d, yes in ((65, 112347, 1344, False), (65, 112348, 1344, True), (311, 151936, 2048, True), (256, 100049, 1536, False), (384, 100003, 1536, False),
+                         (700, 151936, 2048, False), (16, 151936, 2056, False), (16, 128256, 1024, False)):
+        assert logprob_streamed(pkg, T, V, d) == yes, (T, V, d)
     # head training: bad d, missing gradient output, workspace; optimizer: bad step / betas
     assert L.arrol_score_grad(fake, 16, None, fake, 0.0, fake, 4, 12, None, fake, None, fake, 1 << 20, None) == -1
     assert L.arrol_score_grad(fake, 16384, None, fake, 0.0, fake, 4, 16384, None, fake, None, fake, 1 << 20, None) == -1

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle as O
-from helpers import bits, logprob_kernel, mlp_kernels, mlp_tiles, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
+from helpers import bits, logprob_kernel, logprob_streamed, mlp_kernels, mlp_tiles, npy, bf16_tensor_from_bits, f32_to_bf16_bits, to_dev, oracle_survivors
 
 pytestmark = pytest.mark.gpu
 
@@ -337,14 +337,16 @@ def test_logprob_four_wavefront_tiles(A, T, V, d, splits):
     assert torch.equal(one, two)
 
 
-# an lm_head that is loaded past the caches (above 9/8 of 256 MiB): each block form from its first to its last token, several vocabulary tiles a
-# workgroup, and the first size on the other side of the line
-@pytest.mark.parametrize("T,V,d,bn", [(1, 112359, 64 * 21, 64), (64, 112348, 64 * 21, 64), (65, 112347, 64 * 21, 128), (128, 78650, 64 * 30, 128),
-                                      (129, 78700, 64 * 30, 192), (192, 112349, 64 * 21, 192), (257, 112350, 64 * 21, 320), (320, 40003, 64 * 60, 320)])
+# an lm_head that is loaded past the caches (above 9/8 of 256 MiB): each block form from its first to its last token, two to four vocabulary tiles
+# a workgroup and, the last, one; and the 256 x 128 form on the other side of the line
+@pytest.mark.parametrize("T,V,d,bn", [(1, 112359, 64 * 21, 64), (64, 112348, 64 * 21, 64), (65, 112347, 64 * 21, 128), (65, 112349, 64 * 21, 128),
+                                      (128, 78650, 64 * 30, 128), (129, 78700, 64 * 30, 192), (192, 112349, 64 * 21, 192), (257, 112350, 64 * 21, 320),
+                                      (320, 160003, 64 * 15, 320), (320, 40003, 64 * 60, 320)])
 def test_logprob_lm_head_past_the_caches(A, T, V, d, bn):
     say("logprob streamed T=%d V=%d d=%d" % (T, V, d))
-    kernel, _, tokens = logprob_kernel(A, T, V, d, 0)[:3]
-    assert (kernel, tokens) == (2, bn)
+    kernel, rows, tokens, splits = logprob_kernel(A, T, V, d, 0)
+    assert (kernel, tokens) == (2, bn) and (-(-V // rows) > splits) == (d != 64 * 60)
+    assert logprob_streamed(A, T, V, d) == (V * d > 9 * 2 ** 24)
     g = torch.Generator(device=DEV); g.manual_seed(T * 7 + V + d)
     hidden = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
     lm_head = (torch.randn(V, d, generator=g, device=DEV) * (2.0 * d ** -0.5)).to(torch.bfloat16)
