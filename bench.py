@@ -401,7 +401,7 @@ def time_extras(A, W, cfg, dev, torch, lp_hidden, lm_head, targets, cu, reps=10)
     c_pos, c_neg = A.arrol_histogram(s_buf, label, 128)
     q_lut, p_lut, _ = A.arrol_calibrate(c_pos, c_neg, pol)
     out["histogram"] = {"ms": timed(lambda: A.arrol_histogram(s_buf, label, 128)), "shape": "M=%d, B=128" % s_buf.numel()}
-    out["calibrate"] = {"ms": timed(lambda: A.arrol_calibrate(c_pos, c_neg, pol)), "shape": "B=128, 64 bisection steps"}
+    out["calibrate"] = {"ms": timed(lambda: A.arrol_calibrate(c_pos, c_neg, pol)), "shape": "B=128"}
     out["prune_bernoulli"] = {"ms": timed(lambda: A.arrol_prune_bernoulli(s_batch, uniforms, p_lut)),
                               "shape": "N=%d" % s_batch.numel()}
     # quality head variants on the batch's checkpoint hidden states

@@ -348,7 +348,8 @@ __global__ __launch_bounds__(kThreads) void score_mlp_kernel(MlpArgs a) {
 // Where a compute unit has no second workgroup to fill the chain, the groups do: group g takes the steps g, g + KG, ... of the
 // block, a stage is KG steps, and the groups' sums are added in the LDS at the end.  512 x 2048 x 512 with 32 x 32 blocks: 7.7 us
 // with one group, 6.9 with four; 1,024 x 2048 x 512 with 64 x 64: 10.9, 10.4 with two; 4,096 x 4096 x 512 with 128 x 64: 27.1, 25.7.
-// (Of 4,096 x 2048 x 512's 16.7 us the steps take 9.6, the activations kept for the gradient 2.2, an empty launch 2.2.)
+// (Of 4,096 x 2048 x 512's 16.7 us the steps take 9.6, the activations kept for the gradient 2.2, an empty launch 2.2.  Under the profiler it
+// is 16.5, with the loads alone 14.6, without them 15.4, with neither, barriers and all else in place, 10.0: the two are even.)
 // Stage layout: 16-byte chunk c of row r at position c ^ (r & 6) of its 128-byte row, which keeps the fragment reads
 // (lane -> row lane % 16, chunk lane / 16) free of bank conflicts by the serving rule given in ring_nt.h.
 template <int BM_, int BN_, int WM_, int WN_, int KG_, int NS_>
@@ -696,7 +697,8 @@ __global__ __launch_bounds__(256) void mlp_sums_kernel(MlpSums f) {   // where m
 // 64 rollouts x 128 bytes, and the B fragments come out through the transposing LDS read (lane layout as in ring_nt.h).  16-byte
 // chunk c of rollout row r sits at position c ^ 2 ((r / 2) % 2) ^ 4 ((r / 8) % 2): the 32 lanes of a half-wave fall on 32 different
 // 8-byte bank pairs.
-// Bound by the loads into LDS (16 KB a step at 73 bytes per nanosecond and compute unit with 64 x 64).  4,096 x 2048 x 512,
+// Bound by the loads into LDS (16 KB a step at 73 bytes per nanosecond and compute unit with 64 x 64; 4,096 x 2048 x 512 under the profiler 18.7 us,
+// with the loads alone 16.5, without them 14.0, with neither 6.9).  4,096 x 2048 x 512,
 // 256 tiles of 64 x 64: 17.4 us; before, one group of four wavefronts, 128 x 64, 2 splits and the sum of their slabs: 20.0.
 // 1,024: 9.2 -> 7.3; 4,096 x 4096 x 512 with 128 x 64: 26.6 -> 25.6.
 template <int BM_, int WM_, int WN_, int KG_, int NS_>
